@@ -6,13 +6,12 @@
 // v_mfma_f32_32x32x16_{bf16,f16} (same dense rate).
 //
 // Workgroup tile BM x BN x 64, WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) block of 32x32
-// accumulator tiles.  The production shape is 256 x 256 with 2 x 2 wavefronts (one per SIMD, 128 x 128 each,
-// 256 accumulator registers in AGPRs) and a hand-scheduled K loop (gen_gemm_kloop.py); edge tiles and the
-// small 128 x 128 configuration take the compiler-scheduled loop described next.  A and W tiles are staged in LDS (double-buffered; 16-byte chunks XOR-swizzled
-// by row so that the 32-row operand reads spread over the banks) by direct global->LDS loads, which
-// need no staging registers; the next K-slice lands while the current one feeds the MFMAs, one
-// barrier per slice.  Inside a slice the operand fragments of step kk+1 are read while step kk's
-// matrix instructions issue.
+// accumulator tiles.  The large-launch shape is 256 x 256 with 2 x 2 wavefronts (one per SIMD, 128 x 128 each,
+// 256 accumulator registers in AGPRs); launches with few tiles per compute unit take one of seven smaller tiles
+// down to 32 x 32 (see the choice at the launcher).  A and W tiles are staged in LDS (a ring of S stages; 16-byte
+// chunks XOR-swizzled by row so that the 32-row operand reads spread over the banks) by direct global->LDS loads,
+// which need no staging registers.  Every K loop is generated text (gen_gemm_kloop.py), because its waits count loads
+// and fragment reads exactly; rows beyond the matrix are clamped in the load offsets, so edge tiles run the same loop.
 //
 // Epilogues: plain store (bf16 or fp32), residual add into the fp32 stream, and SwiGLU, where the B tile is
 // made of BN/2 gate rows and the BN/2 matching up rows so that a lane holds g and u of one element.
@@ -38,8 +37,8 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 #define PRISM_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define PRISM_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
-template <typename OT, int BM, int BN, int WM, int WN, int EPI>
-__global__ __launch_bounds__(WM *WN * 64) void gemm_16_kernel(const OT *__restrict__ A,
+template <typename OT, int BM, int BN, int WM, int WN, int EPI, int S>
+__global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel(const OT *__restrict__ A,
                                                                const OT *__restrict__ W, void *__restrict__ out_,
                                                                int M, int N, int K, int nM, int nN, QkvEpilogue qe) {
   constexpr int NW = WM * WN;
@@ -49,10 +48,9 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_16_kernel(const OT *__restri
   constexpr int A_ITERS = BM / 8 / NW, B_ITERS = BN / 8 / NW;
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/waves mismatch");
   static_assert(EPI != PRISM_EPI_SWIGLU || TN % 2 == 0, "SwiGLU pairs gate and up tiles");
-  typedef typename Mfma<OT>::vec8 vec8;
   extern __shared__ __align__(16) unsigned char smem[];
-  OT *lA = reinterpret_cast<OT *>(smem);                     // [2][BM][BK]
-  OT *lB = lA + 2 * BM * BK;                                 // [2][BN][BK]
+  OT *lA = reinterpret_cast<OT *>(smem);                     // [S][BM][BK]
+  OT *lB = lA + S * BM * BK;                                 // [S][BN][BK]
 
   // ---- tile mapping: XCD-contiguous ranges, grouped walk ----
   const int n_tiles = nM * nN;
@@ -103,19 +101,6 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_16_kernel(const OT *__restri
     }
     gB[j] = ((uint32_t)gr * (uint32_t)K + swz(row, lane & 7) * 8) * 2u;
   }
-  auto stage_loads = [&](int kt, int buf) {
-    const char *baseA = reinterpret_cast<const char *>(A) + (size_t)kt * BK * 2;   // uniform
-    const char *baseB = reinterpret_cast<const char *>(W) + (size_t)kt * BK * 2;
-#pragma unroll
-    for (int j = 0; j < A_ITERS; ++j)
-      __builtin_amdgcn_global_load_lds(PRISM_GLOBAL_PTR(baseA + gA[j]),
-                                       PRISM_LDS_PTR(lA + buf * BM * BK + (wave * A_ITERS + j) * 8 * BK), 16, 0, 0);
-#pragma unroll
-    for (int j = 0; j < B_ITERS; ++j)
-      __builtin_amdgcn_global_load_lds(PRISM_GLOBAL_PTR(baseB + gB[j]),
-                                       PRISM_LDS_PTR(lB + buf * BN * BK + (wave * B_ITERS + j) * 8 * BK), 16, 0, 0);
-  };
-
   // ---- LDS rows this lane reads as MFMA operands ----
   int rA[TM], rB[TN];
 #pragma unroll
@@ -171,9 +156,6 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_16_kernel(const OT *__restri
   //      through LDS, which is free once the K loop is done: lanes write their row's values, then read back 16 bytes
   //      each along the rows, so that an instruction reads or writes whole lines (2-8 complete rows of the wave's
   //      columns).  LDS requests of one wave are served in order, so no barrier is needed between the two phases.
-  //      The epilogue is a lambda expanded after EACH of the two K loops below rather than once behind their join: the
-  //      accumulators then stay wherever the loop left them (with one copy behind the join the register allocator parks
-  //      dozens of them in scratch memory to reconcile the two loops' assignments).
   auto epilogue = [&]() __attribute__((always_inline)) {
   // Accumulator element (i, j, e), fetched from its accumulation register when it is needed: behind the hand-scheduled
   // loop all 256 of them sit in AGPRs, and read as plain values the compiler would copy the whole set into vector
@@ -196,8 +178,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_16_kernel(const OT *__restri
   const int m_in = lane & 31, n_in = (lane >> 5) * 4;
   constexpr int SWZ = CPR >= 16 ? 15 : CPR - 1;                     // chunk rotation by row: spreads a column of 16-byte
                                                                     // writes (one per row) over the banks
-  static_assert(32 * RB <= 2 * (BM + BN) * BK * (int)sizeof(OT) / NW, "staging block must fit the wave's share of LDS");
-  unsigned char *stg = smem + wave * (2 * (BM + BN) * BK * (int)sizeof(OT) / NW);
+  static_assert(32 * RB <= S * (BM + BN) * BK * (int)sizeof(OT) / NW, "staging block must fit the wave's share of LDS");
+  unsigned char *stg = smem + wave * (S * (BM + BN) * BK * (int)sizeof(OT) / NW);
   // values for columns n .. n + 3 (n a multiple of 4, within the wave's columns) of staged row m
   auto put32 = [&](int m, int n, const f32x4 &v) __attribute__((always_inline)) {
     *reinterpret_cast<f32x4 *>(stg + m * RB + (((n >> 2) ^ (m & SWZ)) << 4)) = v;
@@ -418,69 +400,58 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_16_kernel(const OT *__restri
   }
   };
 
-  // The 256x256 / 2x2-wave configuration runs the hand-scheduled loop; other shapes take the compiler's schedule.
-  constexpr bool kHandScheduled = BM == 256 && BN == 256 && WM == 2 && WN == 2;
-  // interior tiles only: the hand-scheduled loop assumes that the tile's rows of A and W all exist
-  const bool interior = m0 + BM <= M && n0 + (EPI == PRISM_EPI_SWIGLU ? BN / 2 : BN) <= F;
-  if (kHandScheduled && interior) {
-    if constexpr (kHandScheduled) {
-      const unsigned ldsA = (unsigned)(uintptr_t)PRISM_LDS_PTR(lA), ldsB = (unsigned)(uintptr_t)PRISM_LDS_PTR(lB);
-      const unsigned aA0 = ldsA + (unsigned)(rA[0] * BK + swz(rA[0], khalf) * 8) * 2u;
-      const unsigned aB0 = ldsB + (unsigned)(rB[0] * BK + swz(rB[0], khalf) * 8) * 2u;
-      // wave w's load instruction j fills tile rows (8 w + j) * 8 .. + 8 of each operand (1 KiB of LDS)
-      const unsigned stride8 = 8u * (unsigned)K * 2u;
-      const unsigned ldsA_w = __builtin_amdgcn_readfirstlane(ldsA + (unsigned)wave * A_ITERS * 8 * BK * 2);
-      const unsigned ldsB_w = __builtin_amdgcn_readfirstlane(ldsB + (unsigned)wave * B_ITERS * 8 * BK * 2);
-      const uint64_t baseA = (uint64_t)(uintptr_t)A, baseB = (uint64_t)(uintptr_t)W;
+  const unsigned ldsA = (unsigned)(uintptr_t)PRISM_LDS_PTR(lA), ldsB = (unsigned)(uintptr_t)PRISM_LDS_PTR(lB);
+  const unsigned aA0 = ldsA + (unsigned)(rA[0] * BK + swz(rA[0], khalf) * 8) * 2u;
+  const unsigned aB0 = ldsB + (unsigned)(rB[0] * BK + swz(rB[0], khalf) * 8) * 2u;
+  // wave w's load instruction j fills tile rows (w * ITERS + j) * 8 .. + 8 of an operand (1 KiB of LDS)
+  const unsigned ldsA_w = __builtin_amdgcn_readfirstlane(ldsA + (unsigned)wave * A_ITERS * 8 * BK * 2);
+  const unsigned ldsB_w = __builtin_amdgcn_readfirstlane(ldsB + (unsigned)wave * B_ITERS * 8 * BK * 2);
+  const uint64_t baseA = (uint64_t)(uintptr_t)A, baseB = (uint64_t)(uintptr_t)W;
+  constexpr bool kF16 = Mfma<OT>::kIsF16;
+  if constexpr (BM < 256) {
+#define PRISM_ACC1 "+a"(acc[0][0])
+#define PRISM_ACC2 PRISM_ACC1, "+a"(acc[0][1])
+#define PRISM_ACC4 PRISM_ACC2, "+a"(acc[1][0]), "+a"(acc[1][1])
+#define PRISM_G2(g) "v"(g[0]), "v"(g[1])
+#define PRISM_G4(g) PRISM_G2(g), "v"(g[2]), "v"(g[3])
+#define PRISM_G8(g) PRISM_G4(g), "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7])
+#define PRISM_RUN_SMALL(NAME, ACC, GA, GB)                                                                              \
+  do {                                                                                                                  \
+    if constexpr (kF16)                                                                                                 \
+      asm volatile(PRISM_KLOOP_F16_##NAME : ACC : "v"(aA0), "v"(aB0), GA(gA), GB(gB), "s"(ldsA_w), "s"(ldsB_w),         \
+                   "s"(baseA), "s"(baseB), "s"(nk) : PRISM_KLOOP_CLOBBERS_##NAME);                                      \
+    else                                                                                                                \
+      asm volatile(PRISM_KLOOP_BF16_##NAME : ACC : "v"(aA0), "v"(aB0), GA(gA), GB(gB), "s"(ldsA_w), "s"(ldsB_w),        \
+                   "s"(baseA), "s"(baseB), "s"(nk) : PRISM_KLOOP_CLOBBERS_##NAME);                                      \
+  } while (0)
+    if constexpr (BM == 32 && BN == 32) PRISM_RUN_SMALL(32x32_8, PRISM_ACC1, PRISM_G4, PRISM_G4);
+    else if constexpr (BM == 64 && BN == 32) PRISM_RUN_SMALL(64x32_6, PRISM_ACC1, PRISM_G4, PRISM_G2);
+    else if constexpr (BM == 32 && BN == 64) PRISM_RUN_SMALL(32x64_4, PRISM_ACC2, PRISM_G4, PRISM_G8);
+    else if constexpr (BM == 64 && BN == 64) PRISM_RUN_SMALL(64x64_5, PRISM_ACC2, PRISM_G4, PRISM_G4);
+    else if constexpr (BM == 128 && BN == 64) PRISM_RUN_SMALL(128x64_3, PRISM_ACC2, PRISM_G4, PRISM_G2);
+    else if constexpr (S == 3 && EPI == PRISM_EPI_SWIGLU) PRISM_RUN_SMALL(128x128_3_SWIGLU, PRISM_ACC4, PRISM_G4, PRISM_G4);
+    else if constexpr (S == 3) PRISM_RUN_SMALL(128x128_3_PLAIN, PRISM_ACC4, PRISM_G4, PRISM_G4);
+    else if constexpr (EPI == PRISM_EPI_SWIGLU) PRISM_RUN_SMALL(128x128_2_SWIGLU, PRISM_ACC4, PRISM_G4, PRISM_G4);
+    else PRISM_RUN_SMALL(128x128_2_PLAIN, PRISM_ACC4, PRISM_G4, PRISM_G4);
+  } else {
 #define PRISM_RUN_KLOOP(TEXT)                                                                                           \
   asm volatile(TEXT                                                                                                     \
                : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]), "+a"(acc[1][0]), "+a"(acc[1][1]), \
                  "+a"(acc[1][2]), "+a"(acc[1][3]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]), \
                  "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])                                    \
-               : "v"(aA0), "v"(aB0), "v"(gA[0]), "v"(gB[0]), "s"(ldsA_w), "s"(ldsB_w), "s"(stride8), "s"(baseA),       \
-                 "s"(baseB), "s"(nk)                                                                                   \
+               : "v"(aA0), "v"(aB0), PRISM_G8(gA), PRISM_G8(gB), "s"(ldsA_w), "s"(ldsB_w), "s"(baseA), "s"(baseB),     \
+                 "s"(nk)                                                                                               \
                : PRISM_KLOOP4_CLOBBERS)
-      constexpr bool kF16 = Mfma<OT>::kIsF16;
-      if constexpr (EPI == PRISM_EPI_SWIGLU) {
-        if constexpr (kF16) PRISM_RUN_KLOOP(PRISM_KLOOP4_F16_SWIGLU);
-        else PRISM_RUN_KLOOP(PRISM_KLOOP4_BF16_SWIGLU);
-      } else {
-        if constexpr (kF16) PRISM_RUN_KLOOP(PRISM_KLOOP4_F16_PLAIN);
-        else PRISM_RUN_KLOOP(PRISM_KLOOP4_BF16_PLAIN);
-      }
+    if constexpr (EPI == PRISM_EPI_SWIGLU) {
+      if constexpr (kF16) PRISM_RUN_KLOOP(PRISM_KLOOP4_F16_SWIGLU);
+      else PRISM_RUN_KLOOP(PRISM_KLOOP4_BF16_SWIGLU);
+    } else {
+      if constexpr (kF16) PRISM_RUN_KLOOP(PRISM_KLOOP4_F16_PLAIN);
+      else PRISM_RUN_KLOOP(PRISM_KLOOP4_BF16_PLAIN);
+    }
 #undef PRISM_RUN_KLOOP
-      epilogue();
-    }
-  } else {
-    vec8 af[2][TM], bfr[2][TN];
-    auto load_frags = [&](int set, const OT *cA, const OT *cB, int kk) {
-#pragma unroll
-      for (int t = 0; t < TM; ++t)
-        af[set][t] = *reinterpret_cast<const vec8 *>(cA + rA[t] * BK + swz(rA[t], kk * 2 + khalf) * 8);
-#pragma unroll
-      for (int t = 0; t < TN; ++t)
-        bfr[set][t] = *reinterpret_cast<const vec8 *>(cB + rB[t] * BK + swz(rB[t], kk * 2 + khalf) * 8);
-    };
-    stage_loads(0, 0);
-    __syncthreads();                                           // waits for the loads (vmcnt) and the workgroup
-    for (int kt = 0; kt < nk; ++kt) {
-      const int cur = kt & 1;
-      if (kt + 1 < nk) stage_loads(kt + 1, cur ^ 1);           // lands while this slice feeds the MFMAs
-      const OT *cA = lA + cur * BM * BK, *cB = lB + cur * BN * BK;
-      load_frags(0, cA, cB, 0);
-#pragma unroll
-      for (int kk = 0; kk < BK / 16; ++kk) {
-        if (kk + 1 < BK / 16) load_frags((kk + 1) & 1, cA, cB, kk + 1);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = Mfma<OT>::mma(bfr[kk & 1][j], af[kk & 1][i], acc[i][j]);   // transposed tile, see the epilogue
-      }
-      __syncthreads();                                         // next slice landed (vmcnt) and everyone is done with this one
-    }
-    epilogue();
   }
+  epilogue();
 }
 
 bool gemm_16_supported(int epilogue, int N, int K) {
@@ -489,11 +460,11 @@ bool gemm_16_supported(int epilogue, int N, int K) {
   return epilogue >= PRISM_EPI_STORE && epilogue <= PRISM_EPI_STORE_F32;
 }
 
-template <typename OT, int BM, int BN, int WM, int WN, int EPI>
+template <typename OT, int BM, int BN, int WM, int WN, int EPI, int S>
 static int launch_cfg(const OT *A, const OT *W, void *out, int M, int N, int K, hipStream_t s,
                       const QkvEpilogue &qe = QkvEpilogue{}) {
-  constexpr size_t lds = 2 * (size_t)(BM + BN) * BK * sizeof(OT);
-  auto kern = gemm_16_kernel<OT, BM, BN, WM, WN, EPI>;
+  constexpr size_t lds = S * (size_t)(BM + BN) * BK * sizeof(OT);
+  auto kern = gemm_16_kernel<OT, BM, BN, WM, WN, EPI, S>;
   // the attribute is per function: set once per process, also when several contexts launch from different threads
   static std::once_flag attr_once;
   static hipError_t attr_rc = hipSuccess;
@@ -509,39 +480,83 @@ static int launch_cfg(const OT *A, const OT *W, void *out, int M, int N, int K, 
   return PRISM_OK;
 }
 
-// Cost of a round of small tiles relative to a round of big ones: a quarter of the work at about two thirds of the rate
-// (the 128 x 128 loop is compiler-scheduled).  Only used to decide how a launch is tiled, never for results.
-#ifndef PRISM_SMALL_TILE_COST
-#define PRISM_SMALL_TILE_COST 0.4
-#endif
+// ---- which tile a launch uses -----------------------------------------------------------------------------------------
+// Rows are independent, columns are independent, and every tile size gives an element the same bits (one accumulator, K in
+// order), so the choice is made on time alone.  A launch deals its tiles over 256 compute units; n = tiles per unit, rounded
+// up.  A tile's time is its K slices plus a fixed part (dispatch, first slice, epilogue), and a slice's time depends on how
+// many tiles share the unit: alone it is a chain of latencies, together the matrix pipes and LDS.  The constants are a
+// least-squares fit to every tile size on 110 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues; each
+// tile within 12-17 %); the size picked by them was on average within 2 % of the best one measured.  Examples, in us, 128 x 128
+// compiler-scheduled loop before -> now: 100 x 4096 x 12288 167 -> 36 (64 x 32), 391 x 1024 x 3072 44 -> 10 (64 x 32),
+// 777 x 6144 x 1024 with SwiGLU 23 -> 17 (128 x 128), 3699 x 1024 x 3072 49 -> 30 (128 x 128, three stages).
+struct TileCost {
+  int bm, bn, occ;              // tile, workgroups that share a compute unit
+  float alone, shared, fixed;   // us per 64-deep slice: one workgroup on the unit; per workgroup when occ of them share it; us per tile
+};
+enum { kTile256, kTile128, kTile128Deep, kTile128x64, kTile64, kTile32x64, kTile64x32, kTile32, kTileKinds };
+static constexpr TileCost kTileCost[kTileKinds] = {
+    {256, 256, 1, 1.53f, 1.53f, 9.2f}, {128, 128, 2, 0.72f, 0.50f, 4.5f}, {128, 128, 1, 0.52f, 0.52f, 3.4f}, {128, 64, 2, 0.34f, 0.36f, 2.3f},
+    {64, 64, 2, 0.204f, 0.204f, 2.1f}, {32, 64, 3, 0.176f, 0.149f, 2.4f}, {64, 32, 2, 0.128f, 0.128f, 2.3f}, {32, 32, 2, 0.106f, 0.083f, 2.6f}};
+
+static double tile_cost(int kind, int64_t M, int64_t ncols, int K, bool glu) {
+  const TileCost &t = kTileCost[kind];
+  const int64_t tiles = (M + t.bm - 1) / t.bm * ((ncols + (glu ? t.bn / 2 : t.bn) - 1) / (glu ? t.bn / 2 : t.bn)), n = (tiles + 255) / 256;
+  const int64_t full = n / t.occ, rest = n % t.occ;
+  const double slice = full * std::max(t.alone, t.shared * t.occ) + (rest ? std::max(t.alone, t.shared * rest) : 0.f);
+  return (K / BK) * slice + (double)((n + t.occ - 1) / t.occ) * t.fixed;
+}
+
+static int best_tile(int64_t M, int64_t ncols, int K, bool glu, double *cost) {
+  int best = kTile256;
+  *cost = tile_cost(kTile256, M, ncols, K, glu);
+  for (int k = 1; k < kTileKinds; ++k) {
+    if (glu && kTileCost[k].bn == 32) continue;          // SwiGLU pairs a gate and an up tile in a wave
+    const double c = tile_cost(k, M, ncols, K, glu);
+    if (c < *cost) { *cost = c; best = k; }
+  }
+  return best;
+}
+
+template <typename OT, int EPI>
+static int launch_kind(int kind, const OT *A, const OT *W, void *out, int M, int N, int K, hipStream_t s) {
+  switch (kind) {
+    case kTile256: return launch_cfg<OT, 256, 256, 2, 2, EPI, 2>(A, W, out, M, N, K, s);
+    case kTile128: return launch_cfg<OT, 128, 128, 2, 2, EPI, 2>(A, W, out, M, N, K, s);
+    case kTile128Deep: return launch_cfg<OT, 128, 128, 2, 2, EPI, 3>(A, W, out, M, N, K, s);
+    case kTile128x64: return launch_cfg<OT, 128, 64, 4, 1, EPI, 3>(A, W, out, M, N, K, s);
+    case kTile64: return launch_cfg<OT, 64, 64, 2, 1, EPI, 5>(A, W, out, M, N, K, s);
+    case kTile32x64: return launch_cfg<OT, 32, 64, 1, 1, EPI, 4>(A, W, out, M, N, K, s);
+    default: break;
+  }
+  if constexpr (EPI != PRISM_EPI_SWIGLU) {
+    if (kind == kTile64x32) return launch_cfg<OT, 64, 32, 2, 1, EPI, 6>(A, W, out, M, N, K, s);
+    return launch_cfg<OT, 32, 32, 1, 1, EPI, 8>(A, W, out, M, N, K, s);
+  }
+  return PRISM_EUNSUPPORTED;
+}
 
 template <typename OT, int EPI>
 static int launch_epi(const OT *A, const OT *W, void *out, int M, int N, int K, hipStream_t s) {
-  // A launch runs its tiles in rounds of one per compute unit, and a last round that fills only a few of them costs a
-  // whole tile's time.  Rows are independent and both tile sizes give a row the same bits, so the launcher compares three
-  // ways of tiling by their rounds: small tiles only, big tiles only, or the row tiles that fill whole rounds with big
-  // tiles and the remaining rows in a second launch with small ones.
-  constexpr int kCus = 256;
+  if (M == 0) return PRISM_OK;
   constexpr bool kGlu = EPI == PRISM_EPI_SWIGLU;
   const int ncols = kGlu ? N / 2 : N;
-  const int nN = cdiv(ncols, kGlu ? 128 : 256), nM = cdiv(M, 256), nN_small = cdiv(ncols, kGlu ? 64 : 128);
-  const int64_t big_tiles = (int64_t)nM * nN;
-  const double cost_small = PRISM_SMALL_TILE_COST * (double)cdiv((int64_t)cdiv(M, 128) * nN_small, kCus);
-  const double cost_big = (double)cdiv(big_tiles, kCus);
-  const int full_rounds = (int)(big_tiles / kCus);
-  const int rows_big = (int)std::min<int64_t>(nM, (int64_t)full_rounds * kCus / nN);      // row tiles that fit whole rounds
-  const int rest_rows = M - rows_big * 256;
-  double cost_split = 1e30;
-  if (rows_big >= 1 && rest_rows > 0)
-    cost_split = (double)cdiv((int64_t)rows_big * nN, kCus) + PRISM_SMALL_TILE_COST * (double)cdiv((int64_t)cdiv(rest_rows, 128) * nN_small, kCus);
-  if (cost_small <= cost_big && cost_small <= cost_split) return launch_cfg<OT, 128, 128, 2, 2, EPI>(A, W, out, M, N, K, s);
-  if (cost_split < cost_big - 0.05) {
-    const size_t out_elem = EPI == PRISM_EPI_RESIDUAL || EPI == PRISM_EPI_STORE_F32 ? 4 : 2;
-    PRISM_TRY((launch_cfg<OT, 256, 256, 2, 2, EPI>(A, W, out, rows_big * 256, N, K, s)));
-    return launch_cfg<OT, 128, 128, 2, 2, EPI>(A + (size_t)rows_big * 256 * K, W,
-                                                reinterpret_cast<char *>(out) + (size_t)rows_big * 256 * ncols * out_elem, rest_rows, N, K, s);
+  double cost;
+  const int kind = best_tile(M, ncols, K, kGlu, &cost);
+  // The last round of big tiles may fill only a few compute units at a whole tile's price: then the row tiles that fill
+  // whole rounds go to the big tile and the remaining rows to a second launch with whatever suits them.
+  const int nN = cdiv(ncols, kGlu ? 128 : 256), nM = cdiv(M, 256);
+  const int rows_big = (int)std::min<int64_t>(nM, ((int64_t)nM * nN / 256) * 256 / nN) * 256;
+  if (rows_big > 0 && rows_big < M) {
+    double rest;
+    const int rest_kind = best_tile(M - rows_big, ncols, K, kGlu, &rest);
+    if (rest_kind != kTile256 && tile_cost(kTile256, rows_big, ncols, K, kGlu) + rest < 0.98 * cost) {
+      constexpr size_t out_elem = EPI == PRISM_EPI_RESIDUAL || EPI == PRISM_EPI_STORE_F32 ? 4 : 2;
+      PRISM_TRY((launch_kind<OT, EPI>(kTile256, A, W, out, rows_big, N, K, s)));
+      return launch_kind<OT, EPI>(rest_kind, A + (size_t)rows_big * K, W, reinterpret_cast<char *>(out) + (size_t)rows_big * ncols * out_elem,
+                                  M - rows_big, N, K, s);
+    }
   }
-  return launch_cfg<OT, 256, 256, 2, 2, EPI>(A, W, out, M, N, K, s);
+  return launch_kind<OT, EPI>(kind, A, W, out, M, N, K, s);
 }
 
 template <typename OT>
@@ -603,9 +618,9 @@ int launch_gemm_16_qkv(int dtype, const void *Xn, const void *Wqkv, int M, int K
     p.QK = reinterpret_cast<char *>(e.QK) + (size_t)m0 * (e.nq + e.nkv) * 128 * 2;
     const char *a = reinterpret_cast<const char *>(Xn) + (size_t)m0 * K * 2;
     if (dtype == PRISM_DTYPE_BF16)
-      PRISM_TRY((launch_cfg<bf16, 256, 256, 2, 2, kEpiQkv>((const bf16 *)a, (const bf16 *)Wqkv, p.QK, rows, N, K, s, p)));
+      PRISM_TRY((launch_cfg<bf16, 256, 256, 2, 2, kEpiQkv, 2>((const bf16 *)a, (const bf16 *)Wqkv, p.QK, rows, N, K, s, p)));
     else
-      PRISM_TRY((launch_cfg<f16, 256, 256, 2, 2, kEpiQkv>((const f16 *)a, (const f16 *)Wqkv, p.QK, rows, N, K, s, p)));
+      PRISM_TRY((launch_cfg<f16, 256, 256, 2, 2, kEpiQkv, 2>((const f16 *)a, (const f16 *)Wqkv, p.QK, rows, N, K, s, p)));
   }
   return PRISM_OK;
 }

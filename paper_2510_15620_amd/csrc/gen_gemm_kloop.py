@@ -23,13 +23,13 @@ slice bodies free of branches.
 The W fragment is the first MFMA operand, so accumulator tiles come out transposed (a lane owns one row of A).
 """
 # ---- register plan (all clobbered) ----
-GA = [20 + j for j in range(8)]         # byte offset into A of the chunk this lane fetches in load instruction j
-GB = [28 + j for j in range(8)]
+GA = [f"%{18 + j}" for j in range(8)]   # byte offset into A of the chunk this lane fetches in load instruction j (inputs)
+GB = [f"%{26 + j}" for j in range(8)]
 AA = [36 + k for k in range(4)]         # LDS address of the lane's first A fragment row, step k (stage 0)
 AB = [40 + k for k in range(4)]
 F = [{"A": [64 + 4 * i for i in range(4)], "B": [80 + 4 * j for j in range(4)]},
      {"A": [96 + 4 * i for i in range(4)], "B": [112 + 4 * j for j in range(4)]}]
-CLOBBER_V = list(range(20, 44)) + list(range(64, 128))
+CLOBBER_V = list(range(36, 44)) + list(range(64, 128))
 CLOBBER_S = [20, 21, 22, 23, 24, 25, 26, 27, 28, 29]
 
 STAGE = 32768                           # bytes per LDS stage of one operand
@@ -53,10 +53,10 @@ def mfma(mn, fs, i, j):
 
 
 def loads(which, stage):
-    """8 direct-to-LDS loads of this wave for one operand: M0 = LDS destination (wave base %20 / %21 + 1 KiB per
+    """8 direct-to-LDS loads of this wave for one operand: M0 = LDS destination (wave base %34 / %35 + 1 KiB per
     instruction + stage), source = running base s[20:21] / s[22:23] + the lane's byte offset."""
-    base, lds, off = ("s[20:21]", "%20", GA) if which == "A" else ("s[22:23]", "%21", GB)
-    return [f"s_add_u32 m0, {lds}, {stage * STAGE + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 v{off[j]}, {base}"
+    base, lds, off = ("s[20:21]", "%34", GA) if which == "A" else ("s[22:23]", "%35", GB)
+    return [f"s_add_u32 m0, {lds}, {stage * STAGE + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 {off[j]}, {base}"
             for j in range(8)]
 
 
@@ -117,15 +117,10 @@ def slice_body(mn, cur, b_off):
 
 def kloop(mn, b_off):
     s = []
-    # ---- setup: step addresses differ only in the swizzled chunk bits; load instructions are 8 rows apart and
-    #      alternate between the two swizzle phases (chunk ^ 4, i.e. byte offset ^ 64)
+    # ---- setup: step addresses differ only in the swizzled chunk bits
     s += [f"v_mov_b32 v{AA[0]}, %16", f"v_xor_b32 v{AA[1]}, 32, %16", f"v_xor_b32 v{AA[2]}, 64, %16", f"v_xor_b32 v{AA[3]}, 96, %16"]
     s += [f"v_mov_b32 v{AB[0]}, %17", f"v_xor_b32 v{AB[1]}, 32, %17", f"v_xor_b32 v{AB[2]}, 64, %17", f"v_xor_b32 v{AB[3]}, 96, %17"]
-    s += [f"v_mov_b32 v{GA[0]}, %18", f"v_mov_b32 v{GB[0]}, %19"]
-    for j in range(1, 8):
-        s += [f"v_add_u32 v{GA[j]}, %22, v{GA[j - 1]}", f"v_add_u32 v{GB[j]}, %22, v{GB[j - 1]}",
-              f"v_xor_b32 v{GA[j]}, 64, v{GA[j]}", f"v_xor_b32 v{GB[j]}, 64, v{GB[j]}"]
-    s += ["s_mov_b64 s[20:21], %23", "s_mov_b64 s[22:23], %24", "s_mov_b32 s24, %25", "s_sub_u32 s26, %25, 1", "s_mov_b32 s25, 0", "s_mov_b32 s29, 0"]
+    s += ["s_mov_b64 s[20:21], %36", "s_mov_b64 s[22:23], %37", "s_mov_b32 s24, %38", "s_sub_u32 s26, %38, 1", "s_mov_b32 s25, 0", "s_mov_b32 s29, 0"]
     # ---- prologue: slice 0 -> LDS stage 0, first fragments
     s += loads("A", 0) + loads("B", 0) + advance("A") + advance("B")
     s += ["s_waitcnt vmcnt(0)", "s_barrier"] + reads(0, 0, 0, b_off)
@@ -138,6 +133,135 @@ def kloop(mn, b_off):
     return s
 
 
+# ------------------------------------------------------------------------------------------------ small tiles
+# K loop of the tiles below 256 x 256 (see gemm_16.hip for when they are used).  Such launches have few tiles per compute
+# unit, often less than one, so a slice's time is a chain of latencies: what counts is how many slices of loads are in
+# flight and that nothing but the MFMAs and one barrier is left on the chain.
+#   * LDS holds a ring of S slices; slice t+S is requested while slice t feeds the MFMAs, so S-1 slices are in flight;
+#   * fragments are read one phase ahead into the other of two register sets (a phase is a whole slice, or half of one
+#     where the sets would not fit), so a phase's MFMAs start without a wait;
+#   * one barrier per slice: behind it slice t+1 has landed for everybody, and everybody has the last fragments of
+#     slice t in registers, so its stage may be overwritten.
+# The ring is unrolled (stage offsets are immediates).  Loads take their row offsets as inputs, one register per load
+# instruction, so rows beyond the matrix are clamped by the caller and edge tiles run the same loop.
+S_AA, S_AB, S_F = 24, 28, 32              # first VGPRs: step addresses of A and B, fragments
+
+
+class Small:
+    def __init__(self, name, TM, TN, nla, nlb, bm, bn, S, b_off, ks):
+        self.name, self.TM, self.TN, self.nla, self.nlb, self.S, self.ks = name, TM, TN, nla, nlb, S, ks
+        self.a_stage, self.b_stage, self.b_off = bm * 128, bn * 128, b_off
+        n = TM * TN
+        self.aA, self.aB = n, n + 1
+        self.gA, self.gB = n + 2, n + 2 + nla
+        self.ldsA = n + 2 + nla + nlb
+        self.ldsB, self.baseA, self.baseB, self.nk = self.ldsA + 1, self.ldsA + 2, self.ldsA + 3, self.ldsA + 4
+        self.set_regs = ks * (TM + TN) * 4
+        self.last_v = S_F + 2 * self.set_regs - 1
+
+    def frag(self, st, kk, which, i):
+        at = S_F + st * self.set_regs + (kk % self.ks) * (self.TM + self.TN) * 4 + (i if which == "A" else self.TM + i) * 4
+        return v4(at)
+
+    def reads(self, st, phase, stage):
+        out = []
+        for kk in range(phase * self.ks, (phase + 1) * self.ks):
+            for i in range(self.TM):
+                out.append(f"ds_read_b128 {self.frag(st, kk, 'A', i)}, v{S_AA + kk} offset:{stage * self.a_stage + i * 4096}")
+            for j in range(self.TN):
+                out.append(f"ds_read_b128 {self.frag(st, kk, 'B', j)}, v{S_AB + kk} offset:{stage * self.b_stage + self.b_off[j]}")
+        return out
+
+    def loads(self, stage):
+        out = []
+        for j in range(self.nla):
+            out.append(f"s_add_u32 m0, %{self.ldsA}, {stage * self.a_stage + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 %{self.gA + j}, s[20:21]")
+        for j in range(self.nlb):
+            out.append(f"s_add_u32 m0, %{self.ldsB}, {stage * self.b_stage + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 %{self.gB + j}, s[22:23]")
+        return out
+
+    def advance(self):
+        """Both bases to the next slice while that exists (s25 = slice the bases point at, s26 = last slice): near the end
+        the loads re-read the last slice, in bounds, into stages that nobody reads any more."""
+        return ["s_cmp_lt_u32 s25, s26", "s_cselect_b32 s27, 128, 0", "s_cselect_b32 s28, 1, 0", "s_add_u32 s20, s20, s27",
+                "s_addc_u32 s21, s21, 0", "s_add_u32 s22, s22, s27", "s_addc_u32 s23, s23, 0", "s_add_u32 s25, s25, s28"]
+
+    def mfmas(self, mn, st, phase):
+        out = []
+        for kk in range(phase * self.ks, (phase + 1) * self.ks):
+            for i in range(self.TM):
+                for jj in range(self.TN):
+                    j = jj if i % 2 == 0 else self.TN - 1 - jj
+                    acc = f"%{i * self.TN + j}"
+                    out.append(f"{mn} {acc}, {self.frag(st, kk, 'B', j)}, {self.frag(st, kk, 'A', i)}, {acc}")
+        return out
+
+    def text(self, mn):
+        L, S, np_ = self.nla + self.nlb, self.S, 4 // self.ks
+        s = []
+        for k in range(4):
+            s += [f"v_xor_b32 v{S_AA + k}, {32 * k}, %{self.aA}", f"v_xor_b32 v{S_AB + k}, {32 * k}, %{self.aB}"]
+        s += [f"s_mov_b64 s[20:21], %{self.baseA}", f"s_mov_b64 s[22:23], %{self.baseB}", f"s_mov_b32 s24, %{self.nk}",
+              f"s_sub_u32 s26, %{self.nk}, 1", "s_mov_b32 s25, 0"]
+        for t in range(S - 1):
+            s += self.loads(t) + self.advance()
+        s += [f"s_waitcnt vmcnt({(S - 2) * L})", "s_barrier"]
+        s += self.reads(0, 0, 0) + self.loads(S - 1) + self.advance()
+        s += ["L_loop_%=:"]
+        # one turn of the ring; with an odd number of phases per turn the register sets would not alternate, so two turns
+        turns = 1 if (S * np_) % 2 == 0 else 2
+        st = 0
+        for t in range(S * turns):
+            p = t % S
+            for ph in range(np_):
+                last = ph == np_ - 1
+                s += [f"s_waitcnt vmcnt({(S - 2) * L}) lgkmcnt(0)", "s_barrier"] if last else ["s_waitcnt lgkmcnt(0)"]
+                nxt = self.reads(1 - st, 0, (p + 1) % S) if last else self.reads(1 - st, ph + 1, p)
+                mf = self.mfmas(mn, st, ph)
+                ld = self.loads(p) if last else []
+                # fragment reads first (they are on the next phase's chain), two behind every MFMA; loads behind them
+                k = 0
+                for m in mf:
+                    s.append(m)
+                    take = max(2, -(-len(nxt) // max(1, len(mf) // 2)))
+                    s += nxt[k:k + take]
+                    if k >= len(nxt) and ld:
+                        n = -(-len(ld) // max(1, len(mf) // 2))
+                        s += ld[:n]
+                        ld = ld[n:]
+                    k += take
+                s += nxt[k:] + ld
+                if last:
+                    s += self.advance()
+                st = 1 - st
+            s += ["s_sub_u32 s24, s24, 1", "s_cmp_eq_u32 s24, 0"]
+            s += ["s_cbranch_scc1 L_done_%="] if t + 1 < S * turns else ["s_cbranch_scc0 L_loop_%="]
+        s += ["L_done_%=:", "s_waitcnt vmcnt(0) lgkmcnt(0)", "s_nop 15", "s_nop 15"]
+        return s
+
+    def emit(self):
+        for tname, mn in (("F16", "v_mfma_f32_32x32x16_f16"), ("BF16", "v_mfma_f32_32x32x16_bf16")):
+            emit(f"PRISM_KLOOP_{tname}_{self.name}", self.text(mn))
+        regs = ", ".join(f'"v{r}"' for r in range(S_AA, self.last_v + 1)) + ", " + ", ".join(f'"s{r}"' for r in range(20, 29))
+        print(f"#define PRISM_KLOOP_CLOBBERS_{self.name} {regs}, \"scc\", \"memory\"")
+        print()
+
+
+#   name (tile, ring depth): accumulator tiles per wave, loads per wave and slice, tile, ring depth, B fragment offsets,
+#   k-steps per register set
+SMALL = [
+    Small("32x32_8", 1, 1, 4, 4, 32, 32, 8, [0], 4),
+    Small("64x32_6", 1, 1, 4, 2, 64, 32, 6, [0], 4),
+    Small("32x64_4", 1, 2, 4, 8, 32, 64, 4, [0, 4096], 4),
+    Small("64x64_5", 1, 2, 4, 4, 64, 64, 5, [0, 4096], 4),
+    Small("128x64_3", 1, 2, 4, 2, 128, 64, 3, [0, 4096], 4),
+    Small("128x128_3_PLAIN", 2, 2, 4, 4, 128, 128, 3, [0, 4096], 2),
+    Small("128x128_3_SWIGLU", 2, 2, 4, 4, 128, 128, 3, [0, 8192], 2),
+    Small("128x128_2_PLAIN", 2, 2, 4, 4, 128, 128, 2, [0, 4096], 2),
+    Small("128x128_2_SWIGLU", 2, 2, 4, 4, 128, 128, 2, [0, 8192], 2),
+]
+
+
 def emit(name, lines):
     print(f"#define {name} \\")
     for l in lines:
@@ -148,10 +272,10 @@ def emit(name, lines):
 
 def main():
     print("// Generated by gen_gemm_kloop.py - do not edit.  See that file for the schedule.")
-    print("// Operands: %0..%15 accumulators acc[i][j] (operand i*4+j, AGPRs); %16 / %17 LDS byte address of the lane's first")
-    print("// A / B fragment row (step 0, stage 0); %18 / %19 byte offset into A / W of the chunk this lane fetches in its wave's")
-    print("// first load instruction; %20 / %21 LDS byte address of the first row that instruction fills (stage 0, uniform);")
-    print("// %22 bytes between the rows of consecutive load instructions (8 rows); %23 / %24 base of A / W; %25 number of slices.")
+    print("// PRISM_KLOOP4_*: %0..%15 accumulators acc[i][j] (operand i*4+j, AGPRs); %16 / %17 LDS byte address of the lane's")
+    print("// first A / B fragment row (step 0, stage 0); %18..%25 / %26..%33 byte offset into A / W of the chunk this lane fetches")
+    print("// in each of its wave's load instructions; %34 / %35 LDS byte address of the first row the first of them fills (stage 0,")
+    print("// uniform); %36 / %37 base of A / W; %38 number of slices.  The other loops: the same order, with their own counts.")
     print()
     plain = [0, 4096, 8192, 12288]                 # B fragments: 4 consecutive 32-row blocks
     swiglu = [0, 4096, 16384, 20480]               # 2 gate blocks, then the 2 matching up blocks 128 rows further
@@ -159,6 +283,8 @@ def main():
         emit(f"PRISM_KLOOP4_{tname}_PLAIN", kloop(mn, plain))
         emit(f"PRISM_KLOOP4_{tname}_SWIGLU", kloop(mn, swiglu))
     regs = ", ".join(f'"v{r}"' for r in CLOBBER_V) + ", " + ", ".join(f'"s{r}"' for r in CLOBBER_S)
+    for c in SMALL:
+        c.emit()
     # m0 (written before every direct-to-LDS load) is not listed: the compiler reserves it, sets it right before each of
     # its own uses and never keeps a value in it across a statement; hipcc diagnoses it in a clobber list
     print(f"#define PRISM_KLOOP4_CLOBBERS {regs}, \"scc\", \"memory\"")

@@ -154,6 +154,36 @@ def test_gemm_16_rows_beyond_whole_rounds_go_to_small_tiles_with_the_same_bits(d
 
 
 @pytest.mark.parametrize("dtype", SIXTEEN)
+@pytest.mark.parametrize("epi", [B.EPI_RESIDUAL, B.EPI_SWIGLU, B.EPI_STORE_F32])
+@pytest.mark.parametrize("K", [64, 320, 704])
+def test_gemm_16_every_tile_size_gives_a_row_the_same_bits(dtype, epi, K):
+    """The launcher picks one of eight tiles by the number of rows (here from 32 x 32 for one row to 256 x 256); 1, 5 and 11
+    slices are fewer than, about and more than the stages of their rings.  N = 2 * 1048 leaves every tile's last column
+    tile ragged.  The largest launch against fp64, every smaller one bit for bit against its rows."""
+    N, M = 2096, 9001
+    A = _rand((M, K), dtype, 71 + K, 1.0).to(DEV)
+    Wt = _rand((N, K), dtype, 72 + K, 1.0 / math.sqrt(K)).to(DEV)
+    X0 = _rand((M, N), torch.float32, 73, 1.0).to(DEV)
+
+    def run(rows):
+        if epi == B.EPI_SWIGLU:
+            out = torch.full((rows, N // 2), 7.0, dtype=dtype, device=DEV)
+        else:
+            out = X0[:rows].clone() if epi == B.EPI_RESIDUAL else torch.full((rows, N), 7.0, dtype=torch.float32, device=DEV)
+        B.op_gemm(epi, A[:rows], Wt, out)
+        return out
+    whole = run(M)
+    ref = A.double() @ Wt.double().t().contiguous()
+    if epi == B.EPI_SWIGLU:
+        ref = torch.nn.functional.silu(ref[:, :N // 2]) * ref[:, N // 2:]
+        np.testing.assert_allclose(_f64(whole), _f64(ref), rtol=EPS16[dtype] * 1.01, atol=2e-3 * EPS16[dtype] * 256)
+    else:
+        np.testing.assert_allclose(_f64(whole), _f64(ref + X0.double() if epi == B.EPI_RESIDUAL else ref), rtol=1e-4, atol=1e-4)
+    for rows in (1, 31, 33, 64, 65, 100, 129, 200, 300, 513, 777, 1500, 2600, 4100):
+        assert torch.equal(run(rows), whole[:rows]), rows
+
+
+@pytest.mark.parametrize("dtype", SIXTEEN)
 def test_gemm_16_fp32_output(dtype):
     M, N, K = 700, 6144, 1024
     A, Wt = _rand((M, K), dtype, 5), _rand((N, K), dtype, 6, 1.0 / math.sqrt(K))
