@@ -99,8 +99,10 @@ struct QkvEpilogue {
   int nq, nkv, qk_norm;
   float eps;
 };
-static const int kEpiQkv = 4;   // internal epilogue code of launch_gemm_16_qkv
-bool gemm_16_qkv_supported(int M, int nq, int nkv, int hd, int K);
+static const int kEpiQkv = 4, kEpiQkvPairwise = 5;   // internal epilogue codes of launch_gemm_16_qkv: order of the norm's sum of squares
+bool gemm_16_qkv_supported(int nq, int nkv, int hd, int K);
+// at least 256 tiles of 256 x 256: from here on prism_op_qkv_project offers the fused form as a call of its own
+bool gemm_16_qkv_large(int M, int nq, int nkv);
 int launch_gemm_16_qkv(int dtype, const void *Xn, const void *Wqkv, int M, int K, int hd, const QkvEpilogue &e, hipStream_t s);
 
 // dst row dst_idx[i] (i itself if dst_idx is null) = src row src_idx[i], i < n; rows of row_bytes (a multiple of 16) bytes.  src may be pinned host
@@ -117,13 +119,14 @@ int launch_convert_bf16(const void *src, int64_t n, int dtype, void *dst, hipStr
 // cos/sin table for RoPE: tab[pos * (hd/2) + i] = (cos, sin)(pos * base^(-2i/hd)), evaluated in fp64; transposed:
 // tab[i * n_pos + pos]
 int launch_rope_table(float2 *tab, int n_pos, int head_dim, float rope_base, hipStream_t s, bool transposed = false);
-// q/k per-head RMSNorm + RoPE from the fp32 projection.  fp32 mode: in place (QK == nullptr).  bf16 mode:
-// q,k -> QK [T, (nq+nkv)*hd] bf16.
-int launch_qk_finish(int dtype, float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T,
-                     int nq, int nkv, int hd, float eps, int qk_norm, const float2 *rope_tab, void *QK, hipStream_t s);
-// v part of the fp32 projection -> Vt [nkv][hd][vt_stride], IEEE half (in bf16-operand mode: bf16-rounded values)
-int launch_v_finish(int dtype, const float *QKV, int T, int nq, int nkv, int hd, void *Vt, const int32_t *vt_col,
-                    int64_t vt_stride, hipStream_t s);
+// q/k per-head RMSNorm + RoPE from the fp32 projection, in place (fp32 mode)
+int launch_qk_finish_fp32(float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv, int hd,
+                          float eps, int qk_norm, const float2 *rope_tab, hipStream_t s);
+// 16-bit modes: q, k -> QK [T, (nq+nkv)*hd] in the operand type; v -> Vt [nkv][hd][vt_stride], IEEE half (in bf16-operand
+// mode: bf16-rounded values)
+int launch_qkv_finish_16(int dtype, const float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv,
+                         int hd, float eps, int qk_norm, const float2 *rope_tab, void *QK, void *Vt, const int32_t *vt_col,
+                         int64_t vt_stride, hipStream_t s);
 // Copies the V^T columns of a chunk's shared query (positions [0, ql): columns vt_column_of_key(position) of the chunk,
 // whose query sequence starts at column 0) into the column range of each of n_seq sequences (first columns seq_col0[i],
 // [device]); rows = nkv * hd rows of Vt.  Columns of positions >= ql are left alone.

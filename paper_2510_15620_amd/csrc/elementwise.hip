@@ -194,24 +194,109 @@ __global__ __launch_bounds__(256) void qk_finish_kernel(float *__restrict__ QKV,
   }
 }
 
-int launch_qk_finish(int dtype, float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T,
-                     int nq, int nkv, int hd, float eps, int qk_norm, const float2 *rope_tab, void *QK, hipStream_t s) {
+// The same and the V part in one launch, for the 16-bit modes at head_dim 128.  Launch- and latency-bound at the sizes it is
+// for (the fused projection serves large ones).  Blocks of 16 tokens x one group of 4 heads (y): q and k heads take 16 lanes
+// each, a lane holding 4 + 4 values of the two rotation halves as 16-byte loads of all its tokens issued together; V heads
+// (last y) go through LDS, 64 tokens at a time, and leave as 64 consecutive tokens of one d per wave instruction.
+// 0.6B shape, 1154 tokens: 37 us as two kernels that waited for each value in turn.
+template <typename T>
+__global__ __launch_bounds__(256) void qkv_finish_16_kernel(const float *__restrict__ QKV, const int32_t *__restrict__ pos,
+                                                            const T *__restrict__ q_gain, const T *__restrict__ k_gain, int n_tok,
+                                                            int nq, int nkv, float eps, int qk_norm,
+                                                            const float2 *__restrict__ rope_tab, T *__restrict__ out,
+                                                            f16 *__restrict__ Vt, const int32_t *__restrict__ vt_col, int64_t vt_stride) {
+  constexpr int HD = 128, kTok = 16;
+  typedef typename Mfma<T>::vec4 vec4;
+  __shared__ f16 tile[kTok * 4][HD + 2];
+  const int heads = nq + nkv, row = (nq + 2 * nkv) * HD, groups = (heads + 3) / 4;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if ((int)blockIdx.y < groups) {
+    const int h = blockIdx.y * 4 + (lane >> 4), i = (lane & 15) * 4;            // head, first of the lane's 4 rotation pairs
+    if (h >= heads) return;
+    const T *g = h < nq ? q_gain : k_gain;
+    vec4 ga, gb;
+    if (qk_norm) {
+      ga = *reinterpret_cast<const vec4 *>(g + i);
+      gb = *reinterpret_cast<const vec4 *>(g + i + 64);
+    }
+    constexpr int N = kTok / 4;                                                // tokens per wave
+    const int t0 = blockIdx.x * kTok + wave * N;
+    f32x4 a[N], b[N], c0[N], c1[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int t = t0 + k < n_tok ? t0 + k : n_tok - 1;
+      const float *x = QKV + (int64_t)t * row + h * HD + i;
+      a[k] = *reinterpret_cast<const f32x4 *>(x);
+      b[k] = *reinterpret_cast<const f32x4 *>(x + 64);
+      const f32x4 *cs = reinterpret_cast<const f32x4 *>(rope_tab + (int64_t)pos[t] * 64 + i);
+      c0[k] = cs[0];
+      c1[k] = cs[1];
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      float r = 1.f;
+      if (qk_norm) {
+        // pairs (d, d + 64), then halving over the bits of d, 32 first: the order of wave_sum with a pair per lane
+        float p[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          p[q] = __builtin_fmaf(a[k][q], a[k][q], b[k][q] * b[k][q]);
+#pragma unroll
+          for (int o = 8; o > 0; o >>= 1) p[q] += __shfl_xor(p[q], o, 64);
+        }
+        const float ss = (p[0] + p[2]) + (p[1] + p[3]);
+        r = 1.0f / sqrtf(ss / (float)HD + eps);
+      }
+      if (t0 + k >= n_tok) continue;
+      vec4 lo, hi;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float u = a[k][q], v = b[k][q];
+        if (qk_norm) {
+          u = u * r * to_f32(ga[q]);
+          v = v * r * to_f32(gb[q]);
+        }
+        const float c = q < 2 ? c0[k][2 * q] : c1[k][2 * q - 4], s = q < 2 ? c0[k][2 * q + 1] : c1[k][2 * q - 3];
+        lo[q] = from_f32<T>(__builtin_fmaf(u, c, -(v * s)));
+        hi[q] = from_f32<T>(__builtin_fmaf(v, c, u * s));
+      }
+      T *o = out + ((int64_t)(t0 + k) * heads + h) * HD + i;
+      *reinterpret_cast<vec4 *>(o) = lo;
+      *reinterpret_cast<vec4 *>(o + 64) = hi;
+    }
+    return;
+  }
+  // V: blocks of 64 tokens of one head
+  if (blockIdx.x % 4 != 0) return;
+  const int h = blockIdx.y - groups, t0 = blockIdx.x * kTok;
+  const float *src = QKV + (int64_t)(heads + h) * HD;
+  f32x4 v[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int r = k * 8 + (threadIdx.x >> 5), t = t0 + r < n_tok ? t0 + r : n_tok - 1;
+    v[k] = *reinterpret_cast<const f32x4 *>(src + (int64_t)t * row + (threadIdx.x & 31) * 4);
+  }
+  const int t = t0 + lane, col = t < n_tok ? vt_col[t] : 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      tile[k * 8 + (threadIdx.x >> 5)][(threadIdx.x & 31) * 4 + q] = from_f32<f16>(to_f32(from_f32<T>(v[k][q])));
+  __syncthreads();
+  if (t >= n_tok) return;
+  f16 *dst = Vt + (int64_t)h * HD * vt_stride + col;
+#pragma unroll 8
+  for (int d = wave; d < HD; d += 4) dst[(int64_t)d * vt_stride] = tile[lane][d];
+}
+
+int launch_qk_finish_fp32(float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv, int hd,
+                          float eps, int qk_norm, const float2 *rope_tab, hipStream_t s) {
   PRISM_REQUIRE(QKV && pos && rope_tab && T >= 0 && nq > 0 && nkv > 0 && hd > 0 && hd % 2 == 0, PRISM_EINVAL,
                 "qk_finish: bad arguments");
   PRISM_REQUIRE(!qk_norm || (q_gain && k_gain), PRISM_EINVAL, "qk_finish: gains missing");
-  PRISM_REQUIRE(dtype == PRISM_DTYPE_FP32 || QK, PRISM_EINVAL, "qk_finish: 16-bit modes need the QK output");
   if (T == 0) return PRISM_OK;
-  const int64_t items = (int64_t)T * (nq + nkv);
-  const int grid = cdiv(items, 4);
-  if (dtype == PRISM_DTYPE_FP32)
-    qk_finish_kernel<float><<<grid, 256, 0, s>>>(QKV, pos, (const float *)q_gain, (const float *)k_gain, T, nq, nkv, hd,
-                                                  eps, qk_norm, rope_tab, QKV, (nq + 2 * nkv) * hd);
-  else if (dtype == PRISM_DTYPE_BF16)
-    qk_finish_kernel<bf16><<<grid, 256, 0, s>>>(QKV, pos, (const bf16 *)q_gain, (const bf16 *)k_gain, T, nq, nkv, hd,
-                                                 eps, qk_norm, rope_tab, (bf16 *)QK, (nq + nkv) * hd);
-  else
-    qk_finish_kernel<f16><<<grid, 256, 0, s>>>(QKV, pos, (const f16 *)q_gain, (const f16 *)k_gain, T, nq, nkv, hd,
-                                                eps, qk_norm, rope_tab, (f16 *)QK, (nq + nkv) * hd);
+  qk_finish_kernel<float><<<cdiv((int64_t)T * (nq + nkv), 4), 256, 0, s>>>(QKV, pos, (const float *)q_gain, (const float *)k_gain, T, nq, nkv, hd,
+                                                                            eps, qk_norm, rope_tab, QKV, (nq + 2 * nkv) * hd);
   PRISM_HIP(hipGetLastError());
   return PRISM_OK;
 }
@@ -220,7 +305,7 @@ int launch_qk_finish(int dtype, float *QKV, const int32_t *pos, const void *q_ga
 // over keys, so the MFMA operand wants keys contiguous.  P V always runs on the f16 matrix-core
 // instruction (the probabilities keep 11 significand bits), so Vt is IEEE half; in bf16-operand mode
 // the values are rounded to bf16 first (half holds every bf16 value of normal half range exactly).
-// Tile of 64 tokens x hd through LDS.
+// Tile of 64 tokens x hd through LDS.  Serves head sizes other than 128 (and unaligned buffers).
 template <typename OT>
 __global__ __launch_bounds__(256) void v_finish_kernel(const float *__restrict__ QKV, int n_tok, int nq, int nkv, int hd,
                                                        f16 *__restrict__ Vt, const int32_t *__restrict__ vt_col,
@@ -240,14 +325,28 @@ __global__ __launch_bounds__(256) void v_finish_kernel(const float *__restrict__
   }
 }
 
-int launch_v_finish(int dtype, const float *QKV, int T, int nq, int nkv, int hd, void *Vt, const int32_t *vt_col,
-                    int64_t vt_stride, hipStream_t s) {
-  PRISM_REQUIRE(QKV && Vt && vt_col && T >= 0 && hd > 0 && hd <= 128 && is16(dtype), PRISM_EINVAL, "v_finish: bad arguments");
+int launch_qkv_finish_16(int dtype, const float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv,
+                         int hd, float eps, int qk_norm, const float2 *rope_tab, void *QK, void *Vt, const int32_t *vt_col,
+                         int64_t vt_stride, hipStream_t s) {
+  PRISM_REQUIRE(QKV && pos && rope_tab && QK && Vt && vt_col && T >= 0 && nq > 0 && nkv > 0 && is16(dtype) && hd > 0 && hd <= 128, PRISM_EINVAL,
+                "qkv_finish: bad arguments");
+  PRISM_REQUIRE(!qk_norm || (q_gain && k_gain), PRISM_EINVAL, "qk_finish: gains missing");
   if (T == 0) return PRISM_OK;
-  if (dtype == PRISM_DTYPE_BF16)
-    v_finish_kernel<bf16><<<dim3(cdiv(T, 64), nkv), 256, 0, s>>>(QKV, T, nq, nkv, hd, (f16 *)Vt, vt_col, vt_stride);
-  else
-    v_finish_kernel<f16><<<dim3(cdiv(T, 64), nkv), 256, 0, s>>>(QKV, T, nq, nkv, hd, (f16 *)Vt, vt_col, vt_stride);
+  auto run = [&](auto tag) {
+    typedef decltype(tag) OT;
+    const OT *gq = (const OT *)q_gain, *gk = (const OT *)k_gain;
+    // one launch where every access of four values is aligned; otherwise value by value
+    if (hd == 128 && ((uintptr_t)QKV | (uintptr_t)rope_tab) % 16 == 0 && ((uintptr_t)QK | (qk_norm ? (uintptr_t)gq | (uintptr_t)gk : 0)) % 8 == 0) {
+      qkv_finish_16_kernel<OT><<<dim3(cdiv(T, 16), (nq + nkv + 3) / 4 + nkv), 256, 0, s>>>(QKV, pos, gq, gk, T, nq, nkv, eps, qk_norm, rope_tab,
+                                                                                        (OT *)QK, (f16 *)Vt, vt_col, vt_stride);
+      return;
+    }
+    qk_finish_kernel<OT><<<cdiv((int64_t)T * (nq + nkv), 4), 256, 0, s>>>(const_cast<float *>(QKV), pos, gq, gk, T, nq, nkv, hd, eps, qk_norm, rope_tab,
+                                                                          (OT *)QK, (nq + nkv) * hd);
+    v_finish_kernel<OT><<<dim3(cdiv(T, 64), nkv), 256, 0, s>>>(QKV, T, nq, nkv, hd, (f16 *)Vt, vt_col, vt_stride);
+  };
+  if (dtype == PRISM_DTYPE_BF16) run(bf16{});
+  else run(f16{});
   PRISM_HIP(hipGetLastError());
   return PRISM_OK;
 }

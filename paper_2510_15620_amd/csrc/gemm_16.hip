@@ -42,6 +42,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
                                                                const OT *__restrict__ W, void *__restrict__ out_,
                                                                int M, int N, int K, int nM, int nN, QkvEpilogue qe) {
   constexpr int NW = WM * WN;
+  constexpr bool kHeads = EPI == kEpiQkv || EPI == kEpiQkvPairwise;
   constexpr int WMT = BM / WM, WNT = BN / WN;      // wave tile
   constexpr int TM = WMT / 32, TN = WNT / 32;      // 32x32 accumulator tiles per wave
   // one direct-to-LDS instruction of a wave moves 64 x 16 B = 8 tile rows
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     }
   };
 
-  if constexpr (EPI == kEpiQkv) {
+  if constexpr (kHeads) {
     // The wave's 128 columns are one head.  A row's 128 values sit in lanes l and l ^ 32 (64 each); the rotate-half
     // partner of column d is d + 64 = the same register of accumulator tile j + 2, so the per-head RMSNorm (one
     // cross-lane add), the rotation and the single rounding all happen on the accumulators.  What the memory path
@@ -245,6 +246,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
               cs[i & 1][j][g][q] = (qe.rope_tab_t + (int64_t)(j * 32 + g * 8 + q) * qe.rope_stride)[lane_off[i]];
       };
       load_cs(0);
+      constexpr bool kPairwise = EPI == kEpiQkvPairwise;
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int row0 = m0 + wm * WMT + i * 32;
@@ -252,14 +254,34 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
         float r = 1.f;
         if (qe.qk_norm) {
           float ss = 0.f;
+          if (kPairwise) {
+            // the finishing kernel's order: column pairs (d, d + 64), then halving over the bits of d, 32 first
+            float p[4];
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+            for (int q = 0; q < 4; ++q) {
+              float h[2];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-              const float v = AC(i, j, e);
-              ss += v * v;
+              for (int g = 0; g < 2; ++g) {
+                auto pair = [&](int j, int gg) __attribute__((always_inline)) {
+                  const float a = AC(i, j, gg * 4 + q), b = AC(i, j + 2, gg * 4 + q);
+                  return __builtin_fmaf(a, a, b * b);
+                };
+                h[g] = (pair(0, g) + pair(1, g)) + (pair(0, g + 2) + pair(1, g + 2));
+              }
+              p[q] = h[0] + h[1];
+              p[q] += __shfl_xor(p[q], 32);
             }
-          ss += __shfl_xor(ss, 32);
+            ss = (p[0] + p[2]) + (p[1] + p[3]);
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) {
+                const float v = AC(i, j, e);
+                ss += v * v;
+              }
+            ss += __shfl_xor(ss, 32);
+          }
           r = 1.0f / sqrtf(ss / 128.f + qe.eps);
         }
 #pragma unroll
@@ -276,8 +298,8 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
                 a = a * r * to_f32(ga[j][g][q]);
                 b = b * r * to_f32(gb[j][g][q]);
               }
-              lo[q] = from_f32<OT>(a * c.x - b * c.y);
-              hi[q] = from_f32<OT>(b * c.x + a * c.y);
+              lo[q] = from_f32<OT>(__builtin_fmaf(a, c.x, -(b * c.y)));
+              hi[q] = from_f32<OT>(kPairwise ? __builtin_fmaf(b, c.x, a * c.y) : __builtin_fmaf(a, c.y, b * c.x));
             }
             put16(m_in, d, lo);
             put16(m_in, d + 64, hi);
@@ -374,7 +396,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   }
 
   // ---- ragged last column tile (N not a multiple of the tile, or rows not 16-byte aligned): element by element
-  if constexpr (EPI != kEpiQkv) {
+  if constexpr (!kHeads) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int row = m0 + wm * WMT + i * 32 + m_in;
@@ -412,6 +434,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
 #define PRISM_ACC1 "+a"(acc[0][0])
 #define PRISM_ACC2 PRISM_ACC1, "+a"(acc[0][1])
 #define PRISM_ACC4 PRISM_ACC2, "+a"(acc[1][0]), "+a"(acc[1][1])
+#define PRISM_ACC1x4 PRISM_ACC2, "+a"(acc[0][2]), "+a"(acc[0][3])
 #define PRISM_G2(g) "v"(g[0]), "v"(g[1])
 #define PRISM_G4(g) PRISM_G2(g), "v"(g[2]), "v"(g[3])
 #define PRISM_G8(g) PRISM_G4(g), "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7])
@@ -424,7 +447,11 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
       asm volatile(PRISM_KLOOP_BF16_##NAME : ACC : "v"(aA0), "v"(aB0), GA(gA), GB(gB), "s"(ldsA_w), "s"(ldsB_w),        \
                    "s"(baseA), "s"(baseB), "s"(nk) : PRISM_KLOOP_CLOBBERS_##NAME);                                      \
   } while (0)
-    if constexpr (BM == 32 && BN == 32) PRISM_RUN_SMALL(32x32_8, PRISM_ACC1, PRISM_G4, PRISM_G4);
+    if constexpr (kHeads) {
+      if constexpr (BM == 64) PRISM_RUN_SMALL(64x128_3_HEAD, PRISM_ACC1x4, PRISM_G4, PRISM_G8);
+      else if constexpr (S == 3) PRISM_RUN_SMALL(128x128_3_HEAD, PRISM_ACC1x4, PRISM_G4, PRISM_G4);
+      else PRISM_RUN_SMALL(128x128_2_HEAD, PRISM_ACC1x4, PRISM_G4, PRISM_G4);
+    } else if constexpr (BM == 32 && BN == 32) PRISM_RUN_SMALL(32x32_8, PRISM_ACC1, PRISM_G4, PRISM_G4);
     else if constexpr (BM == 64 && BN == 32) PRISM_RUN_SMALL(64x32_6, PRISM_ACC1, PRISM_G4, PRISM_G2);
     else if constexpr (BM == 32 && BN == 64) PRISM_RUN_SMALL(32x64_4, PRISM_ACC2, PRISM_G4, PRISM_G8);
     else if constexpr (BM == 64 && BN == 64) PRISM_RUN_SMALL(64x64_5, PRISM_ACC2, PRISM_G4, PRISM_G4);
@@ -497,24 +524,45 @@ enum { kTile256, kTile128, kTile128Deep, kTile128x64, kTile64, kTile32x64, kTile
 static constexpr TileCost kTileCost[kTileKinds] = {
     {256, 256, 1, 1.53f, 1.53f, 9.2f}, {128, 128, 2, 0.72f, 0.50f, 4.5f}, {128, 128, 1, 0.52f, 0.52f, 3.4f}, {128, 64, 2, 0.34f, 0.36f, 2.3f},
     {64, 64, 2, 0.204f, 0.204f, 2.1f}, {32, 64, 3, 0.176f, 0.149f, 2.4f}, {64, 32, 2, 0.128f, 0.128f, 2.3f}, {32, 32, 2, 0.106f, 0.083f, 2.6f}};
+// The fused q/k/v projection: tiles whose waves own whole heads (fitted to 34 launches of 1 to 12000 rows).  Its epilogue
+// is longer: two dependent loads (position, rotation) and the per-head arithmetic.  391 x 4096 x 1024: 11 us, where the
+// projection to fp32 and its two finishing kernels took 48; 777 x 6144 x 4096: 56.
+enum { kHead256, kHead128, kHead128Deep, kHead64, kHeadKinds };
+static constexpr TileCost kHeadCost[kHeadKinds] = {
+    {256, 256, 1, 1.53f, 1.53f, 20.f}, {128, 128, 2, 0.70f, 0.55f, 5.5f}, {128, 128, 1, 0.52f, 0.52f, 5.0f}, {64, 128, 2, 0.29f, 0.37f, 5.0f}};
 
-static double tile_cost(int kind, int64_t M, int64_t ncols, int K, bool glu) {
-  const TileCost &t = kTileCost[kind];
-  const int64_t tiles = (M + t.bm - 1) / t.bm * ((ncols + (glu ? t.bn / 2 : t.bn) - 1) / (glu ? t.bn / 2 : t.bn)), n = (tiles + 255) / 256;
+static double tile_cost(const TileCost &t, int64_t M, int64_t ncols, int K, bool glu) {
+  const int bn = glu ? t.bn / 2 : t.bn;
+  const int64_t tiles = (M + t.bm - 1) / t.bm * ((ncols + bn - 1) / bn), n = (tiles + 255) / 256;
   const int64_t full = n / t.occ, rest = n % t.occ;
   const double slice = full * std::max(t.alone, t.shared * t.occ) + (rest ? std::max(t.alone, t.shared * rest) : 0.f);
   return (K / BK) * slice + (double)((n + t.occ - 1) / t.occ) * t.fixed;
 }
 
-static int best_tile(int64_t M, int64_t ncols, int K, bool glu, double *cost) {
-  int best = kTile256;
-  *cost = tile_cost(kTile256, M, ncols, K, glu);
-  for (int k = 1; k < kTileKinds; ++k) {
-    if (glu && kTileCost[k].bn == 32) continue;          // SwiGLU pairs a gate and an up tile in a wave
-    const double c = tile_cost(k, M, ncols, K, glu);
-    if (c < *cost) { *cost = c; best = k; }
+// What a launch of M rows runs: rows_big rows (whole 256-row tiles, possibly none) on tile kind 0, the rest on kind `kind`.
+struct TilePlan { int rows_big, kind; };
+static TilePlan plan_tiles(const TileCost *costs, int kinds, int M, int ncols, int K, bool glu) {
+  auto best = [&](int rows, double *cost) {
+    int at = 0;
+    *cost = tile_cost(costs[0], rows, ncols, K, glu);
+    for (int k = 1; k < kinds; ++k) {
+      if (glu && costs[k].bn == 32) continue;              // SwiGLU pairs a gate and an up tile in a wave
+      const double c = tile_cost(costs[k], rows, ncols, K, glu);
+      if (c < *cost) { *cost = c; at = k; }
+    }
+    return at;
+  };
+  double whole, rest;
+  TilePlan p{0, best(M, &whole)};
+  // The last round of big tiles may fill only a few compute units at a whole tile's price: then the row tiles that fill
+  // whole rounds go to the big tile and the remaining rows to a second launch with whatever suits them.
+  const int nN = cdiv(ncols, glu ? 128 : 256), nM = cdiv(M, 256);
+  const int rows_big = (int)std::min<int64_t>(nM, ((int64_t)nM * nN / 256) * 256 / nN) * 256;
+  if (rows_big > 0 && rows_big < M) {
+    const int kind = best(M - rows_big, &rest);
+    if (kind != 0 && tile_cost(costs[0], rows_big, ncols, K, glu) + rest < 0.98 * whole) p = {rows_big, kind};
   }
-  return best;
+  return p;
 }
 
 template <typename OT, int EPI>
@@ -537,26 +585,13 @@ static int launch_kind(int kind, const OT *A, const OT *W, void *out, int M, int
 
 template <typename OT, int EPI>
 static int launch_epi(const OT *A, const OT *W, void *out, int M, int N, int K, hipStream_t s) {
-  if (M == 0) return PRISM_OK;
   constexpr bool kGlu = EPI == PRISM_EPI_SWIGLU;
+  constexpr size_t out_elem = EPI == PRISM_EPI_RESIDUAL || EPI == PRISM_EPI_STORE_F32 ? 4 : 2;
   const int ncols = kGlu ? N / 2 : N;
-  double cost;
-  const int kind = best_tile(M, ncols, K, kGlu, &cost);
-  // The last round of big tiles may fill only a few compute units at a whole tile's price: then the row tiles that fill
-  // whole rounds go to the big tile and the remaining rows to a second launch with whatever suits them.
-  const int nN = cdiv(ncols, kGlu ? 128 : 256), nM = cdiv(M, 256);
-  const int rows_big = (int)std::min<int64_t>(nM, ((int64_t)nM * nN / 256) * 256 / nN) * 256;
-  if (rows_big > 0 && rows_big < M) {
-    double rest;
-    const int rest_kind = best_tile(M - rows_big, ncols, K, kGlu, &rest);
-    if (rest_kind != kTile256 && tile_cost(kTile256, rows_big, ncols, K, kGlu) + rest < 0.98 * cost) {
-      constexpr size_t out_elem = EPI == PRISM_EPI_RESIDUAL || EPI == PRISM_EPI_STORE_F32 ? 4 : 2;
-      PRISM_TRY((launch_kind<OT, EPI>(kTile256, A, W, out, rows_big, N, K, s)));
-      return launch_kind<OT, EPI>(rest_kind, A + (size_t)rows_big * K, W, reinterpret_cast<char *>(out) + (size_t)rows_big * ncols * out_elem,
-                                  M - rows_big, N, K, s);
-    }
-  }
-  return launch_kind<OT, EPI>(kind, A, W, out, M, N, K, s);
+  const TilePlan p = plan_tiles(kTileCost, kTileKinds, M, ncols, K, kGlu);
+  if (p.rows_big > 0) PRISM_TRY((launch_kind<OT, EPI>(kTile256, A, W, out, p.rows_big, N, K, s)));
+  return launch_kind<OT, EPI>(p.kind, A + (size_t)p.rows_big * K, W, reinterpret_cast<char *>(out) + (size_t)p.rows_big * ncols * out_elem,
+                              M - p.rows_big, N, K, s);
 }
 
 template <typename OT>
@@ -595,34 +630,63 @@ int launch_gemm_16(int dtype, int epilogue, const void *A, const void *W, void *
   return PRISM_OK;
 }
 
-bool gemm_16_qkv_supported(int M, int nq, int nkv, int hd, int K) {
-  // one head per wavefront of the 256 x 256 tile; smaller problems take the unfused path
-  return hd == 128 && nq > 0 && nkv > 0 && (nq + 2 * nkv) % 2 == 0 && K > 0 && K % BK == 0 &&
-         (int64_t)cdiv(M, 256) * ((nq + 2 * nkv) / 2) >= 256;
+bool gemm_16_qkv_large(int M, int nq, int nkv) {
+  return (nq + 2 * nkv) % 2 == 0 && (int64_t)cdiv(M, 256) * ((nq + 2 * nkv) / 2) >= 256;
+}
+
+bool gemm_16_qkv_supported(int nq, int nkv, int hd, int K) {
+  return hd == 128 && nq > 0 && nkv > 0 && K > 0 && K % BK == 0;          // one head per wavefront
+}
+
+template <typename OT, int EPI>
+static int launch_head(int kind, const QkvEpilogue &e, const OT *A, const OT *W, int M, int N, int K, hipStream_t s) {
+  switch (kind) {
+    case kHead256: return launch_cfg<OT, 256, 256, 2, 2, EPI, 2>(A, W, e.QK, M, N, K, s, e);
+    case kHead128: return launch_cfg<OT, 128, 128, 4, 1, EPI, 2>(A, W, e.QK, M, N, K, s, e);
+    case kHead128Deep: return launch_cfg<OT, 128, 128, 4, 1, EPI, 3>(A, W, e.QK, M, N, K, s, e);
+    default: return launch_cfg<OT, 64, 128, 2, 1, EPI, 3>(A, W, e.QK, M, N, K, s, e);
+  }
+}
+
+template <typename OT, int EPI>
+static int launch_qkv_typed(const QkvEpilogue &e, const OT *A, const OT *W, int M, int N, int K, hipStream_t s) {
+  const int step = rows_per_launch(K);
+  // an odd number of heads leaves half a 256-wide tile outside the matrix, and that tile's epilogue has no column guard
+  const bool wide = (e.nq + 2 * e.nkv) % 2 == 0;
+  auto rows_on = [&](int kind, int m0, int rows) {             // every per-row array moves with the rows
+    QkvEpilogue p = e;
+    p.pos += m0;
+    p.vt_col += m0;
+    p.QK = reinterpret_cast<char *>(e.QK) + (size_t)m0 * (e.nq + e.nkv) * 128 * 2;
+    return launch_head<OT, EPI>(kind, p, A + (size_t)m0 * K, W, rows, N, K, s);
+  };
+  for (int m0 = 0; m0 < M; m0 += step) {
+    const int rows = std::min(step, M - m0);
+    TilePlan p = plan_tiles(kHeadCost, kHeadKinds, rows, N, K, false);
+    if (!wide && (p.rows_big > 0 || p.kind == kHead256)) p = {0, kHead128};
+    if (p.rows_big > 0) PRISM_TRY(rows_on(kHead256, m0, p.rows_big));
+    PRISM_TRY(rows_on(p.kind, m0 + p.rows_big, rows - p.rows_big));
+  }
+  return PRISM_OK;
 }
 
 int launch_gemm_16_qkv(int dtype, const void *Xn, const void *Wqkv, int M, int K, int hd, const QkvEpilogue &e, hipStream_t s) {
   PRISM_REQUIRE(Xn && Wqkv && M >= 0 && is16(dtype) && e.pos && e.vt_col && e.rope_tab_t && e.rope_stride > 0 && e.QK && e.Vt, PRISM_EINVAL,
                 "qkv gemm: bad arguments");
   PRISM_REQUIRE(!e.qk_norm || (e.q_gain && e.k_gain), PRISM_EINVAL, "qkv gemm: gains missing");
-  PRISM_REQUIRE(gemm_16_qkv_supported(M, e.nq, e.nkv, hd, K), PRISM_EUNSUPPORTED, "qkv gemm: shape not supported by the fused epilogue");
+  PRISM_REQUIRE(gemm_16_qkv_supported(e.nq, e.nkv, hd, K), PRISM_EUNSUPPORTED, "qkv gemm: shape not supported by the fused epilogue");
   const int N = (e.nq + 2 * e.nkv) * 128;
   PRISM_REQUIRE((int64_t)N * K * 2 < ((int64_t)1 << 32) && (int64_t)256 * K * 2 < ((int64_t)1 << 32), PRISM_EUNSUPPORTED,
                 "qkv gemm: the weight operand exceeds 4 GiB");
-  const int step = rows_per_launch(K);
-  for (int m0 = 0; m0 < M; m0 += step) {
-    const int rows = std::min(step, M - m0);
-    QkvEpilogue p = e;                       // row panel: every per-row array moves with the rows
-    p.pos = e.pos + m0;
-    p.vt_col = e.vt_col + m0;
-    p.QK = reinterpret_cast<char *>(e.QK) + (size_t)m0 * (e.nq + e.nkv) * 128 * 2;
-    const char *a = reinterpret_cast<const char *>(Xn) + (size_t)m0 * K * 2;
-    if (dtype == PRISM_DTYPE_BF16)
-      PRISM_TRY((launch_cfg<bf16, 256, 256, 2, 2, kEpiQkv, 2>((const bf16 *)a, (const bf16 *)Wqkv, p.QK, rows, N, K, s, p)));
-    else
-      PRISM_TRY((launch_cfg<f16, 256, 256, 2, 2, kEpiQkv, 2>((const f16 *)a, (const f16 *)Wqkv, p.QK, rows, N, K, s, p)));
-  }
-  return PRISM_OK;
+  // Below the size where prism_op_qkv_project is offered, a caller composes prism_op_gemm and prism_op_qkv_finish; the
+  // projection gives the bits of that composition there, and those of prism_op_qkv_project above.
+  const bool pairwise = !gemm_16_qkv_large(M, e.nq, e.nkv);
+  auto run = [&](auto tag) {
+    typedef decltype(tag) OT;
+    return pairwise ? launch_qkv_typed<OT, kEpiQkvPairwise>(e, (const OT *)Xn, (const OT *)Wqkv, M, N, K, s)
+                    : launch_qkv_typed<OT, kEpiQkv>(e, (const OT *)Xn, (const OT *)Wqkv, M, N, K, s);
+  };
+  return dtype == PRISM_DTYPE_BF16 ? run(bf16{}) : run(f16{});
 }
 
 }  // namespace prism

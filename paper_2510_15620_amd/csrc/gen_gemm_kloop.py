@@ -259,6 +259,10 @@ SMALL = [
     Small("128x128_3_SWIGLU", 2, 2, 4, 4, 128, 128, 3, [0, 8192], 2),
     Small("128x128_2_PLAIN", 2, 2, 4, 4, 128, 128, 2, [0, 4096], 2),
     Small("128x128_2_SWIGLU", 2, 2, 4, 4, 128, 128, 2, [0, 8192], 2),
+    # q/k/v projection: a wave owns the 128 columns of one head
+    Small("64x128_3_HEAD", 1, 4, 4, 8, 64, 128, 3, [0, 4096, 8192, 12288], 2),
+    Small("128x128_3_HEAD", 1, 4, 4, 4, 128, 128, 3, [0, 4096, 8192, 12288], 2),
+    Small("128x128_2_HEAD", 1, 4, 4, 4, 128, 128, 2, [0, 4096, 8192, 12288], 2),
 ]
 
 

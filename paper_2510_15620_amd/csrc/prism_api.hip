@@ -113,7 +113,7 @@ struct prism_ctx {
   std::vector<Span> spans;
   bool profiling = false;
   int span_mask = ~0;                             // kinds that get event spans while profiling
-  float2 *rope_tab = nullptr, *rope_tab_t = nullptr;   // [pos][i] for the stand-alone finishing kernel, [i][pos] for the fused epilogue
+  float2 *rope_tab = nullptr, *rope_tab_t = nullptr;   // [pos][i] for the finishing kernel of the fp32 mode, [i][pos] for the fused epilogue
 
   // scratch, grown on demand
   float *X[2] = {nullptr, nullptr};
@@ -592,12 +592,13 @@ static int ensure_scratch(prism_ctx *c, const Plan &p, bool need_second_x, int n
     PRISM_HIP(hipStreamSynchronize(c->stream));
     const int64_t old = c->chunk_cap, cap = p.max_chunk_tokens;
     const bool bf = is16(c->op);
-    dev_free(c, c->Xn, (size_t)old * m.hidden * e); dev_free(c, c->QKV, (size_t)old * (Dq + 2 * Dkv) * 4);
+    dev_free(c, c->Xn, (size_t)old * m.hidden * e);
+    if (!bf) dev_free(c, c->QKV, (size_t)old * (Dq + 2 * Dkv) * 4);
     if (bf) dev_free(c, c->QK, (size_t)old * (Dq + Dkv) * e);
     dev_free(c, c->AO, (size_t)old * Dq * e); dev_free(c, c->S, (size_t)old * m.ffn * e);
     c->Xn = c->QKV = c->QK = c->AO = c->S = nullptr; c->chunk_cap = 0;
     PRISM_TRY(dev_alloc(c, (void **)&c->Xn, (size_t)cap * m.hidden * e));
-    PRISM_TRY(dev_alloc(c, (void **)&c->QKV, (size_t)cap * (Dq + 2 * Dkv) * 4));     // fp32 projection
+    if (!bf) PRISM_TRY(dev_alloc(c, (void **)&c->QKV, (size_t)cap * (Dq + 2 * Dkv) * 4));   // fp32 mode: the projection
     if (bf) PRISM_TRY(dev_alloc(c, (void **)&c->QK, (size_t)cap * (Dq + Dkv) * e));   // finished q, k
     PRISM_TRY(dev_alloc(c, (void **)&c->AO, (size_t)cap * Dq * e));
     PRISM_TRY(dev_alloc(c, (void **)&c->S, (size_t)cap * m.ffn * e));
@@ -844,27 +845,20 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
     // ---- attention block: X += Attn(RMSNorm(X)) Wo^T
     if (!resume) {
     PRISM_TRY(timed_span(c, 5, 0.0, [&] { return launch_rmsnorm(Xc, wbuf + L.attn_norm, Tc, H, m.rms_eps, c->op, c->Xn, s); }));
-    // 16-bit modes at head_dim 128 with enough rows: norm, RoPE, rounding and the V transposition happen in the
-    // projection's epilogue; otherwise the projection is stored in fp32 and finished by separate kernels
-    const bool fused_qkv = bf && gemm_16_qkv_supported(Tc, m.n_q_heads, m.n_kv_heads, m.head_dim, H);
+    // 16-bit modes: norm, RoPE, rounding and the V transposition happen in the projection's epilogue (0.6B shape, 391
+    // rows: 11 us, where the projection to fp32 and two finishing kernels took 48); fp32 mode finishes the projection in place
     PRISM_TRY(timed_span(c, 0, tk * (Dq + 2 * Dkv) * H, [&] {
-      if (fused_qkv) {
-        QkvEpilogue e;
-        e.pos = pos; e.vt_col = c->d_meta + mo.vtcol + ch.r0;
-        e.q_gain = wbuf + L.q_norm; e.k_gain = wbuf + L.k_norm;
-        e.rope_tab_t = c->rope_tab_t; e.rope_stride = PRISM_MAX_SEQ; e.QK = c->QK; e.Vt = c->Vt; e.vt_stride = c->vt_cap;
-        e.nq = m.n_q_heads; e.nkv = m.n_kv_heads; e.qk_norm = m.qk_norm; e.eps = m.rms_eps;
-        return launch_gemm_16_qkv(c->op, c->Xn, wbuf + L.wqkv, Tc, H, m.head_dim, e, s);
-      }
-      return gemm(bf ? PRISM_EPI_STORE_F32 : PRISM_EPI_STORE, c->Xn, wbuf + L.wqkv, c->QKV, Tc, Dq + 2 * Dkv, H);
+      if (!bf) return gemm(PRISM_EPI_STORE, c->Xn, wbuf + L.wqkv, c->QKV, Tc, Dq + 2 * Dkv, H);
+      QkvEpilogue e;
+      e.pos = pos; e.vt_col = c->d_meta + mo.vtcol + ch.r0;
+      e.q_gain = wbuf + L.q_norm; e.k_gain = wbuf + L.k_norm;
+      e.rope_tab_t = c->rope_tab_t; e.rope_stride = PRISM_MAX_SEQ; e.QK = c->QK; e.Vt = c->Vt; e.vt_stride = c->vt_cap;
+      e.nq = m.n_q_heads; e.nkv = m.n_kv_heads; e.qk_norm = m.qk_norm; e.eps = m.rms_eps;
+      return launch_gemm_16_qkv(c->op, c->Xn, wbuf + L.wqkv, Tc, H, m.head_dim, e, s);
     }, Tc));
-    if (!fused_qkv) PRISM_TRY(timed_span(c, 5, 0.0, [&] {
-      PRISM_TRY(launch_qk_finish(c->op, (float *)c->QKV, pos, wbuf + L.q_norm, wbuf + L.k_norm, Tc, m.n_q_heads,
-                                 m.n_kv_heads, m.head_dim, m.rms_eps, m.qk_norm, c->rope_tab, c->QK, s));
-      if (bf)
-        PRISM_TRY(launch_v_finish(c->op, (const float *)c->QKV, Tc, m.n_q_heads, m.n_kv_heads, m.head_dim, c->Vt,
-                                  c->d_meta + mo.vtcol + ch.r0, c->vt_cap, s));
-      return (int)PRISM_OK;
+    if (!bf) PRISM_TRY(timed_span(c, 5, 0.0, [&] {
+      return launch_qk_finish_fp32((float *)c->QKV, pos, wbuf + L.q_norm, wbuf + L.k_norm, Tc, m.n_q_heads, m.n_kv_heads, m.head_dim,
+                                   m.rms_eps, m.qk_norm, c->rope_tab, s);
     }));
     if (p.ql > 0)   // every sequence's V^T columns cover all its positions: the query's part is copied in (a few MB)
       PRISM_TRY(timed_span(c, 5, 0.0, [&] {
@@ -1370,10 +1364,11 @@ extern "C" int prism_op_qkv_finish(int32_t dtype, void *QKV, const int32_t *pos,
   TmpDev tab;
   PRISM_TRY(tab.alloc((size_t)max_pos * (head_dim / 2) * sizeof(float2)));
   PRISM_TRY(launch_rope_table((float2 *)tab.p, max_pos, head_dim, rope_base, s));
-  PRISM_TRY(launch_qk_finish(dtype, (float *)QKV, pos, q_gain, k_gain, T, n_q_heads, n_kv_heads, head_dim, eps, qk_norm,
-                             (const float2 *)tab.p, QK, s));
   if (is16(dtype))
-    PRISM_TRY(launch_v_finish(dtype, (const float *)QKV, T, n_q_heads, n_kv_heads, head_dim, Vt, vt_col, vt_stride, s));
+    PRISM_TRY(launch_qkv_finish_16(dtype, (const float *)QKV, pos, q_gain, k_gain, T, n_q_heads, n_kv_heads, head_dim, eps, qk_norm,
+                                   (const float2 *)tab.p, QK, Vt, vt_col, vt_stride, s));
+  else
+    PRISM_TRY(launch_qk_finish_fp32((float *)QKV, pos, q_gain, k_gain, T, n_q_heads, n_kv_heads, head_dim, eps, qk_norm, (const float2 *)tab.p, s));
   PRISM_HIP(hipStreamSynchronize(s));   // the table is freed on return
   return PRISM_OK;
 }
@@ -1384,7 +1379,7 @@ extern "C" int prism_op_qkv_project(int32_t dtype, const void *Xn, const void *W
                                     void *QK, void *Vt, const int32_t *vt_col, int64_t vt_stride, void *stream) {
   PRISM_REQUIRE(max_pos > 0 && max_pos <= PRISM_MAX_SEQ, PRISM_EINVAL, "qkv_project: max_pos");
   PRISM_REQUIRE(is16(dtype) && Xn && Wqkv && pos && QK && Vt && vt_col && vt_stride > 0 && T >= 0, PRISM_EINVAL, "qkv_project: bad arguments");
-  PRISM_REQUIRE(gemm_16_qkv_supported(T, n_q_heads, n_kv_heads, head_dim, hidden), PRISM_EUNSUPPORTED,
+  PRISM_REQUIRE(gemm_16_qkv_supported(n_q_heads, n_kv_heads, head_dim, hidden) && gemm_16_qkv_large(T, n_q_heads, n_kv_heads), PRISM_EUNSUPPORTED,
                 "qkv_project: needs head_dim 128, hidden a multiple of 64 and at least 256 tiles of 256 x 256 "
                 "(use prism_op_gemm + prism_op_qkv_finish otherwise)");
   hipStream_t s = (hipStream_t)stream;

@@ -8,6 +8,8 @@ import torch
 
 from oracle import prism_oracle as O
 from paper_2510_15620_amd import binding as B
+from paper_2510_15620_amd import workloads as W
+from tests.helpers import oracle_model, oracle_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -432,3 +434,28 @@ def test_compact_and_topk():
     order = O.rank_order(s.astype(np.float64))[:4]
     assert pos.cpu().numpy().tolist() == order.tolist() == [5, 1, 3, 6]
     assert np.array_equal(sc.cpu().numpy(), s[order])
+
+
+@pytest.mark.parametrize("dtype", SIXTEEN)
+@pytest.mark.parametrize("nq,nkv,lens", [(32, 8, [700, 1, 1024, 64, 911]), (16, 8, [33, 1, 400]), (3, 3, [70, 5]), (1, 1, [513, 2])])
+def test_projection_of_a_whole_call_at_every_tile_size(dtype, nq, nkv, lens):
+    """The fused projection of a select runs at every size (tiles of 64, 128 or 256 rows; an odd number of heads keeps to the
+    128-wide ones).  Against the oracle through one layer: the final scores see every query, key and value."""
+    hd, H = 128, 256
+    m = W.ModelShape(1, H, nq, nkv, hd, 256, 64, "bf16")
+    d = torch.Generator().manual_seed(9)
+    draw = lambda *s, std=0.05: (torch.randn(*s, generator=d) * std).to(torch.bfloat16)
+    lw = {n: ((1 + draw(s[0])).to(torch.bfloat16) if len(s) == 1 else draw(*s)) for n, s in W.layer_tensor_shapes(m).items()}
+    wt = W.Weights(draw(64, H, std=1.0), [lw], (1 + draw(H)).to(torch.bfloat16))
+    q = np.arange(7, dtype=np.int32)
+    r = np.random.RandomState(3)
+    cands = [r.randint(0, 64, n).astype(np.int32) for n in lens]
+    ref = O.select(q, cands, len(lens), oracle_weights(wt), oracle_model(m), checkpoints=[], n_clusters=3, tau=0.0, mode=O.MODE_DROP_ONLY)
+    dev = W.Weights(wt.embed.to(DEV), [{k: v.to(DEV) for k, v in lw.items()}], wt.final_norm.to(DEV))
+    for share in (True, False):
+        p = B.Prism(m, dev, operand=OPERAND[dtype], share_query=share)
+        _, _, rep = p.select(q, cands, len(lens))
+        p.destroy()
+        # one layer: each of the contractions rounds its operands to the operand type; scores are sums of 256 O(1) products
+        fin = ref.events[-1]
+        np.testing.assert_allclose(rep.scores[-1][fin.live], fin.scores, atol=64 * EPS16[dtype] * max(1.0, np.abs(fin.scores).max()), rtol=0)
