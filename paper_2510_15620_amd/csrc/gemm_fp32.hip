@@ -1,77 +1,162 @@
-// fp32 layer contractions for the fp32 mode (small models, 1e-4 parity runs): a plain LDS-tiled
-// kernel on the vector ALUs with every edge bounds-checked, so any M, N, K works.
-// C = A W^T with A [M,K], W [N,K] row-major.  64x64 output tile, 256 threads, 4x4 per thread.
+// fp32 layer contractions for the fp32 mode (small models, 1e-4 parity runs) on the fp32 matrix instruction
+// v_mfma_f32_16x16x4_f32 (157 TFLOP/s; the vector pipes reach half of that without packed instructions), with every edge
+// bounds-checked, so any M, N, K works.  C = A W^T with A [M,K], W [N,K] row-major, fp32 products and sums throughout.
+//
+// Workgroup tile BM x BN x BK, 4 wavefronts of TM x TN accumulator tiles of 16 x 16.  The 16-wide instruction rather than
+// the 32-wide one: half the cycles per step of K on an accumulator, and these launches are short chains, not full pipes.
+// A slice goes memory -> registers -> LDS (rows padded by 16 bytes: the 16 rows an operand read touches then start in
+// different banks), the next slice's loads in flight while one is multiplied, one barrier per slice.  A lane reads four
+// consecutive k of its row as one 16-byte operand chunk and feeds them to four instructions, so instruction s of a
+// 16-deep block sums k = s, 4 + s, 8 + s, 12 + s of it; the order is the same for every tile size.
+// Layer of the tiny configuration (hidden 256, ffn 688): q/k/v, down and gate/up projections on 354 rows 44, 132 and 52 us
+// on the vector pipes -> 5, 9 and 10 us; on 12859 rows 100, 183 and 195 -> 43, 63 and 104 (78-87 TFLOP/s).
 #include "common.h"
 
 namespace prism {
 
-template <int EPI>
+template <int BM, int BN, int BK, int WM, int WN, int EPI, bool VEC>
 __global__ __launch_bounds__(256) void gemm_fp32_kernel(const float *__restrict__ A, const float *__restrict__ W,
                                                         float *__restrict__ out, int M, int N, int K) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 1];
-  __shared__ float Bs[BK][BN + 1];
-  __shared__ float Us[EPI == PRISM_EPI_SWIGLU ? BK : 1][BN + 1];
-  const int F = EPI == PRISM_EPI_SWIGLU ? N / 2 : N;       // output columns
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {}, accu[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    for (int idx = threadIdx.x; idx < BM * BK; idx += 256) {
-      const int r = idx / BK, c = idx % BK;
-      As[c][r] = (m0 + r < M && k0 + c < K) ? A[(int64_t)(m0 + r) * K + k0 + c] : 0.f;
-      Bs[c][r] = (n0 + r < F && k0 + c < K) ? W[(int64_t)(n0 + r) * K + k0 + c] : 0.f;
-      if (EPI == PRISM_EPI_SWIGLU)
-        Us[c][r] = (n0 + r < F && k0 + c < K) ? W[(int64_t)(F + n0 + r) * K + k0 + c] : 0.f;
+  constexpr bool kGlu = EPI == PRISM_EPI_SWIGLU;             // B tile: BN / 2 gate rows, then the BN / 2 matching up rows
+  constexpr int WMT = BM / WM, WNT = BN / WN, TM = WMT / 16, TN = WNT / 16, LD = BK + 4;
+  constexpr int Q = BK / 4, NL = (BM + BN) * Q / 256;        // float4s per row, per thread and slice
+  static_assert(WM * WN == 4 && (BM + BN) * Q % 256 == 0 && (!kGlu || TN % 2 == 0), "tile");
+  __shared__ __align__(16) float lds[2][(BM + BN) * LD];
+  const int F = kGlu ? N / 2 : N;                            // output columns
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * (kGlu ? BN / 2 : BN);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave / WN, wn = wave % WN;
+
+  f32x4 st[NL];
+  auto load = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int idx = threadIdx.x + j * 256, row = idx / Q, k = k0 + idx % Q * 4;
+      const bool a = row < BM;
+      const int br = row - BM;
+      const int c = kGlu ? n0 + (br % (BN / 2)) : n0 + br;
+      const bool ok = a ? m0 + row < M : c < F;
+      const float *p = a ? A + (int64_t)(m0 + row) * K + k : W + ((int64_t)c + (kGlu && br >= BN / 2 ? F : 0)) * K + k;
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (VEC) {
+        if (ok && k < K) v = *reinterpret_cast<const f32x4 *>(p);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) if (ok && k + q < K) v[q] = p[q];
+      }
+      st[j] = v;
     }
-    __syncthreads();
+  };
+  auto store = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4], u[4];
+    for (int j = 0; j < NL; ++j) {
+      const int idx = threadIdx.x + j * 256;
+      *reinterpret_cast<f32x4 *>(&lds[buf][idx / Q * LD + idx % Q * 4]) = st[j];
+    }
+  };
+
+  f32x4 acc[TM][TN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = As[kk][ty * 4 + i];
-        b[i] = Bs[kk][tx * 4 + i];
-        if (EPI == PRISM_EPI_SWIGLU) u[i] = Us[kk][tx * 4 + i];
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int r16 = lane & 15, k4 = (lane >> 4) * 4;
+  const int nk = (K + BK - 1) / BK;
+  load(0);
+  store(0);
+  if (nk > 1) load(BK);
+  __syncthreads();
+  for (int t = 0; t < nk; ++t) {
+    const float *la = lds[t & 1] + (wm * WMT + r16) * LD + k4, *lb = lds[t & 1] + BM * LD + r16 * LD + k4;
+#pragma unroll
+    for (int kb = 0; kb < BK; kb += 16) {
+      f32x4 a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const f32x4 *>(la + i * 16 * LD + kb);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        // SwiGLU: accumulator tiles j and j + TN / 2 are a gate tile and the up tile of the same columns
+        const int row = kGlu ? (j / (TN / 2)) * (BN / 2) + wn * (WNT / 2) + (j % (TN / 2)) * 16 : wn * WNT + j * 16;
+        b[j] = *reinterpret_cast<const f32x4 *>(lb + row * LD + kb);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] += a[i] * b[j];
-          if (EPI == PRISM_EPI_SWIGLU) accu[i][j] += a[i] * u[j];
-        }
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][s], a[i][s], acc[i][j], 0, 0, 0);
     }
-    __syncthreads();
+    if (t + 1 < nk) {
+      store((t + 1) & 1);                                    // its readers finished slice t - 1 before the last barrier
+      if (t + 2 < nk) load((t + 2) * BK);
+      __syncthreads();
+    }
   }
+  // W was the first operand: a lane holds row lane % 16 and four consecutive columns of an accumulator tile
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < F) {
-        float *o = out + (int64_t)m * F + n;
-        if (EPI == PRISM_EPI_STORE) *o = acc[i][j];
-        else if (EPI == PRISM_EPI_RESIDUAL) *o += acc[i][j];
-        else {
-          const float g = acc[i][j];
-          *o = g / (1.0f + expf(-g)) * accu[i][j];
-        }
+    for (int j = 0; j < (kGlu ? TN / 2 : TN); ++j) {
+      const int m = m0 + wm * WMT + i * 16 + r16, n = n0 + (kGlu ? wn * (WNT / 2) : wn * WNT) + j * 16 + k4;
+      if (m >= M) continue;
+      float *o = out + (int64_t)m * F + n;
+      f32x4 v = acc[i][j];
+      if (kGlu) {
+        const f32x4 u = acc[i][j + (kGlu ? TN / 2 : 0)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = v[q] / (1.0f + expf(-v[q])) * u[q];
+      }
+      if (VEC && F % 4 == 0) {
+        if (n >= F) continue;
+        if (EPI == PRISM_EPI_RESIDUAL) v += *reinterpret_cast<const f32x4 *>(o);
+        *reinterpret_cast<f32x4 *>(o) = v;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (n + q < F) o[q] = EPI == PRISM_EPI_RESIDUAL ? o[q] + v[q] : v[q];
       }
     }
+}
+
+template <int EPI, bool VEC>
+static void launch_tiles(const float *A, const float *W, float *out, int M, int N, int K, hipStream_t s) {
+  const int F = EPI == PRISM_EPI_SWIGLU ? N / 2 : N, half = EPI == PRISM_EPI_SWIGLU ? 2 : 1;
+  // Fewer than two 64 x 64 tiles per compute unit: 32 x 32 tiles (32 x 64 for SwiGLU, whose waves pair gate and up tiles)
+  // with twice the slice depth keep more units busy and halve the number of slices in the chain.
+  if ((int64_t)cdiv(M, 64) * cdiv(F, 64 / half) < 512) {
+    if constexpr (EPI == PRISM_EPI_SWIGLU)
+      gemm_fp32_kernel<32, 64, 64, 2, 2, EPI, VEC><<<dim3(cdiv(F, 32), cdiv(M, 32)), 256, 0, s>>>(A, W, out, M, N, K);
+    else
+      gemm_fp32_kernel<32, 32, 64, 2, 2, EPI, VEC><<<dim3(cdiv(F, 32), cdiv(M, 32)), 256, 0, s>>>(A, W, out, M, N, K);
+    return;
+  }
+  gemm_fp32_kernel<64, 64, 32, 2, 2, EPI, VEC><<<dim3(cdiv(F, 64 / half), cdiv(M, 64)), 256, 0, s>>>(A, W, out, M, N, K);
 }
 
 int launch_gemm_fp32(int epilogue, const float *A, const float *W, void *out, int M, int N, int K, hipStream_t s) {
   PRISM_REQUIRE(A && W && out && M >= 0 && N > 0 && K > 0, PRISM_EINVAL, "gemm fp32: bad arguments");
   PRISM_REQUIRE(epilogue != PRISM_EPI_SWIGLU || N % 2 == 0, PRISM_EINVAL, "gemm fp32: SwiGLU needs an even row count");
+  PRISM_REQUIRE(epilogue == PRISM_EPI_STORE || epilogue == PRISM_EPI_RESIDUAL || epilogue == PRISM_EPI_SWIGLU, PRISM_EINVAL,
+                "gemm: unknown epilogue %d", epilogue);
   if (M == 0) return PRISM_OK;
-  const int F = epilogue == PRISM_EPI_SWIGLU ? N / 2 : N;
-  dim3 grid(cdiv(F, 64), cdiv(M, 64));
-  if (epilogue == PRISM_EPI_STORE) gemm_fp32_kernel<PRISM_EPI_STORE><<<grid, 256, 0, s>>>(A, W, (float *)out, M, N, K);
-  else if (epilogue == PRISM_EPI_RESIDUAL) gemm_fp32_kernel<PRISM_EPI_RESIDUAL><<<grid, 256, 0, s>>>(A, W, (float *)out, M, N, K);
-  else if (epilogue == PRISM_EPI_SWIGLU) gemm_fp32_kernel<PRISM_EPI_SWIGLU><<<grid, 256, 0, s>>>(A, W, (float *)out, M, N, K);
-  else PRISM_REQUIRE(false, PRISM_EINVAL, "gemm: unknown epilogue %d", epilogue);
-  PRISM_HIP(hipGetLastError());
+  float *o = (float *)out;
+  // rows that start on 16 bytes move four values at a time
+  const bool vec = K % 4 == 0 && ((uintptr_t)A | (uintptr_t)W | (uintptr_t)out) % 16 == 0;
+  // grid.y is limited to 65535 blocks: very tall operands in panels (rows are independent)
+  const int panel = 65535 * 32, F = epilogue == PRISM_EPI_SWIGLU ? N / 2 : N;
+  for (int m0 = 0; m0 < M; m0 += panel) {
+    const int rows = M - m0 < panel ? M - m0 : panel;
+    const float *a = A + (int64_t)m0 * K;
+    float *c = o + (int64_t)m0 * F;
+    switch (epilogue * 2 + (vec ? 1 : 0)) {
+      case PRISM_EPI_STORE * 2 + 1: launch_tiles<PRISM_EPI_STORE, true>(a, W, c, rows, N, K, s); break;
+      case PRISM_EPI_STORE * 2: launch_tiles<PRISM_EPI_STORE, false>(a, W, c, rows, N, K, s); break;
+      case PRISM_EPI_RESIDUAL * 2 + 1: launch_tiles<PRISM_EPI_RESIDUAL, true>(a, W, c, rows, N, K, s); break;
+      case PRISM_EPI_RESIDUAL * 2: launch_tiles<PRISM_EPI_RESIDUAL, false>(a, W, c, rows, N, K, s); break;
+      case PRISM_EPI_SWIGLU * 2 + 1: launch_tiles<PRISM_EPI_SWIGLU, true>(a, W, c, rows, N, K, s); break;
+      default: launch_tiles<PRISM_EPI_SWIGLU, false>(a, W, c, rows, N, K, s); break;
+    }
+    PRISM_HIP(hipGetLastError());
+  }
   return PRISM_OK;
 }
 

@@ -185,6 +185,37 @@ def test_gemm_16_every_tile_size_gives_a_row_the_same_bits(dtype, epi, K):
         assert torch.equal(run(rows), whole[:rows]), rows
 
 
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
+@pytest.mark.parametrize("N,K", [(200, 64), (200, 68), (202, 688), (198, 67), (1376, 256), (2, 1)])
+def test_gemm_fp32_tiles(epi, N, K):
+    """fp32 on the matrix instruction: two tile sizes (chosen by the number of tiles), rows of 16-byte aligned and other
+    lengths, slices cut off by K, columns cut off by N.  Against fp64: |error| of a K-term fp32 sum of products is at most
+    K 2^-24 sum |a w| (SwiGLU: of each factor, plus the exponential's and two products' roundings); and rows do not
+    depend on how many are computed with them."""
+    M = 6001
+    g = torch.Generator().manual_seed(N * 1000 + K)
+    A, Wt = torch.randn(M, K, generator=g), torch.randn(N, K, generator=g) / math.sqrt(K)
+    X0 = torch.randn(M, N, generator=g)
+    a, w, cols = A.to(DEV), Wt.to(DEV), N // 2 if epi == B.EPI_SWIGLU else N
+
+    def run(rows):
+        out = X0[:rows].to(DEV) if epi == B.EPI_RESIDUAL else torch.full((rows, cols), 7.0, device=DEV)
+        B.op_gemm(epi, a[:rows], w, out)
+        return out
+    whole = run(M)
+    ref, mag = A.double() @ Wt.double().T, A.double().abs() @ Wt.double().abs().T
+    bound = (K + 2) * 2.0 ** -24 * mag
+    if epi == B.EPI_RESIDUAL:
+        ref, bound = ref + X0.double(), bound + 2.0 ** -23 * (X0.double().abs() + mag)
+    if epi == B.EPI_SWIGLU:
+        gt, up, bg, bu = ref[:, :cols], ref[:, cols:], bound[:, :cols], bound[:, cols:]
+        ref = torch.nn.functional.silu(gt) * up
+        bound = 1.1 * bg * up.abs() + gt.abs() * bu + bg * bu + 2.0 ** -20 * ref.abs()      # |silu'| < 1.1, |silu(x)| <= |x|
+    assert ((whole.cpu().double() - ref).abs() <= bound + 1e-30).all()
+    for rows in (1, 31, 33, 354, 1000):
+        assert torch.equal(run(rows), whole[:rows]), rows
+
+
 @pytest.mark.parametrize("dtype", SIXTEEN)
 def test_gemm_16_fp32_output(dtype):
     M, N, K = 700, 6144, 1024
@@ -346,6 +377,31 @@ def test_attention(dtype, nq, nkv, hd, lens):
     # bf16 mode: exact operands, f16 probabilities, fp32 accumulation, one bf16 rounding of the output
     tol = dict(rtol=1e-4, atol=1e-5) if dtype == torch.float32 else dict(rtol=2 ** -8 if dtype == torch.bfloat16 else 2 ** -9, atol=2e-3)
     np.testing.assert_allclose(_f64(out), ref, **tol)
+
+
+@pytest.mark.parametrize("nq,nkv,hd", [(4, 2, 64), (6, 3, 32), (3, 1, 128), (2, 2, 48)])
+def test_attention_fp32_work_items(nq, nkv, hd):
+    """fp32 attention by work items (head sizes 32, 64, 128; 48 goes token by token): sequences around the 16-key tiles and the
+    64-query items, more than one item per sequence.  A sequence holding infinities and NaN behind its first 20 tokens
+    changes neither those nor any other sequence."""
+    lens = [1, 15, 16, 17, 63, 64, 65, 200, 333, 40, 31]
+    T = sum(lens)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    QKV = _rand((T, (nq + 2 * nkv) * hd), torch.float32, 500 + hd, 1.0)
+    x = _f64(QKV).reshape(T, nq + 2 * nkv, hd)
+    ref = np.concatenate([O.causal_gqa_attention(x[a:b, :nq], x[a:b, nq:nq + nkv], x[a:b, nq + nkv:]).reshape(b - a, -1)
+                          for a, b in zip(cu[:-1], cu[1:])])
+    out, again = torch.zeros(T, nq * hd, device=DEV), torch.zeros(T, nq * hd, device=DEV)
+    B.op_attention(B.DTYPE_FP32, QKV.to(DEV), None, 0, cu, None, nq, nkv, hd, out)
+    np.testing.assert_allclose(_f64(out), ref, rtol=1e-5, atol=2e-6)
+    dirty = QKV.clone()
+    i = lens.index(200)
+    dirty[cu[i] + 20:cu[i + 1]] = torch.tensor([float("nan"), float("inf"), -float("inf"), 1e38]).repeat(180 * QKV.shape[1] // 4).view(180, -1)
+    B.op_attention(B.DTYPE_FP32, dirty.to(DEV), None, 0, cu, None, nq, nkv, hd, again)
+    clean = torch.ones(T, dtype=torch.bool)
+    clean[cu[i] + 20:cu[i + 1]] = False
+    assert torch.equal(again.cpu()[clean], out.cpu()[clean])
+    assert not torch.isfinite(again.cpu()[cu[i + 1] - 1]).any()
 
 
 def test_attention_refuses_a_transposed_v_stride_beyond_its_32_bit_offsets():
