@@ -132,9 +132,6 @@ int launch_qkv_finish_16(int dtype, const float *QKV, const int32_t *pos, const 
 // [device]); rows = nkv * hd rows of Vt.  Columns of positions >= ql are left alone.
 int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, const int32_t *seq_col0, int n_seq, hipStream_t s);
 
-// generic fp32 attention: one workgroup per (token, q head); pos[t] = position of t in its sequence
-int launch_attention_fp32(const float *QKV, const int32_t *pos, int T, int nq, int nkv, int hd, float *out,
-                          hipStream_t s);
 // matrix-core attention (hd == 128).  tiles: per work item {row base of the sequence, sequence length, first query of
 // the tile, column of the sequence's first key in Vt, length and first row of a shared prefix}; see attn_16.hip.
 // Positions below pre_len are a prefix whose q/k rows are stored once, at pre_row0 + position, and shared by several
@@ -147,12 +144,17 @@ struct AttnTile { int32_t row_base, seq_len, q0, vt_col0, pre_len, pre_row0, out
 int launch_attention_16(int dtype, const void *QK, const void *Vt, int64_t vt_stride, const AttnTile *tiles, int n_tiles,
                         int T, int nq, int nkv, int hd, void *out, hipStream_t s);
 bool attention_16_supported(int nq, int nkv, int hd);
+// fp32 attention.  tiles: work items of kAttn32BQ queries (row_base, seq_len, q0 and out_base are read), for the head sizes
+// that attention_fp32_tiled names; other head sizes go by pos[t], the position of token t in its sequence.
+static const int kAttn32BQ = 64;
+bool attention_fp32_tiled(int hd);
+int launch_attention_fp32(const float *QKV, const int32_t *pos, const AttnTile *tiles, int n_tiles, int T, int nq, int nkv, int hd, float *out,
+                          hipStream_t s);
 int attention_16_block_queries(int nq, int nkv);   // queries per AttnTile for this head grouping
 // Column of key p of a sequence in the V^T buffer, relative to the sequence's first column: within every group of 16
 // the keys are stored in the order 0-3, 8-11, 4-7, 12-15 (the order in which the matrix cores' accumulator layout hands
 // the probabilities to the second contraction), i.e. bits 2 and 3 of p are swapped.
 __host__ __device__ inline int vt_column_of_key(int p) { return (p & ~12) | ((p & 4) << 1) | ((p & 8) >> 1); }
-static const int kAttnBQ = 64;   // query rows per attention work item
 
 int launch_score(const float *X, const int32_t *last_row, int n, int hidden, const void *final_norm,
                  const void *w_yes, const void *w_no, int dtype, float eps, float *scores, hipStream_t s);

@@ -499,8 +499,8 @@ static void build_plan(const prism_ctx *c, Plan &p) {
   p.max_chunk_tokens = p.max_vt_cols = 0;
   p.seq_tokens = 0;
   const int step = c->opt.chunk_cands > 0 ? c->opt.chunk_cands : std::max(n, 1);
-  const bool mfma = is16(c->op);
-  const int bq = mfma ? attention_16_block_queries(c->m.n_q_heads, c->m.n_kv_heads) : 0;
+  const bool tiled = is16(c->op) || attention_fp32_tiled(c->m.head_dim);     // the attention kernel takes work items
+  const int bq = is16(c->op) ? attention_16_block_queries(c->m.n_q_heads, c->m.n_kv_heads) : kAttn32BQ;
   const int ql = p.ql;
   int64_t r = 0;
   for (int c0 = 0; c0 < n; c0 += step) {
@@ -519,7 +519,7 @@ static void build_plan(const prism_ctx *c, Plan &p) {
       p.row0[i] = r;
       r += p.own(i);
       p.seq_tokens += p.len[i];
-      if (mfma) {
+      if (tiled) {
         // rows relative to the chunk; position t >= ql of the sequence is row row_base + t
         const int32_t row_base = (int32_t)(p.row0[i] - ch.r0) - ql;
         // a sequence's query blocks stay together (they share its K/V in one XCD's L2), the late ones, which loop
@@ -874,7 +874,8 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
         if (bf)
           return launch_attention_16(c->op, c->QK, c->Vt, c->vt_cap, (const AttnTile *)(c->d_meta + mo.ltiles) + ch.c0, nc, Tc,
                                      m.n_q_heads, m.n_kv_heads, m.head_dim, c->AO, s);
-        return launch_attention_fp32((const float *)c->QKV, pos, Tc, m.n_q_heads, m.n_kv_heads, m.head_dim, (float *)c->AO, s);
+        return launch_attention_fp32((const float *)c->QKV, pos, (const AttnTile *)(c->d_meta + mo.ltiles) + ch.c0, nc, Tc, m.n_q_heads,
+                                     m.n_kv_heads, m.head_dim, (float *)c->AO, s);
       }));
       // last_row holds rows of the packed pool; this chunk's rows start at ch.r0
       const int32_t *last_row = c->d_meta + mo.lastrow + ch.c0;
@@ -903,7 +904,8 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
         return launch_attention_16(c->op, c->QK, c->Vt, c->vt_cap, (const AttnTile *)(c->d_meta + mo.tiles) + ch.tile0,
                                    ch.n_tiles, Tc, m.n_q_heads, m.n_kv_heads, m.head_dim, c->AO, s);
       }
-      return launch_attention_fp32((const float *)c->QKV, pos, Tc, m.n_q_heads, m.n_kv_heads, m.head_dim, (float *)c->AO, s);
+      return launch_attention_fp32((const float *)c->QKV, pos, (const AttnTile *)(c->d_meta + mo.tiles) + ch.tile0, ch.n_tiles, Tc,
+                                   m.n_q_heads, m.n_kv_heads, m.head_dim, (float *)c->AO, s);
     }, Tc));
     PRISM_TRY(timed_span(c, 1, tk * H * Dq, [&] { return gemm(PRISM_EPI_RESIDUAL, c->AO, wbuf + L.wo, Xc, Tc, H, Dq); }, Tc));
     // ---- FFN block: X += (silu(Xn Wg^T) * (Xn Wu^T)) Wd^T
@@ -1416,12 +1418,21 @@ extern "C" int prism_op_attention(int32_t dtype, const void *QK, const void *Vt,
   const bool bf = is16(dtype);
   PRISM_REQUIRE(bf || dtype == PRISM_DTYPE_FP32, PRISM_EINVAL, "attention: unknown dtype %d", dtype);
   if (!bf) {
-    std::vector<int32_t> pos(T);
-    for (int i = 0; i < n_seqs; ++i) for (int t = cu[i]; t < cu[i + 1]; ++t) pos[t] = t - cu[i];
-    TmpDev d_pos;
-    PRISM_TRY(d_pos.alloc((size_t)T * 4));
-    PRISM_HIP(hipMemcpyAsync(d_pos.p, pos.data(), (size_t)T * 4, hipMemcpyHostToDevice, s));
-    PRISM_TRY(launch_attention_fp32((const float *)QK, (const int32_t *)d_pos.p, T, nq, nkv, hd, (float *)out, s));
+    // what goes to the device: work items, or every token's position for the head sizes served without them
+    std::vector<AttnTile> tiles;
+    std::vector<int32_t> pos;
+    const bool tiled = attention_fp32_tiled(hd) && ((uintptr_t)QK | (uintptr_t)out) % 16 == 0;
+    for (int i = 0; i < n_seqs; ++i) {
+      const int L = cu[i + 1] - cu[i];
+      if (tiled) for (int q0 = (L - 1) / kAttn32BQ * kAttn32BQ; q0 >= 0; q0 -= kAttn32BQ) tiles.push_back({cu[i], L, q0, 0, 0, 0, cu[i], 0});
+      else for (int t = 0; t < L; ++t) pos.push_back(t);
+    }
+    const size_t bytes = tiled ? tiles.size() * sizeof(AttnTile) : pos.size() * 4;
+    TmpDev d;
+    PRISM_TRY(d.alloc(bytes));
+    PRISM_HIP(hipMemcpyAsync(d.p, tiled ? (const void *)tiles.data() : pos.data(), bytes, hipMemcpyHostToDevice, s));
+    PRISM_TRY(launch_attention_fp32((const float *)QK, tiled ? nullptr : (const int32_t *)d.p, tiled ? (const AttnTile *)d.p : nullptr,
+                                    (int)tiles.size(), T, nq, nkv, hd, (float *)out, s));
     PRISM_HIP(hipStreamSynchronize(s));
     return PRISM_OK;
   }
