@@ -361,7 +361,8 @@ __global__ __launch_bounds__(256) void score_kernel(const float *__restrict__ X,
   __shared__ float red[4];
   const float *x = X + (int64_t)(last_row ? last_row[blockIdx.x] : (int)blockIdx.x) * hidden;   // no list: state c is row c
   float ss = 0.f, dy = 0.f, dn = 0.f;
-  for (int i = threadIdx.x; i < hidden; i += 256) {
+#pragma unroll 8
+  for (int i = threadIdx.x; i < hidden; i += 256) {          // unrolled: the loads of eight steps are in flight together
     const float v = x[i];
     ss += v * v;
     const float z = v * to_f32(gain[i]);
@@ -438,24 +439,31 @@ int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, co
 }
 
 // ------------------------------------------------------------------------------------------------
-// Final top-K (Sec. 2.1): rank by counting (score descending, lower position first on ties).
-__global__ __launch_bounds__(1024) void topk_kernel(const float *__restrict__ scores, const int8_t *__restrict__ tag,
+// Final top-K (Sec. 2.1): rank by counting (score descending, lower position first on ties).  Latency- and issue-bound: n^2
+// comparisons.  16 lanes per entry, 16 entries per workgroup, so the pool spreads over the compute units; the scores are read
+// once into LDS.  500 entries 37 us (one workgroup, a memory load per comparison) -> 4; 4096: 1490 -> 10.
+__global__ __launch_bounds__(256) void topk_kernel(const float *__restrict__ scores, const int8_t *__restrict__ tag,
                                                     int want, int n, int K, int32_t *__restrict__ out_pos,
                                                     float *__restrict__ out_scores) {
-  // entries whose tag differs from `want` do not take part (tag == nullptr: all take part)
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    if (tag && tag[i] != want) continue;
-    const float si = scores[i];
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      if (tag && tag[j] != want) continue;
-      const float sj = scores[j];
-      rank += (sj > si) || (sj == si && j < i);
-    }
-    if (rank < K) {
-      out_pos[rank] = i;
-      out_scores[rank] = si;
-    }
+  // entries whose tag differs from `want` do not take part (tag == nullptr: all take part): like a NaN, a NaN in their
+  // place compares false with everything
+  __shared__ float sc[PRISM_MAX_CANDS];
+  for (int j = threadIdx.x; j < n; j += 256) sc[j] = tag && tag[j] != want ? __uint_as_float(0x7fc00000u) : scores[j];
+  __syncthreads();
+  const int i = blockIdx.x * 16 + (threadIdx.x >> 4);
+  if (i >= n || (tag && tag[i] != want)) return;
+  const float si = sc[i];
+  int rank = 0;
+#pragma unroll 4
+  for (int j = threadIdx.x & 15; j < n; j += 16) {
+    const float sj = sc[j];
+    rank += (sj > si) || (sj == si && j < i);
+  }
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 64);
+  if ((threadIdx.x & 15) == 0 && rank < K) {
+    out_pos[rank] = i;
+    out_scores[rank] = si;
   }
 }
 
@@ -463,7 +471,7 @@ int launch_topk_masked(const float *scores, const int8_t *tag, int want, int n, 
                        float *out_scores, hipStream_t s) {
   PRISM_REQUIRE(scores && out_pos && out_scores && n >= 0 && K >= 0, PRISM_EINVAL, "topk: bad arguments");
   if (n == 0 || K == 0) return PRISM_OK;
-  topk_kernel<<<1, 1024, 0, s>>>(scores, tag, want, n, K, out_pos, out_scores);
+  topk_kernel<<<cdiv(n, 16), 256, 0, s>>>(scores, tag, want, n, K, out_pos, out_scores);
   PRISM_HIP(hipGetLastError());
   return PRISM_OK;
 }

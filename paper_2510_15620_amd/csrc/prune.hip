@@ -2,7 +2,7 @@
 // Sec. 4.5): dispersion gate on the coefficient of variation, K-Means of the scalar scores, routing
 // around the boundary cluster.
 //
-// The paper runs K-Means on the CPU (~1 ms); here it is one workgroup on the device so the scores
+// The paper runs K-Means on the CPU (~1 ms); here it runs on the device so the scores
 // never leave HBM before the decision.  K-Means of scalars is solved exactly: every optimum of the
 // within-cluster sum of squares is a partition of the ranked scores into consecutive runs, so a
 // dynamic programme over split positions finds it, with no seed and no iteration count.
@@ -10,6 +10,7 @@
 // All decisions are taken in fp64 with a fixed operation order (sequential sums, no fused
 // multiply-add: this file is compiled with -ffp-contract=off), so that a host implementation that
 // follows the same order reaches the same bits.
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -26,146 +27,320 @@ __device__ __forceinline__ double run_cost(const double *P, const double *Q, int
   return (Q[j] - Q[i]) - sp * sp / (double)(j - i);
 }
 
-__global__ __launch_bounds__(1024) void route_kernel(const float *__restrict__ scores, int n, int K_rem, int k_req,
-                                                     float tau, int8_t *__restrict__ fate, double *__restrict__ stats,
-                                                     RouteWs ws) {
-  __shared__ double sh_val[1024];
-  __shared__ int sh_idx[1024];
-  __shared__ int sh_flag;      // 1: clustering runs
-  __shared__ int sh_distinct;
-  __shared__ int sh_splits[PRISM_MAX_CLUSTERS + 1];
-  __shared__ double sh_means[PRISM_MAX_CLUSTERS];
-  __shared__ int sh_k, sh_b;
+// The decision in four phases.  What bounds them: the sums of the first two are chains of dependent fp64 additions in a
+// prescribed order (n of them, about 4 ns each); the table of the third has n^2 / 2 entries per stage, each with an fp64
+// division when done plainly.  Small pools (up to kOneGroup) run all phases in one workgroup on LDS; larger ones as
+// 2 + (k - 2) launches: phase 1 and 2 side by side on two compute units, the table on all of them, the rest on one.
+// us per call, 3 clusters, one workgroup on global memory before -> now: 12 candidates 12 -> 11, 100: 53 -> 17, 500: 232 -> 36,
+// 4096: 4895 -> 181; 8 clusters on 4096: 18700 -> 330.  (128 candidates, 8 clusters: 41 as one workgroup, 45 at 129.)
+
+// f(i, x[i]) for i = 0 .. n - 1, in order, by one thread; x in LDS, 16-byte aligned.  Sixteen values are read ahead, so that
+// the chain of additions in f is all there is to wait for.
+template <typename F>
+__device__ __forceinline__ void in_order(const float *x, int n, F f) {
+  const f32x4 *q = reinterpret_cast<const f32x4 *>(x);
+  int i = 0;
+  if (n >= 16) {
+    f32x4 cur[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) cur[j] = q[j];
+    for (; i + 16 <= n; i += 16) {
+      f32x4 next[4];
+      const int at = i + 32 <= n ? i / 4 + 4 : 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) next[j] = q[at + j];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) f(i + j, cur[j / 4][j % 4]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) cur[j] = next[j];
+    }
+  }
+  for (; i < n; ++i) f(i, x[i]);
+}
+
+// ---- phase 1: mean and population std, sequential in index order; the gate.  One thread; sc is in LDS.
+__device__ void stats_phase(const float *sc, int n, int K_rem, float tau, double *stats) {
+  double tot = 0.0;
+  in_order(sc, n, [&](int, float x) { tot = tot + (double)x; });
+  const double mean = n > 0 ? tot / (double)n : 0.0;
+  double acc = 0.0;
+  in_order(sc, n, [&](int, float x) {
+    const double d = (double)x - mean;
+    acc = acc + d * d;
+  });
+  const double sd = n > 0 ? sqrt(acc / (double)n) : 0.0;
+  const int gate = (n > K_rem) && (sd > (double)tau * fabs(mean));   // CV > tau, division-free
+  stats[0] = mean;
+  stats[1] = sd;
+  stats[2] = (double)gate;
+  stats[3] = 0.0;
+}
+
+// ---- phase 2, from the scores in rank order (sorted, in LDS): sequential prefix sums of x and x^2 (a thread each, in different
+// wavefronts), number of clusters, first row of costs E[1][i] = cost(i, n).  The whole workgroup.
+__device__ void prefix_phase(const float *sorted, int n, int k_req, int *sh_distinct, const RouteWs &ws) {
   const int tid = threadIdx.x, nt = blockDim.x;
-
-  for (int i = tid; i < n; i += nt) fate[i] = PRISM_FATE_DEFERRED;
+  if (tid == 0) *sh_distinct = 0;
+  __syncthreads();
+  int local = 0;
+  for (int r = tid; r < n; r += nt) {
+    ws.ranked[r] = (double)sorted[r];
+    local += r == 0 || sorted[r - 1] != sorted[r];
+  }
+  if (local) atomicAdd(sh_distinct, local);
+  double run = 0.0;
   if (tid == 0) {
-    // mean and population std, sequential in index order
-    double tot = 0.0;
-    for (int i = 0; i < n; ++i) tot = tot + (double)scores[i];
-    const double mean = n > 0 ? tot / (double)n : 0.0;
-    double acc = 0.0;
-    for (int i = 0; i < n; ++i) {
-      const double d = (double)scores[i] - mean;
-      acc = acc + d * d;
-    }
-    const double sd = n > 0 ? sqrt(acc / (double)n) : 0.0;
-    const int gate = (n > K_rem) && (sd > (double)tau * fabs(mean));   // CV > tau, division-free
-    stats[0] = mean;
-    stats[1] = sd;
-    stats[2] = (double)gate;
-    stats[3] = 0.0;
-    sh_flag = gate;
-    sh_distinct = 0;
-  }
-  __syncthreads();
-  if (!sh_flag) return;
-
-  // rank: score descending, lower index first on ties
-  for (int i = tid; i < n; i += nt) {
-    const float si = scores[i];
-    int r = 0;
-    for (int j = 0; j < n; ++j) {
-      const float sj = scores[j];
-      r += (sj > si) || (sj == si && j < i);
-    }
-    ws.order[r] = i;
-    ws.ranked[r] = (double)si;
-  }
-  __syncthreads();
-  {
-    int local = 0;
-    for (int r = tid; r < n; r += nt) local += (r == 0) || (ws.ranked[r] != ws.ranked[r - 1]);
-    if (local) atomicAdd(&sh_distinct, local);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int k = k_req < sh_distinct ? k_req : sh_distinct;
-    sh_k = k;
-    if (k <= 1) sh_flag = 0;
-    // sequential prefix sums of x and x^2
     ws.P[0] = 0.0;
+    in_order(sorted, n, [&](int i, float x) { ws.P[i + 1] = run = run + (double)x; });
+  } else if (tid == 64) {
     ws.Q[0] = 0.0;
-    for (int i = 0; i < n; ++i) {
-      const double x = ws.ranked[i];
-      ws.P[i + 1] = ws.P[i] + x;
-      ws.Q[i + 1] = ws.Q[i] + x * x;
-    }
+    in_order(sorted, n, [&](int i, float x) { ws.Q[i + 1] = run = run + (double)x * (double)x; });
   }
   __syncthreads();
-  if (!sh_flag) return;
-  const int k = sh_k;
-
-  // E[m][i]: best cost of cutting ranked[i:] into m runs.  E[1][i] = cost(i, n).
-  double *Eprev = ws.E0, *Ecur = ws.E1;
-  for (int i = tid; i < n; i += nt) Eprev[i] = run_cost(ws.P, ws.Q, i, n);
+  for (int i = tid; i < n; i += nt) ws.E0[i] = run_cost(ws.P, ws.Q, i, n);
+  if (tid == 0) ws.arg[0] = k_req < *sh_distinct ? k_req : *sh_distinct;       // row 0 of the split table is not used otherwise
   __syncthreads();
-  for (int m = 2; m <= k; ++m) {
-    int32_t *arg = ws.arg + (int64_t)m * (n + 1);
-    if (m < k) {
-      for (int i = tid; i <= n - m; i += nt) {
-        double best = INFINITY;
-        int best_s = -1;
-        for (int s = i + 1; s <= n - (m - 1); ++s) {
-          const double c = run_cost(ws.P, ws.Q, i, s) + Eprev[s];
-          if (c < best) { best = c; best_s = s; }
-        }
-        Ecur[i] = best;
-        arg[i] = best_s;
+}
+
+// Order of a large pool: score descending, lower index first on ties, by a bitonic sort of (score, index) keys in LDS; the
+// scores are left in rank order.  A pool whose gate is open holds finite scores only (an infinity or NaN makes the std NaN), so
+// the key order is the order of the scores.
+__device__ void sort_phase(float *sc, int n, unsigned long long *key, const RouteWs &ws) {
+  const int tid = threadIdx.x, nt = blockDim.x;
+  int np = 2;
+  while (np < n) np *= 2;
+  for (int i = tid; i < np; i += nt) {
+    unsigned long long v = ~0ull;
+    if (i < n) {
+      const float s = sc[i] == 0.f ? 0.f : sc[i];                              // -0 ties with 0
+      const unsigned u = __float_as_uint(s);
+      v = (unsigned long long)(u & 0x80000000u ? u : ~(u | 0x80000000u)) << 32 | (unsigned)i;   // larger score, smaller key
+    }
+    key[i] = v;
+  }
+  __syncthreads();
+  for (int size = 2; size <= np; size *= 2)
+    for (int d = size / 2; d > 0; d /= 2) {
+      for (int t = tid; t < np / 2; t += nt) {
+        const int i = 2 * t - (t & (d - 1)), j = i + d;
+        const unsigned long long x = key[i], y = key[j];
+        if ((x > y) == ((i & size) == 0)) { key[i] = y; key[j] = x; }
       }
-    } else {
-      // last stage is only read at i = 0: spread the candidates for s over the workgroup and
-      // reduce to the smallest cost, smallest s among equals
-      double best = INFINITY;
-      int best_s = 0x7fffffff;
-      for (int s = 1 + tid; s <= n - (m - 1); s += nt) {
-        const double c = run_cost(ws.P, ws.Q, 0, s) + Eprev[s];
-        if (c < best) { best = c; best_s = s; }
-      }
-      sh_val[tid] = best;
-      sh_idx[tid] = best_s;
       __syncthreads();
-      for (int off = nt >> 1; off > 0; off >>= 1) {
-        if (tid < off) {
-          const double c = sh_val[tid + off];
-          const int s = sh_idx[tid + off];
-          if (c < sh_val[tid] || (c == sh_val[tid] && s < sh_idx[tid])) { sh_val[tid] = c; sh_idx[tid] = s; }
-        }
-        __syncthreads();
-      }
-      if (tid == 0) arg[0] = sh_idx[0];
     }
-    __syncthreads();
-    double *t = Eprev; Eprev = Ecur; Ecur = t;
+  float mine[PRISM_MAX_CANDS / 1024];
+#pragma unroll
+  for (int j = 0; j < PRISM_MAX_CANDS / 1024; ++j) {
+    const int r = tid + j * 1024;
+    if (r < n) {
+      const int i = (int)(key[r] & 0xffffffffu);
+      ws.order[r] = i;
+      mine[j] = sc[i];
+    }
   }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PRISM_MAX_CANDS / 1024; ++j)
+    if (tid + j * 1024 < n) sc[tid + j * 1024] = mine[j];
+  __syncthreads();
+}
 
+// ---- phase 3: row m of the table: E[m][i] = best cost of cutting ranked[i:] into m runs, split at the smallest s among equal
+// costs.  One wavefront per i.  A cost with the division replaced by a single-precision reciprocal is off by at most
+// 2^-22 of the pool's sum of squares S (every term of a cost is at most S), so only the s whose approximate cost comes
+// within 1e-6 S of the smallest approximate one can be the answer, and only those take the division.
+__device__ void table_phase(int m, int n, const RouteWs &ws, int wave, int n_waves) {
+  const double *P = ws.P, *Q = ws.Q, *Eprev = m % 2 == 0 ? ws.E0 : ws.E1;
+  double *Ecur = m % 2 == 0 ? ws.E1 : ws.E0;
+  int32_t *arg = ws.arg + (int64_t)m * (n + 1);
+  const int lane = threadIdx.x & 63, last = n - (m - 1);
+  const double margin = 1e-6 * Q[n];
+  for (int i = wave; i <= n - m; i += n_waves) {
+    const double Pi = P[i], Qi = Q[i];
+    auto rough = [&](int s) {
+      const double sp = P[s] - Pi;
+      return (Q[s] - Qi) - sp * sp * (double)__builtin_amdgcn_rcpf((float)(s - i)) + Eprev[s];
+    };
+    double least = INFINITY;
+    for (int s = i + 1 + lane; s <= last; s += 64) {
+      const double c = rough(s);
+      if (c < least) least = c;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      const double c = __shfl_xor(least, o, 64);
+      if (c < least) least = c;
+    }
+    double best = INFINITY;
+    int best_s = 0x7fffffff;
+    for (int s = i + 1 + lane; s <= last; s += 64) {
+      if (rough(s) > least + margin) continue;
+      const double c = run_cost(P, Q, i, s) + Eprev[s];
+      if (c < best) { best = c; best_s = s; }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      const double c = __shfl_xor(best, o, 64);
+      const int s = __shfl_xor(best_s, o, 64);
+      if (c < best || (c == best && s < best_s)) { best = c; best_s = s; }
+    }
+    if (lane == 0) {
+      Ecur[i] = best;
+      arg[i] = best_s;
+    }
+  }
+}
+
+// ---- phase 4: the last stage is only needed at i = 0; then the split positions, cluster means (sequential sums, a thread per
+// cluster), the boundary cluster and the fates.  The whole workgroup (up to 1024 threads).
+struct RouteShared {
+  double val[16];
+  int idx[16], splits[PRISM_MAX_CLUSTERS + 1], b;
+  double means[PRISM_MAX_CLUSTERS];
+};
+__device__ void fate_phase(int k, int n, int K_rem, int8_t *fate, double *stats, const RouteWs &ws, RouteShared &sh) {
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  const double *Eprev = k % 2 == 0 ? ws.E0 : ws.E1;
+  double best = INFINITY;
+  int best_s = 0x7fffffff;
+  for (int s = 1 + tid; s <= n - (k - 1); s += nt) {
+    const double c = run_cost(ws.P, ws.Q, 0, s) + Eprev[s];
+    if (c < best) { best = c; best_s = s; }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double c = __shfl_xor(best, o, 64);
+    const int s = __shfl_xor(best_s, o, 64);
+    if (c < best || (c == best && s < best_s)) { best = c; best_s = s; }
+  }
+  if (lane == 0) { sh.val[wave] = best; sh.idx[wave] = best_s; }
+  __syncthreads();
   if (tid == 0) {
-    // split positions, cluster means (sequential sums), boundary cluster
-    sh_splits[0] = 0;
-    int i = 0;
-    for (int m = k, c = 1; m >= 2; --m, ++c) {
+    for (int w = 1; w < (nt >> 6); ++w)
+      if (sh.val[w] < best || (sh.val[w] == best && sh.idx[w] < best_s)) { best = sh.val[w]; best_s = sh.idx[w]; }
+    sh.splits[0] = 0;
+    int i = best_s;
+    sh.splits[1] = i;
+    for (int m = k - 1, c = 2; m >= 2; --m, ++c) {
       i = ws.arg[(int64_t)m * (n + 1) + i];
-      sh_splits[c] = i;
+      sh.splits[c] = i;
     }
-    sh_splits[k] = n;
+    sh.splits[k] = n;
     int b = 0;
-    for (int c = 0; c < k; ++c) {
-      double tot = 0.0;
-      for (int r = sh_splits[c]; r < sh_splits[c + 1]; ++r) tot = tot + ws.ranked[r];
-      sh_means[c] = tot / (double)(sh_splits[c + 1] - sh_splits[c]);
-      if (sh_splits[c] <= K_rem - 1 && K_rem - 1 < sh_splits[c + 1]) b = c;
-    }
-    sh_b = b;
+    for (int c = 0; c < k; ++c)
+      if (sh.splits[c] <= K_rem - 1 && K_rem - 1 < sh.splits[c + 1]) b = c;
+    sh.b = b;
     stats[3] = (double)k;
   }
   __syncthreads();
-  const double mb = sh_means[sh_b];
+  if (lane == 0)
+  for (int cl = wave; cl < k; cl += nt >> 6) {               // a cluster per wavefront
+    double tot = 0.0;
+#pragma unroll 8
+    for (int r = sh.splits[cl]; r < sh.splits[cl + 1]; ++r) tot = tot + ws.ranked[r];
+    sh.means[cl] = tot / (double)(sh.splits[cl + 1] - sh.splits[cl]);
+  }
+  __syncthreads();
+  const double mb = sh.means[sh.b];
   for (int r = tid; r < n; r += nt) {
     int c = 0;
-    while (r >= sh_splits[c + 1]) ++c;
-    const double mc = sh_means[c];
+    while (r >= sh.splits[c + 1]) ++c;
+    const double mc = sh.means[c];
     fate[ws.order[r]] = mc > mb ? PRISM_FATE_SELECTED : (mc < mb ? PRISM_FATE_DROPPED : PRISM_FATE_DEFERRED);
   }
+}
+
+static constexpr int kOneGroup = 128;
+
+// everything in one workgroup, n <= kOneGroup: rank by counting and the plain costs, 4 and 16 lanes per candidate
+__global__ __launch_bounds__(512) void route_small_kernel(const float *__restrict__ scores, int n, int K_rem, int k_req, float tau,
+                                                          int8_t *__restrict__ fate, double *__restrict__ stats) {
+  __shared__ __align__(16) float sc[kOneGroup], sorted[kOneGroup];
+  __shared__ double arr[5][kOneGroup + 1];
+  __shared__ int32_t order[kOneGroup], arg[(PRISM_MAX_CLUSTERS + 1) * (kOneGroup + 1)];
+  __shared__ double st[4];
+  __shared__ int distinct;
+  __shared__ RouteShared sh;
+  const RouteWs ws{arr[0], arr[1], arr[2], arr[3], arr[4], order, arg};
+  const int tid = threadIdx.x;
+  if (tid < n) {
+    sc[tid] = scores[tid];
+    fate[tid] = PRISM_FATE_DEFERRED;
+  }
+  __syncthreads();
+  {
+    const int i = tid >> 2;                                  // ranks while thread 0 of the last wavefront sums
+    const float si = i < n ? sc[i] : 0.f;
+    int r = 0;
+    for (int j = tid & 3; j < n; j += 4) {
+      const float sj = sc[j];
+      r += (sj > si) || (sj == si && j < i);
+    }
+    r += __shfl_xor(r, 1, 64);
+    r += __shfl_xor(r, 2, 64);
+    if (i < n && (tid & 3) == 0) {
+      order[r] = i;
+      sorted[r] = si;
+    }
+  }
+  if (tid == 511) stats_phase(sc, n, K_rem, tau, st);
+  __syncthreads();
+  if (tid < 4) stats[tid] = st[tid];
+  if (st[2] == 0.0) return;
+  prefix_phase(sorted, n, k_req, &distinct, ws);
+  const int k = arg[0];
+  if (k <= 1) return;
+  for (int m = 2; m < k; ++m) {
+    const double *Eprev = m % 2 == 0 ? ws.E0 : ws.E1;
+    double *Ecur = m % 2 == 0 ? ws.E1 : ws.E0;
+    for (int i = tid >> 4; i <= n - m; i += 32) {
+      double best = INFINITY;
+      int best_s = 0x7fffffff;
+      for (int s = i + 1 + (tid & 15); s <= n - (m - 1); s += 16) {
+        const double c = run_cost(ws.P, ws.Q, i, s) + Eprev[s];
+        if (c < best) { best = c; best_s = s; }
+      }
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) {
+        const double c = __shfl_xor(best, o, 64);
+        const int s = __shfl_xor(best_s, o, 64);
+        if (c < best || (c == best && s < best_s)) { best = c; best_s = s; }
+      }
+      if ((tid & 15) == 0) {
+        Ecur[i] = best;
+        arg[m * (n + 1) + i] = best_s;
+      }
+    }
+    __syncthreads();
+  }
+  fate_phase(k, n, K_rem, fate, stats, ws, sh);
+}
+
+// n > kOneGroup.  Block 0: phase 1 and the default fates; block 1: phase 2 (wasted when the gate turns out closed).
+__global__ __launch_bounds__(1024) void route_prepare_kernel(const float *__restrict__ scores, int n, int K_rem, int k_req, float tau,
+                                                             int8_t *__restrict__ fate, double *__restrict__ stats, RouteWs ws) {
+  __shared__ __align__(16) float sc[PRISM_MAX_CANDS];
+  __shared__ unsigned long long key[PRISM_MAX_CANDS];
+  __shared__ int distinct;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    sc[i] = scores[i];
+    if (blockIdx.x == 0) fate[i] = PRISM_FATE_DEFERRED;
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) stats_phase(sc, n, K_rem, tau, stats);
+    return;
+  }
+  sort_phase(sc, n, key, ws);
+  prefix_phase(sc, n, k_req, &distinct, ws);
+}
+
+__global__ __launch_bounds__(256) void route_table_kernel(int m, int n, const double *__restrict__ stats, RouteWs ws) {
+  if (stats[2] == 0.0 || m >= ws.arg[0]) return;
+  table_phase(m, n, ws, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4);
+}
+
+__global__ __launch_bounds__(1024) void route_fate_kernel(int n, int K_rem, int8_t *__restrict__ fate, double *__restrict__ stats, RouteWs ws) {
+  __shared__ RouteShared sh;
+  if (stats[2] == 0.0 || ws.arg[0] <= 1) return;
+  fate_phase(ws.arg[0], n, K_rem, fate, stats, ws, sh);
 }
 
 static RouteWs carve(void *workspace, int n, int k) {
@@ -195,7 +370,19 @@ int launch_route(const float *scores, int n, int K_rem, int n_clusters, float ta
   PRISM_REQUIRE(n_clusters >= 2 && n_clusters <= PRISM_MAX_CLUSTERS, PRISM_EINVAL, "route: n_clusters = %d outside 2..%d",
                 n_clusters, PRISM_MAX_CLUSTERS);
   PRISM_REQUIRE(K_rem >= 1 && tau >= 0.f, PRISM_EINVAL, "route: K_rem = %d, tau = %g", K_rem, (double)tau);
-  route_kernel<<<1, 1024, 0, s>>>(scores, n, K_rem, n_clusters, tau, fate, stats, carve(workspace, n, n_clusters));
+  if (n <= kOneGroup) {
+    route_small_kernel<<<1, 512, 0, s>>>(scores, n, K_rem, n_clusters, tau, fate, stats);
+    PRISM_HIP(hipGetLastError());
+    return PRISM_OK;
+  }
+  const RouteWs ws = carve(workspace, n, n_clusters);
+  route_prepare_kernel<<<2, 1024, 0, s>>>(scores, n, K_rem, n_clusters, tau, fate, stats, ws);
+  PRISM_HIP(hipGetLastError());
+  for (int m = 2; m < n_clusters; ++m) {
+    route_table_kernel<<<std::min(cdiv(n, 4), 1024), 256, 0, s>>>(m, n, stats, ws);
+    PRISM_HIP(hipGetLastError());
+  }
+  route_fate_kernel<<<1, 1024, 0, s>>>(n, K_rem, fate, stats, ws);
   PRISM_HIP(hipGetLastError());
   return PRISM_OK;
 }

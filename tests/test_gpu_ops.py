@@ -515,3 +515,29 @@ def test_projection_of_a_whole_call_at_every_tile_size(dtype, nq, nkv, lens):
         # one layer: each of the contractions rounds its operands to the operand type; scores are sums of 256 O(1) products
         fin = ref.events[-1]
         np.testing.assert_allclose(rep.scores[-1][fin.live], fin.scores, atol=64 * EPS16[dtype] * max(1.0, np.abs(fin.scores).max()), rtol=0)
+
+
+@pytest.mark.parametrize("n,k", [(2, 2), (3, 8), (64, 8), (127, 4), (128, 8), (129, 8), (130, 2), (513, 5), (1000, 3), (4096, 3)])
+@pytest.mark.parametrize("shape", ["normal", "duplicates", "tiny spread", "clusters"])
+def test_route_around_its_workgroup_boundary(n, k, shape):
+    """One workgroup up to 128 candidates, several launches beyond: the same decisions as the oracle, bit for bit, on scores
+    with many ties, with a spread far below their mean (costs that differ in the last bits only) and with clear clusters;
+    -0 and 0 tie."""
+    r = np.random.default_rng(n * 10 + k)
+    s = r.normal(size=n)
+    if shape == "duplicates":
+        s = np.round(s * 2) / 2 * np.where(r.random(n) < 0.5, 1.0, -1.0)          # -0.0 among them
+    elif shape == "tiny spread":
+        s = 1000.0 + s * 1e-3
+    elif shape == "clusters":
+        s = r.choice([-3.0, 0.0, 5.0, 40.0], size=n) + s * 0.01
+    _route_case(s.astype(np.float32).tolist(), max(1, n // 5), k, 0.0)
+
+
+@pytest.mark.parametrize("n,K", [(1, 1), (15, 15), (17, 3), (500, 20), (4096, 4096)])
+def test_topk_of_any_pool(n, K):
+    s = np.round(np.random.default_rng(n).normal(size=n), 1).astype(np.float32)    # many ties
+    pos, sc = torch.zeros(K, dtype=torch.int32, device=DEV), torch.zeros(K, device=DEV)
+    B.op_topk(torch.from_numpy(s).to(DEV), K, pos, sc)
+    order = O.rank_order(s.astype(np.float64))[:K]
+    assert np.array_equal(pos.cpu().numpy(), order) and np.array_equal(sc.cpu().numpy(), s[order])
