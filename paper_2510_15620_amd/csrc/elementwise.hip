@@ -394,17 +394,26 @@ int launch_score(const float *X, const int32_t *last_row, int n, int hidden, con
 
 // ------------------------------------------------------------------------------------------------
 // Compaction (Sec. 4.1: continue only on the remaining candidates): each kept sequence's rows move
-// to their new offset in a second buffer, order preserved.  HBM-bound: 2 * T' * H * 4 bytes.
+// to their new offset in a second buffer, order preserved.  HBM-bound: 2 * T' * H * 4 bytes.  A block moves 16 KiB pieces of its
+// sequence, four 16-byte loads per lane in flight, past the caches (neither copy is read again soon): 4.65 -> 4.97 TB/s on
+// 109 sequences of 1 GB in all, where a large plain copy reaches 4.67.
 __global__ __launch_bounds__(256) void compact_kernel(const float *__restrict__ Xs, float *__restrict__ Xd,
                                                       const int32_t *__restrict__ src_start,
                                                       const int32_t *__restrict__ dst_start,
                                                       const int32_t *__restrict__ len, int hidden) {
-  const int c = blockIdx.x;
-  const int n = len[c], h4 = hidden / 4;
-  const float4 *src = reinterpret_cast<const float4 *>(Xs + (int64_t)src_start[c] * hidden);
-  float4 *dst = reinterpret_cast<float4 *>(Xd + (int64_t)dst_start[c] * hidden);
-  for (int r = blockIdx.y; r < n; r += gridDim.y)
-    for (int i = threadIdx.x; i < h4; i += 256) dst[(int64_t)r * h4 + i] = src[(int64_t)r * h4 + i];
+  const int c = blockIdx.x, h4 = hidden / 4;
+  const int64_t total = (int64_t)len[c] * h4;
+  const f32x4 *src = reinterpret_cast<const f32x4 *>(Xs) + (int64_t)src_start[c] * h4;
+  f32x4 *dst = reinterpret_cast<f32x4 *>(Xd) + (int64_t)dst_start[c] * h4;
+  for (int64_t at = (int64_t)blockIdx.y * 1024 + threadIdx.x; at < total; at += (int64_t)gridDim.y * 1024) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (at + u * 256 < total) v[u] = __builtin_nontemporal_load(src + at + u * 256);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (at + u * 256 < total) __builtin_nontemporal_store(v[u], dst + at + u * 256);
+  }
 }
 
 int launch_compact(const float *Xs, float *Xd, const int32_t *src_start, const int32_t *dst_start,
@@ -412,7 +421,10 @@ int launch_compact(const float *Xs, float *Xd, const int32_t *src_start, const i
   PRISM_REQUIRE(Xs && Xd && Xs != Xd && src_start && dst_start && len && n_keep >= 0 && hidden % 4 == 0, PRISM_EINVAL,
                 "compact: bad arguments");
   if (n_keep == 0) return PRISM_OK;
-  compact_kernel<<<dim3(n_keep, 32), 256, 0, s>>>(Xs, Xd, src_start, dst_start, len, hidden);
+  // enough blocks to cover the memory latency also for a few sequences, not thousands of idle ones for many (64 per sequence
+  // measured 4.97 TB/s, 32 4.77, 256 5.00)
+  const int per_seq = n_keep >= 2048 ? 8 : n_keep >= 256 ? 16384 / n_keep : 64;
+  compact_kernel<<<dim3(n_keep, per_seq), 256, 0, s>>>(Xs, Xd, src_start, dst_start, len, hidden);
   PRISM_HIP(hipGetLastError());
   return PRISM_OK;
 }
