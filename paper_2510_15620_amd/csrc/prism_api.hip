@@ -104,7 +104,8 @@ struct prism_ctx {
   bool own_stream = false;
   int ring = 2;                                   // layer slots of the streaming ring (two_slot); 2 is the paper's double buffer
   std::vector<hipEvent_t> ev_ready, ev_free;      // per ring slot
-  hipEvent_t ev_t[4] = {nullptr, nullptr, nullptr, nullptr};
+  hipEvent_t ev_t[2] = {nullptr, nullptr};        // first and last launch of a call
+  std::vector<hipEvent_t> ev_check;               // 2 per check, for the report
   std::vector<hipEvent_t> ev_layer;               // 4 per layer (two intervals: a layer may run in two passes), for the report
   std::vector<hipEvent_t> ev_xfer;                // 2 per layer on the side stream around a streamed layer's transfers, for the report
   // per-launch spans for the report: events come from a pool that only grows
@@ -125,9 +126,11 @@ struct prism_ctx {
   int64_t chunk_cap = 0, vt_cap = 0;              // tokens / V^T columns
   int32_t *d_meta = nullptr; int64_t meta_cap = 0;   // int32 words
   int32_t *h_meta = nullptr; int64_t h_meta_cap = 0; // pinned staging
+  // what a check or the final ranking hands to the host, in one block so that one copy brings it over; a call of n candidates
+  // lays it out by n: [stats][scores n][fate n][top positions n][top scores n], h_res (pinned) alike
+  char *d_res = nullptr, *h_res = nullptr;
   float *d_scores = nullptr; int8_t *d_fate = nullptr; double *d_stats = nullptr; void *route_ws = nullptr;
   int32_t *d_top_pos = nullptr; float *d_top_scores = nullptr;
-  char *h_res = nullptr;                          // pinned: scores, fate, stats, topk
   std::vector<int8_t> forced; int forced_events = 0, forced_cands = 0;
   int64_t bytes_now = 0, bytes_peak = 0;
 
@@ -158,6 +161,8 @@ struct prism_ctx {
 };
 
 namespace prism {
+
+static constexpr size_t kResultBytes = 64 + 13 * (size_t)PRISM_MAX_CANDS;
 
 static int dev_alloc(prism_ctx *c, void **p, size_t bytes) {
   bytes = (size_t)round_up(bytes ? bytes : 256, 256);
@@ -354,7 +359,7 @@ extern "C" int prism_create(const prism_model *model, const prism_weights *weigh
     CREATE_HIP(hipEventCreateWithFlags(&c->ev_ready[i], hipEventDisableTiming));
     CREATE_HIP(hipEventCreateWithFlags(&c->ev_free[i], hipEventDisableTiming));
   }
-  for (int i = 0; i < 4; ++i) CREATE_HIP(hipEventCreate(&c->ev_t[i]));
+  for (hipEvent_t &e : c->ev_t) CREATE_HIP(hipEventCreate(&e));
 
   const int n_slots = c->two_slot ? std::min(c->ring, model->n_layers) : model->n_layers;
   c->layer_buf.assign(n_slots, nullptr);
@@ -371,13 +376,9 @@ extern "C" int prism_create(const prism_model *model, const prism_weights *weigh
   CREATE_TRY(launch_rope_table(c->rope_tab, PRISM_MAX_SEQ, model->head_dim, model->rope_base, c->stream));
   CREATE_TRY(dev_alloc(c, (void **)&c->rope_tab_t, (size_t)PRISM_MAX_SEQ * (model->head_dim / 2) * sizeof(float2)));
   CREATE_TRY(launch_rope_table(c->rope_tab_t, PRISM_MAX_SEQ, model->head_dim, model->rope_base, c->stream, true));
-  CREATE_TRY(dev_alloc(c, (void **)&c->d_scores, PRISM_MAX_CANDS * sizeof(float)));
-  CREATE_TRY(dev_alloc(c, (void **)&c->d_fate, PRISM_MAX_CANDS));
-  CREATE_TRY(dev_alloc(c, (void **)&c->d_stats, 4 * sizeof(double)));
+  CREATE_TRY(dev_alloc(c, (void **)&c->d_res, kResultBytes));
   CREATE_TRY(dev_alloc(c, &c->route_ws, route_workspace_bytes(PRISM_MAX_CANDS, PRISM_MAX_CLUSTERS)));
-  CREATE_TRY(dev_alloc(c, (void **)&c->d_top_pos, PRISM_MAX_CANDS * sizeof(int32_t)));
-  CREATE_TRY(dev_alloc(c, (void **)&c->d_top_scores, PRISM_MAX_CANDS * sizeof(float)));
-  CREATE_HIP(hipHostMalloc((void **)&c->h_res, PRISM_MAX_CANDS * 16 + 256, hipHostMallocDefault));
+  CREATE_HIP(hipHostMalloc((void **)&c->h_res, kResultBytes, hipHostMallocDefault));
   if (c->offload) {
     CREATE_HIP(hipStreamCreateWithFlags(&c->xin_stream, hipStreamNonBlocking));
     CREATE_HIP(hipStreamCreateWithFlags(&c->xout_stream, hipStreamNonBlocking));
@@ -421,14 +422,15 @@ extern "C" void prism_destroy(prism_ctx *c) {
     for (hipEvent_t e : {c->ev_in[i], c->ev_done[i], c->ev_out[i]}) if (e) (void)hipEventDestroy(e);
   if (c->xin_stream) (void)hipStreamDestroy(c->xin_stream);
   if (c->xout_stream) (void)hipStreamDestroy(c->xout_stream);
-  void *ptrs[] = {c->AOl, c->Xnl, c->Sl, c->Xl, c->rope_tab, c->rope_tab_t, c->X[0], c->X[1], c->Xn, c->QKV, c->QK, c->Vt, c->AO, c->S, c->d_meta, c->d_scores, c->d_fate,
-                  c->d_stats, c->route_ws, c->d_top_pos, c->d_top_scores};
+  void *ptrs[] = {c->AOl, c->Xnl, c->Sl, c->Xl, c->rope_tab, c->rope_tab_t, c->X[0], c->X[1], c->Xn, c->QKV, c->QK, c->Vt, c->AO, c->S, c->d_meta, c->d_res,
+                  c->route_ws};
   for (void *p : ptrs) if (p) (void)hipFree(p);
   if (c->h_meta) (void)hipHostFree(c->h_meta);
   if (c->h_res) (void)hipHostFree(c->h_res);
   for (hipEvent_t e : c->ev_ready) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev_free) if (e) (void)hipEventDestroy(e);
-  for (int i = 0; i < 4; ++i) if (c->ev_t[i]) (void)hipEventDestroy(c->ev_t[i]);
+  for (hipEvent_t e : c->ev_t) if (e) (void)hipEventDestroy(e);
+  for (hipEvent_t e : c->ev_check) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev_layer) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev_xfer) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev_pool) if (e) (void)hipEventDestroy(e);
@@ -990,6 +992,14 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   PRISM_TRY(ensure_scratch(c, p, may_prune, n_cands, max_tiles));
   const MetaOff mo = meta_offsets(p.T, n_cands, max_tiles);
   hipStream_t s = c->stream;
+  // layout of the result block for this call (every part starts on 64 bytes)
+  const size_t n_res = (size_t)round_up(n_cands, 64), res_scores = 64, res_fate = res_scores + 4 * n_res, res_top = res_fate + n_res,
+               res_end = res_top + 8 * n_res;
+  c->d_stats = (double *)c->d_res;
+  c->d_scores = (float *)(c->d_res + res_scores);
+  c->d_fate = (int8_t *)(c->d_res + res_fate);
+  c->d_top_pos = (int32_t *)(c->d_res + res_top);
+  c->d_top_scores = (float *)(c->d_res + res_top + 4 * n_res);
 
   // tokens, packed: sequence i = query ++ candidate i; with a shared query the query's tokens once per chunk
   {
@@ -1074,12 +1084,16 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   std::vector<int> final_idx;
   std::vector<float> final_scores;
   size_t next_ckpt = 0;
-  double ms_checks = 0.0;
-  float *h_scores = (float *)c->h_res;
-  int8_t *h_fate = (int8_t *)(c->h_res + PRISM_MAX_CANDS * 4);
-  double *h_stats = (double *)(c->h_res + PRISM_MAX_CANDS * 5);
-  int32_t *h_top_pos = (int32_t *)(c->h_res + PRISM_MAX_CANDS * 5 + 64);
-  float *h_top_scores = (float *)(c->h_res + PRISM_MAX_CANDS * 9 + 64);
+  int n_checks = 0;
+  const double *h_stats = (const double *)c->h_res;
+  const float *h_scores = (const float *)(c->h_res + res_scores), *h_top_scores = (const float *)(c->h_res + res_top + 4 * n_res);
+  const int8_t *h_fate = (const int8_t *)(c->h_res + res_fate);
+  const int32_t *h_top_pos = (const int32_t *)(c->h_res + res_top);
+  auto fetch = [&](size_t from, size_t to) -> int {      // bytes [from, to) of the result block, on the host when this returns
+    PRISM_HIP(hipMemcpyAsync(c->h_res + from, c->d_res + from, to - from, hipMemcpyDeviceToHost, s));
+    PRISM_HIP(hipStreamSynchronize(s));
+    return PRISM_OK;
+  };
 
   auto record_event = [&](int layer, int n_before, const std::vector<int> &live_before, bool gate, int n_clusters,
                           double mean, double sd, const int8_t *fate /* may be null */, const std::vector<char> *keep) {
@@ -1137,16 +1151,19 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     bool compacted = false;
 
     // ---- pruning check on the output of layer l + 1, before layer l + 2 runs (Sec. 3.4, 4.1)
-    if (timed) PRISM_HIP(hipEventRecord(c->ev_t[2], s));
+    if (timed) {
+      while ((int)c->ev_check.size() < 2 * (n_checks + 1)) {
+        c->ev_check.push_back(nullptr);
+        PRISM_HIP(hipEventCreate(&c->ev_check.back()));
+      }
+      PRISM_HIP(hipEventRecord(c->ev_check[2 * n_checks], s));
+    }
     if (!c->offload && !peek)   // offload mode scored every chunk while it was on the device, the first pass its last rows
       PRISM_TRY(launch_score(c->X[cur], c->d_meta + mo.lastrow, n_live, m.hidden, c->final_norm, c->w_yes, c->w_no, m.dtype,
                              m.rms_eps, c->d_scores, s));
     PRISM_TRY(launch_route(c->d_scores, n_live, K_rem, c->opt.n_clusters, c->opt.cv_threshold, c->d_fate, c->d_stats,
                            c->route_ws, s));
-    PRISM_HIP(hipMemcpyAsync(h_scores, c->d_scores, (size_t)n_live * 4, hipMemcpyDeviceToHost, s));
-    PRISM_HIP(hipMemcpyAsync(h_fate, c->d_fate, (size_t)n_live, hipMemcpyDeviceToHost, s));
-    PRISM_HIP(hipMemcpyAsync(h_stats, c->d_stats, 4 * sizeof(double), hipMemcpyDeviceToHost, s));
-    PRISM_HIP(hipStreamSynchronize(s));
+    PRISM_TRY(fetch(0, res_top));
     const bool gate = h_stats[2] != 0.0;
     const int n_clu = (int)h_stats[3];
     std::vector<char> keep(n_live, 1);
@@ -1167,18 +1184,14 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
       if (n_sel > 0) {
         // selected candidates leave with their exit-time score, best first
         PRISM_TRY(launch_topk_masked(c->d_scores, c->d_fate, PRISM_FATE_SELECTED, n_live, n_sel, c->d_top_pos, c->d_top_scores, s));
-        PRISM_HIP(hipMemcpyAsync(h_top_pos, c->d_top_pos, (size_t)n_sel * 4, hipMemcpyDeviceToHost, s));
-        PRISM_HIP(hipMemcpyAsync(h_top_scores, c->d_top_scores, (size_t)n_sel * 4, hipMemcpyDeviceToHost, s));
-        PRISM_HIP(hipStreamSynchronize(s));
+        PRISM_TRY(fetch(res_top, res_end));
         for (int i = 0; i < n_sel; ++i) { early_idx.push_back(p.live[h_top_pos[i]]); early_scores.push_back(h_top_scores[i]); }
         K_rem -= n_sel;
       }
       if (n_def == K_rem) {
         // Sec. 4.1: the deferred set fills the remaining slots exactly -> the forward stops here
         PRISM_TRY(launch_topk_masked(c->d_scores, c->d_fate, PRISM_FATE_DEFERRED, n_live, n_def, c->d_top_pos, c->d_top_scores, s));
-        PRISM_HIP(hipMemcpyAsync(h_top_pos, c->d_top_pos, (size_t)n_def * 4, hipMemcpyDeviceToHost, s));
-        PRISM_HIP(hipMemcpyAsync(h_top_scores, c->d_top_scores, (size_t)n_def * 4, hipMemcpyDeviceToHost, s));
-        PRISM_HIP(hipStreamSynchronize(s));
+        PRISM_TRY(fetch(res_top, res_end));
         for (int i = 0; i < n_def; ++i) { final_idx.push_back(p.live[h_top_pos[i]]); final_scores.push_back(h_top_scores[i]); }
         terminated = true;
       }
@@ -1228,13 +1241,8 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
       p = q;
       compacted = true;
     }
-    if (timed) {
-      PRISM_HIP(hipEventRecord(c->ev_t[3], s));
-      PRISM_HIP(hipEventSynchronize(c->ev_t[3]));
-      float ms = 0.f;
-      PRISM_HIP(hipEventElapsedTime(&ms, c->ev_t[2], c->ev_t[3]));
-      ms_checks += ms;
-    }
+    if (timed) PRISM_HIP(hipEventRecord(c->ev_check[2 * n_checks + 1], s));   // read after the call's last synchronisation
+    ++n_checks;
     if (peek) {
       if (!terminated) {
         // second pass: the layer for the survivors.  If the pool is one chunk, the scratch still holds this layer's q, k
@@ -1257,11 +1265,8 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     const int k_out = std::min(K_rem, n_live);
     // (the last layer has scored every candidate from its gathered last-token state)
     PRISM_TRY(launch_topk(c->d_scores, n_live, k_out, c->d_top_pos, c->d_top_scores, s));
-    PRISM_HIP(hipMemcpyAsync(h_scores, c->d_scores, (size_t)n_live * 4, hipMemcpyDeviceToHost, s));
-    PRISM_HIP(hipMemcpyAsync(h_top_pos, c->d_top_pos, (size_t)k_out * 4, hipMemcpyDeviceToHost, s));
-    PRISM_HIP(hipMemcpyAsync(h_top_scores, c->d_top_scores, (size_t)k_out * 4, hipMemcpyDeviceToHost, s));
     if (timed) PRISM_HIP(hipEventRecord(c->ev_t[1], s));
-    PRISM_HIP(hipStreamSynchronize(s));
+    PRISM_TRY(fetch(res_scores, res_end));
     for (int i = 0; i < k_out; ++i) { final_idx.push_back(p.live[h_top_pos[i]]); final_scores.push_back(h_top_scores[i]); }
     record_event(m.n_layers, n_live, p.live, false, 0, 0.0, 0.0, nullptr, nullptr);
   } else {
@@ -1299,7 +1304,12 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
       mx += ms;
     }
     rep->ms_transfers = mx;
-    rep->ms_checks = ms_checks;
+    double mc = 0.0;
+    for (int k = 0; k < n_checks; ++k) {
+      PRISM_HIP(hipEventElapsedTime(&ms, c->ev_check[2 * k], c->ev_check[2 * k + 1]));
+      mc += ms;
+    }
+    rep->ms_checks = mc;
     rep->token_layers = token_layers;
     rep->peak_hbm_bytes = c->bytes_peak;
     rep->bytes_streamed = bytes_streamed;
