@@ -24,8 +24,9 @@
 // start at a multiple of 64 so every 16-byte chunk is aligned.
 // Shared prefix (paper Sec. 3.3: every (query, candidate) sequence begins with the same query): positions below
 // pre_len of a work item's sequence have their q/k rows stored once, at pre_row0 + position, for all sequences of the
-// launch; the K staging picks the row per key.  V^T needs no such case: every sequence's columns cover all its
-// positions.  The output row base is a field of its own (out_base), so that a launch can read q and k in one row layout
+// launch; the K staging picks the row per key.  Their V^T columns are stored once too, at columns 0 .. pre_len, and the
+// V^T staging picks them in whole groups of 16 keys (the unit of the column order); only the prefix's last, incomplete
+// group is expected in every sequence's own columns.  The output row base is a field of its own (out_base), so that a launch can read q and k in one row layout
 // and write its output in another.
 #include <type_traits>
 
@@ -105,6 +106,7 @@ void attention_16_kernel(const OT *__restrict__ QK, const f16 *__restrict__ Vt, 
   }
   const char *const kcol = reinterpret_cast<const char *>(QK + (int64_t)(nq + kvh) * HD);
   const char *const vrow = reinterpret_cast<const char *>(Vt + (int64_t)kvh * HD * vt_stride + it.vt_col0);
+  const int pre16 = it.pre_len & ~15;      // V^T of the keys below comes from the prefix's own columns, which start at 0
   auto stage_tile = [&](int kt, auto buf_tag) {
     constexpr int BUF = decltype(buf_tag)::value;
     OT *const lK = BUF ? lK1 : lK0;
@@ -127,9 +129,19 @@ void attention_16_kernel(const OT *__restrict__ QK, const f16 *__restrict__ Vt, 
       }
     }
     const char *vb = vrow + (int64_t)k0 * 2;
+    if (k0 >= pre16) {
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
-      __builtin_amdgcn_global_load_lds(PRISM_GLOBAL_PTR(vb + oV[j]), PRISM_LDS_PTR(&lV[(wave_u * NI + j) * 8 * BKV]), 16, 0, 0);
+      for (int j = 0; j < NI; ++j)
+        __builtin_amdgcn_global_load_lds(PRISM_GLOBAL_PTR(vb + oV[j]), PRISM_LDS_PTR(&lV[(wave_u * NI + j) * 8 * BKV]), 16, 0, 0);
+    } else {
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        // chunk of this lane: two chunks hold the 16 keys of a group, which is the prefix's or the sequence's as a whole
+        const int vr = (wave * NI + j) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((vr >> 1) & 7);
+        const char *src = (k0 + (chunk >> 1) * 16 < pre16 ? vb - (int64_t)it.vt_col0 * 2 : vb) + oV[j];
+        __builtin_amdgcn_global_load_lds(PRISM_GLOBAL_PTR(src), PRISM_LDS_PTR(&lV[(wave_u * NI + j) * 8 * BKV]), 16, 0, 0);
+      }
+    }
   };
 
   f32x16 o[HD / 32];

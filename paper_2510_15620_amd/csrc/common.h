@@ -127,9 +127,10 @@ int launch_qk_finish_fp32(float *QKV, const int32_t *pos, const void *q_gain, co
 int launch_qkv_finish_16(int dtype, const float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv,
                          int hd, float eps, int qk_norm, const float2 *rope_tab, void *QK, void *Vt, const int32_t *vt_col,
                          int64_t vt_stride, hipStream_t s);
-// Copies the V^T columns of a chunk's shared query (positions [0, ql): columns vt_column_of_key(position) of the chunk,
-// whose query sequence starts at column 0) into the column range of each of n_seq sequences (first columns seq_col0[i],
-// [device]); rows = nkv * hd rows of Vt.  Columns of positions >= ql are left alone.
+// Copies the last, incomplete group of 16 V^T columns of a chunk's shared query (positions [ql & ~15, ql), at columns
+// vt_column_of_key(position) of the chunk, whose query sequence starts at column 0) into the column range of each of n_seq
+// sequences (first columns seq_col0[i], [device]); rows = nkv * hd rows of Vt.  Columns of positions >= ql are left alone;
+// nothing is launched if ql is a multiple of 16.  The attention kernel reads the whole groups from the query's own columns.
 int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, const int32_t *seq_col0, int n_seq, hipStream_t s);
 
 // matrix-core attention (hd == 128).  tiles: per work item {row base of the sequence, sequence length, first query of
@@ -137,7 +138,8 @@ int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, co
 // Positions below pre_len are a prefix whose q/k rows are stored once, at pre_row0 + position, and shared by several
 // sequences (Sec. 3.3 batches (query, candidate) pairs that all begin with the same query; under a causal mask the
 // query tokens' states do not depend on the candidate); position p >= pre_len has row row_base + p.  Without a prefix
-// pre_len = 0 and row_base is the sequence's first row.  V^T columns are per sequence for ALL its positions.
+// pre_len = 0 and row_base is the sequence's first row.  V^T columns: those of whole groups of 16 prefix positions are read
+// at columns 0 .. pre_len, all others at the sequence's own.
 // out_base: the tile's output for position p goes to row out_base + p (normally row_base; it differs when the layout the
 // q/k rows were projected in is not the one the layer continues in).
 struct AttnTile { int32_t row_base, seq_len, q0, vt_col0, pre_len, pre_row0, out_base, reserved; };

@@ -430,22 +430,20 @@ int launch_compact(const float *Xs, float *Xd, const int32_t *src_start, const i
 }
 
 // ------------------------------------------------------------------------------------------------
-// Shared query: its V^T columns, written once per chunk, are copied into every sequence's column range.
-__global__ __launch_bounds__(256) void vt_prefix_broadcast_kernel(f16 *__restrict__ Vt, int64_t vt_stride, int rows, int ql,
-                                                                   const int32_t *__restrict__ seq_col0) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
+// Shared query: the attention kernel reads its V^T columns in whole groups of 16 where they were written; the columns of a last,
+// incomplete group are copied into every sequence's column range.  16 lanes per row and sequence.
+__global__ __launch_bounds__(256) void vt_prefix_tail_kernel(f16 *__restrict__ Vt, int64_t vt_stride, int rows, int ql,
+                                                             const int32_t *__restrict__ seq_col0) {
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 4), col = (ql & ~15) + (threadIdx.x & 15);
+  if (row >= rows || vt_column_of_key(col) >= ql) return;                  // the mapping is its own inverse
   f16 *v = Vt + (int64_t)row * vt_stride;
-  const int col0 = seq_col0[blockIdx.y];
-  const int ncol = (ql + 15) & ~15;
-  for (int cidx = threadIdx.x & 63; cidx < ncol; cidx += 64)
-    if (vt_column_of_key(cidx) < ql) v[col0 + cidx] = v[cidx];        // the mapping is its own inverse
+  v[seq_col0[blockIdx.y] + col] = v[col];
 }
 
 int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, const int32_t *seq_col0, int n_seq, hipStream_t s) {
   PRISM_REQUIRE(Vt && seq_col0 && vt_stride > 0 && rows > 0 && ql > 0 && n_seq >= 0, PRISM_EINVAL, "vt prefix broadcast: bad arguments");
-  if (n_seq == 0) return PRISM_OK;
-  vt_prefix_broadcast_kernel<<<dim3(cdiv(rows, 4), n_seq), 256, 0, s>>>((f16 *)Vt, vt_stride, rows, ql, seq_col0);
+  if (n_seq == 0 || ql % 16 == 0) return PRISM_OK;
+  vt_prefix_tail_kernel<<<dim3(cdiv(rows, 16), n_seq), 256, 0, s>>>((f16 *)Vt, vt_stride, rows, ql, seq_col0);
   PRISM_HIP(hipGetLastError());
   return PRISM_OK;
 }

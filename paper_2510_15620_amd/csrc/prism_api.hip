@@ -862,7 +862,7 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
       return launch_qk_finish_fp32((float *)c->QKV, pos, wbuf + L.q_norm, wbuf + L.k_norm, Tc, m.n_q_heads, m.n_kv_heads, m.head_dim,
                                    m.rms_eps, m.qk_norm, c->rope_tab, s);
     }));
-    if (p.ql > 0)   // every sequence's V^T columns cover all its positions: the query's part is copied in (a few MB)
+    if (p.ql % 16 != 0)   // the query's last, incomplete group of V^T columns goes into every sequence's columns
       PRISM_TRY(timed_span(c, 5, 0.0, [&] {
         return launch_vt_prefix_broadcast(c->Vt, c->vt_cap, Dkv, p.ql, c->d_meta + mo.seqcol + ch.c0, ch.c1 - ch.c0, s);
       }));

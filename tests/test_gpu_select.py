@@ -7,6 +7,8 @@ every checkpoint, the surviving sets, the final top-K.  Comparison rule:
 The oracle is the exact (fp64) one.  Only the bf16-operand variant of the 16-bit mode is compared with the
 oracle run in the same operand precision as well.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -294,6 +296,18 @@ def test_sharing_the_query_rows_changes_nothing(name, kw):
     assert np.array_equal(shared[2].scores, own[2].scores, equal_nan=True)
     assert np.array_equal(shared[2].fate, own[2].fate) and shared[2].layer.tolist() == own[2].layer.tolist()
     assert shared[2].token_layers == own[2].token_layers            # counted in sequence tokens either way
+
+
+@pytest.mark.parametrize("query_len", [1, 15, 16, 17, 48, 63, 64, 65, 130, 208])
+@pytest.mark.parametrize("chunk", [0, 4])
+def test_sharing_a_query_of_any_length_changes_nothing(query_len, chunk):
+    """The shared query's V^T columns are read in whole groups of 16 keys where they were written, an incomplete last group
+    from every sequence's own columns: queries below, at and above the sizes of a group (16) and of a key tile (64)."""
+    w = dataclasses.replace(W.WORKLOADS["mini_bf16"], query_len=query_len)
+    wt = W.make_weights(w, "cuda")
+    shared, own = run(w, wt, chunk_cands=chunk), run(w, wt, share_query=False, chunk_cands=chunk)
+    assert shared[0].tolist() == own[0].tolist() and np.array_equal(shared[1], own[1])
+    assert np.array_equal(shared[2].scores, own[2].scores, equal_nan=True)
 
 
 @pytest.mark.parametrize("name,kw", [("cfg1_tiny", {}), ("mini_fp32", {"chunk_cands": 4}), ("mini_bf16", {}), ("mini_bf16", {"chunk_cands": 3}),
