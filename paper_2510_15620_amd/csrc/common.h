@@ -105,7 +105,11 @@ bool gemm_16_qkv_supported(int nq, int nkv, int hd, int K);
 bool gemm_16_qkv_large(int M, int nq, int nkv);
 int launch_gemm_16_qkv(int dtype, const void *Xn, const void *Wqkv, int M, int K, int hd, const QkvEpilogue &e, hipStream_t s);
 
-// dst row dst_idx[i] (i itself if dst_idx is null) = src row src_idx[i], i < n; rows of row_bytes (a multiple of 16) bytes.  src may be pinned host
+// rows of two tables by one index list: dst0[i] = src0[idx[i]], dst1[i] = src1[idx[i]], i < n; row sizes multiples of 16 bytes
+int launch_gather_rows(const void *src0, const void *src1, const int32_t *idx, void *dst0, void *dst1, int n, size_t row_bytes0,
+                       size_t row_bytes1, hipStream_t s);
+
+// dst row dst_idx[i] = src row src_idx[i], i < n; rows of row_bytes (a multiple of 16) bytes.  src may be pinned host
 // memory (its device-visible address): the embedding-table cache fetches its misses this way (Sec. 4.4).
 int launch_copy_rows(const void *src, const int32_t *src_idx, void *dst, const int32_t *dst_idx, int n, size_t row_bytes,
                      hipStream_t s);

@@ -884,8 +884,8 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
       char *AOl = c->AOl + (size_t)ch.c0 * Dq * e, *Xnl = c->Xnl + (size_t)ch.c0 * H * e, *Sl = c->Sl + (size_t)ch.c0 * F * e;
       float *Xl = c->Xl + (size_t)ch.c0 * H;
       PRISM_TRY(timed_span(c, 5, 0.0, [&] {
-        PRISM_TRY(launch_copy_rows(c->AO - ch.r0 * (int64_t)Dq * (int64_t)e, last_row, AOl, nullptr, nc, (size_t)Dq * e, s));
-        return launch_copy_rows(Xc - ch.r0 * H, last_row, Xl, nullptr, nc, (size_t)H * 4, s);
+        return launch_gather_rows(c->AO - ch.r0 * (int64_t)Dq * (int64_t)e, Xc - ch.r0 * H, last_row, AOl, Xl, nc, (size_t)Dq * e,
+                                  (size_t)H * 4, s);
       }));
       // (timed with the elementwise kind: these launches are a different, tiny kernel configuration and would blur the
       // per-launch figures of the layer GEMMs)
