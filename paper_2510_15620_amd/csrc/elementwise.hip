@@ -1,5 +1,7 @@
 // Bandwidth- and latency-bound steps of the path: embedding gather, RMSNorm, q/k norm + RoPE,
 // V rounding + transposition, the intermediate scorer, compaction and the final top-K.
+#include <type_traits>
+
 #include "common.h"
 
 namespace prism {
@@ -311,13 +313,69 @@ __global__ __launch_bounds__(256) void qkv_finish_16_kernel(const float *__restr
   for (int d = wave; d < HD; d += 4) dst[(int64_t)d * vt_stride] = tile[lane][d];
 }
 
+// The same in place for the fp32 mode where a head's pairs fit a power of two of lanes (head sizes 32, 64 and 128): P lanes per
+// (token, head), so that no lane idles, and U of them per lane with their loads issued together: four where that still gives
+// every compute unit two workgroups, one below (354 tokens: 3.6 us, with four 5.0).
+// 12859 tokens, 6 heads of 64: 26 -> 12 us.  The sum of squares keeps wave_sum's order (lanes beyond P added zeros).
+template <int P, int U>
+__global__ __launch_bounds__(256) void qk_finish_fp32_kernel(float *__restrict__ QKV, const int32_t *__restrict__ pos,
+                                                             const float *__restrict__ q_gain, const float *__restrict__ k_gain, int64_t items,
+                                                             int nq, int nkv, float eps, int qk_norm, const float2 *__restrict__ rope_tab) {
+  constexpr int HD = 2 * P, G = 256 / P;                     // G items side by side in a workgroup, U rounds
+  const int heads = nq + nkv, i = threadIdx.x % P;
+  const int64_t first = (int64_t)blockIdx.x * (G * U) + threadIdx.x / P;
+  float a[U], b[U];
+  float2 cs[U];
+  float *x[U];
+  int h[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t item = first + u * G < items ? first + u * G : items - 1;
+    const int t = (int)(item / heads);
+    h[u] = (int)(item - (int64_t)t * heads);
+    x[u] = QKV + (int64_t)t * (nq + 2 * nkv) * HD + h[u] * HD + i;
+    a[u] = x[u][0];
+    b[u] = x[u][P];
+    cs[u] = rope_tab[(int64_t)pos[t] * P + i];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (qk_norm) {
+      float ss = __builtin_fmaf(a[u], a[u], b[u] * b[u]);
+#pragma unroll
+      for (int o = P / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+      const float r = 1.0f / sqrtf(ss / (float)HD + eps);
+      const float *g = h[u] < nq ? q_gain : k_gain;
+      a[u] = a[u] * r * g[i];
+      b[u] = b[u] * r * g[i + P];
+    }
+    if (first + u * G >= items) return;
+    x[u][0] = __builtin_fmaf(a[u], cs[u].x, -(b[u] * cs[u].y));
+    x[u][P] = __builtin_fmaf(b[u], cs[u].x, a[u] * cs[u].y);
+  }
+}
+
 int launch_qk_finish_fp32(float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv, int hd,
                           float eps, int qk_norm, const float2 *rope_tab, hipStream_t s) {
   PRISM_REQUIRE(QKV && pos && rope_tab && T >= 0 && nq > 0 && nkv > 0 && hd > 0 && hd % 2 == 0, PRISM_EINVAL,
                 "qk_finish: bad arguments");
   PRISM_REQUIRE(!qk_norm || (q_gain && k_gain), PRISM_EINVAL, "qk_finish: gains missing");
   if (T == 0) return PRISM_OK;
-  qk_finish_kernel<float><<<cdiv((int64_t)T * (nq + nkv), 4), 256, 0, s>>>(QKV, pos, (const float *)q_gain, (const float *)k_gain, T, nq, nkv, hd,
+  const int64_t items = (int64_t)T * (nq + nkv);
+  auto run = [&](auto p) {
+    constexpr int P = decltype(p)::value;
+    auto go = [&](auto u) {
+      constexpr int U = decltype(u)::value;
+      qk_finish_fp32_kernel<P, U><<<cdiv(items, 256 / P * U), 256, 0, s>>>(QKV, pos, (const float *)q_gain, (const float *)k_gain, items, nq, nkv, eps,
+                                                                          qk_norm, rope_tab);
+    };
+    if (cdiv(items, 256 / P * 4) >= 512) go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 1>{});
+  };
+  if (hd == 32) run(std::integral_constant<int, 16>{});
+  else if (hd == 64) run(std::integral_constant<int, 32>{});
+  else if (hd == 128) run(std::integral_constant<int, 64>{});
+  else qk_finish_kernel<float><<<cdiv((int64_t)T * (nq + nkv), 4), 256, 0, s>>>(QKV, pos, (const float *)q_gain, (const float *)k_gain, T, nq, nkv, hd,
                                                                             eps, qk_norm, rope_tab, QKV, (nq + 2 * nkv) * hd);
   PRISM_HIP(hipGetLastError());
   return PRISM_OK;

@@ -541,3 +541,22 @@ def test_topk_of_any_pool(n, K):
     B.op_topk(torch.from_numpy(s).to(DEV), K, pos, sc)
     order = O.rank_order(s.astype(np.float64))[:K]
     assert np.array_equal(pos.cpu().numpy(), order) and np.array_equal(sc.cpu().numpy(), s[order])
+
+
+@pytest.mark.parametrize("hd,nq,nkv,T", [(32, 3, 1, 5), (64, 4, 2, 354), (64, 4, 2, 12859), (128, 1, 1, 9001), (48, 2, 1, 77)])
+@pytest.mark.parametrize("qk_norm", [True, False])
+def test_qk_finish_fp32_head_sizes(hd, nq, nkv, T, qk_norm):
+    """fp32 finishing, one or four (token, head) items per lane group by the number of items, other head sizes one at a time:
+    against fp64 at the bound of the single-kernel test; v is left as it was."""
+    pos = (np.arange(T) % 517).astype(np.int32)
+    QKV = _rand((T, (nq + 2 * nkv) * hd), torch.float32, T + hd, 1.5)
+    gq, gk = 1 + _rand((hd,), torch.float32, 41, 0.1), 1 + _rand((hd,), torch.float32, 42, 0.1)
+    x = _f64(QKV).reshape(T, nq + 2 * nkv, hd)
+    q, k = x[:, :nq], x[:, nq:nq + nkv]
+    if qk_norm:
+        q, k = O.rmsnorm(q, _f64(gq), 1e-6), O.rmsnorm(k, _f64(gk), 1e-6)
+    d = QKV.to(DEV).clone()
+    B.op_qkv_finish(B.DTYPE_FP32, d, torch.from_numpy(pos).to(DEV), 517, gq.to(DEV), gk.to(DEV), nq, nkv, hd, 1e-6, 1e6, qk_norm)
+    ref = np.concatenate([O.rope(q, pos, 1e6), O.rope(k, pos, 1e6), x[:, nq + nkv:]], axis=1).reshape(T, -1)
+    np.testing.assert_allclose(_f64(d), ref, rtol=1e-5, atol=2e-5)
+    assert torch.equal(d.cpu()[:, (nq + nkv) * hd:], QKV[:, (nq + nkv) * hd:])
