@@ -267,12 +267,12 @@ int prism_op_qkv_finish(int32_t dtype, void *QKV, const int32_t *pos, int32_t ma
                         float eps, float rope_base, int32_t qk_norm, void *QK, void *Vt, const int32_t *vt_col,
                         int64_t vt_stride, void *stream);
 
-/* The fused form of prism_op_gemm (fp32 store) + prism_op_qkv_finish for the 16-bit modes, which is what prism_select
- * runs whenever it applies: [Q|K|V] = Xn Wqkv^T with Xn [T, hidden] and Wqkv [(nq+2nkv)*hd, hidden] ([device], dtype),
+/* The fused form of prism_op_gemm (fp32 store) + prism_op_qkv_finish for the 16-bit modes (prism_select runs the fused
+ * kernel for launches of every size; below the size given here with the finishing kernel's summation order): [Q|K|V] = Xn Wqkv^T with Xn [T, hidden] and Wqkv [(nq+2nkv)*hd, hidden] ([device], dtype),
  * then per-head RMSNorm (optional) and RoPE on q and k and the transposed half-precision V, all applied to the fp32
  * accumulators in the GEMM's epilogue (one rounding, no fp32 intermediate in memory).  Outputs, pos, vt_col, gains as
- * in prism_op_qkv_finish.  Needs head_dim == 128, hidden % 64 == 0 and ceil(T / 256) * (nq + 2 nkv) / 2 >= 256 (one
- * head per wavefront of a 256 x 256 tile, enough tiles to fill the chip); PRISM_EUNSUPPORTED otherwise.
+ * in prism_op_qkv_finish.  Needs head_dim == 128, hidden % 64 == 0 and ceil(T / 256) * (nq + 2 nkv) / 2 >= 256 (enough
+ * 256 x 256 tiles to fill the chip); PRISM_EUNSUPPORTED otherwise.
  * Synchronises the stream before returning. */
 int prism_op_qkv_project(int32_t dtype, const void *Xn, const void *Wqkv, const int32_t *pos, int32_t max_pos,
                          const void *q_gain, const void *k_gain, int32_t T, int32_t hidden, int32_t n_q_heads,
@@ -311,12 +311,12 @@ int prism_op_route(const float *scores, int32_t n, int32_t K_rem, int32_t n_clus
                    int8_t *fate, double *stats, void *stream);
 
 /* prism_op_route for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc.  Same arguments, same kernel, same results as prism_op_route; the kernel's workspace
- * (328 192 bytes, enough for n = PRISM_MAX_CANDS and n_clusters = PRISM_MAX_CLUSTERS; larger requests are rejected with
+ * harnesses that forbid hipMalloc.  Same arguments, same kernels, same results as prism_op_route; the kernels' workspace
+ * (329 472 bytes, enough for n = PRISM_MAX_CANDS and n_clusters = PRISM_MAX_CLUSTERS; larger requests are rejected with
  * PRISM_EINVAL) is a static device array of the library, one copy per device, held until the process ends.  The call
  * allocates and frees nothing and does NOT synchronise: fate and stats are ready when `stream` has drained.  Every
  * call on a device uses that device's one workspace, so calls that overlap on a device (different streams or threads)
- * race; the kernel overwrites every workspace entry before reading it, so consecutive calls need no clearing. */
+ * race; the kernels overwrite every workspace entry before reading it, so consecutive calls need no clearing. */
 int prism_op_route_static(const float *scores, int32_t n, int32_t K_rem, int32_t n_clusters, float tau,
                           int8_t *fate, double *stats, void *stream);
 
