@@ -57,6 +57,8 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
   T *o = out + (int64_t)blockIdx.x * hidden;
   // NV > 0: the row (at most NV * 1024 values) stays in registers between the two passes; it is not needed again before
   // the layer's next GEMM epilogue, so the loads bypass the caches' retention.  NV == 0: any width, the row is read twice.
+  // The gains are requested with the row, not behind the sum: a launch of a few hundred rows is one round of latencies.
+  struct alignas(sizeof(T) * 4) Quad { T v[4]; } g[NV > 0 ? NV : 1];
   f32x4_t keep[NV > 0 ? NV : 1];
   float ss = 0.f;
   if (NV > 0) {
@@ -65,6 +67,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
       const int i = threadIdx.x * 4 + k * 1024;
       if (i < hidden) {
         keep[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(x + i));
+        g[k] = *reinterpret_cast<const Quad *>(gain + i);
         ss += keep[k][0] * keep[k][0] + keep[k][1] * keep[k][1] + keep[k][2] * keep[k][2] + keep[k][3] * keep[k][3];
       }
     }
@@ -76,8 +79,8 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
   }
   ss = block_sum_256(ss, red);
   const float r = 1.0f / sqrtf(ss / (float)hidden + eps);
-  auto emit = [&](int i, float a, float b, float c, float d) {
-    struct alignas(sizeof(T) * 4) Quad { T v[4]; } q, g = *reinterpret_cast<const Quad *>(gain + i);
+  auto emit = [&](int i, float a, float b, float c, float d, const Quad &g) {
+    Quad q;
     q.v[0] = from_f32<T>(a * r * to_f32(g.v[0]));
     q.v[1] = from_f32<T>(b * r * to_f32(g.v[1]));
     q.v[2] = from_f32<T>(c * r * to_f32(g.v[2]));
@@ -88,12 +91,12 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int i = threadIdx.x * 4 + k * 1024;
-      if (i < hidden) emit(i, keep[k][0], keep[k][1], keep[k][2], keep[k][3]);
+      if (i < hidden) emit(i, keep[k][0], keep[k][1], keep[k][2], keep[k][3], g[k]);
     }
   } else {
     for (int i = threadIdx.x * 4; i < hidden; i += 1024) {
       float4 v = *reinterpret_cast<const float4 *>(x + i);
-      emit(i, v.x, v.y, v.z, v.w);
+      emit(i, v.x, v.y, v.z, v.w, *reinterpret_cast<const Quad *>(gain + i));
     }
   }
 }

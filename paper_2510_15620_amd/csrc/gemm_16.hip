@@ -126,8 +126,11 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   const int nk = K / BK;
 
   // ---- epilogue geometry (see the epilogue): everything it reads or writes goes along the rows, 16 bytes per lane.
-  //      Residual epilogue: the old values of a 32-row block are requested one block ahead.  (Requesting the first
-  //      block before the K loop was tried: holding 64 registers across the loop makes the compiler spill.)
+  //      Residual epilogue: the old values of a 32-row block are requested one block ahead, the first block's
+  //      before the K loop where registers are left (tiles below 256; the big tile spills).  The same for what the q/k/v
+  //      epilogue reads by row: a small tile's loop is a few microseconds, and each dependent load behind it about one.
+  //      (28 layers of the 0.6B shape on 391 rows, with the same in the RMSNorm: 2749 -> 2687 us.)
+  constexpr bool kEarly = BM < 256;
   constexpr bool kF32Out = EPI == PRISM_EPI_RESIDUAL || EPI == PRISM_EPI_STORE_F32;
   constexpr int ES = kF32Out ? 4 : 2;                               // bytes per output element
   constexpr int OUTW = EPI == PRISM_EPI_SWIGLU ? WNT / 2 : WNT;    // output columns of the wave
@@ -147,6 +150,22 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     }
   };
 
+
+  int row_in[kHeads ? TM : 1];                                      // q, k heads: positions; v heads: V^T columns
+  auto load_rows = [&]() __attribute__((always_inline)) {
+    if constexpr (kHeads) {
+      const int32_t *src = ((n0 + wn * WNT) >> 7) < qe.nq + qe.nkv ? qe.pos : qe.vt_col;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int row = m0 + wm * WMT + i * 32 + (lane & 31);
+        row_in[i] = src[row < M ? row : M - 1];
+      }
+    }
+  };
+  if constexpr (kEarly) {
+    if constexpr (kHeads) load_rows();
+    else if (full_n) load_old(0);
+  }
 
   // ---- epilogue.  The W fragment was the instruction's first operand, so the 32x32 accumulator tile is
   //      transposed: a lane holds ONE row of A, m = lane % 32, and the output columns
@@ -213,6 +232,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     static_assert(WNT == 128 && TN == 4, "one head per wavefront");
     typedef typename Mfma<OT>::vec4 vec4;
     const int head = (n0 + wn * WNT) >> 7;                 // wave-uniform
+    if constexpr (!kEarly) load_rows();                    // all row blocks' at once: one memory latency, not one per block
     if (head < qe.nq + qe.nkv) {
       const OT *gain = reinterpret_cast<const OT *>(head < qe.nq ? qe.q_gain : qe.k_gain);
       vec4 ga[2][4], gb[2][4];
@@ -227,14 +247,11 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
       }
       const int64_t pitch = (int64_t)(qe.nq + qe.nkv) * 128 * 2;
       // (cos, sin) of (pos, d) sits at [d * stride + pos]: a wave-uniform base per column plus one 32-bit lane offset.
-      // The positions of all four row blocks are fetched first and the 32 pairs of block i + 1 are requested before
-      // block i is worked on, so the tile pays the two memory latencies once, not once per block.
+      // The 32 pairs of block i + 1 are requested before block i is worked on, so the tile pays the memory latency once,
+      // not once per block.
       unsigned lane_off[TM];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * WMT + i * 32 + m_in;
-        lane_off[i] = (unsigned)n_in * (unsigned)qe.rope_stride + (unsigned)qe.pos[row < M ? row : M - 1];
-      }
+      for (int i = 0; i < TM; ++i) lane_off[i] = (unsigned)n_in * (unsigned)qe.rope_stride + (unsigned)row_in[i];
       float2 cs[2][2][4][4];
       auto load_cs = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
@@ -309,17 +326,11 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
       }
     } else {
       // v head: rounded to the operand type, stored as half, transposed (32 consecutive tokens of one d are contiguous)
-      int vcol[TM];                                          // all four blocks' columns first: one memory latency, not four
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * WMT + i * 32 + m_in;
-        vcol[i] = qe.vt_col[row < M ? row : M - 1];
-      }
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int row = m0 + wm * WMT + i * 32 + m_in;
         if (row >= M) continue;
-        f16 *vt = reinterpret_cast<f16 *>(qe.Vt) + (int64_t)(head - qe.nq - qe.nkv) * 128 * qe.vt_stride + vcol[i];
+        f16 *vt = reinterpret_cast<f16 *>(qe.Vt) + (int64_t)(head - qe.nq - qe.nkv) * 128 * qe.vt_stride + row_in[i];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -333,7 +344,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   }
 
   if (full_n) {
-    load_old(0);
+    if constexpr (!kEarly) load_old(0);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int row0 = m0 + wm * WMT + i * 32;                       // first row of the block
