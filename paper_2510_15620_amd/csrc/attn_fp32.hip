@@ -9,7 +9,8 @@
 // become the same row of the NB accumulator tiles), one tile of 16 keys ahead; the four waves of a workgroup and the heads of a
 // group meet in L1 and L2.  Bound by the chain of a tile (32 NB / 4 matrix instructions, softmax) with few waves per SIMD.
 // The tile on the diagonal, the only one with masked keys, takes its P V part on the vector pipes under the mask: a weight of
-// zero times a non-finite value of a token in the future would otherwise reach the sum.
+// zero times a non-finite value of a token in the future would otherwise reach the sum.  Until a query has met a finite score
+// its running maximum is -inf and its weights are taken relative to 0, so leading keys that score -inf weigh nothing.
 // 4 heads of 64, 12859 tokens of 160-512-token sequences: 771 us as one workgroup per (token, head) -> 85 us.
 //
 // attention_fp32_any_kernel: any other head size: the definition, one workgroup per (token, query head), score row in LDS.
@@ -82,12 +83,13 @@ __global__ __launch_bounds__(256) void attention_fp32_kernel(const float *__rest
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     const float m_new = fmaxf(m_run, mx);
-    const float alpha = expf(m_run - m_new);
+    const float ref = m_new == -INFINITY ? 0.f : m_new;      // all keys so far score -inf: weights exp(-inf) = 0, not exp(-inf + inf)
+    const float alpha = expf(m_run - ref);
     m_run = m_new;
     float sum = 0.f;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      p[s] = expf(p[s] - m_new);
+      p[s] = expf(p[s] - ref);
       sum += p[s];
     }
     l_run = l_run * alpha + sum;

@@ -404,6 +404,32 @@ def test_attention_fp32_work_items(nq, nkv, hd):
     assert not torch.isfinite(again.cpu()[cu[i + 1] - 1]).any()
 
 
+@pytest.mark.parametrize("hd", [32, 64, 128, 48])
+@pytest.mark.parametrize("n_blocked", [15, 16, 20, 64, 70])
+@pytest.mark.parametrize("by", ["infinite keys", "overflow"])
+def test_attention_fp32_scores_of_minus_infinity(hd, n_blocked, by):
+    """The first n_blocked keys of a sequence score -inf, through infinities in K or through an overflow of finite q . k: they
+    weigh nothing, and a query that sees a finite score has the softmax over the finite ones, also where all keys of its
+    first tiles (16 keys each) are blocked.  A query without any finite score has 0 / 0, as by the definition."""
+    nq, nkv, L, other = 4, 2, 150, 30
+    QKV = _rand((L + other, (nq + 2 * nkv) * hd), torch.float32, 700 + hd + n_blocked, 1.0)
+    x = QKV.view(L + other, nq + 2 * nkv, hd)
+    x[:, :nq] = x[:, :nq].abs() + 0.1
+    x[:n_blocked, nq:nq + nkv] = -math.inf
+    ref = [O.causal_gqa_attention(_f64(s[:, :nq]), np.maximum(_f64(s[:, nq:nq + nkv]), -1e30), _f64(s[:, nq + nkv:])).reshape(len(s), -1)
+           for s in (x[:L], x[L:])]                          # -1e30: the same weights of zero beside scores of order one
+    if by == "overflow":
+        x[:, :nq] *= 16
+        x[n_blocked:, nq:nq + nkv] /= 16
+        x[:n_blocked, nq:nq + nkv] = -3e38
+    out = torch.zeros(L + other, nq * hd, device=DEV)
+    B.op_attention(B.DTYPE_FP32, QKV.to(DEV), None, 0, np.array([0, L, L + other], np.int32), None, nq, nkv, hd, out)
+    got = _f64(out)
+    assert np.isnan(got[:n_blocked]).all()
+    np.testing.assert_allclose(got[n_blocked:L], ref[0][n_blocked:], rtol=1e-5, atol=2e-6)
+    np.testing.assert_allclose(got[L:], ref[1], rtol=1e-5, atol=2e-6)
+
+
 def test_attention_refuses_a_transposed_v_stride_beyond_its_32_bit_offsets():
     """The 16-bit kernel addresses the 128 rows of a KV head's V^T with 32-bit byte offsets: a row stride of 2^24 columns
     (128 rows x 2 bytes = 4 GiB) is refused before anything is launched (the buffers here are tiny and never touched)."""
