@@ -1428,10 +1428,15 @@ extern "C" int prism_op_attention(int32_t dtype, const void *QK, const void *Vt,
   const bool bf = is16(dtype);
   PRISM_REQUIRE(bf || dtype == PRISM_DTYPE_FP32, PRISM_EINVAL, "attention: unknown dtype %d", dtype);
   if (!bf) {
-    // what goes to the device: work items, or every token's position for the head sizes served without them
+    // what goes to the device: work items, or every token's position for the head sizes served without them.  The kernels
+    // run over [0, T): tokens in front of the first sequence belong to none and attend to themselves only
     std::vector<AttnTile> tiles;
     std::vector<int32_t> pos;
     const bool tiled = attention_fp32_tiled(hd) && ((uintptr_t)QK | (uintptr_t)out) % 16 == 0;
+    for (int t = 0; t < cu[0]; ++t) {
+      if (tiled) tiles.push_back({t, 1, 0, 0, 0, 0, t, 0});
+      else pos.push_back(0);
+    }
     for (int i = 0; i < n_seqs; ++i) {
       const int L = cu[i + 1] - cu[i];
       if (tiled) for (int q0 = (L - 1) / kAttn32BQ * kAttn32BQ; q0 >= 0; q0 -= kAttn32BQ) tiles.push_back({cu[i], L, q0, 0, 0, 0, cu[i], 0});

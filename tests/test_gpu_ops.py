@@ -430,6 +430,22 @@ def test_attention_fp32_scores_of_minus_infinity(hd, n_blocked, by):
     np.testing.assert_allclose(got[L:], ref[1], rtol=1e-5, atol=2e-6)
 
 
+@pytest.mark.parametrize("hd", [64, 48])
+def test_attention_fp32_sequences_that_start_behind_token_zero(hd):
+    """cu_seqlens[0] > 0, with work items (head size 64) and with positions token by token (48): the sequences are what they
+    are when they start at token 0, to the bit, and a token in front of them attends to itself, so its output is its value."""
+    nq, nkv, lens, skip = 4, 2, [70, 1, 33], 37
+    T = sum(lens)
+    QKV = _rand((skip + T, (nq + 2 * nkv) * hd), torch.float32, 800 + hd, 1.0)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    front, behind = torch.zeros(T, nq * hd, device=DEV), torch.zeros(skip + T, nq * hd, device=DEV)
+    B.op_attention(B.DTYPE_FP32, QKV[skip:].contiguous().to(DEV), None, 0, cu, None, nq, nkv, hd, front)
+    B.op_attention(B.DTYPE_FP32, QKV.to(DEV), None, 0, cu + skip, None, nq, nkv, hd, behind)
+    assert torch.equal(behind[skip:], front)
+    v = QKV.view(skip + T, nq + 2 * nkv, hd)[:skip, nq + nkv:].repeat_interleave(nq // nkv, dim=1)
+    assert torch.equal(behind[:skip].cpu(), v.reshape(skip, -1))
+
+
 def test_attention_refuses_a_transposed_v_stride_beyond_its_32_bit_offsets():
     """The 16-bit kernel addresses the 128 rows of a KV head's V^T with 32-bit byte offsets: a row stride of 2^24 columns
     (128 rows x 2 bytes = 4 GiB) is refused before anything is launched (the buffers here are tiny and never touched)."""
