@@ -326,8 +326,8 @@ int prism_op_route_static(const float *scores, int32_t n, int32_t K_rem, int32_t
 int prism_op_compact(const float *X_src, float *X_dst, const int32_t *src_start, const int32_t *dst_start,
                      const int32_t *len, int32_t n_keep, int32_t hidden, void *stream);
 
-/* Final top-K (Sec. 2.1): ranks n scores (descending, ties by lower position) and writes the first K
- * positions and scores. */
+/* Final top-K (Sec. 2.1): ranks n scores (descending, ties by lower position, NaN behind every number) and writes the
+ * first K positions and scores. */
 int prism_op_topk(const float *scores, int32_t n, int32_t K, int32_t *out_pos, float *out_scores, void *stream);
 
 #ifdef __cplusplus

@@ -532,25 +532,32 @@ int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, co
 }
 
 // ------------------------------------------------------------------------------------------------
-// Final top-K (Sec. 2.1): rank by counting (score descending, lower position first on ties).  Latency- and issue-bound: n^2
-// comparisons.  16 lanes per entry, 16 entries per workgroup, so the pool spreads over the compute units; the scores are read
-// once into LDS.  500 entries 37 us (one workgroup, a memory load per comparison) -> 4; 4096: 1490 -> 10.
+// Final top-K (Sec. 2.1): rank by counting (score descending, lower position first on ties, NaN behind every number).
+// Latency- and issue-bound: n^2 comparisons.  16 lanes per entry, 16 entries per workgroup, so the pool spreads over the
+// compute units; the scores are read once into LDS, as whole numbers of the same order, in which NaN has a place too: every
+// rank below K is written by exactly one entry, whatever the scores are (the host uses the positions as indices).
+// 500 entries 37 us (one workgroup, a memory load per comparison) -> 4; 4096: 1490 -> 10.
 __global__ __launch_bounds__(256) void topk_kernel(const float *__restrict__ scores, const int8_t *__restrict__ tag,
                                                     int want, int n, int K, int32_t *__restrict__ out_pos,
                                                     float *__restrict__ out_scores) {
-  // entries whose tag differs from `want` do not take part (tag == nullptr: all take part): like a NaN, a NaN in their
-  // place compares false with everything
-  __shared__ float sc[PRISM_MAX_CANDS];
-  for (int j = threadIdx.x; j < n; j += 256) sc[j] = tag && tag[j] != want ? __uint_as_float(0x7fc00000u) : scores[j];
-  __syncthreads();
+  // entries whose tag differs from `want` do not take part (tag == nullptr: all take part): 0, below NaN's 1
+  __shared__ uint32_t key[PRISM_MAX_CANDS];
   const int i = blockIdx.x * 16 + (threadIdx.x >> 4);
-  if (i >= n || (tag && tag[i] != want)) return;
-  const float si = sc[i];
+  const float si = scores[i < n ? i : 0];                                      // requested with the rest, not behind the count
+  for (int j = threadIdx.x; j < n; j += 256) {
+    const float s = scores[j];
+    const uint32_t u = __float_as_uint(s == 0.f ? 0.f : s);                    // -0 ties with 0
+    const uint32_t k = s != s ? 1u : (u & 0x80000000u ? ~u : u | 0x80000000u);
+    key[j] = tag && tag[j] != want ? 0u : k;
+  }
+  __syncthreads();
+  if (i >= n || key[i] == 0u) return;
+  const uint32_t ki = key[i];
   int rank = 0;
 #pragma unroll 4
   for (int j = threadIdx.x & 15; j < n; j += 16) {
-    const float sj = sc[j];
-    rank += (sj > si) || (sj == si && j < i);
+    const uint32_t kj = key[j];
+    rank += (kj > ki) || (kj == ki && j < i);
   }
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 64);

@@ -585,6 +585,18 @@ def test_topk_of_any_pool(n, K):
     assert np.array_equal(pos.cpu().numpy(), order) and np.array_equal(sc.cpu().numpy(), s[order])
 
 
+@pytest.mark.parametrize("n,K", [(1, 1), (17, 17), (300, 40)])
+def test_topk_ranks_nan_behind_every_number(n, K):
+    """Infinities, zeros of both signs and NaN of both signs among the scores: K different positions, NaN last by position."""
+    r = np.random.default_rng(n)
+    s = r.choice(np.array([np.inf, -np.inf, 0.0, -0.0, 1.5, -1.5, np.nan, -np.nan, 3e38, -3e38, 1e-45], np.float32), size=n)
+    pos, sc = torch.full((K,), -1, dtype=torch.int32, device=DEV), torch.zeros(K, device=DEV)
+    B.op_topk(torch.from_numpy(s).to(DEV), K, pos, sc)
+    order = np.array(sorted(range(n), key=lambda i: (np.isnan(s[i]), -s[i] if not np.isnan(s[i]) else 0.0, i)))[:K]
+    assert np.array_equal(pos.cpu().numpy(), order)
+    assert np.array_equal(sc.cpu().numpy().view(np.int32), s[order].view(np.int32))
+
+
 @pytest.mark.parametrize("hd,nq,nkv,T", [(32, 3, 1, 5), (64, 4, 2, 354), (64, 4, 2, 12859), (128, 1, 1, 9001), (48, 2, 1, 77)])
 @pytest.mark.parametrize("qk_norm", [True, False])
 def test_qk_finish_fp32_head_sizes(hd, nq, nkv, T, qk_norm):

@@ -335,3 +335,20 @@ def test_two_pass_checked_layers_change_nothing(name, kw):
         assert np.array_equal(two[2].scores[0], one[2].scores[0], equal_nan=True)      # the first check sees the full pool either way
         np.testing.assert_allclose(two[2].scores, one[2].scores, rtol=0, atol=1e-3, equal_nan=True)
         np.testing.assert_allclose(two[1], one[1], rtol=0, atol=1e-3)
+
+
+@pytest.mark.parametrize("mode", [B.MODE_DROP_ONLY, B.MODE_THREE_WAY])
+def test_a_call_whose_scores_are_all_nan_returns_k_candidates(mode):
+    """A model that overflows (here: a NaN gain in front of the head) has no order to give: every check's gate stays closed and
+    the call returns the first K candidates with NaN scores.  A small call behind a larger one of the same context reads a
+    part of the result block that held the larger call's scores."""
+    w = W.WORKLOADS["mini_bf16"]
+    wt = W.make_weights(w, "cuda")
+    wt = dataclasses.replace(wt, final_norm=torch.full_like(wt.final_norm, float("nan")))
+    q, cands = W.make_tokens(w)
+    p = B.Prism(w.model, wt, checkpoints=w.checkpoints, cv_threshold=0.0, n_clusters=w.n_clusters, mode=mode)
+    for pool, K in ((cands * 12, 5), (cands, w.K), (cands[:3], 2), (cands[:1], 1)):
+        idx, scores, rep = p.select(q, pool, K)
+        assert idx.tolist() == list(range(K)) and np.isnan(scores).all()
+        assert not rep.gate.any() and (rep.n_after == len(pool)).all()
+    p.destroy()
