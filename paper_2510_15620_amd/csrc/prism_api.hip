@@ -1089,8 +1089,10 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   const float *h_scores = (const float *)(c->h_res + res_scores), *h_top_scores = (const float *)(c->h_res + res_top + 4 * n_res);
   const int8_t *h_fate = (const int8_t *)(c->h_res + res_fate);
   const int32_t *h_top_pos = (const int32_t *)(c->h_res + res_top);
-  auto fetch = [&](size_t from, size_t to) -> int {      // bytes [from, to) of the result block, on the host when this returns
+  // bytes [from, to) of the result block, on the host when this returns; `copied` is recorded behind the copy
+  auto fetch = [&](size_t from, size_t to, hipEvent_t copied = nullptr) -> int {
     PRISM_HIP(hipMemcpyAsync(c->h_res + from, c->d_res + from, to - from, hipMemcpyDeviceToHost, s));
+    if (copied) PRISM_HIP(hipEventRecord(copied, s));
     PRISM_HIP(hipStreamSynchronize(s));
     return PRISM_OK;
   };
@@ -1265,8 +1267,7 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     const int k_out = std::min(K_rem, n_live);
     // (the last layer has scored every candidate from its gathered last-token state)
     PRISM_TRY(launch_topk(c->d_scores, n_live, k_out, c->d_top_pos, c->d_top_scores, s));
-    if (timed) PRISM_HIP(hipEventRecord(c->ev_t[1], s));
-    PRISM_TRY(fetch(res_scores, res_end));
+    PRISM_TRY(fetch(res_scores, res_end, timed ? c->ev_t[1] : nullptr));     // the call's time includes its results' copy
     for (int i = 0; i < k_out; ++i) { final_idx.push_back(p.live[h_top_pos[i]]); final_scores.push_back(h_top_scores[i]); }
     record_event(m.n_layers, n_live, p.live, false, 0, 0.0, 0.0, nullptr, nullptr);
   } else {
