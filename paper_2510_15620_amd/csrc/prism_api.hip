@@ -114,7 +114,7 @@ struct prism_ctx {
   std::vector<Span> spans;
   bool profiling = false;
   int span_mask = ~0;                             // kinds that get event spans while profiling
-  float2 *rope_tab = nullptr, *rope_tab_t = nullptr;   // [pos][i] for the finishing kernel of the fp32 mode, [i][pos] for the fused epilogue
+  float2 *rope_tab = nullptr;                     // (cos, sin): [pos][i] in the fp32 mode (finishing kernel), else [i][pos] (fused epilogue)
 
   // scratch, grown on demand
   float *X[2] = {nullptr, nullptr};
@@ -373,9 +373,7 @@ extern "C" int prism_create(const prism_model *model, const prism_weights *weigh
     for (int l = 0; l < model->n_layers; ++l) CREATE_TRY(issue_layer_copy(c, l, l, c->stream, hipMemcpyDeviceToDevice, nullptr));
   }
   CREATE_TRY(dev_alloc(c, (void **)&c->rope_tab, (size_t)PRISM_MAX_SEQ * (model->head_dim / 2) * sizeof(float2)));
-  CREATE_TRY(launch_rope_table(c->rope_tab, PRISM_MAX_SEQ, model->head_dim, model->rope_base, c->stream));
-  CREATE_TRY(dev_alloc(c, (void **)&c->rope_tab_t, (size_t)PRISM_MAX_SEQ * (model->head_dim / 2) * sizeof(float2)));
-  CREATE_TRY(launch_rope_table(c->rope_tab_t, PRISM_MAX_SEQ, model->head_dim, model->rope_base, c->stream, true));
+  CREATE_TRY(launch_rope_table(c->rope_tab, PRISM_MAX_SEQ, model->head_dim, model->rope_base, c->stream, is16(c->op)));
   CREATE_TRY(dev_alloc(c, (void **)&c->d_res, kResultBytes));
   CREATE_TRY(dev_alloc(c, &c->route_ws, route_workspace_bytes(PRISM_MAX_CANDS, PRISM_MAX_CLUSTERS)));
   CREATE_HIP(hipHostMalloc((void **)&c->h_res, kResultBytes, hipHostMallocDefault));
@@ -422,7 +420,7 @@ extern "C" void prism_destroy(prism_ctx *c) {
     for (hipEvent_t e : {c->ev_in[i], c->ev_done[i], c->ev_out[i]}) if (e) (void)hipEventDestroy(e);
   if (c->xin_stream) (void)hipStreamDestroy(c->xin_stream);
   if (c->xout_stream) (void)hipStreamDestroy(c->xout_stream);
-  void *ptrs[] = {c->AOl, c->Xnl, c->Sl, c->Xl, c->rope_tab, c->rope_tab_t, c->X[0], c->X[1], c->Xn, c->QKV, c->QK, c->Vt, c->AO, c->S, c->d_meta, c->d_res,
+  void *ptrs[] = {c->AOl, c->Xnl, c->Sl, c->Xl, c->rope_tab, c->X[0], c->X[1], c->Xn, c->QKV, c->QK, c->Vt, c->AO, c->S, c->d_meta, c->d_res,
                   c->route_ws};
   for (void *p : ptrs) if (p) (void)hipFree(p);
   if (c->h_meta) (void)hipHostFree(c->h_meta);
@@ -854,7 +852,7 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
       QkvEpilogue e;
       e.pos = pos; e.vt_col = c->d_meta + mo.vtcol + ch.r0;
       e.q_gain = wbuf + L.q_norm; e.k_gain = wbuf + L.k_norm;
-      e.rope_tab_t = c->rope_tab_t; e.rope_stride = PRISM_MAX_SEQ; e.QK = c->QK; e.Vt = c->Vt; e.vt_stride = c->vt_cap;
+      e.rope_tab_t = c->rope_tab; e.rope_stride = PRISM_MAX_SEQ; e.QK = c->QK; e.Vt = c->Vt; e.vt_stride = c->vt_cap;
       e.nq = m.n_q_heads; e.nkv = m.n_kv_heads; e.qk_norm = m.qk_norm; e.eps = m.rms_eps;
       return launch_gemm_16_qkv(c->op, c->Xn, wbuf + L.wqkv, Tc, H, m.head_dim, e, s);
     }, Tc));

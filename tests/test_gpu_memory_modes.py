@@ -137,3 +137,19 @@ def test_embedding_table_must_be_pinned():
     with pytest.raises(B.PrismError) as e:
         B.Prism(w.model, hw, **_opts(w, embed_on_host=True))
     assert e.value.code == B.EINVAL
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_a_context_holds_the_rotation_table_of_its_mode_only(dtype):
+    """(cos, sin) of 8192 positions at head_dim 128 are 4 MiB, in the order that the context's mode reads.  Everything else of
+    this one-layer model and its pool of 20 tokens is below 2 MiB, so a second table would show in the peak."""
+    m = W.ModelShape(1, 128, 1, 1, 128, 128, 64, dtype)
+    d = torch.Generator().manual_seed(3)
+    t = torch.float32 if dtype == "fp32" else torch.bfloat16
+    draw = lambda *s: (torch.randn(*s, generator=d) * 0.05).to(t).cuda()
+    wt = W.Weights(draw(64, 128), [{n: draw(*s) for n, s in W.layer_tensor_shapes(m).items()}], draw(128))
+    p = B.Prism(m, wt)
+    peak = p.select([1, 2], [[3, 4, 5, 6], [7, 8, 9], [10, 11]], 1)[2].peak_hbm_bytes
+    p.destroy()
+    table = B.MAX_SEQ * (m.head_dim // 2) * 8
+    assert table < peak < table + (2 << 20)
