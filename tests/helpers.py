@@ -36,11 +36,61 @@ def oracle_select(w: W.Workload, wt=None, tokens=None, **over):
     return O.select(q, cands, K, oracle_weights(wt), oracle_model(w.model, operand), **kw)
 
 
-# --------------------------------------------------------------------------- full-size goldens and the margin rule
+# --------------------------------------------------------------------------- which tile a 16-bit GEMM launch takes
 
 import json
 import os
+import re
 from types import SimpleNamespace
+
+GEMM_SOURCE = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2510_15620_amd", "csrc", "gemm_16.hip")
+
+
+def _tile_table(src: str, enum_first: str, table: str):
+    """[(kind, bm, bn, occ, alone, shared, fixed)] as the launcher's source states them."""
+    kinds = [k.strip() for k in re.search(r"enum \{ (" + enum_first + r"[^}]*) \};", src).group(1).split(",")][:-1]
+    rows = re.findall(r"\{([^{}]*)\}", re.search(table + r"\[[^]]*\] = \{(.*?)\};", src, re.S).group(1))
+    assert len(rows) == len(kinds), (kinds, rows)
+    return [(k, *(int(v) for v in r.split(",")[:3]), *(np.float32(v.strip().rstrip("f")) for v in r.split(",")[3:])) for k, r in zip(kinds, rows)]
+
+
+def _tile_cost(t, rows, cols, K, glu):
+    _, bm, bn, occ, alone, shared, fixed = t
+    n = (-(-rows // bm) * -(-cols // (bn // 2 if glu else bn)) + 255) // 256
+    full, rest = divmod(n, occ)
+    f = np.float32
+    per_slice = f(full) * max(alone, shared * f(occ)) + (max(alone, shared * f(rest)) if rest else f(0))
+    return (K // 64) * float(per_slice) + float((n + occ - 1) // occ) * float(fixed)
+
+
+def _plan(costs, rows, cols, K, glu):
+    """The launcher's choice (plan_tiles) from its own cost table: [(rows, kind)], one entry per launch."""
+    def best(r):
+        take = [(i, t) for i, t in enumerate(costs) if i == 0 or not (glu and t[2] == 32)]
+        return min(((_tile_cost(t, r, cols, K, glu), i, t[0]) for i, t in take))
+    whole, _, kind = best(rows)
+    n_cols, n_rows = -(-cols // (128 if glu else 256)), -(-rows // 256)
+    big = min(n_rows, n_rows * n_cols // 256 * 256 // n_cols) * 256
+    if 0 < big < rows:
+        c, i, rest_kind = best(rows - big)
+        if i != 0 and _tile_cost(costs[0], big, cols, K, glu) + c < 0.98 * whole:
+            return [(big, costs[0][0]), (rows - big, rest_kind)]
+    return [(rows, kind)]
+
+
+def gemm_plan(M, N, K, glu=False):
+    """Tile kinds of a 16-bit prism_op_gemm (M K 2 bytes below 4 GiB)."""
+    return _plan(_tile_table(open(GEMM_SOURCE).read(), "kTile256", "kTileCost"), M, N // 2 if glu else N, K, glu)
+
+
+def head_plan(M, nq, nkv, K):
+    """Tile kinds of the fused q/k/v projection."""
+    heads = nq + 2 * nkv
+    plan = _plan(_tile_table(open(GEMM_SOURCE).read(), "kHead256", "kHeadCost"), M, heads * 128, K, False)
+    return plan if heads % 2 == 0 or all(k != "kHead256" for _, k in plan) else [(M, "kHead128")]
+
+
+# --------------------------------------------------------------------------- full-size goldens and the margin rule
 
 GOLDEN_DIR = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden")
 
