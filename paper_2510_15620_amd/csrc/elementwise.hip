@@ -536,7 +536,7 @@ int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, co
 // Latency- and issue-bound: n^2 comparisons.  16 lanes per entry, 16 entries per workgroup, so the pool spreads over the
 // compute units; the scores are read once into LDS, as whole numbers of the same order, in which NaN has a place too: every
 // rank below K is written by exactly one entry, whatever the scores are (the host uses the positions as indices).
-// 500 entries 37 us (one workgroup, a memory load per comparison) -> 4; 4096: 1490 -> 10.
+// 500 entries 37 us (one workgroup, a memory load per comparison) -> 3.6; 4096: 1490 -> 11.
 __global__ __launch_bounds__(256) void topk_kernel(const float *__restrict__ scores, const int8_t *__restrict__ tag,
                                                     int want, int n, int K, int32_t *__restrict__ out_pos,
                                                     float *__restrict__ out_scores) {
@@ -556,8 +556,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float *__restrict__ sco
   int rank = 0;
 #pragma unroll 4
   for (int j = threadIdx.x & 15; j < n; j += 16) {
-    const uint32_t kj = key[j];
-    rank += (kj > ki) || (kj == ki && j < i);
+    rank += key[j] > ki - (j < i ? 1u : 0u);                                   // j in front of i also when equal
   }
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 64);
