@@ -268,7 +268,8 @@ int prism_op_qkv_finish(int32_t dtype, void *QKV, const int32_t *pos, int32_t ma
                         int64_t vt_stride, void *stream);
 
 /* The fused form of prism_op_gemm (fp32 store) + prism_op_qkv_finish for the 16-bit modes (prism_select runs the fused
- * kernel for launches of every size; below the size given here with the finishing kernel's summation order): [Q|K|V] = Xn Wqkv^T with Xn [T, hidden] and Wqkv [(nq+2nkv)*hd, hidden] ([device], dtype),
+ * kernel for launches of every size; below the size given here with the finishing kernel's summation order, so with the
+ * bits of the two calls): [Q|K|V] = Xn Wqkv^T with Xn [T, hidden] and Wqkv [(nq+2nkv)*hd, hidden] ([device], dtype),
  * then per-head RMSNorm (optional) and RoPE on q and k and the transposed half-precision V, all applied to the fp32
  * accumulators in the GEMM's epilogue (one rounding, no fp32 intermediate in memory).  Outputs, pos, vt_col, gains as
  * in prism_op_qkv_finish.  Needs head_dim == 128, hidden % 64 == 0 and ceil(T / 256) * (nq + 2 nkv) / 2 >= 256 (enough

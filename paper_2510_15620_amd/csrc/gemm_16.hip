@@ -522,9 +522,9 @@ static int launch_cfg(const OT *A, const OT *W, void *out, int M, int N, int K, 
 // Rows are independent, columns are independent, and every tile size gives an element the same bits (one accumulator, K in
 // order), so the choice is made on time alone.  A launch deals its tiles over 256 compute units; n = tiles per unit, rounded
 // up.  A tile's time is its K slices plus a fixed part (dispatch, first slice, epilogue), and a slice's time depends on how
-// many tiles share the unit: alone it is a chain of latencies, together the matrix pipes and LDS.  The constants are a
-// least-squares fit to every tile size on 110 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues; each
-// tile within 12-17 %); the size picked by them was on average within 2 % of the best one measured.  Examples, in us, 128 x 128
+// many tiles share the unit: alone it is a chain of latencies, together the matrix pipes and LDS.  The constants describe
+// every tile size on 171 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues) within 12-18 % (root mean
+// square); the size picked by them is on average within 1 % of the best one measured, at worst 9 %.  Examples, in us, 128 x 128
 // compiler-scheduled loop before -> now: 100 x 4096 x 12288 167 -> 36 (64 x 32), 391 x 1024 x 3072 44 -> 10 (64 x 32),
 // 777 x 6144 x 1024 with SwiGLU 23 -> 17 (128 x 128), 3699 x 1024 x 3072 49 -> 30 (128 x 128, three stages).
 struct TileCost {
@@ -535,9 +535,10 @@ enum { kTile256, kTile128, kTile128Deep, kTile128x64, kTile64, kTile32x64, kTile
 static constexpr TileCost kTileCost[kTileKinds] = {
     {256, 256, 1, 1.53f, 1.53f, 9.2f}, {128, 128, 2, 0.72f, 0.50f, 4.5f}, {128, 128, 1, 0.52f, 0.52f, 3.4f}, {128, 64, 2, 0.34f, 0.36f, 2.3f},
     {64, 64, 2, 0.204f, 0.204f, 2.1f}, {32, 64, 3, 0.176f, 0.149f, 2.4f}, {64, 32, 2, 0.128f, 0.128f, 2.3f}, {32, 32, 2, 0.106f, 0.083f, 2.6f}};
-// The fused q/k/v projection: tiles whose waves own whole heads (fitted to 34 launches of 1 to 12000 rows).  Its epilogue
-// is longer: two dependent loads (position, rotation) and the per-head arithmetic.  391 x 4096 x 1024: 11 us, where the
-// projection to fp32 and its two finishing kernels took 48; 777 x 6144 x 4096: 56.
+// The fused q/k/v projection: tiles whose waves own whole heads (34 launches of 1 to 12000 rows: within 11-19 %, the picked
+// size on average within 1 % of the best, at worst 12 %).  Its epilogue is longer: two dependent loads (position, rotation)
+// and the per-head arithmetic.  391 x 4096 x 1024: 11 us, where the projection to fp32 and its two finishing kernels took 48;
+// 777 x 6144 x 4096: 56.
 enum { kHead256, kHead128, kHead128Deep, kHead64, kHeadKinds };
 static constexpr TileCost kHeadCost[kHeadKinds] = {
     {256, 256, 1, 1.53f, 1.53f, 20.f}, {128, 128, 2, 0.70f, 0.55f, 5.5f}, {128, 128, 1, 0.52f, 0.52f, 5.0f}, {64, 128, 2, 0.29f, 0.37f, 5.0f}};

@@ -1,6 +1,6 @@
 // fp32 layer contractions for the fp32 mode (small models, 1e-4 parity runs) on the fp32 matrix instruction
-// v_mfma_f32_16x16x4_f32 (157 TFLOP/s; the vector pipes reach half of that without packed instructions), with every edge
-// bounds-checked, so any M, N, K works.  C = A W^T with A [M,K], W [N,K] row-major, fp32 products and sums throughout.
+// v_mfma_f32_16x16x4_f32 (157 TFLOP/s published, 150 reached by a large product; the vector pipes reach half of that without
+// packed instructions), with every edge bounds-checked, so any M, N, K works.  C = A W^T with A [M,K], W [N,K] row-major, fp32 products and sums throughout.
 //
 // Workgroup tile BM x BN x BK, 4 wavefronts of TM x TN accumulator tiles of 16 x 16.  The 16-wide instruction rather than
 // the 32-wide one: half the cycles per step of K on an accumulator, and these launches are short chains, not full pipes.

@@ -979,8 +979,8 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   }
   const int Kc = std::min(K, n_cands);
   const int mode = K >= n_cands ? PRISM_MODE_NO_PRUNING : c->opt.mode;
-  // the query is held and computed once per chunk where the path supports it: the matrix-core attention kernel (the
-  // fp32 kernel finds sequences by their positions) and a device-resident residual stream
+  // the query is held and computed once per chunk where the path supports it: the 16-bit attention kernel (the fp32
+  // kernels find all of a sequence's keys in consecutive rows) and a device-resident residual stream
   p.ql = (!c->opt.no_query_sharing && is16(c->op) && !c->offload && n_cands > 1 &&
           attention_16_supported(m.n_q_heads, m.n_kv_heads, m.head_dim)) ? query_len : 0;
   build_plan(c, p);
