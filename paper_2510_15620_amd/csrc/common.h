@@ -72,6 +72,15 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
+// v + the value of lane ^ 32, or ^ 16, in every lane (vector instructions, no LDS round trip)
+__device__ __forceinline__ float sum_xor32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float sum_xor16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
@@ -99,7 +108,7 @@ struct QkvEpilogue {
   int nq, nkv, qk_norm;
   float eps;
 };
-static const int kEpiQkv = 4, kEpiQkvPairwise = 5;   // internal epilogue codes of launch_gemm_16_qkv: order of the norm's sum of squares
+static const int kEpiQkv = 4;   // internal epilogue code of launch_gemm_16_qkv
 bool gemm_16_qkv_supported(int nq, int nkv, int hd, int K);
 // at least 256 tiles of 256 x 256: from here on prism_op_qkv_project offers the fused form as a call of its own
 bool gemm_16_qkv_large(int M, int nq, int nkv);

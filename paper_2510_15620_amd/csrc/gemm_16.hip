@@ -3,21 +3,22 @@
 //
 // C = A W^T, A [M,K] and W [N,K] row-major, both bf16 or both IEEE half (K-contiguous, which is what
 // the MFMA operand registers want: 8 consecutive k per lane), fp32 accumulation in
-// v_mfma_f32_32x32x16_{bf16,f16} (same dense rate).
+// v_mfma_f32_16x16x32_{bf16,f16} (256 x 256 tile) or v_mfma_f32_32x32x16_{bf16,f16} (the others): same dense rate, and
+// the same bits for the same k in the same order.
 //
-// Workgroup tile BM x BN x 64, WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) block of 32x32
-// accumulator tiles.  The large-launch shape is 256 x 256 with 2 x 2 wavefronts (one per SIMD, 128 x 128 each,
+// Workgroup tile BM x BN x 64, WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) block of the accumulator.  The
+// large-launch shape is 256 x 256 with 2 x 2 wavefronts (one per SIMD, 128 x 128 each,
 // 256 accumulator registers in AGPRs); launches with few tiles per compute unit take one of seven smaller tiles
-// down to 32 x 32 (see the choice at the launcher).  A and W tiles are staged in LDS (a ring of S stages; 16-byte
-// chunks XOR-swizzled by row so that the 32-row operand reads spread over the banks) by direct global->LDS loads,
-// which need no staging registers.  Every K loop is generated text (gen_gemm_kloop.py), because its waits count loads
+// down to 32 x 32 (see the choice at the launcher).  A and W tiles are staged in LDS (a ring of S stages, 256 x 256: three
+// of A and two of W; 16-byte chunks XOR-swizzled by row so that the 16- and 32-row operand reads spread over the banks) by direct
+// global->LDS loads, which need no staging registers.  Every K loop is generated text (gen_gemm_kloop.py), because its waits count loads
 // and fragment reads exactly; rows beyond the matrix are clamped in the load offsets, so edge tiles run the same loop.
 //
 // Epilogues: plain store (bf16 or fp32), residual add into the fp32 stream, and SwiGLU, where the B tile is
 // made of BN/2 gate rows and the BN/2 matching up rows so that a lane holds g and u of one element.
 //
 // Workgroup ids are remapped so that each XCD (ids are dealt round-robin over the 8 XCDs) owns a
-// contiguous range of tiles, walked in groups of 8 (4 for the residual epilogue) row-tiles, to keep the operand panels in its L2.
+// contiguous range of tiles, walked in groups of 4 or 8 row-tiles, to keep the operand panels in its L2.
 #include <algorithm>
 #include <mutex>
 
@@ -37,12 +38,15 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 #define PRISM_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define PRISM_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
+// LDS bytes of a tile's operand stages
+template <int BM, int BN, int S> constexpr int stage_bytes() { return ((BM == 256 ? 3 : S) * BM + S * BN) * BK * 2; }
+
 template <typename OT, int BM, int BN, int WM, int WN, int EPI, int S>
 __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel(const OT *__restrict__ A,
                                                                const OT *__restrict__ W, void *__restrict__ out_,
                                                                int M, int N, int K, int nM, int nN, QkvEpilogue qe) {
   constexpr int NW = WM * WN;
-  constexpr bool kHeads = EPI == kEpiQkv || EPI == kEpiQkvPairwise;
+  constexpr bool kHeads = EPI == kEpiQkv;
   constexpr int WMT = BM / WM, WNT = BN / WN;      // wave tile
   constexpr int TM = WMT / 32, TN = WNT / 32;      // 32x32 accumulator tiles per wave
   // one direct-to-LDS instruction of a wave moves 64 x 16 B = 8 tile rows
@@ -50,8 +54,9 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/waves mismatch");
   static_assert(EPI != PRISM_EPI_SWIGLU || TN % 2 == 0, "SwiGLU pairs gate and up tiles");
   extern __shared__ __align__(16) unsigned char smem[];
-  OT *lA = reinterpret_cast<OT *>(smem);                     // [S][BM][BK]
-  OT *lB = lA + S * BM * BK;                                 // [S][BN][BK]
+  static_assert(BM != 256 || S == 2, "the 256 x 256 loop has three stages of A and two of W");
+  OT *lA = reinterpret_cast<OT *>(smem);                     // [S, or 3 if BM == 256][BM][BK]
+  OT *lB = lA + (BM == 256 ? 3 : S) * BM * BK;               // [S][BN][BK]
 
   // ---- tile mapping: XCD-contiguous ranges, grouped walk ----
   const int n_tiles = nM * nN;
@@ -62,9 +67,10 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     bid = x * per + r;
     if (r >= per || bid >= n_tiles) return;
   }
-  // measured: 8 row-tiles per group is best where the row panel is small (K = hidden); the down projection's row
-  // panels are three times as long and the O projection's few column tiles leave little to share: 4 is 2 % faster there
-  constexpr int GM = EPI == PRISM_EPI_RESIDUAL ? 4 : 8;
+  // 256 x 256: an XCD runs 32 tiles at a time, 4 row-tiles x 8 column-tiles of them or 8 x 4 - the same operand bytes - but 4 is
+  // 3 % faster at 24576 x 24576 x 4096 (1364 -> 1410 TFLOP/s; 3, 5, 6, 8, 16: 1-4 % slower, on some chips 6 %), and 4 % than 8
+  // at 32768 x 4096 x 12288
+  constexpr int GM = BM == 256 || EPI == PRISM_EPI_RESIDUAL ? 4 : 8;
   const int group = bid / (GM * nN), first_m = group * GM;
   const int gsz = (nM - first_m) < GM ? (nM - first_m) : GM;
   const int tile_m = first_m + (bid % (GM * nN)) % gsz, tile_n = (bid % (GM * nN)) / gsz;
@@ -102,26 +108,20 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     }
     gB[j] = ((uint32_t)gr * (uint32_t)K + swz(row, lane & 7) * 8) * 2u;
   }
-  // ---- LDS rows this lane reads as MFMA operands ----
-  int rA[TM], rB[TN];
-#pragma unroll
-  for (int t = 0; t < TM; ++t) rA[t] = wm * WMT + t * 32 + (lane & 31);
-#pragma unroll
-  for (int t = 0; t < TN; ++t) {
-    if (EPI == PRISM_EPI_SWIGLU)
-      rB[t] = (t / (TN / 2)) * (BN / 2) + wn * (WNT / 2) + (t % (TN / 2)) * 32 + (lane & 31);
-    else
-      rB[t] = wn * WNT + t * 32 + (lane & 31);
-  }
-  const int khalf = lane >> 5;                               // which 8 of the 16 k of an MFMA this lane feeds
+  // ---- LDS rows this lane reads as MFMA operands: row (A) and first column (B) of its first fragment ----
+  constexpr bool k16 = BM == 256;                            // 16x16x32 MFMAs: a lane feeds 8 of the 32 k of one of 16 rows,
+  const int frow = lane & (k16 ? 15 : 31), kpart = lane >> (k16 ? 4 : 5);   // else 8 of the 16 k of one of 32 rows
+  const int rA0 = wm * WMT + frow, rB0 = wn * (EPI == PRISM_EPI_SWIGLU ? WNT / 2 : WNT) + frow;
 
-  f32x16 acc[TM][TN];
+  f32x16 acc[TM][TN];                                        // k16: cleared by the K loop
+  if constexpr (!k16) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  }
 
   const int nk = K / BK;
 
@@ -151,13 +151,14 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   };
 
 
-  int row_in[kHeads ? TM : 1];                                      // q, k heads: positions; v heads: V^T columns
+  constexpr int RPB = k16 ? 2 : 1;                                  // rows of a 32-row block that a lane holds
+  int row_in[kHeads ? TM * RPB : 1];                                // q, k heads: positions; v heads: V^T columns
   auto load_rows = [&]() __attribute__((always_inline)) {
     if constexpr (kHeads) {
       const int32_t *src = ((n0 + wn * WNT) >> 7) < qe.nq + qe.nkv ? qe.pos : qe.vt_col;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * WMT + i * 32 + (lane & 31);
+      for (int i = 0; i < TM * RPB; ++i) {
+        const int row = m0 + wm * WMT + i * (32 / RPB) + frow;
         row_in[i] = src[row < M ? row : M - 1];
       }
     }
@@ -167,9 +168,10 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     else if (full_n) load_old(0);
   }
 
-  // ---- epilogue.  The W fragment was the instruction's first operand, so the 32x32 accumulator tile is
-  //      transposed: a lane holds ONE row of A, m = lane % 32, and the output columns
-  //      n = (e / 4) * 8 + (lane / 32) * 4 + e % 4, e = 0..15: four runs of 4 consecutive columns.
+  // ---- epilogue.  The W fragment was the instruction's first operand, so the 32 x 32 accumulator block (i, j) is
+  //      transposed: a lane holds four runs g = 0..3 of 4 consecutive columns, elements e = 4 g + q, of ONE row of A
+  //      (32x32x16: row lane % 32, columns 8 g + 4 (lane / 32) + q) or of two (16x16x32: tile (g / 2, g % 2) of the block, row
+  //      16 (g / 2) + lane % 16, columns 16 (g % 2) + 4 (lane / 16) + q); m_of and n_of below.
   //      Written straight from that layout, one store instruction touches 32 rows with 16-32 bytes in each, and
   //      the number of cache lines an instruction touches - not the bytes - is what the memory path charges for
   //      (measured: 12-29 us per 256 x 256 tile, a tenth to a fifth of the tile's time).  So every block of 32 rows goes
@@ -195,11 +197,12 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     return r;
   };
   __syncthreads();              // every wave's operand loads have landed and nobody reads operands any more
-  const int m_in = lane & 31, n_in = (lane >> 5) * 4;
+  auto m_of = [&](int g) __attribute__((always_inline)) { return k16 ? (g >> 1) * 16 + frow : frow; };
+  auto n_of = [&](int g) __attribute__((always_inline)) { return k16 ? (g & 1) * 16 + kpart * 4 : g * 8 + kpart * 4; };
   constexpr int SWZ = CPR >= 16 ? 15 : CPR - 1;                     // chunk rotation by row: spreads a column of 16-byte
                                                                     // writes (one per row) over the banks
-  static_assert(32 * RB <= S * (BM + BN) * BK * (int)sizeof(OT) / NW, "staging block must fit the wave's share of LDS");
-  unsigned char *stg = smem + wave * (S * (BM + BN) * BK * (int)sizeof(OT) / NW);
+  static_assert(32 * RB <= stage_bytes<BM, BN, S>() / NW, "staging block must fit the wave's share of LDS");
+  unsigned char *stg = smem + wave * (stage_bytes<BM, BN, S>() / NW);
   // values for columns n .. n + 3 (n a multiple of 4, within the wave's columns) of staged row m
   auto put32 = [&](int m, int n, const f32x4 &v) __attribute__((always_inline)) {
     *reinterpret_cast<f32x4 *>(stg + m * RB + (((n >> 2) ^ (m & SWZ)) << 4)) = v;
@@ -223,11 +226,11 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   };
 
   if constexpr (kHeads) {
-    // The wave's 128 columns are one head.  A row's 128 values sit in lanes l and l ^ 32 (64 each); the rotate-half
-    // partner of column d is d + 64 = the same register of accumulator tile j + 2, so the per-head RMSNorm (one
-    // cross-lane add), the rotation and the single rounding all happen on the accumulators.  What the memory path
-    // charges for is cache lines touched per instruction, so the cos/sin pairs come from the TRANSPOSED table (the 32
-    // tokens of a row block are consecutive positions of a sequence almost always: two to four lines per load instead of
+    // The wave's 128 columns are one head.  A row's 128 values sit in 2 (16x16x32: 4) lanes with the same lane % 32 (% 16);
+    // the rotate-half partner of column d is d + 64 = the same register of accumulator block j + 2, so the per-head RMSNorm
+    // (cross-lane adds), the rotation and the single rounding all happen on the accumulators.  What the memory path
+    // charges for is cache lines touched per instruction, so the cos/sin pairs come from the TRANSPOSED table (the 16 or 32
+    // tokens of a load are consecutive positions of a sequence almost always: two to four lines per load instead of
     // one or two per lane) and the finished q / k rows go through the staging block like the other epilogues' outputs.
     static_assert(WNT == 128 && TN == 4, "one head per wavefront");
     typedef typename Mfma<OT>::vec4 vec4;
@@ -235,23 +238,24 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     if constexpr (!kEarly) load_rows();                    // all row blocks' at once: one memory latency, not one per block
     if (head < qe.nq + qe.nkv) {
       const OT *gain = reinterpret_cast<const OT *>(head < qe.nq ? qe.q_gain : qe.k_gain);
-      vec4 ga[2][4], gb[2][4];
+      constexpr int NG = k16 ? 2 : 4;                      // distinct column groups of a lane in 32 columns
+      vec4 ga[2][NG], gb[2][NG];
       if (qe.qk_norm) {
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            ga[j][g] = *reinterpret_cast<const vec4 *>(gain + j * 32 + g * 8 + n_in);
-            gb[j][g] = *reinterpret_cast<const vec4 *>(gain + j * 32 + g * 8 + n_in + 64);
+          for (int g = 0; g < NG; ++g) {
+            ga[j][g] = *reinterpret_cast<const vec4 *>(gain + j * 32 + n_of(g));
+            gb[j][g] = *reinterpret_cast<const vec4 *>(gain + j * 32 + n_of(g) + 64);
           }
       }
       const int64_t pitch = (int64_t)(qe.nq + qe.nkv) * 128 * 2;
       // (cos, sin) of (pos, d) sits at [d * stride + pos]: a wave-uniform base per column plus one 32-bit lane offset.
       // The 32 pairs of block i + 1 are requested before block i is worked on, so the tile pays the memory latency once,
       // not once per block.
-      unsigned lane_off[TM];
+      unsigned lane_off[TM * RPB];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) lane_off[i] = (unsigned)n_in * (unsigned)qe.rope_stride + (unsigned)row_in[i];
+      for (int i = 0; i < TM * RPB; ++i) lane_off[i] = (unsigned)(kpart * 4) * (unsigned)qe.rope_stride + (unsigned)row_in[i];
       float2 cs[2][2][4][4];
       auto load_cs = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
@@ -259,86 +263,75 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
 #pragma unroll
           for (int g = 0; g < 4; ++g)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-              cs[i & 1][j][g][q] = (qe.rope_tab_t + (int64_t)(j * 32 + g * 8 + q) * qe.rope_stride)[lane_off[i]];
+            for (int q = 0; q < 4; ++q) {
+              const int d = j * 32 + (k16 ? (g & 1) * 16 : g * 8) + q;         // without the lane's part
+              cs[i & 1][j][g][q] = (qe.rope_tab_t + (int64_t)d * qe.rope_stride)[lane_off[k16 ? i * 2 + (g >> 1) : i]];
+            }
       };
       load_cs(0);
-      constexpr bool kPairwise = EPI == kEpiQkvPairwise;
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int row0 = m0 + wm * WMT + i * 32;
         if (i + 1 < TM) load_cs(i + 1);
-        float r = 1.f;
+        float r[RPB];
+#pragma unroll
+        for (int h = 0; h < RPB; ++h) r[h] = 1.f;
         if (qe.qk_norm) {
-          float ss = 0.f;
-          if (kPairwise) {
-            // the finishing kernel's order: column pairs (d, d + 64), then halving over the bits of d, 32 first
+          // the finishing kernel's order of the sum of squares: column pairs (d, d + 64), then halving over the bits of d, 32 first
+#pragma unroll
+          for (int h = 0; h < RPB; ++h) {
             float p[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              float h[2];
-#pragma unroll
-              for (int g = 0; g < 2; ++g) {
-                auto pair = [&](int j, int gg) __attribute__((always_inline)) {
-                  const float a = AC(i, j, gg * 4 + q), b = AC(i, j + 2, gg * 4 + q);
-                  return __builtin_fmaf(a, a, b * b);
-                };
-                h[g] = (pair(0, g) + pair(1, g)) + (pair(0, g + 2) + pair(1, g + 2));
-              }
-              p[q] = h[0] + h[1];
-              p[q] += __shfl_xor(p[q], 32);
+              auto pair = [&](int j, int g) __attribute__((always_inline)) {
+                const float a = AC(i, j, g * 4 + q), b = AC(i, j + 2, g * 4 + q);
+                return __builtin_fmaf(a, a, b * b);
+              };
+              auto both = [&](int g) __attribute__((always_inline)) { return pair(0, g) + pair(1, g); };
+              if constexpr (k16) p[q] = sum_xor16(sum_xor32(both(h * 2) + both(h * 2 + 1)));
+              else p[q] = sum_xor32((both(0) + both(2)) + (both(1) + both(3)));
             }
-            ss = (p[0] + p[2]) + (p[1] + p[3]);
-          } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-              for (int e = 0; e < 16; ++e) {
-                const float v = AC(i, j, e);
-                ss += v * v;
-              }
-            ss += __shfl_xor(ss, 32);
+            r[h] = 1.0f / sqrtf(((p[0] + p[2]) + (p[1] + p[3])) / 128.f + qe.eps);
           }
-          r = 1.0f / sqrtf(ss / 128.f + qe.eps);
         }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            const int d = j * 32 + g * 8 + n_in;
             vec4 lo, hi;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               const float2 c = cs[i & 1][j][g][q];
               float a = AC(i, j, g * 4 + q), b = AC(i, j + 2, g * 4 + q);
               if (qe.qk_norm) {
-                a = a * r * to_f32(ga[j][g][q]);
-                b = b * r * to_f32(gb[j][g][q]);
+                a = a * r[k16 ? g >> 1 : 0] * to_f32(ga[j][g % NG][q]);
+                b = b * r[k16 ? g >> 1 : 0] * to_f32(gb[j][g % NG][q]);
               }
               lo[q] = from_f32<OT>(__builtin_fmaf(a, c.x, -(b * c.y)));
-              hi[q] = from_f32<OT>(kPairwise ? __builtin_fmaf(b, c.x, a * c.y) : __builtin_fmaf(a, c.y, b * c.x));
+              hi[q] = from_f32<OT>(__builtin_fmaf(b, c.x, a * c.y));
             }
-            put16(m_in, d, lo);
-            put16(m_in, d + 64, hi);
+            put16(m_of(g), j * 32 + n_of(g), lo);
+            put16(m_of(g), j * 32 + n_of(g) + 64, hi);
           }
         }
         flush_store(reinterpret_cast<unsigned char *>(qe.QK), pitch, (int64_t)head * 128 * 2, row0);
       }
     } else {
-      // v head: rounded to the operand type, stored as half, transposed (32 consecutive tokens of one d are contiguous)
+      // v head: rounded to the operand type, stored as half, transposed (16 or 32 consecutive tokens of one d are contiguous)
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * WMT + i * 32 + m_in;
-        if (row >= M) continue;
-        f16 *vt = reinterpret_cast<f16 *>(qe.Vt) + (int64_t)(head - qe.nq - qe.nkv) * 128 * qe.vt_stride + row_in[i];
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int h = 0; h < RPB; ++h) {
+          if (m0 + wm * WMT + i * 32 + h * 16 + frow >= M) continue;
+          f16 *vt = reinterpret_cast<f16 *>(qe.Vt) + (int64_t)(head - qe.nq - qe.nkv) * 128 * qe.vt_stride + row_in[i * RPB + h];
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int d = j * 32 + (e >> 2) * 8 + n_in + (e & 3);
-            vt[(int64_t)d * qe.vt_stride] = from_f32<f16>(to_f32(from_f32<OT>(AC(i, j, e))));
-          }
-      }
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int g = h * 2; g < h * 2 + 4 / RPB; ++g)
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+                vt[(int64_t)(j * 32 + n_of(g) + q) * qe.vt_stride] = from_f32<f16>(to_f32(from_f32<OT>(AC(i, j, g * 4 + q))));
+        }
     }
     return;
   }
@@ -359,7 +352,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
               const float gt = AC(i, j, g * 4 + q), up = AC(i, j + TN / 2, g * 4 + q);
               v[q] = from_f32<OT>(gt / (1.0f + __expf(-gt)) * up);
             }
-            put16(m_in, j * 32 + g * 8 + n_in, v);
+            put16(m_of(g), j * 32 + n_of(g), v);
           }
         flush_store(reinterpret_cast<unsigned char *>(out_), (int64_t)F * 2, (int64_t)(n0 + wn * OUTW) * 2, row0);
       } else if (EPI == PRISM_EPI_RESIDUAL) {
@@ -373,7 +366,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
             f32x4 v;
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = AC(i, j, g * 4 + q);
-            put32(m_in, j * 32 + g * 8 + n_in, v);
+            put32(m_of(g), j * 32 + n_of(g), v);
           }
 #pragma unroll
         for (int rr = 0; rr < NI; ++rr) {
@@ -392,12 +385,12 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
               f32x4 v;
 #pragma unroll
               for (int q = 0; q < 4; ++q) v[q] = AC(i, j, g * 4 + q);
-              put32(m_in, j * 32 + g * 8 + n_in, v);
+              put32(m_of(g), j * 32 + n_of(g), v);
             } else {
               typename Mfma<OT>::vec4 v;
 #pragma unroll
               for (int q = 0; q < 4; ++q) v[q] = from_f32<OT>(AC(i, j, g * 4 + q));
-              put16(m_in, j * 32 + g * 8 + n_in, v);
+              put16(m_of(g), j * 32 + n_of(g), v);
             }
           }
         flush_store(reinterpret_cast<unsigned char *>(out_), (int64_t)N * ES, (int64_t)(n0 + wn * OUTW) * ES, row0);
@@ -410,14 +403,12 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   if constexpr (!kHeads) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int row = m0 + wm * WMT + i * 32 + m_in;
-      if (row >= M) continue;
 #pragma unroll
       for (int j = 0; j < (EPI == PRISM_EPI_SWIGLU ? TN / 2 : TN); ++j)
         for (int g = 0; g < 4; ++g)
           for (int q = 0; q < 4; ++q) {
-            const int col = n0 + wn * OUTW + j * 32 + g * 8 + n_in + q;
-            if (col >= F) continue;
+            const int row = m0 + wm * WMT + i * 32 + m_of(g), col = n0 + wn * OUTW + j * 32 + n_of(g) + q;
+            if (row >= M || col >= F) continue;
             if (EPI == PRISM_EPI_SWIGLU) {
               const float gt = AC(i, j, g * 4 + q), up = AC(i, j + TN / 2, g * 4 + q);
               reinterpret_cast<OT *>(out_)[(int64_t)row * F + col] = from_f32<OT>(gt / (1.0f + __expf(-gt)) * up);
@@ -434,8 +425,8 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   };
 
   const unsigned ldsA = (unsigned)(uintptr_t)PRISM_LDS_PTR(lA), ldsB = (unsigned)(uintptr_t)PRISM_LDS_PTR(lB);
-  const unsigned aA0 = ldsA + (unsigned)(rA[0] * BK + swz(rA[0], khalf) * 8) * 2u;
-  const unsigned aB0 = ldsB + (unsigned)(rB[0] * BK + swz(rB[0], khalf) * 8) * 2u;
+  const unsigned aA0 = ldsA + (unsigned)(rA0 * BK + swz(rA0, kpart) * 8) * 2u;
+  const unsigned aB0 = ldsB + (unsigned)(rB0 * BK + swz(rB0, kpart) * 8) * 2u;
   // wave w's load instruction j fills tile rows (w * ITERS + j) * 8 .. + 8 of an operand (1 KiB of LDS)
   const unsigned ldsA_w = __builtin_amdgcn_readfirstlane(ldsA + (unsigned)wave * A_ITERS * 8 * BK * 2);
   const unsigned ldsB_w = __builtin_amdgcn_readfirstlane(ldsB + (unsigned)wave * B_ITERS * 8 * BK * 2);
@@ -472,21 +463,21 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     else if constexpr (EPI == PRISM_EPI_SWIGLU) PRISM_RUN_SMALL(128x128_2_SWIGLU, PRISM_ACC4, PRISM_G4, PRISM_G4);
     else PRISM_RUN_SMALL(128x128_2_PLAIN, PRISM_ACC4, PRISM_G4, PRISM_G4);
   } else {
-#define PRISM_RUN_KLOOP(TEXT)                                                                                           \
-  asm volatile(TEXT                                                                                                     \
-               : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]), "+a"(acc[1][0]), "+a"(acc[1][1]), \
-                 "+a"(acc[1][2]), "+a"(acc[1][3]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]), \
-                 "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])                                    \
-               : "v"(aA0), "v"(aB0), PRISM_G8(gA), PRISM_G8(gB), "s"(ldsA_w), "s"(ldsB_w), "s"(baseA), "s"(baseB),     \
-                 "s"(nk)                                                                                               \
-               : PRISM_KLOOP4_CLOBBERS)
-    if constexpr (EPI == PRISM_EPI_SWIGLU) {
-      if constexpr (kF16) PRISM_RUN_KLOOP(PRISM_KLOOP4_F16_SWIGLU);
-      else PRISM_RUN_KLOOP(PRISM_KLOOP4_BF16_SWIGLU);
-    } else {
-      if constexpr (kF16) PRISM_RUN_KLOOP(PRISM_KLOOP4_F16_PLAIN);
-      else PRISM_RUN_KLOOP(PRISM_KLOOP4_BF16_PLAIN);
-    }
+    // the second 64 columns of the wave: SwiGLU's are the up rows, half a tile further (the swizzle repeats every 16 rows)
+    const unsigned aB1 = aB0 + (unsigned)((EPI == PRISM_EPI_SWIGLU ? BN / 2 : 64) * BK) * 2u;
+#define PRISM_AB(j) [ga##j] "v"(gA[j]), [gb##j] "v"(gB[j])
+#define PRISM_RUN_KLOOP(TY)                                                                                                    \
+  asm volatile(PRISM_KLOOP_256(TY)                                                                                             \
+               : "={a[0:15]}"(acc[0][0]), "={a[16:31]}"(acc[0][1]), "={a[32:47]}"(acc[0][2]), "={a[48:63]}"(acc[0][3]),          \
+                 "={a[64:79]}"(acc[1][0]), "={a[80:95]}"(acc[1][1]), "={a[96:111]}"(acc[1][2]), "={a[112:127]}"(acc[1][3]),      \
+                 "={a[128:143]}"(acc[2][0]), "={a[144:159]}"(acc[2][1]), "={a[160:175]}"(acc[2][2]), "={a[176:191]}"(acc[2][3]), \
+                 "={a[192:207]}"(acc[3][0]), "={a[208:223]}"(acc[3][1]), "={a[224:239]}"(acc[3][2]), "={a[240:255]}"(acc[3][3])  \
+               : [aa] "v"(aA0), [ab] "v"(aB0), [ab2] "v"(aB1), PRISM_AB(0), PRISM_AB(1), PRISM_AB(2), PRISM_AB(3), PRISM_AB(4),  \
+                 PRISM_AB(5), PRISM_AB(6), PRISM_AB(7), [la] "s"(ldsA_w), [lb] "s"(ldsB_w), [pa] "s"(baseA), [pb] "s"(baseB),     \
+                 [nk] "s"(nk)                                                                                                   \
+               : PRISM_KLOOP_256_CLOBBERS)
+    if constexpr (kF16) PRISM_RUN_KLOOP("f16");
+    else PRISM_RUN_KLOOP("bf16");
 #undef PRISM_RUN_KLOOP
   }
   epilogue();
@@ -501,7 +492,7 @@ bool gemm_16_supported(int epilogue, int N, int K) {
 template <typename OT, int BM, int BN, int WM, int WN, int EPI, int S>
 static int launch_cfg(const OT *A, const OT *W, void *out, int M, int N, int K, hipStream_t s,
                       const QkvEpilogue &qe = QkvEpilogue{}) {
-  constexpr size_t lds = S * (size_t)(BM + BN) * BK * sizeof(OT);
+  constexpr size_t lds = stage_bytes<BM, BN, S>();
   auto kern = gemm_16_kernel<OT, BM, BN, WM, WN, EPI, S>;
   // the attribute is per function: set once per process, also when several contexts launch from different threads
   static std::once_flag attr_once;
@@ -527,13 +518,15 @@ static int launch_cfg(const OT *A, const OT *W, void *out, int M, int N, int K, 
 // square); the size picked by them is on average within 1 % of the best one measured, at worst 9 %.  Examples, in us, 128 x 128
 // compiler-scheduled loop before -> now: 100 x 4096 x 12288 167 -> 36 (64 x 32), 391 x 1024 x 3072 44 -> 10 (64 x 32),
 // 777 x 6144 x 1024 with SwiGLU 23 -> 17 (128 x 128), 3699 x 1024 x 3072 49 -> 30 (128 x 128, three stages).
+// (256 x 256: on chips of different speed a slice takes 1.34-1.7 us, the fixed part 11 us with SwiGLU and 17 with a residual or a
+// head; 1024 x 24576 x 4096 with SwiGLU 233 us on 128 x 128 tiles, 203 on these; 1536 x 6144 x 4096 with heads 103 and 90.)
 struct TileCost {
   int bm, bn, occ;              // tile, workgroups that share a compute unit
   float alone, shared, fixed;   // us per 64-deep slice: one workgroup on the unit; per workgroup when occ of them share it; us per tile
 };
 enum { kTile256, kTile128, kTile128Deep, kTile128x64, kTile64, kTile32x64, kTile64x32, kTile32, kTileKinds };
 static constexpr TileCost kTileCost[kTileKinds] = {
-    {256, 256, 1, 1.53f, 1.53f, 9.2f}, {128, 128, 2, 0.72f, 0.50f, 4.5f}, {128, 128, 1, 0.52f, 0.52f, 3.4f}, {128, 64, 2, 0.34f, 0.36f, 2.3f},
+    {256, 256, 1, 1.45f, 1.45f, 9.2f}, {128, 128, 2, 0.72f, 0.50f, 4.5f}, {128, 128, 1, 0.52f, 0.52f, 3.4f}, {128, 64, 2, 0.34f, 0.36f, 2.3f},
     {64, 64, 2, 0.204f, 0.204f, 2.1f}, {32, 64, 3, 0.176f, 0.149f, 2.4f}, {64, 32, 2, 0.128f, 0.128f, 2.3f}, {32, 32, 2, 0.106f, 0.083f, 2.6f}};
 // The fused q/k/v projection: tiles whose waves own whole heads (34 launches of 1 to 12000 rows: within 11-19 %, the picked
 // size on average within 1 % of the best, at worst 12 %).  Its epilogue is longer: two dependent loads (position, rotation)
@@ -541,7 +534,7 @@ static constexpr TileCost kTileCost[kTileKinds] = {
 // 777 x 6144 x 4096: 56.
 enum { kHead256, kHead128, kHead128Deep, kHead64, kHeadKinds };
 static constexpr TileCost kHeadCost[kHeadKinds] = {
-    {256, 256, 1, 1.53f, 1.53f, 20.f}, {128, 128, 2, 0.70f, 0.55f, 5.5f}, {128, 128, 1, 0.52f, 0.52f, 5.0f}, {64, 128, 2, 0.29f, 0.37f, 5.0f}};
+    {256, 256, 1, 1.40f, 1.40f, 17.f}, {128, 128, 2, 0.70f, 0.55f, 5.5f}, {128, 128, 1, 0.52f, 0.52f, 5.0f}, {64, 128, 2, 0.29f, 0.37f, 5.0f}};
 
 static double tile_cost(const TileCost &t, int64_t M, int64_t ncols, int K, bool glu) {
   const int bn = glu ? t.bn / 2 : t.bn;
@@ -650,17 +643,17 @@ bool gemm_16_qkv_supported(int nq, int nkv, int hd, int K) {
   return hd == 128 && nq > 0 && nkv > 0 && K > 0 && K % BK == 0;          // one head per wavefront
 }
 
-template <typename OT, int EPI>
+template <typename OT>
 static int launch_head(int kind, const QkvEpilogue &e, const OT *A, const OT *W, int M, int N, int K, hipStream_t s) {
   switch (kind) {
-    case kHead256: return launch_cfg<OT, 256, 256, 2, 2, EPI, 2>(A, W, e.QK, M, N, K, s, e);
-    case kHead128: return launch_cfg<OT, 128, 128, 4, 1, EPI, 2>(A, W, e.QK, M, N, K, s, e);
-    case kHead128Deep: return launch_cfg<OT, 128, 128, 4, 1, EPI, 3>(A, W, e.QK, M, N, K, s, e);
-    default: return launch_cfg<OT, 64, 128, 2, 1, EPI, 3>(A, W, e.QK, M, N, K, s, e);
+    case kHead256: return launch_cfg<OT, 256, 256, 2, 2, kEpiQkv, 2>(A, W, e.QK, M, N, K, s, e);
+    case kHead128: return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 2>(A, W, e.QK, M, N, K, s, e);
+    case kHead128Deep: return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 3>(A, W, e.QK, M, N, K, s, e);
+    default: return launch_cfg<OT, 64, 128, 2, 1, kEpiQkv, 3>(A, W, e.QK, M, N, K, s, e);
   }
 }
 
-template <typename OT, int EPI>
+template <typename OT>
 static int launch_qkv_typed(const QkvEpilogue &e, const OT *A, const OT *W, int M, int N, int K, hipStream_t s) {
   const int step = rows_per_launch(K);
   // an odd number of heads leaves half a 256-wide tile outside the matrix, and that tile's epilogue has no column guard
@@ -670,7 +663,7 @@ static int launch_qkv_typed(const QkvEpilogue &e, const OT *A, const OT *W, int 
     p.pos += m0;
     p.vt_col += m0;
     p.QK = reinterpret_cast<char *>(e.QK) + (size_t)m0 * (e.nq + e.nkv) * 128 * 2;
-    return launch_head<OT, EPI>(kind, p, A + (size_t)m0 * K, W, rows, N, K, s);
+    return launch_head(kind, p, A + (size_t)m0 * K, W, rows, N, K, s);
   };
   for (int m0 = 0; m0 < M; m0 += step) {
     const int rows = std::min(step, M - m0);
@@ -690,15 +683,9 @@ int launch_gemm_16_qkv(int dtype, const void *Xn, const void *Wqkv, int M, int K
   const int N = (e.nq + 2 * e.nkv) * 128;
   PRISM_REQUIRE((int64_t)N * K * 2 < ((int64_t)1 << 32) && (int64_t)256 * K * 2 < ((int64_t)1 << 32), PRISM_EUNSUPPORTED,
                 "qkv gemm: the weight operand exceeds 4 GiB");
-  // Below the size where prism_op_qkv_project is offered, a caller composes prism_op_gemm and prism_op_qkv_finish; the
-  // projection gives the bits of that composition there, and those of prism_op_qkv_project above.
-  const bool pairwise = !gemm_16_qkv_large(M, e.nq, e.nkv);
-  auto run = [&](auto tag) {
-    typedef decltype(tag) OT;
-    return pairwise ? launch_qkv_typed<OT, kEpiQkvPairwise>(e, (const OT *)Xn, (const OT *)Wqkv, M, N, K, s)
-                    : launch_qkv_typed<OT, kEpiQkv>(e, (const OT *)Xn, (const OT *)Wqkv, M, N, K, s);
-  };
-  return dtype == PRISM_DTYPE_BF16 ? run(bf16{}) : run(f16{});
+  // one order of every sum, the finishing kernel's, so this gives the bits of prism_op_gemm + prism_op_qkv_finish at every size
+  return dtype == PRISM_DTYPE_BF16 ? launch_qkv_typed(e, (const bf16 *)Xn, (const bf16 *)Wqkv, M, N, K, s)
+                                   : launch_qkv_typed(e, (const f16 *)Xn, (const f16 *)Wqkv, M, N, K, s);
 }
 
 }  // namespace prism

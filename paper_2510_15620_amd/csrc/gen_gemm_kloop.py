@@ -1,62 +1,78 @@
 #!/usr/bin/env python3
-"""Generates gemm_16_kloop.inc: the hand-scheduled K loop of the 256x256x64 GEMM tile.
+"""Generates gemm_16_kloop.inc: the hand-scheduled K loops of the GEMM tiles.
 
     python gen_gemm_kloop.py > gemm_16_kloop.inc        (the output is committed too)
 
-Workgroup: 4 wavefronts (one per SIMD, so each owns 512 registers), wave grid 2x2, wave tile 128x128 =
-4x4 accumulator tiles of v_mfma_f32_32x32x16 kept in 256 AGPRs: the largest wave tile the register file
-allows, i.e. the fewest LDS bytes per MFMA (the kernel is power-limited on MI355X, so bytes moved per flop,
-not latency, set its speed).  A slice is 64 deep: 4 steps of 16 MFMAs.
+The 256x256x64 tile.  4 wavefronts (one per SIMD, so each owns 512 registers), wave grid 2x2, wave tile 128x128 = 8x8
+accumulator tiles of v_mfma_f32_16x16x32 kept in 256 AGPRs: the largest wave tile the register file allows, i.e. the
+fewest LDS bytes per MFMA.  A slice is 64 deep: 2 steps of 64 MFMAs (16 cycles each, 2048 in all).
 
-Pipeline (t = slice):
-  * global memory -> LDS directly (global_load_lds_dwordx4, no staging registers): the 16 loads of slice t+1
-    are issued behind the even MFMAs of steps 0 and 1 of slice t into LDS stage (t+1) % 2.  Each instruction
-    fills 8 tile rows (1 KiB); the XOR swizzle is applied on the source side (lane l fetches the chunk that
-    belongs in slot l % 8 of row l / 8);
-  * LDS -> fragments one step ahead, one read behind every odd MFMA of a step (an even stream, no bursts);
-  * one barrier per slice, after MFMA 8 of the last step (preceded by s_waitcnt vmcnt(0): this wave's share of
-    slice t+1 has landed); behind it the first fragments of slice t+1 are read while MFMAs 9-16 keep the
-    matrix pipe busy.
-Near the end of K the loads re-read the last slice (in bounds, into the stage nobody reads), which keeps the
-slice bodies free of branches.
+What bounds it: power.  On operands that toggle the chip lowers its clock until the energy per flop fits, so time follows
+the energy of a slice first and its stalls second.  Measured on f16 normals, 24576 x 24576 x 4096 / 32768 x 4096 x 12288 (a
+product alone, no memory traffic at all, reaches 1600-1620 TFLOP/s):
+  * 32x32x16 MFMAs, two stages, loads in two bursts of 8: 1228-1252 / 1181-1205 TFLOP/s (1.53 us a slice at 1.59 GHz, pipes 85 %
+    busy inside the loop; 74 % down projection);
+  * 16x16x32 MFMAs and single loads: 1365-1375 / 1330-1340 (1.38 us at 1.73 GHz, as busy: the same product - to the bit - for
+    less energy; alone the two instructions are level, 1590 against 1620);
+  * + pairs of rows in the MFMA order (below) and 4 row tiles a group: 1410 / 1340;
+  * + a third stage for A, loads spread over three quarters of a slice: 1427 / 1420 (93 % busy at 1.57-1.65 GHz).
+
+Pipeline (t = slice, positions are MFMAs 0..127 of the slice):
+  * global memory -> LDS directly (global_load_lds_dwordx4, no staging registers).  Each instruction fills 8 tile rows
+    (1 KiB); the XOR swizzle is applied on the source side (lane l fetches the chunk that belongs in slot l % 8 of row l / 8);
+  * LDS holds three stages of A and two of B (160 KiB).  Behind the slice's barrier (position PB) the stages of slice t are
+    free: B of slice t+2 and then A of slice t+3 are requested, one load every LSTRIDE MFMAs.  Every 3, 4, 5, 7 or 8 was slower: a
+    load occupies the CU's address path for 16 cycles, the four waves issue theirs together, and a wave that waits there
+    issues no MFMA;
+  * the barrier waits for all but the 8 youngest loads (A of slice t+2): B has a whole slice to arrive, A two;
+  * LDS -> fragments one step ahead into the other of two register sets, one read every RSTRIDE MFMAs.
+Near the end of K the loads re-read the last slice (in bounds, into stages nobody reads), which keeps the slice bodies
+free of branches.  The stage offsets are immediates, so the loop is unrolled over 6 slices.
 
 The W fragment is the first MFMA operand, so accumulator tiles come out transposed (a lane owns one row of A).
 """
 # ---- register plan (all clobbered) ----
-GA = [f"%{18 + j}" for j in range(8)]   # byte offset into A of the chunk this lane fetches in load instruction j (inputs)
-GB = [f"%{26 + j}" for j in range(8)]
-AA = [36 + k for k in range(4)]         # LDS address of the lane's first A fragment row, step k (stage 0)
-AB = [40 + k for k in range(4)]
-F = [{"A": [64 + 4 * i for i in range(4)], "B": [80 + 4 * j for j in range(4)]},
-     {"A": [96 + 4 * i for i in range(4)], "B": [112 + 4 * j for j in range(4)]}]
-CLOBBER_V = list(range(36, 44)) + list(range(64, 128))
-CLOBBER_S = [20, 21, 22, 23, 24, 25, 26, 27, 28, 29]
+AA, AA2, AB, AB2 = [116, 117], [118, 119], [120, 121], [122, 123]   # LDS address of the lane's first fragment row, per step: A stages
+                                                                    # 0 and 1, A stage 2, B columns 0-63, B columns 64-127 of the wave
+F = [{"A": [128 + 64 * s + 4 * i for i in range(8)], "B": [160 + 64 * s + 4 * j for j in range(8)]} for s in range(2)]
+CLOBBER_V = list(range(116, 124)) + list(range(128, 256))
+CLOBBER_S = list(range(20, 30))
 
 STAGE = 32768                           # bytes per LDS stage of one operand
-A_FRAG_OFF = [0, 4096, 8192, 12288]     # 32 rows x 128 B apart
+A_STAGES, B_STAGES, PERIOD = 3, 2, 6
+TILE_ROWS = 2048                        # 16 rows x 128 B
+RSTRIDE, PB, LSTRIDE = 3, 56, 6
 
 
 def v4(r):
     return f"v[{r}:{r + 3}]"
 
 
-def reads(fs, k, stage, b_off):
-    """The 8 fragment reads of step k from `stage` into fragment set fs, in the order a0,b0,b1,b2,b3,a1,a2,a3."""
-    ra = lambda i: f"ds_read_b128 {v4(F[fs]['A'][i])}, v{AA[k]} offset:{stage * STAGE + A_FRAG_OFF[i]}"
-    rb = lambda j: f"ds_read_b128 {v4(F[fs]['B'][j])}, v{AB[k]} offset:{stage * STAGE + b_off[j]}"
-    return [ra(0), rb(0), rb(1), rb(2), rb(3), ra(1), ra(2), ra(3)]
+def acc(i, j):
+    """16 x 16 tile (i, j) of the wave: the 32 x 32 block (i / 2, j / 2) is operand acc[i / 2][j / 2] of the kernel, 16 registers, its
+    four tiles in the order (0,0), (0,1), (1,0), (1,1)."""
+    r = ((i // 2) * 4 + j // 2) * 16 + ((i % 2) * 2 + j % 2) * 4
+    return f"a[{r}:{r + 3}]"
 
 
-def mfma(mn, fs, i, j):
-    acc = f"%{i * 4 + j}"
-    return f"{mn} {acc}, {v4(F[fs]['B'][j])}, {v4(F[fs]['A'][i])}, {acc}"
+def reads(fs, k, t):
+    """The 16 fragment reads of step k of slice t into fragment set fs, in the order of their first use."""
+    sa, sb = t % A_STAGES, t % B_STAGES
+    base, off = (AA2, 0) if sa == 2 else (AA, sa * STAGE)              # a read's immediate offset ends at 64 KiB
+    ra = lambda i: f"ds_read_b128 {v4(F[fs]['A'][i])}, v{base[k]} offset:{off + i * TILE_ROWS}"
+    rb = lambda j: f"ds_read_b128 {v4(F[fs]['B'][j])}, v{(AB if j < 4 else AB2)[k]} offset:{sb * STAGE + j % 4 * TILE_ROWS}"
+    return [ra(0), rb(0), ra(1)] + [rb(j) for j in range(1, 8)] + [ra(i) for i in range(2, 8)]
+
+
+def mfma(fs, i, j):
+    return f'v_mfma_f32_16x16x32_" TY " {acc(i, j)}, {v4(F[fs]["B"][j])}, {v4(F[fs]["A"][i])}, {acc(i, j)}'
 
 
 def loads(which, stage):
-    """8 direct-to-LDS loads of this wave for one operand: M0 = LDS destination (wave base %34 / %35 + 1 KiB per
-    instruction + stage), source = running base s[20:21] / s[22:23] + the lane's byte offset."""
-    base, lds, off = ("s[20:21]", "%34", GA) if which == "A" else ("s[22:23]", "%35", GB)
-    return [f"s_add_u32 m0, {lds}, {stage * STAGE + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 {off[j]}, {base}"
+    """8 direct-to-LDS loads of this wave for one operand: M0 = LDS destination (wave base + 1 KiB per instruction + stage),
+    source = running base s[20:21] / s[22:23] + the lane's byte offset."""
+    base, lds, off = ("s[20:21]", "%[la]", "ga") if which == "A" else ("s[22:23]", "%[lb]", "gb")
+    return [f"s_add_u32 m0, {lds}, {stage * STAGE + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 %[{off}{j}], {base}"
             for j in range(8)]
 
 
@@ -68,67 +84,56 @@ def advance(which):
             f"s_add_u32 {lo}, {lo}, s27", f"s_addc_u32 {hi}, {hi}, 0", f"s_add_u32 {idx}, {idx}, s28"]
 
 
-# LDS reads return in order, so lgkmcnt(n) = "all but the n youngest have landed".  The 8 reads of a step's operands
-# (a0,b0,b1,b2,b3,a1,a2,a3) are issued during the step before, one behind every odd MFMA (1,3,..,15), so that LDS sees an
-# even stream instead of bursts.  Before MFMA m the queue holds what is left of those 8 plus the younger reads already
-# issued in this step: MFMA 1 needs a0,b0 -> b1..a3 = 6 may be pending; MFMA 2 needs b1 -> 5 older + 1 younger = 6;
-# MFMA 3 needs b2 -> 4 + 1 = 5; MFMA 4 needs b3 -> 3 + 2 = 5; MFMA 5 needs a1 -> 2 + 2 = 4; MFMA 9 needs a2 -> 1 + 4 = 5;
-# MFMA 13 needs a3 -> 0 + 6 = 6.
-WAITS = {1: 6, 2: 6, 3: 5, 4: 5, 5: 4, 9: 5, 13: 6}
-# last step of a slice: no reads of a next step; everything has landed before the barrier behind MFMA 8 (other waves
-# overwrite this stage right after it)
-WAITS_LAST = {1: 6, 2: 5, 3: 4, 4: 3, 5: 2}
-
-
-def slice_body(mn, cur, b_off):
-    """Slice t, whose operands sit in LDS stage `cur`.  Stage 1 - cur receives slice t+1: its A half was requested during
-    the last step of slice t-1, its B half is requested here during step 0.  After this slice's barrier stage `cur` is
-    free and the A half of slice t+2 is requested into it."""
-    nxt = 1 - cur
+def mfma_order():
+    """Two rows of accumulator tiles at a time, column by column, turning at the ends: consecutive MFMAs differ in one operand
+    fragment (fewer operand bits toggle; 0.8 % faster than row by row)."""
     out = []
-    # boustrophedon over the 4 x 4 accumulator tiles: consecutive matrix instructions differ in ONE operand fragment, also
-    # where a row of tiles ends (fewer operand-bus toggles for the same arithmetic; the part runs at its power limit)
-    order = [(i, j if i % 2 == 0 else 3 - j) for i in range(4) for j in range(4)]
-    for k in range(4):
-        fs = k & 1
-        behind_odd = reads(1 - fs, k + 1, cur, b_off) if k < 3 else []          # behind MFMAs 1,3,..,15
-        behind_even = loads("B", nxt) if k == 0 else []                         # behind MFMAs 2,4,..,16
-        after_barrier = loads("A", cur) if k == 3 else []                       # behind MFMAs 9..16 of the last step
-        waits = WAITS if k < 3 else WAITS_LAST
-        for m, (i, j) in enumerate(order, start=1):
-            if k == 3 and m == 9:
-                out += ["s_waitcnt vmcnt(0) lgkmcnt(0)", "s_barrier"]
-                out += reads(0, 0, nxt, b_off)                                  # first fragments of the next slice
-            if waits.get(m) is not None:
-                out.append(f"s_waitcnt lgkmcnt({waits[m]})")
-            out.append(mfma(mn, fs, i, j))
-            if m % 2 == 1 and behind_odd:
-                out.append(behind_odd[m // 2])
-            elif m % 2 == 0 and behind_even:
-                out.append(behind_even[m // 2 - 1])
-            if m >= 9 and after_barrier:
-                out.append(after_barrier[m - 9])
-        if k == 0:
-            out += advance("B")
-        if k == 3:
-            out += advance("A")
+    for p in range(4):
+        for n, j in enumerate(range(8) if p % 2 == 0 else range(7, -1, -1)):
+            out += [(2 * p + i, j) for i in ((0, 1) if n % 2 == 0 else (1, 0))]
     return out
 
 
-def kloop(mn, b_off):
+def slice_body(t):
+    behind = {}                                         # position -> what is issued behind that MFMA
+    for n, r in enumerate(reads(1, 1, t)):
+        behind.setdefault(n * RSTRIDE, []).append(r)
+    for n, r in enumerate(reads(0, 0, t + 1)):
+        behind.setdefault(64 + n * RSTRIDE, []).append(r)
+    # the loads requested behind this slice's barrier, and those of the slice before that reach into this one (they go to the
+    # stages that were freed by its barrier)
+    for s, shift in ((t, 0), (t - 1, 128)):
+        for n, l in enumerate(loads("B", s % B_STAGES) + loads("A", s % A_STAGES)):
+            p = PB + 1 + n * LSTRIDE - shift
+            if 0 <= p < 128 and (shift == 0 or p < PB):
+                behind.setdefault(p, []).append(l)
+    assert 15 * RSTRIDE < PB and PB + 1 + 15 * LSTRIDE - 128 < PB
+    out = []
+    for m in range(128):
+        if m in (0, 64):
+            out.append("s_waitcnt lgkmcnt(0)")          # the step's fragments; the last was requested 18 MFMAs ago
+        if m == PB:
+            out += ["s_waitcnt vmcnt(8) lgkmcnt(0)"] + advance("A") + advance("B") + ["s_barrier"]
+        out.append(mfma(m // 64, *mfma_order()[m % 64]))
+        out += behind.get(m, [])
+    return out
+
+
+def kloop():
     s = []
-    # ---- setup: step addresses differ only in the swizzled chunk bits
-    s += [f"v_mov_b32 v{AA[0]}, %16", f"v_xor_b32 v{AA[1]}, 32, %16", f"v_xor_b32 v{AA[2]}, 64, %16", f"v_xor_b32 v{AA[3]}, 96, %16"]
-    s += [f"v_mov_b32 v{AB[0]}, %17", f"v_xor_b32 v{AB[1]}, 32, %17", f"v_xor_b32 v{AB[2]}, 64, %17", f"v_xor_b32 v{AB[3]}, 96, %17"]
-    s += ["s_mov_b64 s[20:21], %36", "s_mov_b64 s[22:23], %37", "s_mov_b32 s24, %38", "s_sub_u32 s26, %38, 1", "s_mov_b32 s25, 0", "s_mov_b32 s29, 0"]
-    # ---- prologue: slice 0 -> LDS stage 0, first fragments
-    s += loads("A", 0) + loads("B", 0) + advance("A") + advance("B")
-    s += ["s_waitcnt vmcnt(0)", "s_barrier"] + reads(0, 0, 0, b_off)
-    s += loads("A", 1) + advance("A")                                           # A half of slice 1
-    s += ["L_loop_%=:"] + slice_body(mn, 0, b_off)
-    s += ["s_sub_u32 s24, s24, 1", "s_cmp_eq_u32 s24, 0", "s_cbranch_scc1 L_done_%="]
-    s += slice_body(mn, 1, b_off)
-    s += ["s_sub_u32 s24, s24, 1", "s_cmp_lg_u32 s24, 0", "s_cbranch_scc1 L_loop_%="]
+    for k in range(2):                                  # the steps' addresses differ only in a swizzled chunk bit
+        s += [f"v_xor_b32 v{r[k]}, {64 * k}, %[{a}]" for r, a in ((AA, "aa"), (AB, "ab"), (AB2, "ab2"))]
+        s += [f"v_add_u32 v{AA2[k]}, {2 * STAGE}, v{AA[k]}"]
+    s += ["s_mov_b64 s[20:21], %[pa]", "s_mov_b64 s[22:23], %[pb]", "s_mov_b32 s24, %[nk]", "s_sub_u32 s26, %[nk], 1",
+          "s_mov_b32 s25, 0", "s_mov_b32 s29, 0"]
+    # ---- prologue: B and A of slices 0 and 1, A of slice 2; the accumulators are cleared while the first of them arrive
+    s += loads("B", 0) + advance("B") + loads("A", 0) + advance("A") + loads("B", 1) + loads("A", 1) + advance("A") + loads("A", 2)
+    s += [f"v_accvgpr_write_b32 a{r}, 0" for r in range(256)]
+    s += ["s_waitcnt vmcnt(24)", "s_barrier"] + reads(0, 0, 0)
+    s += ["L_loop_%=:"]
+    for t in range(PERIOD):
+        s += slice_body(t) + ["s_sub_u32 s24, s24, 1", "s_cmp_eq_u32 s24, 0"]
+        s += ["s_cbranch_scc1 L_done_%="] if t + 1 < PERIOD else ["s_cbranch_scc0 L_loop_%="]
     s += ["L_done_%=:", "s_waitcnt vmcnt(0) lgkmcnt(0)", "s_nop 15", "s_nop 15"]   # MFMA results settle before the epilogue reads them
     return s
 
@@ -276,22 +281,19 @@ def emit(name, lines):
 
 def main():
     print("// Generated by gen_gemm_kloop.py - do not edit.  See that file for the schedule.")
-    print("// PRISM_KLOOP4_*: %0..%15 accumulators acc[i][j] (operand i*4+j, AGPRs); %16 / %17 LDS byte address of the lane's")
-    print("// first A / B fragment row (step 0, stage 0); %18..%25 / %26..%33 byte offset into A / W of the chunk this lane fetches")
-    print("// in each of its wave's load instructions; %34 / %35 LDS byte address of the first row the first of them fills (stage 0,")
-    print("// uniform); %36 / %37 base of A / W; %38 number of slices.  The other loops: the same order, with their own counts.")
+    print("// PRISM_KLOOP_256(TY), TY = \"f16\" or \"bf16\": accumulators a[0:255] (32 x 32 block (i, j) of the wave in a[(4i+j)*16 : +15]);")
+    print("// aa / ab / ab2 LDS byte address of the lane's first fragment row of A, of B columns 0-63 and 64-127 (step 0, stage 0);")
+    print("// ga0..7 / gb0..7 byte offset into A / W of the chunk this lane fetches in each of its wave's load instructions; la / lb")
+    print("// LDS byte address of the first row the first of them fills (stage 0, uniform); pa / pb base of A / W; nk number of slices.")
+    print("// PRISM_KLOOP_*: accumulators acc[i][j] first (AGPRs), then the same values by position (see class Small).")
     print()
-    plain = [0, 4096, 8192, 12288]                 # B fragments: 4 consecutive 32-row blocks
-    swiglu = [0, 4096, 16384, 20480]               # 2 gate blocks, then the 2 matching up blocks 128 rows further
-    for tname, mn in (("F16", "v_mfma_f32_32x32x16_f16"), ("BF16", "v_mfma_f32_32x32x16_bf16")):
-        emit(f"PRISM_KLOOP4_{tname}_PLAIN", kloop(mn, plain))
-        emit(f"PRISM_KLOOP4_{tname}_SWIGLU", kloop(mn, swiglu))
+    emit("PRISM_KLOOP_256(TY)", kloop())
     regs = ", ".join(f'"v{r}"' for r in CLOBBER_V) + ", " + ", ".join(f'"s{r}"' for r in CLOBBER_S)
     for c in SMALL:
         c.emit()
     # m0 (written before every direct-to-LDS load) is not listed: the compiler reserves it, sets it right before each of
     # its own uses and never keeps a value in it across a statement; hipcc diagnoses it in a clobber list
-    print(f"#define PRISM_KLOOP4_CLOBBERS {regs}, \"scc\", \"memory\"")
+    print(f"#define PRISM_KLOOP_256_CLOBBERS {regs}, \"scc\", \"memory\"")
 
 
 if __name__ == "__main__":
