@@ -45,7 +45,7 @@ template <> __device__ __forceinline__ float from_f32<float>(float v) { return v
 template <> __device__ __forceinline__ bf16 from_f32<bf16>(float v) { return (bf16)v; }  // round-to-nearest-even
 __device__ __forceinline__ float to_f32(f16 v) { return (float)v; }
 // IEEE half, round-to-nearest-even, saturating at the largest finite half instead of overflowing to infinity
-template <> __device__ __forceinline__ f16 from_f32<f16>(float v) { return (f16)fminf(fmaxf(v, -65504.0f), 65504.0f); }
+template <> __device__ __forceinline__ f16 from_f32<f16>(float v) { return (f16)__builtin_amdgcn_fmed3f(v, -65504.0f, 65504.0f); }
 
 // matrix-core instruction of a 16-bit operand type: D(32x32, fp32) += A(32x16) B(16x32)
 template <typename T> struct Mfma;

@@ -21,6 +21,7 @@
 // contiguous range of tiles, walked in groups of 4 or 8 row-tiles, to keep the operand panels in its L2.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "gemm_16_kloop.inc"
@@ -37,6 +38,10 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 
 #define PRISM_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define PRISM_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+
+// silu(g) * u in fp32, rounded to 16 bits by its callers.  The reciprocal instruction (1 ulp) instead of the ten instructions of a
+// correctly rounded division, which were half of the SwiGLU epilogue: 13.8 -> 9.2 thousand cycles of a 256 x 256 tile.
+__device__ __forceinline__ float silu_mul(float g, float u) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u; }
 
 // LDS bytes of a tile's operand stages
 template <int BM, int BN, int S> constexpr int stage_bytes() { return ((BM == 256 ? 3 : S) * BM + S * BN) * BK * 2; }
@@ -79,7 +84,8 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   constexpr int BNO = EPI == PRISM_EPI_SWIGLU ? BN / 2 : BN; // output columns per tile
   const int n0 = tile_n * (EPI == PRISM_EPI_SWIGLU ? BN / 2 : BN);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // read from a lane, so that what follows from the wave's place stays in scalar registers
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
 
   // ---- global -> LDS staging without registers (global_load_lds_dwordx4).  Instruction j of wave w
@@ -139,13 +145,22 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   const int f_row = lane / CPR, f_chunk = lane % CPR;               // lane -> (row within an instruction, chunk)
   const bool full_n = n0 + BNO <= F && (F * ES) % 16 == 0;
   f32x4 old[2][EPI == PRISM_EPI_RESIDUAL ? NI : 1];
-  float *xo = reinterpret_cast<float *>(out_) + n0 + wn * OUTW + f_chunk * 4;
-  auto load_old = [&](int i) __attribute__((always_inline)) {
+  // An access goes to a wave-uniform address (scalar) plus a lane offset that stays the same: multiplying rows by the pitch per
+  // lane and access took a third of the epilogue's vector time.
+  const int64_t out_pitch = (int64_t)F * ES;                        // bytes
+  const unsigned f_off = (unsigned)f_row * (unsigned)out_pitch + (unsigned)f_chunk * 16u;   // < 32 rows: far below 4 GiB
+  unsigned char *const out_w = reinterpret_cast<unsigned char *>(out_) + (int64_t)(m0 + wm * WMT) * out_pitch + (int64_t)(n0 + wn * OUTW) * ES;
+  const int rows_left = M - m0 - wm * WMT;                          // of the wave's rows inside the matrix
+  const int64_t out_step = NR * out_pitch;
+  const unsigned char *old_at = out_w;                              // steps along with the loads
+  // (whole: every row is inside the matrix, no guard per access)
+  auto load_old = [&](int i, auto whole) __attribute__((always_inline)) {
     if constexpr (EPI == PRISM_EPI_RESIDUAL) {
 #pragma unroll
       for (int rr = 0; rr < NI; ++rr) {
-        const int row = m0 + wm * WMT + i * 32 + rr * NR + f_row;
-        old[i & 1][rr] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(xo + (int64_t)(row < M ? row : M - 1) * N));
+        const int r = i * 32 + rr * NR;
+        if (whole || r + f_row < rows_left) old[i & 1][rr] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(old_at + f_off));
+        old_at += out_step;
       }
     }
   };
@@ -165,7 +180,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   };
   if constexpr (kEarly) {
     if constexpr (kHeads) load_rows();
-    else if (full_n) load_old(0);
+    else if (full_n) load_old(0, std::false_type{});
   }
 
   // ---- epilogue.  The W fragment was the instruction's first operand, so the 32 x 32 accumulator block (i, j) is
@@ -214,14 +229,15 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     const int r = rr * NR + f_row;
     return *reinterpret_cast<const uint4 *>(stg + r * RB + ((f_chunk ^ (r & SWZ)) << 4));
   };
-  // Flushes the staged block to rows row0 + r of a row-major destination (row pitch `pitch` bytes, the wave's first
-  // column at byte col_byte0 of a row).
-  auto flush_store = [&](unsigned char *dst, int64_t pitch, int64_t col_byte0, int row0) __attribute__((always_inline)) {
+  // Flushes the staged block i of the wave's rows to a row-major destination (wave-uniform address of the wave's first row and
+  // column, row pitch, the lane's offset).
+  auto flush_store = [&](unsigned char *dst, int64_t pitch, unsigned off, int i) __attribute__((always_inline)) {
+    dst += (int64_t)i * 32 * pitch;
 #pragma unroll
     for (int rr = 0; rr < NI; ++rr) {
-      const int row = row0 + rr * NR + f_row;
       const uint4 v = staged(rr);
-      if (row < M) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t *>(dst + (int64_t)row * pitch + col_byte0 + f_chunk * 16));
+      if (i * 32 + rr * NR + f_row < rows_left) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t *>(dst + off));
+      dst += NR * pitch;
     }
   };
 
@@ -250,12 +266,15 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
           }
       }
       const int64_t pitch = (int64_t)(qe.nq + qe.nkv) * 128 * 2;
-      // (cos, sin) of (pos, d) sits at [d * stride + pos]: a wave-uniform base per column plus one 32-bit lane offset.
+      unsigned char *const qk_w = reinterpret_cast<unsigned char *>(qe.QK) + (int64_t)(m0 + wm * WMT) * pitch + (int64_t)head * 128 * 2;
+      const unsigned qk_off = (unsigned)f_row * (unsigned)pitch + (unsigned)f_chunk * 16u;
+      // (cos, sin) of (pos, d) sits at [d * stride + pos]: a wave-uniform base per column plus one 32-bit lane offset (in bytes, or
+      // the compiler cannot rule out a carry and adds 64-bit addresses per lane).
       // The 32 pairs of block i + 1 are requested before block i is worked on, so the tile pays the memory latency once,
       // not once per block.
       unsigned lane_off[TM * RPB];
 #pragma unroll
-      for (int i = 0; i < TM * RPB; ++i) lane_off[i] = (unsigned)(kpart * 4) * (unsigned)qe.rope_stride + (unsigned)row_in[i];
+      for (int i = 0; i < TM * RPB; ++i) lane_off[i] = ((unsigned)(kpart * 4) * (unsigned)qe.rope_stride + (unsigned)row_in[i]) * 8u;
       float2 cs[2][2][4][4];
       auto load_cs = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
@@ -265,13 +284,13 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               const int d = j * 32 + (k16 ? (g & 1) * 16 : g * 8) + q;         // without the lane's part
-              cs[i & 1][j][g][q] = (qe.rope_tab_t + (int64_t)d * qe.rope_stride)[lane_off[k16 ? i * 2 + (g >> 1) : i]];
+              const char *col = reinterpret_cast<const char *>(qe.rope_tab_t + (int64_t)d * qe.rope_stride);
+              cs[i & 1][j][g][q] = *reinterpret_cast<const float2 *>(col + lane_off[k16 ? i * 2 + (g >> 1) : i]);
             }
       };
       load_cs(0);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int row0 = m0 + wm * WMT + i * 32;
         if (i + 1 < TM) load_cs(i + 1);
         float r[RPB];
 #pragma unroll
@@ -314,7 +333,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
             put16(m_of(g), j * 32 + n_of(g) + 64, hi);
           }
         }
-        flush_store(reinterpret_cast<unsigned char *>(qe.QK), pitch, (int64_t)head * 128 * 2, row0);
+        flush_store(qk_w, pitch, qk_off, i);
       }
     } else {
       // v head: rounded to the operand type, stored as half, transposed (16 or 32 consecutive tokens of one d are contiguous)
@@ -323,42 +342,29 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
 #pragma unroll
         for (int h = 0; h < RPB; ++h) {
           if (m0 + wm * WMT + i * 32 + h * 16 + frow >= M) continue;
-          f16 *vt = reinterpret_cast<f16 *>(qe.Vt) + (int64_t)(head - qe.nq - qe.nkv) * 128 * qe.vt_stride + row_in[i * RPB + h];
+          f16 *vt = reinterpret_cast<f16 *>(qe.Vt) + ((int64_t)(head - qe.nq - qe.nkv) * 128 + kpart * 4) * qe.vt_stride + row_in[i * RPB + h];
 #pragma unroll
           for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int g = h * 2; g < h * 2 + 4 / RPB; ++g)
 #pragma unroll
               for (int q = 0; q < 4; ++q)
-                vt[(int64_t)(j * 32 + n_of(g) + q) * qe.vt_stride] = from_f32<f16>(to_f32(from_f32<OT>(AC(i, j, g * 4 + q))));
+                vt[(int64_t)(j * 32 + (k16 ? (g & 1) * 16 : g * 8) + q) * qe.vt_stride] = from_f32<f16>(to_f32(from_f32<OT>(AC(i, j, g * 4 + q))));
         }
     }
     return;
   }
 
-  if (full_n) {
-    if constexpr (!kEarly) load_old(0);
+  if (EPI == PRISM_EPI_RESIDUAL && full_n) {
+    // read-modify-write of the fp32 stream, whole lines per instruction; the loads of the next block are requested
+    // before this block is staged, so the tile pays the memory latency once, not per block
+    auto residual = [&](auto whole) __attribute__((always_inline)) {
+      if constexpr (!kEarly) load_old(0, whole);
+      int64_t new_at = 0;
+      asm volatile("" : "+s"(new_at));       // a chain of its own: 64 addresses shared with the loads would not fit the scalar registers
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int row0 = m0 + wm * WMT + i * 32;                       // first row of the block
-      if (EPI == PRISM_EPI_SWIGLU) {
-#pragma unroll
-        for (int j = 0; j < TN / 2; ++j)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            typename Mfma<OT>::vec4 v;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const float gt = AC(i, j, g * 4 + q), up = AC(i, j + TN / 2, g * 4 + q);
-              v[q] = from_f32<OT>(gt / (1.0f + __expf(-gt)) * up);
-            }
-            put16(m_of(g), j * 32 + n_of(g), v);
-          }
-        flush_store(reinterpret_cast<unsigned char *>(out_), (int64_t)F * 2, (int64_t)(n0 + wn * OUTW) * 2, row0);
-      } else if (EPI == PRISM_EPI_RESIDUAL) {
-        // read-modify-write of the fp32 stream, whole lines per instruction; the loads of the next block are requested
-        // before this block is staged, so the tile pays the memory latency once, not per block
-        if (i + 1 < TM) load_old(i + 1);
+      for (int i = 0; i < TM; ++i) {
+        if (i + 1 < TM) load_old(i + 1, whole);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -370,12 +376,32 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
           }
 #pragma unroll
         for (int rr = 0; rr < NI; ++rr) {
-          const int row = row0 + rr * NR + f_row;
+          const int r = i * 32 + rr * NR;
           const uint4 u = staged(rr);
           f32x4 v = old[i & 1][rr];
           v[0] += __uint_as_float(u.x); v[1] += __uint_as_float(u.y); v[2] += __uint_as_float(u.z); v[3] += __uint_as_float(u.w);
-          if (row < M) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(xo + (int64_t)row * N));
+          if (whole || r + f_row < rows_left) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(out_w + new_at + f_off));
+          new_at += out_step;
         }
+      }
+    };
+    if (rows_left >= WMT) residual(std::true_type{});
+    else residual(std::false_type{});
+    return;
+  }
+  if (full_n) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if (EPI == PRISM_EPI_SWIGLU) {
+#pragma unroll
+        for (int j = 0; j < TN / 2; ++j)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            typename Mfma<OT>::vec4 v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = from_f32<OT>(silu_mul(AC(i, j, g * 4 + q), AC(i, j + TN / 2, g * 4 + q)));
+            put16(m_of(g), j * 32 + n_of(g), v);
+          }
       } else {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
@@ -393,8 +419,8 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
               put16(m_of(g), j * 32 + n_of(g), v);
             }
           }
-        flush_store(reinterpret_cast<unsigned char *>(out_), (int64_t)N * ES, (int64_t)(n0 + wn * OUTW) * ES, row0);
       }
+      flush_store(out_w, out_pitch, f_off, i);
     }
     return;
   }
@@ -410,8 +436,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
             const int row = m0 + wm * WMT + i * 32 + m_of(g), col = n0 + wn * OUTW + j * 32 + n_of(g) + q;
             if (row >= M || col >= F) continue;
             if (EPI == PRISM_EPI_SWIGLU) {
-              const float gt = AC(i, j, g * 4 + q), up = AC(i, j + TN / 2, g * 4 + q);
-              reinterpret_cast<OT *>(out_)[(int64_t)row * F + col] = from_f32<OT>(gt / (1.0f + __expf(-gt)) * up);
+              reinterpret_cast<OT *>(out_)[(int64_t)row * F + col] = from_f32<OT>(silu_mul(AC(i, j, g * 4 + q), AC(i, j + TN / 2, g * 4 + q)));
             } else if (EPI == PRISM_EPI_RESIDUAL) {
               reinterpret_cast<float *>(out_)[(int64_t)row * N + col] += AC(i, j, g * 4 + q);
             } else if (EPI == PRISM_EPI_STORE_F32) {
