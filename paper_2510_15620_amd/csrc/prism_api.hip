@@ -2,6 +2,7 @@
 // checkpoints between layers (Sec. 3.4, 4.1), chunked execution within a layer (Sec. 4.3) and
 // overlapped layer streaming from pinned host memory on a side stream (Sec. 4.2).
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -104,13 +105,11 @@ struct prism_ctx {
   bool own_stream = false;
   int ring = 2;                                   // layer slots of the streaming ring (two_slot); 2 is the paper's double buffer
   std::vector<hipEvent_t> ev_ready, ev_free;      // per ring slot
-  hipEvent_t ev_t[2] = {nullptr, nullptr};        // first and last launch of a call
-  std::vector<hipEvent_t> ev_check;               // 2 per check, for the report
-  std::vector<hipEvent_t> ev_layer;               // 4 per layer (two intervals: a layer may run in two passes), for the report
   std::vector<hipEvent_t> ev_xfer;                // 2 per layer on the side stream around a streamed layer's transfers, for the report
-  // per-launch spans for the report: events come from a pool that only grows
+  // moments on the compute stream for the report (see mark): events come from a pool that only grows
   struct Span { int kind; hipEvent_t a, b; double flops; int rows; };
   std::vector<hipEvent_t> ev_pool; size_t ev_used = 0;
+  hipEvent_t last_mark = nullptr;                 // the youngest moment, null once something was queued behind it
   std::vector<Span> spans;
   bool profiling = false;
   int span_mask = ~0;                             // kinds that get event spans while profiling
@@ -359,8 +358,6 @@ extern "C" int prism_create(const prism_model *model, const prism_weights *weigh
     CREATE_HIP(hipEventCreateWithFlags(&c->ev_ready[i], hipEventDisableTiming));
     CREATE_HIP(hipEventCreateWithFlags(&c->ev_free[i], hipEventDisableTiming));
   }
-  for (hipEvent_t &e : c->ev_t) CREATE_HIP(hipEventCreate(&e));
-
   const int n_slots = c->two_slot ? std::min(c->ring, model->n_layers) : model->n_layers;
   c->layer_buf.assign(n_slots, nullptr);
   for (int s = 0; s < n_slots; ++s) CREATE_TRY(dev_alloc(c, (void **)&c->layer_buf[s], c->lay.bytes));
@@ -427,9 +424,6 @@ extern "C" void prism_destroy(prism_ctx *c) {
   if (c->h_res) (void)hipHostFree(c->h_res);
   for (hipEvent_t e : c->ev_ready) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev_free) if (e) (void)hipEventDestroy(e);
-  for (hipEvent_t e : c->ev_t) if (e) (void)hipEventDestroy(e);
-  for (hipEvent_t e : c->ev_check) if (e) (void)hipEventDestroy(e);
-  for (hipEvent_t e : c->ev_layer) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev_xfer) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev_pool) if (e) (void)hipEventDestroy(e);
   if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
@@ -664,25 +658,36 @@ static int upload_meta(prism_ctx *c, const Plan &p, const MetaOff &mo, bool with
   return PRISM_OK;
 }
 
-static int span_event(prism_ctx *c, hipEvent_t *e) {
+// The moment on the compute stream behind everything queued so far, as an event of the pool.  What such a record costs is idle
+// time between two kernels: 2.9 us with an ordinary event, 1.05 us without its system-scope fence (these events only measure
+// time; results reach the host by a copy and a stream synchronisation), and some 3.5 us for each further record at the same place,
+// so a moment that several intervals share is recorded once.  A call with a report on the 0.6B shape, six short candidates:
+// 2670 -> 2333 us, forty candidates 7219 -> 6909.
+static int mark(prism_ctx *c, hipEvent_t *e) {
+  if (c->last_mark) { *e = c->last_mark; return PRISM_OK; }
   if (c->ev_used == c->ev_pool.size()) {
     hipEvent_t n = nullptr;
-    PRISM_HIP(hipEventCreate(&n));
+    PRISM_HIP(hipEventCreateWithFlags(&n, hipEventDisableSystemFence));
     c->ev_pool.push_back(n);
   }
   *e = c->ev_pool[c->ev_used++];
   PRISM_HIP(hipEventRecord(*e, c->stream));
+  c->last_mark = *e;
   return PRISM_OK;
 }
+
+// To be called by whatever queues work on the compute stream outside timed_span: the next moment is a later one.
+static void queued(prism_ctx *c) { c->last_mark = nullptr; }
 
 // Times the launches issued by `body` as one span of the given kind (only when a report was asked for).
 template <typename Fn>
 static int timed_span(prism_ctx *c, int kind, double flops, Fn body, int rows = 0) {
-  if (!c->profiling || !((c->span_mask >> kind) & 1)) return body();
+  if (!c->profiling || !((c->span_mask >> kind) & 1)) { queued(c); return body(); }
   prism_ctx::Span sp{kind, nullptr, nullptr, flops, rows};
-  PRISM_TRY(span_event(c, &sp.a));
+  PRISM_TRY(mark(c, &sp.a));
+  queued(c);
   PRISM_TRY(body());
-  PRISM_TRY(span_event(c, &sp.b));
+  PRISM_TRY(mark(c, &sp.b));
   c->spans.push_back(sp);
   return PRISM_OK;
 }
@@ -833,6 +838,7 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
       // with one chunk per layer the next visit needs THIS visit's write-back, so it is requested afterwards
       if (nch >= 2 && next_ci >= 0) { PRISM_TRY(prefetch_chunk(c, p, next_ci, c->ostep + 1, false)); c->primed = true; }
       PRISM_HIP(hipStreamWaitEvent(s, c->ev_in[slot], 0));
+      queued(c);
       Xc = c->Xo[slot];
     }
     const int32_t *pos = c->d_meta + mo.pos + ch.r0;
@@ -893,6 +899,7 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
         PRISM_TRY(gemm(PRISM_EPI_SWIGLU, Xnl, wbuf + L.wgu, Sl, nc, 2 * F, H));
         return gemm(PRISM_EPI_RESIDUAL, Sl, wbuf + L.wd, Xl, nc, H, F);
       }));
+      queued(c);
       PRISM_TRY(launch_score(Xl, nullptr, nc, m.hidden, c->final_norm, c->w_yes, c->w_no, m.dtype, m.rms_eps,
                              c->d_scores + ch.c0, s));
     } else {
@@ -914,6 +921,7 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
     PRISM_TRY(timed_span(c, 3, tk * H * F, [&] { return gemm(PRISM_EPI_RESIDUAL, c->S, wbuf + L.wd, Xc, Tc, H, F); }, Tc));
     }
     if (c->offload) {
+      queued(c);
       if (score_after && !last_only)   // last_row holds rows of the packed pool; this chunk's rows start at ch.r0
         PRISM_TRY(launch_score(Xc - ch.r0 * H, c->d_meta + mo.lastrow + ch.c0, ch.c1 - ch.c0, m.hidden, c->final_norm, c->w_yes,
                                c->w_no, m.dtype, m.rms_eps, c->d_scores + ch.c0, s));
@@ -1023,12 +1031,13 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     for (size_t i = old; i < c->ev_xfer.size(); ++i) PRISM_HIP(hipEventCreate(&c->ev_xfer[i]));
   }
   int n_xfer_timed = 0;
-  if (timed && (int)c->ev_layer.size() < 4 * m.n_layers) {
-    const size_t old = c->ev_layer.size();
-    c->ev_layer.resize(4 * m.n_layers, nullptr);
-    for (size_t i = old; i < c->ev_layer.size(); ++i) PRISM_HIP(hipEventCreate(&c->ev_layer[i]));
-  }
-  if (timed) PRISM_HIP(hipEventRecord(c->ev_t[0], s));
+  // moments of the report: the call's first and last launch, the checks, and the layers (two intervals: a layer may run in two passes)
+  typedef std::array<hipEvent_t, 2> Interval;
+  Interval t_call{};
+  std::vector<Interval> t_check, t_layer;
+  queued(c);
+  if (timed) PRISM_TRY(mark(c, &t_call[0]));
+  queued(c);
   PRISM_TRY(upload_meta(c, p, mo, true));
   int cur = 0;
   c->embed_hit = c->embed_miss = 0;
@@ -1082,15 +1091,15 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   std::vector<int> final_idx;
   std::vector<float> final_scores;
   size_t next_ckpt = 0;
-  int n_checks = 0;
   const double *h_stats = (const double *)c->h_res;
   const float *h_scores = (const float *)(c->h_res + res_scores), *h_top_scores = (const float *)(c->h_res + res_top + 4 * n_res);
   const int8_t *h_fate = (const int8_t *)(c->h_res + res_fate);
   const int32_t *h_top_pos = (const int32_t *)(c->h_res + res_top);
-  // bytes [from, to) of the result block, on the host when this returns; `copied` is recorded behind the copy
-  auto fetch = [&](size_t from, size_t to, hipEvent_t copied = nullptr) -> int {
+  // bytes [from, to) of the result block, on the host when this returns; `copied` becomes the moment behind the copy
+  auto fetch = [&](size_t from, size_t to, hipEvent_t *copied = nullptr) -> int {
+    queued(c);
     PRISM_HIP(hipMemcpyAsync(c->h_res + from, c->d_res + from, to - from, hipMemcpyDeviceToHost, s));
-    if (copied) PRISM_HIP(hipEventRecord(copied, s));
+    if (copied) PRISM_TRY(mark(c, copied));
     PRISM_HIP(hipStreamSynchronize(s));
     return PRISM_OK;
   };
@@ -1113,11 +1122,10 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     rep->ev_n_after[e] = n_after; rep->ev_tokens_after[e] = (int32_t)tok_after;
   };
 
-  std::vector<char> second_pass(m.n_layers, 0);
   for (int l = 0; l < m.n_layers && !terminated; ++l) {
     const int slot = c->two_slot ? l % c->ring : l;
-    if (c->two_slot) PRISM_HIP(hipStreamWaitEvent(s, c->ev_ready[slot], 0));
-    if (timed) PRISM_HIP(hipEventRecord(c->ev_layer[4 * l], s));
+    if (c->two_slot) { PRISM_HIP(hipStreamWaitEvent(s, c->ev_ready[slot], 0)); queued(c); }
+    if (timed) { t_layer.emplace_back(); PRISM_TRY(mark(c, &t_layer.back()[0])); }
     // known before the layer runs: will its output be scored for pruning, and is it the last one
     while (next_ckpt < c->checkpoints.size() && c->checkpoints[next_ckpt] < l + 1) ++next_ckpt;
     const bool check_after = next_ckpt < c->checkpoints.size() && c->checkpoints[next_ckpt] == l + 1 && l + 1 < m.n_layers &&
@@ -1129,10 +1137,9 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     // their layer finished.  The scores are the same bits either way (the GEMM variants and the other kernels compute a
     // row identically wherever it sits).
     const bool peek = check_after && !c->offload && !c->opt.single_pass_checks;
-    second_pass[l] = false;
     PRISM_TRY(run_layer(c, p, mo, c->X[cur], c->layer_buf[slot], check_after || last_layer, !last_layer,
                         !last_layer && !check_after, last_layer || peek));
-    if (timed) PRISM_HIP(hipEventRecord(c->ev_layer[4 * l + 1], s));
+    if (timed) PRISM_TRY(mark(c, &t_layer.back()[1]));
     token_layers += p.seq_tokens;
     layers_run = l + 1;
     // this layer's kernels are queued: the layer that arrived last (the one the ring's newest slot holds) can be finished
@@ -1151,13 +1158,8 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     bool compacted = false;
 
     // ---- pruning check on the output of layer l + 1, before layer l + 2 runs (Sec. 3.4, 4.1)
-    if (timed) {
-      while ((int)c->ev_check.size() < 2 * (n_checks + 1)) {
-        c->ev_check.push_back(nullptr);
-        PRISM_HIP(hipEventCreate(&c->ev_check.back()));
-      }
-      PRISM_HIP(hipEventRecord(c->ev_check[2 * n_checks], s));
-    }
+    if (timed) { t_check.emplace_back(); PRISM_TRY(mark(c, &t_check.back()[0])); }
+    queued(c);
     if (!c->offload && !peek)   // offload mode scored every chunk while it was on the device, the first pass its last rows
       PRISM_TRY(launch_score(c->X[cur], c->d_meta + mo.lastrow, n_live, m.hidden, c->final_norm, c->w_yes, c->w_no, m.dtype,
                              m.rms_eps, c->d_scores, s));
@@ -1241,19 +1243,17 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
       p = q;
       compacted = true;
     }
-    if (timed) PRISM_HIP(hipEventRecord(c->ev_check[2 * n_checks + 1], s));   // read after the call's last synchronisation
-    ++n_checks;
+    if (timed) PRISM_TRY(mark(c, &t_check.back()[1]));   // read after the call's last synchronisation
     if (peek) {
       if (!terminated) {
         // second pass: the layer for the survivors.  If the pool is one chunk, the scratch still holds this layer's q, k
         // and V^T (in the layout before the prune) and the pass starts at the attention step, which writes its output
         // in the survivors' layout
-        if (timed) PRISM_HIP(hipEventRecord(c->ev_layer[4 * l + 2], s));
+        if (timed) { t_layer.emplace_back(); PRISM_TRY(mark(c, &t_layer.back()[0])); }
         PRISM_TRY(run_layer(c, p, mo, c->X[cur], c->layer_buf[slot], false, true, false, false,
                             p.chunks.size() == 1 && (!compacted || !p.xtiles.empty())));
         p.xtiles.clear();
-        if (timed) PRISM_HIP(hipEventRecord(c->ev_layer[4 * l + 3], s));
-        second_pass[l] = true;
+        if (timed) PRISM_TRY(mark(c, &t_layer.back()[1]));
       }
       PRISM_TRY(release_slot());
     }
@@ -1265,11 +1265,12 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     const int k_out = std::min(K_rem, n_live);
     // (the last layer has scored every candidate from its gathered last-token state)
     PRISM_TRY(launch_topk(c->d_scores, n_live, k_out, c->d_top_pos, c->d_top_scores, s));
-    PRISM_TRY(fetch(res_scores, res_end, timed ? c->ev_t[1] : nullptr));     // the call's time includes its results' copy
+    PRISM_TRY(fetch(res_scores, res_end, timed ? &t_call[1] : nullptr));     // the call's time includes its results' copy
     for (int i = 0; i < k_out; ++i) { final_idx.push_back(p.live[h_top_pos[i]]); final_scores.push_back(h_top_scores[i]); }
     record_event(m.n_layers, n_live, p.live, false, 0, 0.0, 0.0, nullptr, nullptr);
   } else {
-    if (timed) PRISM_HIP(hipEventRecord(c->ev_t[1], s));
+    queued(c);
+    if (timed) PRISM_TRY(mark(c, &t_call[1]));
     PRISM_HIP(hipStreamSynchronize(s));
   }
   if (c->two_slot) PRISM_HIP(hipStreamSynchronize(c->copy_stream));
@@ -1285,30 +1286,21 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   if (rep) {
     rep->n_events = std::min(n_events, rep->cap_events);
     float ms = 0.f;
-    PRISM_HIP(hipEventElapsedTime(&ms, c->ev_t[0], c->ev_t[1]));
+    PRISM_HIP(hipEventElapsedTime(&ms, t_call[0], t_call[1]));
     rep->ms_total = ms;
-    double ml = 0.0;
-    for (int l = 0; l < layers_run; ++l) {
-      PRISM_HIP(hipEventElapsedTime(&ms, c->ev_layer[4 * l], c->ev_layer[4 * l + 1]));
-      ml += ms;
-      if (second_pass[l]) {
-        PRISM_HIP(hipEventElapsedTime(&ms, c->ev_layer[4 * l + 2], c->ev_layer[4 * l + 3]));
-        ml += ms;
-      }
-    }
-    rep->ms_layers = ml;
+    auto total = [&](const std::vector<Interval> &v, double *sum) -> int {
+      *sum = 0.0;
+      for (const Interval &t : v) { PRISM_HIP(hipEventElapsedTime(&ms, t[0], t[1])); *sum += ms; }
+      return PRISM_OK;
+    };
+    PRISM_TRY(total(t_layer, &rep->ms_layers));
+    PRISM_TRY(total(t_check, &rep->ms_checks));
     double mx = 0.0;
     for (int l = 0; l < n_xfer_timed; ++l) {
       PRISM_HIP(hipEventElapsedTime(&ms, c->ev_xfer[2 * l], c->ev_xfer[2 * l + 1]));
       mx += ms;
     }
     rep->ms_transfers = mx;
-    double mc = 0.0;
-    for (int k = 0; k < n_checks; ++k) {
-      PRISM_HIP(hipEventElapsedTime(&ms, c->ev_check[2 * k], c->ev_check[2 * k + 1]));
-      mc += ms;
-    }
-    rep->ms_checks = mc;
     rep->token_layers = token_layers;
     rep->peak_hbm_bytes = c->bytes_peak;
     rep->bytes_streamed = bytes_streamed;
