@@ -3,14 +3,13 @@
 //
 // C = A W^T, A [M,K] and W [N,K] row-major, both bf16 or both IEEE half (K-contiguous, which is what
 // the MFMA operand registers want: 8 consecutive k per lane), fp32 accumulation in
-// v_mfma_f32_16x16x32_{bf16,f16} (256 x 256 tile) or v_mfma_f32_32x32x16_{bf16,f16} (the others): same dense rate, and
-// the same bits for the same k in the same order.
+// v_mfma_f32_16x16x32_{bf16,f16}.
 //
 // Workgroup tile BM x BN x 64, WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) block of the accumulator.  The
 // large-launch shape is 256 x 256 with 2 x 2 wavefronts (one per SIMD, 128 x 128 each,
 // 256 accumulator registers in AGPRs); launches with few tiles per compute unit take one of seven smaller tiles
 // down to 32 x 32 (see the choice at the launcher).  A and W tiles are staged in LDS (a ring of S stages, 256 x 256: three
-// of A and two of W; 16-byte chunks XOR-swizzled by row so that the 16- and 32-row operand reads spread over the banks) by direct
+// of A and two of W; 16-byte chunks XOR-swizzled by row so that the 16-row operand reads spread over the banks) by direct
 // global->LDS loads, which need no staging registers.  Every K loop is generated text (gen_gemm_kloop.py), because its waits count loads
 // and fragment reads exactly; rows beyond the matrix are clamped in the load offsets, so edge tiles run the same loop.
 //
@@ -47,17 +46,18 @@ __device__ __forceinline__ float silu_mul(float g, float u) { return g * __built
 template <int BM, int BN, int S> constexpr int stage_bytes() { return ((BM == 256 ? 3 : S) * BM + S * BN) * BK * 2; }
 
 template <typename OT, int BM, int BN, int WM, int WN, int EPI, int S>
-__global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel(const OT *__restrict__ A,
+__global__ __launch_bounds__(WM *WN * 64, (stage_bytes<BM, BN, S>() > 81920 ? 1 : 2)) void gemm_16_kernel(const OT *__restrict__ A,
                                                                const OT *__restrict__ W, void *__restrict__ out_,
                                                                int M, int N, int K, int nM, int nN, QkvEpilogue qe) {
   constexpr int NW = WM * WN;
   constexpr bool kHeads = EPI == kEpiQkv;
   constexpr int WMT = BM / WM, WNT = BN / WN;      // wave tile
-  constexpr int TM = WMT / 32, TN = WNT / 32;      // 32x32 accumulator tiles per wave
+  constexpr int TM = WMT / 16, TN = WNT / 16;      // 16 x 16 accumulator tiles per wave
   // one direct-to-LDS instruction of a wave moves 64 x 16 B = 8 tile rows
   constexpr int A_ITERS = BM / 8 / NW, B_ITERS = BN / 8 / NW;
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/waves mismatch");
   static_assert(EPI != PRISM_EPI_SWIGLU || TN % 2 == 0, "SwiGLU pairs gate and up tiles");
+  static_assert(TM * TN * 4 <= 256, "accumulator registers");
   extern __shared__ __align__(16) unsigned char smem[];
   static_assert(BM != 256 || S == 2, "the 256 x 256 loop has three stages of A and two of W");
   OT *lA = reinterpret_cast<OT *>(smem);                     // [S, or 3 if BM == 256][BM][BK]
@@ -92,47 +92,35 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   //      fills tile rows (w * ITERS + j) * 8 .. + 8, lane l landing at row l / 8, chunk slot l % 8.
   //      The XOR swizzle is applied on the source side: slot p of row r receives chunk swz(r, p).
   const int lrow = lane >> 3;
-  // byte offsets from A / W (both operands are below 4 GiB: checked by the launcher)
+  // byte offsets from the tile's first row of A / W, rows beyond the matrix clamped; four loads share one destination register and
+  // carry 0, 1, 2, 3 KiB in the instruction, which shifts the source too: taken off here, with 4 KiB in hand (kBias)
+  constexpr uint32_t kBias = 4096;
   uint32_t gA[A_ITERS], gB[B_ITERS];
 #pragma unroll
   for (int j = 0; j < A_ITERS; ++j) {
     const int row = (wave * A_ITERS + j) * 8 + lrow;
-    int gr = m0 + row;
-    gr = gr < M ? gr : M - 1;
-    gA[j] = ((uint32_t)gr * (uint32_t)K + swz(row, lane & 7) * 8) * 2u;
+    const int r = m0 + row < M ? row : M - 1 - m0;
+    gA[j] = ((uint32_t)r * (uint32_t)K + swz(row, lane & 7) * 8) * 2u + kBias - j % 4 * 1024u;
   }
 #pragma unroll
   for (int j = 0; j < B_ITERS; ++j) {
     const int row = (wave * B_ITERS + j) * 8 + lrow;
-    int gr;
-    if (EPI == PRISM_EPI_SWIGLU) {
-      const int half = row / (BN / 2), rr = row % (BN / 2);
-      gr = n0 + rr; gr = gr < F ? gr : F - 1;
-      gr += half * F;
-    } else {
-      gr = n0 + row; gr = gr < N ? gr : N - 1;
-    }
-    gB[j] = ((uint32_t)gr * (uint32_t)K + swz(row, lane & 7) * 8) * 2u;
+    const int half = EPI == PRISM_EPI_SWIGLU ? row / (BN / 2) : 0, rr = row - half * (BN / 2);   // gate rows, then up rows
+    const int r = (n0 + rr < F ? rr : F - 1 - n0) + half * F;
+    gB[j] = ((uint32_t)r * (uint32_t)K + swz(row, lane & 7) * 8) * 2u + kBias - j % 4 * 1024u;
   }
-  // ---- LDS rows this lane reads as MFMA operands: row (A) and first column (B) of its first fragment ----
-  constexpr bool k16 = BM == 256;                            // 16x16x32 MFMAs: a lane feeds 8 of the 32 k of one of 16 rows,
-  const int frow = lane & (k16 ? 15 : 31), kpart = lane >> (k16 ? 4 : 5);   // else 8 of the 16 k of one of 32 rows
+  // ---- LDS rows this lane reads as MFMA operands: row (A) and first column (B) of its first fragment; it feeds 8 of the
+  //      32 k of one of 16 rows to an MFMA
+  const int frow = lane & 15, kpart = lane >> 4;
   const int rA0 = wm * WMT + frow, rB0 = wn * (EPI == PRISM_EPI_SWIGLU ? WNT / 2 : WNT) + frow;
 
-  f32x16 acc[TM][TN];                                        // k16: cleared by the K loop
-  if constexpr (!k16) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  }
+  // accumulator tile (i, j) is a[4 t .. 4 t + 3], t = i TN + j: four tiles to an operand of the K loop, which clears them
+  f32x16 acc[(TM * TN + 3) / 4];
 
   const int nk = K / BK;
 
   // ---- epilogue geometry (see the epilogue): everything it reads or writes goes along the rows, 16 bytes per lane.
-  //      Residual epilogue: the old values of a 32-row block are requested one block ahead, the first block's
+  //      Residual epilogue: the old values of a block of 32 rows (16 in the smallest tiles) are requested one block ahead, the first block's
   //      before the K loop where registers are left (tiles below 256; the big tile spills).  The same for what the q/k/v
   //      epilogue reads by row: a small tile's loop is a few microseconds, and each dependent load behind it about one.
   //      (28 layers of the 0.6B shape on 391 rows, with the same in the RMSNorm: 2749 -> 2687 us.)
@@ -141,8 +129,12 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   constexpr int ES = kF32Out ? 4 : 2;                               // bytes per output element
   constexpr int OUTW = EPI == PRISM_EPI_SWIGLU ? WNT / 2 : WNT;    // output columns of the wave
   constexpr int RB = OUTW * ES, CPR = RB / 16;                      // bytes / 16-byte chunks per staged row
-  constexpr int NR = 1024 / RB, NI = 32 / NR;                       // rows per instruction, instructions per 32-row block
-  const int f_row = lane / CPR, f_chunk = lane % CPR;               // lane -> (row within an instruction, chunk)
+  constexpr int BR = WMT < 32 ? WMT : 32, RPB = BR / 16;            // rows of a block, of those in a lane
+  constexpr int NBLK = WMT / BR;                                    // blocks of the wave
+  constexpr int NR = 1024 / RB < BR ? 1024 / RB : BR, NI = BR / NR; // rows per instruction, instructions per block
+  // lane -> (row within an instruction, chunk); 16 rows of 16 16-bit columns are less than an instruction moves: half the lanes idle
+  const int f_row = lane / CPR % NR, f_chunk = lane % CPR;
+  const bool f_on = lane / CPR < NR;
   const bool full_n = n0 + BNO <= F && (F * ES) % 16 == 0;
   f32x4 old[2][EPI == PRISM_EPI_RESIDUAL ? NI : 1];
   // An access goes to a wave-uniform address (scalar) plus a lane offset that stays the same: multiplying rows by the pitch per
@@ -158,7 +150,7 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     if constexpr (EPI == PRISM_EPI_RESIDUAL) {
 #pragma unroll
       for (int rr = 0; rr < NI; ++rr) {
-        const int r = i * 32 + rr * NR;
+        const int r = i * BR + rr * NR;
         if (whole || r + f_row < rows_left) old[i & 1][rr] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(old_at + f_off));
         old_at += out_step;
       }
@@ -166,14 +158,13 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   };
 
 
-  constexpr int RPB = k16 ? 2 : 1;                                  // rows of a 32-row block that a lane holds
-  int row_in[kHeads ? TM * RPB : 1];                                // q, k heads: positions; v heads: V^T columns
+  int row_in[kHeads ? TM : 1];                                // q, k heads: positions; v heads: V^T columns
   auto load_rows = [&]() __attribute__((always_inline)) {
     if constexpr (kHeads) {
       const int32_t *src = ((n0 + wn * WNT) >> 7) < qe.nq + qe.nkv ? qe.pos : qe.vt_col;
 #pragma unroll
-      for (int i = 0; i < TM * RPB; ++i) {
-        const int row = m0 + wm * WMT + i * (32 / RPB) + frow;
+      for (int i = 0; i < TM; ++i) {
+        const int row = m0 + wm * WMT + i * 16 + frow;
         row_in[i] = src[row < M ? row : M - 1];
       }
     }
@@ -183,18 +174,16 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
     else if (full_n) load_old(0, std::false_type{});
   }
 
-  // ---- epilogue.  The W fragment was the instruction's first operand, so the 32 x 32 accumulator block (i, j) is
-  //      transposed: a lane holds four runs g = 0..3 of 4 consecutive columns, elements e = 4 g + q, of ONE row of A
-  //      (32x32x16: row lane % 32, columns 8 g + 4 (lane / 32) + q) or of two (16x16x32: tile (g / 2, g % 2) of the block, row
-  //      16 (g / 2) + lane % 16, columns 16 (g % 2) + 4 (lane / 16) + q); m_of and n_of below.
+  // ---- epilogue.  The W fragment was the instruction's first operand, so the 16 x 16 accumulator tile (i, j) is transposed:
+  //      a lane holds ONE row of A, 16 i + lane % 16, and 4 consecutive output columns 16 j + 4 (lane / 16) + q, q = 0..3.
   //      Written straight from that layout, one store instruction touches 32 rows with 16-32 bytes in each, and
   //      the number of cache lines an instruction touches - not the bytes - is what the memory path charges for
-  //      (measured: 12-29 us per 256 x 256 tile, a tenth to a fifth of the tile's time).  So every block of 32 rows goes
+  //      (measured: 12-29 us per 256 x 256 tile, a tenth to a fifth of the tile's time).  So every block of rows goes
   //      through LDS, which is free once the K loop is done: lanes write their row's values, then read back 16 bytes
   //      each along the rows, so that an instruction reads or writes whole lines (2-8 complete rows of the wave's
   //      columns).  LDS requests of one wave are served in order, so no barrier is needed between the two phases.
   auto epilogue = [&]() __attribute__((always_inline)) {
-  // Accumulator element (i, j, e), fetched from its accumulation register when it is needed: behind the hand-scheduled
+  // Accumulator element (i, j, q), fetched from its accumulation register when it is needed: behind the hand-scheduled
   // loop all 256 of them sit in AGPRs, and read as plain values the compiler would copy the whole set into vector
   // registers at once, leaving none for the epilogue's own arithmetic.
   // (The compiler does not look inside these statements, so the wait between a matrix instruction and the first read
@@ -202,21 +191,24 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   // instructions before it, then 32 idle cycles - more than the deepest instruction needs to retire.  All of these are
   // volatile, which keeps them in this order.)
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+  for (int t = 0; t < (TM * TN + 3) / 4; ++t) asm volatile("" : "+a"(acc[t]));
   asm volatile("s_nop 15\n\ts_nop 15");
-  auto AC = [&](int i, int j, int e) __attribute__((always_inline)) {
+  auto AC = [&](int i, int j, int q) __attribute__((always_inline)) {
     float r;
-    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(r) : "a"(acc[i][j][e]));
+    const int t = i * TN + j;
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(r) : "a"(acc[t / 4][t % 4 * 4 + q]));
     return r;
   };
   __syncthreads();              // every wave's operand loads have landed and nobody reads operands any more
-  auto m_of = [&](int g) __attribute__((always_inline)) { return k16 ? (g >> 1) * 16 + frow : frow; };
-  auto n_of = [&](int g) __attribute__((always_inline)) { return k16 ? (g & 1) * 16 + kpart * 4 : g * 8 + kpart * 4; };
   constexpr int SWZ = CPR >= 16 ? 15 : CPR - 1;                     // chunk rotation by row: spreads a column of 16-byte
                                                                     // writes (one per row) over the banks
-  static_assert(32 * RB <= stage_bytes<BM, BN, S>() / NW, "staging block must fit the wave's share of LDS");
+  // the lane's place again, from the thread index: kept over the loop, one of these ends in scratch memory, and its reload waits for
+  // every old value requested before it
+  unsigned again = threadIdx.x;
+  asm volatile("" : "+v"(again));
+  const int e_row = again & 15, e_col = (again & 63) >> 4 << 2;     // row and column in an accumulator tile
+  static_assert(NR * RB == 1024 || !kF32Out, "the residual's accesses have no idle lanes");
+  static_assert(BR * RB <= stage_bytes<BM, BN, S>() / NW, "staging block must fit the wave's share of LDS");
   unsigned char *stg = smem + wave * (stage_bytes<BM, BN, S>() / NW);
   // values for columns n .. n + 3 (n a multiple of 4, within the wave's columns) of staged row m
   auto put32 = [&](int m, int n, const f32x4 &v) __attribute__((always_inline)) {
@@ -232,125 +224,114 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   // Flushes the staged block i of the wave's rows to a row-major destination (wave-uniform address of the wave's first row and
   // column, row pitch, the lane's offset).
   auto flush_store = [&](unsigned char *dst, int64_t pitch, unsigned off, int i) __attribute__((always_inline)) {
-    dst += (int64_t)i * 32 * pitch;
+    dst += (int64_t)i * BR * pitch;
 #pragma unroll
     for (int rr = 0; rr < NI; ++rr) {
       const uint4 v = staged(rr);
-      if (i * 32 + rr * NR + f_row < rows_left) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t *>(dst + off));
+      if (f_on && i * BR + rr * NR + f_row < rows_left) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t *>(dst + off));
       dst += NR * pitch;
     }
   };
 
   if constexpr (kHeads) {
-    // The wave's 128 columns are one head.  A row's 128 values sit in 2 (16x16x32: 4) lanes with the same lane % 32 (% 16);
-    // the rotate-half partner of column d is d + 64 = the same register of accumulator block j + 2, so the per-head RMSNorm
-    // (cross-lane adds), the rotation and the single rounding all happen on the accumulators.  What the memory path
-    // charges for is cache lines touched per instruction, so the cos/sin pairs come from the TRANSPOSED table (the 16 or 32
-    // tokens of a load are consecutive positions of a sequence almost always: two to four lines per load instead of
+    // The wave's 128 columns are one head.  A row's 128 values sit in the 4 lanes with the same lane % 16; the rotate-half
+    // partner of column d is d + 64 = the same register of accumulator tile j + 4, so the per-head RMSNorm
+    // (two cross-lane adds), the rotation and the single rounding all happen on the accumulators.  What the memory path
+    // charges for is cache lines touched per instruction, so the cos/sin pairs come from the TRANSPOSED table (the 16
+    // tokens of a load are consecutive positions of a sequence almost always: four lines per load instead of
     // one or two per lane) and the finished q / k rows go through the staging block like the other epilogues' outputs.
-    static_assert(WNT == 128 && TN == 4, "one head per wavefront");
+    static_assert(WNT == 128, "one head per wavefront");
     typedef typename Mfma<OT>::vec4 vec4;
     const int head = (n0 + wn * WNT) >> 7;                 // wave-uniform
-    if constexpr (!kEarly) load_rows();                    // all row blocks' at once: one memory latency, not one per block
+    if constexpr (!kEarly) load_rows();                    // all rows' at once: one memory latency, not one per block
     if (head < qe.nq + qe.nkv) {
       const OT *gain = reinterpret_cast<const OT *>(head < qe.nq ? qe.q_gain : qe.k_gain);
-      constexpr int NG = k16 ? 2 : 4;                      // distinct column groups of a lane in 32 columns
-      vec4 ga[2][NG], gb[2][NG];
+      vec4 ga[4], gb[4];
       if (qe.qk_norm) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            ga[j][g] = *reinterpret_cast<const vec4 *>(gain + j * 32 + n_of(g));
-            gb[j][g] = *reinterpret_cast<const vec4 *>(gain + j * 32 + n_of(g) + 64);
-          }
+        for (int j = 0; j < 4; ++j) {
+          ga[j] = *reinterpret_cast<const vec4 *>(gain + j * 16 + e_col);
+          gb[j] = *reinterpret_cast<const vec4 *>(gain + j * 16 + e_col + 64);
+        }
       }
       const int64_t pitch = (int64_t)(qe.nq + qe.nkv) * 128 * 2;
       unsigned char *const qk_w = reinterpret_cast<unsigned char *>(qe.QK) + (int64_t)(m0 + wm * WMT) * pitch + (int64_t)head * 128 * 2;
       const unsigned qk_off = (unsigned)f_row * (unsigned)pitch + (unsigned)f_chunk * 16u;
       // (cos, sin) of (pos, d) sits at [d * stride + pos]: a wave-uniform base per column plus one 32-bit lane offset (in bytes, or
       // the compiler cannot rule out a carry and adds 64-bit addresses per lane).
-      // The 32 pairs of block i + 1 are requested before block i is worked on, so the tile pays the memory latency once,
+      // The pairs of block i + 1 are requested before block i is worked on, so the tile pays the memory latency once,
       // not once per block.
-      unsigned lane_off[TM * RPB];
+      unsigned lane_off[TM];
 #pragma unroll
-      for (int i = 0; i < TM * RPB; ++i) lane_off[i] = ((unsigned)(kpart * 4) * (unsigned)qe.rope_stride + (unsigned)row_in[i]) * 8u;
-      float2 cs[2][2][4][4];
-      auto load_cs = [&](int i) __attribute__((always_inline)) {
+      for (int i = 0; i < TM; ++i) lane_off[i] = ((unsigned)(e_col) * (unsigned)qe.rope_stride + (unsigned)row_in[i]) * 8u;
+      float2 cs[2][RPB][4][4];
+      auto load_cs = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int h = 0; h < RPB; ++h)
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
+          for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const int d = j * 32 + (k16 ? (g & 1) * 16 : g * 8) + q;         // without the lane's part
-              const char *col = reinterpret_cast<const char *>(qe.rope_tab_t + (int64_t)d * qe.rope_stride);
-              cs[i & 1][j][g][q] = *reinterpret_cast<const float2 *>(col + lane_off[k16 ? i * 2 + (g >> 1) : i]);
+              const char *col = reinterpret_cast<const char *>(qe.rope_tab_t + (int64_t)(j * 16 + q) * qe.rope_stride);
+              cs[b & 1][h][j][q] = *reinterpret_cast<const float2 *>(col + lane_off[b * RPB + h]);
             }
       };
       load_cs(0);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        if (i + 1 < TM) load_cs(i + 1);
+      for (int b = 0; b < NBLK; ++b) {
+        if (b + 1 < NBLK) load_cs(b + 1);
         float r[RPB];
 #pragma unroll
-        for (int h = 0; h < RPB; ++h) r[h] = 1.f;
-        if (qe.qk_norm) {
-          // the finishing kernel's order of the sum of squares: column pairs (d, d + 64), then halving over the bits of d, 32 first
-#pragma unroll
-          for (int h = 0; h < RPB; ++h) {
+        for (int h = 0; h < RPB; ++h) {
+          r[h] = 1.f;
+          if (qe.qk_norm) {
+            // the finishing kernel's order of the sum of squares: column pairs (d, d + 64), then halving over the bits of d, 32 first
+            const int i = b * RPB + h;
             float p[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              auto pair = [&](int j, int g) __attribute__((always_inline)) {
-                const float a = AC(i, j, g * 4 + q), b = AC(i, j + 2, g * 4 + q);
-                return __builtin_fmaf(a, a, b * b);
+              auto pair = [&](int j) __attribute__((always_inline)) {
+                const float x = AC(i, j, q), y = AC(i, j + 4, q);
+                return __builtin_fmaf(x, x, y * y);
               };
-              auto both = [&](int g) __attribute__((always_inline)) { return pair(0, g) + pair(1, g); };
-              if constexpr (k16) p[q] = sum_xor16(sum_xor32(both(h * 2) + both(h * 2 + 1)));
-              else p[q] = sum_xor32((both(0) + both(2)) + (both(1) + both(3)));
+              p[q] = sum_xor16(sum_xor32((pair(0) + pair(2)) + (pair(1) + pair(3))));
             }
             r[h] = 1.0f / sqrtf(((p[0] + p[2]) + (p[1] + p[3])) / 128.f + qe.eps);
           }
         }
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int h = 0; h < RPB; ++h)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
+          for (int j = 0; j < 4; ++j) {
             vec4 lo, hi;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const float2 c = cs[i & 1][j][g][q];
-              float a = AC(i, j, g * 4 + q), b = AC(i, j + 2, g * 4 + q);
+              const float2 c = cs[b & 1][h][j][q];
+              float x = AC(b * RPB + h, j, q), y = AC(b * RPB + h, j + 4, q);
               if (qe.qk_norm) {
-                a = a * r[k16 ? g >> 1 : 0] * to_f32(ga[j][g % NG][q]);
-                b = b * r[k16 ? g >> 1 : 0] * to_f32(gb[j][g % NG][q]);
+                x = x * r[h] * to_f32(ga[j][q]);
+                y = y * r[h] * to_f32(gb[j][q]);
               }
-              lo[q] = from_f32<OT>(__builtin_fmaf(a, c.x, -(b * c.y)));
-              hi[q] = from_f32<OT>(__builtin_fmaf(b, c.x, a * c.y));
+              lo[q] = from_f32<OT>(__builtin_fmaf(x, c.x, -(y * c.y)));
+              hi[q] = from_f32<OT>(__builtin_fmaf(y, c.x, x * c.y));
             }
-            put16(m_of(g), j * 32 + n_of(g), lo);
-            put16(m_of(g), j * 32 + n_of(g) + 64, hi);
+            put16(h * 16 + e_row, j * 16 + e_col, lo);
+            put16(h * 16 + e_row, j * 16 + e_col + 64, hi);
           }
-        }
-        flush_store(qk_w, pitch, qk_off, i);
+        flush_store(qk_w, pitch, qk_off, b);
       }
     } else {
-      // v head: rounded to the operand type, stored as half, transposed (16 or 32 consecutive tokens of one d are contiguous)
+      // v head: rounded to the operand type, stored as half, transposed (16 consecutive tokens of one d are contiguous)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) {
+        if (m0 + wm * WMT + i * 16 + e_row >= M) continue;
+        f16 *vt = reinterpret_cast<f16 *>(qe.Vt) + ((int64_t)(head - qe.nq - qe.nkv) * 128 + e_col) * qe.vt_stride + row_in[i];
 #pragma unroll
-        for (int h = 0; h < RPB; ++h) {
-          if (m0 + wm * WMT + i * 32 + h * 16 + frow >= M) continue;
-          f16 *vt = reinterpret_cast<f16 *>(qe.Vt) + ((int64_t)(head - qe.nq - qe.nkv) * 128 + kpart * 4) * qe.vt_stride + row_in[i * RPB + h];
+        for (int j = 0; j < 8; ++j)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int g = h * 2; g < h * 2 + 4 / RPB; ++g)
-#pragma unroll
-              for (int q = 0; q < 4; ++q)
-                vt[(int64_t)(j * 32 + (k16 ? (g & 1) * 16 : g * 8) + q) * qe.vt_stride] = from_f32<f16>(to_f32(from_f32<OT>(AC(i, j, g * 4 + q))));
-        }
+          for (int q = 0; q < 4; ++q)
+            vt[(int64_t)(j * 16 + q) * qe.vt_stride] = from_f32<f16>(to_f32(from_f32<OT>(AC(i, j, q))));
+      }
     }
     return;
   }
@@ -363,22 +344,22 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
       int64_t new_at = 0;
       asm volatile("" : "+s"(new_at));       // a chain of its own: 64 addresses shared with the loads would not fit the scalar registers
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        if (i + 1 < TM) load_old(i + 1, whole);
+      for (int b = 0; b < NBLK; ++b) {
+        if (b + 1 < NBLK) load_old(b + 1, whole);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int h = 0; h < RPB; ++h)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
+          for (int j = 0; j < TN; ++j) {
             f32x4 v;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = AC(i, j, g * 4 + q);
-            put32(m_of(g), j * 32 + n_of(g), v);
+            for (int q = 0; q < 4; ++q) v[q] = AC(b * RPB + h, j, q);
+            put32(h * 16 + e_row, j * 16 + e_col, v);
           }
 #pragma unroll
         for (int rr = 0; rr < NI; ++rr) {
-          const int r = i * 32 + rr * NR;
+          const int r = b * BR + rr * NR;
           const uint4 u = staged(rr);
-          f32x4 v = old[i & 1][rr];
+          f32x4 v = old[b & 1][rr];
           v[0] += __uint_as_float(u.x); v[1] += __uint_as_float(u.y); v[2] += __uint_as_float(u.z); v[3] += __uint_as_float(u.w);
           if (whole || r + f_row < rows_left) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(out_w + new_at + f_off));
           new_at += out_step;
@@ -391,36 +372,25 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   }
   if (full_n) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      if (EPI == PRISM_EPI_SWIGLU) {
+    for (int b = 0; b < NBLK; ++b) {
 #pragma unroll
-        for (int j = 0; j < TN / 2; ++j)
+      for (int h = 0; h < RPB; ++h)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
+        for (int j = 0; j < OUTW / 16; ++j) {
+          const int i = b * RPB + h, row = h * 16 + e_row, col = j * 16 + e_col;
+          if constexpr (EPI == PRISM_EPI_STORE_F32) {
+            f32x4 v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = AC(i, j, q);
+            put32(row, col, v);
+          } else {
             typename Mfma<OT>::vec4 v;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = from_f32<OT>(silu_mul(AC(i, j, g * 4 + q), AC(i, j + TN / 2, g * 4 + q)));
-            put16(m_of(g), j * 32 + n_of(g), v);
+            for (int q = 0; q < 4; ++q) v[q] = from_f32<OT>(EPI == PRISM_EPI_SWIGLU ? silu_mul(AC(i, j, q), AC(i, j + TN / 2, q)) : AC(i, j, q));
+            put16(row, col, v);
           }
-      } else {
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            if (EPI == PRISM_EPI_STORE_F32) {
-              f32x4 v;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) v[q] = AC(i, j, g * 4 + q);
-              put32(m_of(g), j * 32 + n_of(g), v);
-            } else {
-              typename Mfma<OT>::vec4 v;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) v[q] = from_f32<OT>(AC(i, j, g * 4 + q));
-              put16(m_of(g), j * 32 + n_of(g), v);
-            }
-          }
-      }
-      flush_store(out_w, out_pitch, f_off, i);
+        }
+      flush_store(out_w, out_pitch, f_off, b);
     }
     return;
   }
@@ -428,24 +398,22 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   // ---- ragged last column tile (N not a multiple of the tile, or rows not 16-byte aligned): element by element
   if constexpr (!kHeads) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < (EPI == PRISM_EPI_SWIGLU ? TN / 2 : TN); ++j)
-        for (int g = 0; g < 4; ++g)
-          for (int q = 0; q < 4; ++q) {
-            const int row = m0 + wm * WMT + i * 32 + m_of(g), col = n0 + wn * OUTW + j * 32 + n_of(g) + q;
-            if (row >= M || col >= F) continue;
-            if (EPI == PRISM_EPI_SWIGLU) {
-              reinterpret_cast<OT *>(out_)[(int64_t)row * F + col] = from_f32<OT>(silu_mul(AC(i, j, g * 4 + q), AC(i, j + TN / 2, g * 4 + q)));
-            } else if (EPI == PRISM_EPI_RESIDUAL) {
-              reinterpret_cast<float *>(out_)[(int64_t)row * N + col] += AC(i, j, g * 4 + q);
-            } else if (EPI == PRISM_EPI_STORE_F32) {
-              reinterpret_cast<float *>(out_)[(int64_t)row * N + col] = AC(i, j, g * 4 + q);
-            } else {
-              reinterpret_cast<OT *>(out_)[(int64_t)row * N + col] = from_f32<OT>(AC(i, j, g * 4 + q));
-            }
+      for (int j = 0; j < OUTW / 16; ++j)
+        for (int q = 0; q < 4; ++q) {
+          const int row = m0 + wm * WMT + i * 16 + e_row, col = n0 + wn * OUTW + j * 16 + e_col + q;
+          if (row >= M || col >= F) continue;
+          if (EPI == PRISM_EPI_SWIGLU) {
+            reinterpret_cast<OT *>(out_)[(int64_t)row * F + col] = from_f32<OT>(silu_mul(AC(i, j, q), AC(i, j + TN / 2, q)));
+          } else if (EPI == PRISM_EPI_RESIDUAL) {
+            reinterpret_cast<float *>(out_)[(int64_t)row * N + col] += AC(i, j, q);
+          } else if (EPI == PRISM_EPI_STORE_F32) {
+            reinterpret_cast<float *>(out_)[(int64_t)row * N + col] = AC(i, j, q);
+          } else {
+            reinterpret_cast<OT *>(out_)[(int64_t)row * N + col] = from_f32<OT>(AC(i, j, q));
           }
-    }
+        }
   }
   };
 
@@ -455,56 +423,43 @@ __global__ __launch_bounds__(WM *WN * 64, BM == 256 ? 1 : 2) void gemm_16_kernel
   // wave w's load instruction j fills tile rows (w * ITERS + j) * 8 .. + 8 of an operand (1 KiB of LDS)
   const unsigned ldsA_w = __builtin_amdgcn_readfirstlane(ldsA + (unsigned)wave * A_ITERS * 8 * BK * 2);
   const unsigned ldsB_w = __builtin_amdgcn_readfirstlane(ldsB + (unsigned)wave * B_ITERS * 8 * BK * 2);
-  const uint64_t baseA = (uint64_t)(uintptr_t)A, baseB = (uint64_t)(uintptr_t)W;
-  constexpr bool kF16 = Mfma<OT>::kIsF16;
-  if constexpr (BM < 256) {
-#define PRISM_ACC1 "+a"(acc[0][0])
-#define PRISM_ACC2 PRISM_ACC1, "+a"(acc[0][1])
-#define PRISM_ACC4 PRISM_ACC2, "+a"(acc[1][0]), "+a"(acc[1][1])
-#define PRISM_ACC1x4 PRISM_ACC2, "+a"(acc[0][2]), "+a"(acc[0][3])
-#define PRISM_G2(g) "v"(g[0]), "v"(g[1])
-#define PRISM_G4(g) PRISM_G2(g), "v"(g[2]), "v"(g[3])
-#define PRISM_G8(g) PRISM_G4(g), "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7])
-#define PRISM_RUN_SMALL(NAME, ACC, GA, GB)                                                                              \
-  do {                                                                                                                  \
-    if constexpr (kF16)                                                                                                 \
-      asm volatile(PRISM_KLOOP_F16_##NAME : ACC : "v"(aA0), "v"(aB0), GA(gA), GB(gB), "s"(ldsA_w), "s"(ldsB_w),         \
-                   "s"(baseA), "s"(baseB), "s"(nk) : PRISM_KLOOP_CLOBBERS_##NAME);                                      \
-    else                                                                                                                \
-      asm volatile(PRISM_KLOOP_BF16_##NAME : ACC : "v"(aA0), "v"(aB0), GA(gA), GB(gB), "s"(ldsA_w), "s"(ldsB_w),        \
-                   "s"(baseA), "s"(baseB), "s"(nk) : PRISM_KLOOP_CLOBBERS_##NAME);                                      \
+  const uint64_t baseA = (uint64_t)(uintptr_t)A + (uint64_t)m0 * K * 2 - kBias, baseB = (uint64_t)(uintptr_t)W + (uint64_t)n0 * K * 2 - kBias;
+  // the upper half of the wave's columns: SwiGLU's are the up rows, half a tile further (the swizzle repeats every 16 rows)
+  const unsigned aB1 = aB0 + (unsigned)((EPI == PRISM_EPI_SWIGLU ? BN / 2 : WNT / 2) * BK) * 2u;
+#define PRISM_ACC1 "={a[0:15]}"(acc[0])
+#define PRISM_ACC2 PRISM_ACC1, "={a[16:31]}"(acc[1])
+#define PRISM_ACC4 PRISM_ACC2, "={a[32:47]}"(acc[2]), "={a[48:63]}"(acc[3])
+#define PRISM_ACC16                                                                                                               \
+  PRISM_ACC4, "={a[64:79]}"(acc[4]), "={a[80:95]}"(acc[5]), "={a[96:111]}"(acc[6]), "={a[112:127]}"(acc[7]),                        \
+      "={a[128:143]}"(acc[8]), "={a[144:159]}"(acc[9]), "={a[160:175]}"(acc[10]), "={a[176:191]}"(acc[11]), "={a[192:207]}"(acc[12]), \
+      "={a[208:223]}"(acc[13]), "={a[224:239]}"(acc[14]), "={a[240:255]}"(acc[15])
+  // (offsets of loads that a tile does not have are never named by its loop)
+#define PRISM_AB(j) [ga##j] "v"(gA[j < A_ITERS ? j : 0]), [gb##j] "v"(gB[j < B_ITERS ? j : 0])
+#define PRISM_RUN_TY(LOOP, CLOBBERS, ...)                                                                                       \
+  asm volatile(LOOP : __VA_ARGS__                                                                                              \
+               : [aa] "v"(aA0), [ab] "v"(aB0), [ab2] "v"(aB1), PRISM_AB(0), PRISM_AB(1), PRISM_AB(2), PRISM_AB(3), PRISM_AB(4), \
+                 PRISM_AB(5), PRISM_AB(6), PRISM_AB(7), [la] "s"(ldsA_w), [lb] "s"(ldsB_w), [pa] "s"(baseA), [pb] "s"(baseB),   \
+                 [nk] "s"(nk)                                                                                                  \
+               : CLOBBERS)
+#define PRISM_RUN(NAME, ...)                                                                                                    \
+  do {                                                                                                                         \
+    if constexpr (Mfma<OT>::kIsF16) PRISM_RUN_TY(PRISM_KLOOP_##NAME("f16"), PRISM_KLOOP_CLOBBERS_##NAME, __VA_ARGS__);          \
+    else PRISM_RUN_TY(PRISM_KLOOP_##NAME("bf16"), PRISM_KLOOP_CLOBBERS_##NAME, __VA_ARGS__);                                    \
   } while (0)
-    if constexpr (kHeads) {
-      if constexpr (BM == 64) PRISM_RUN_SMALL(64x128_3_HEAD, PRISM_ACC1x4, PRISM_G4, PRISM_G8);
-      else if constexpr (S == 3) PRISM_RUN_SMALL(128x128_3_HEAD, PRISM_ACC1x4, PRISM_G4, PRISM_G4);
-      else PRISM_RUN_SMALL(128x128_2_HEAD, PRISM_ACC1x4, PRISM_G4, PRISM_G4);
-    } else if constexpr (BM == 32 && BN == 32) PRISM_RUN_SMALL(32x32_8, PRISM_ACC1, PRISM_G4, PRISM_G4);
-    else if constexpr (BM == 64 && BN == 32) PRISM_RUN_SMALL(64x32_6, PRISM_ACC1, PRISM_G4, PRISM_G2);
-    else if constexpr (BM == 32 && BN == 64) PRISM_RUN_SMALL(32x64_4, PRISM_ACC2, PRISM_G4, PRISM_G8);
-    else if constexpr (BM == 64 && BN == 64) PRISM_RUN_SMALL(64x64_5, PRISM_ACC2, PRISM_G4, PRISM_G4);
-    else if constexpr (BM == 128 && BN == 64) PRISM_RUN_SMALL(128x64_3, PRISM_ACC2, PRISM_G4, PRISM_G2);
-    else if constexpr (S == 3 && EPI == PRISM_EPI_SWIGLU) PRISM_RUN_SMALL(128x128_3_SWIGLU, PRISM_ACC4, PRISM_G4, PRISM_G4);
-    else if constexpr (S == 3) PRISM_RUN_SMALL(128x128_3_PLAIN, PRISM_ACC4, PRISM_G4, PRISM_G4);
-    else if constexpr (EPI == PRISM_EPI_SWIGLU) PRISM_RUN_SMALL(128x128_2_SWIGLU, PRISM_ACC4, PRISM_G4, PRISM_G4);
-    else PRISM_RUN_SMALL(128x128_2_PLAIN, PRISM_ACC4, PRISM_G4, PRISM_G4);
-  } else {
-    // the second 64 columns of the wave: SwiGLU's are the up rows, half a tile further (the swizzle repeats every 16 rows)
-    const unsigned aB1 = aB0 + (unsigned)((EPI == PRISM_EPI_SWIGLU ? BN / 2 : 64) * BK) * 2u;
-#define PRISM_AB(j) [ga##j] "v"(gA[j]), [gb##j] "v"(gB[j])
-#define PRISM_RUN_KLOOP(TY)                                                                                                    \
-  asm volatile(PRISM_KLOOP_256(TY)                                                                                             \
-               : "={a[0:15]}"(acc[0][0]), "={a[16:31]}"(acc[0][1]), "={a[32:47]}"(acc[0][2]), "={a[48:63]}"(acc[0][3]),          \
-                 "={a[64:79]}"(acc[1][0]), "={a[80:95]}"(acc[1][1]), "={a[96:111]}"(acc[1][2]), "={a[112:127]}"(acc[1][3]),      \
-                 "={a[128:143]}"(acc[2][0]), "={a[144:159]}"(acc[2][1]), "={a[160:175]}"(acc[2][2]), "={a[176:191]}"(acc[2][3]), \
-                 "={a[192:207]}"(acc[3][0]), "={a[208:223]}"(acc[3][1]), "={a[224:239]}"(acc[3][2]), "={a[240:255]}"(acc[3][3])  \
-               : [aa] "v"(aA0), [ab] "v"(aB0), [ab2] "v"(aB1), PRISM_AB(0), PRISM_AB(1), PRISM_AB(2), PRISM_AB(3), PRISM_AB(4),  \
-                 PRISM_AB(5), PRISM_AB(6), PRISM_AB(7), [la] "s"(ldsA_w), [lb] "s"(ldsB_w), [pa] "s"(baseA), [pb] "s"(baseB),     \
-                 [nk] "s"(nk)                                                                                                   \
-               : PRISM_KLOOP_256_CLOBBERS)
-    if constexpr (kF16) PRISM_RUN_KLOOP("f16");
-    else PRISM_RUN_KLOOP("bf16");
-#undef PRISM_RUN_KLOOP
-  }
+  if constexpr (BM == 256) PRISM_RUN(256, PRISM_ACC16);
+  else if constexpr (kHeads && BM == 64) PRISM_RUN(64x128_3_HEAD, PRISM_ACC2);
+  else if constexpr (kHeads && S == 3) PRISM_RUN(128x128_3_HEAD, PRISM_ACC4);
+  else if constexpr (kHeads) PRISM_RUN(128x128_2_HEAD, PRISM_ACC4);
+  else if constexpr (BM == 32 && BN == 32) PRISM_RUN(32x32_8, PRISM_ACC1);
+  else if constexpr (BM == 64 && BN == 32) PRISM_RUN(64x32_6, PRISM_ACC1);
+  else if constexpr (BM == 32 && BN == 64) PRISM_RUN(32x64_4, PRISM_ACC1);
+  else if constexpr (BM == 64 && BN == 64) PRISM_RUN(64x64_5, PRISM_ACC1);
+  else if constexpr (BM == 128 && BN == 64) PRISM_RUN(128x64_3, PRISM_ACC2);
+  else if constexpr (S == 4) PRISM_RUN(128x128_4, PRISM_ACC4);
+  else PRISM_RUN(128x128_2, PRISM_ACC4);
+#undef PRISM_RUN
+#undef PRISM_RUN_TY
+#undef PRISM_AB
   epilogue();
 }
 
@@ -600,15 +555,15 @@ static int launch_kind(int kind, const OT *A, const OT *W, void *out, int M, int
   switch (kind) {
     case kTile256: return launch_cfg<OT, 256, 256, 2, 2, EPI, 2>(A, W, out, M, N, K, s);
     case kTile128: return launch_cfg<OT, 128, 128, 2, 2, EPI, 2>(A, W, out, M, N, K, s);
-    case kTile128Deep: return launch_cfg<OT, 128, 128, 2, 2, EPI, 3>(A, W, out, M, N, K, s);
+    case kTile128Deep: return launch_cfg<OT, 128, 128, 2, 2, EPI, 4>(A, W, out, M, N, K, s);
     case kTile128x64: return launch_cfg<OT, 128, 64, 4, 1, EPI, 3>(A, W, out, M, N, K, s);
-    case kTile64: return launch_cfg<OT, 64, 64, 2, 1, EPI, 5>(A, W, out, M, N, K, s);
-    case kTile32x64: return launch_cfg<OT, 32, 64, 1, 1, EPI, 4>(A, W, out, M, N, K, s);
+    case kTile64: return launch_cfg<OT, 64, 64, 2, 2, EPI, 5>(A, W, out, M, N, K, s);
+    case kTile32x64: return launch_cfg<OT, 32, 64, 1, 2, EPI, 4>(A, W, out, M, N, K, s);
     default: break;
   }
   if constexpr (EPI != PRISM_EPI_SWIGLU) {
     if (kind == kTile64x32) return launch_cfg<OT, 64, 32, 2, 1, EPI, 6>(A, W, out, M, N, K, s);
-    return launch_cfg<OT, 32, 32, 1, 1, EPI, 8>(A, W, out, M, N, K, s);
+    return launch_cfg<OT, 32, 32, 2, 2, EPI, 8>(A, W, out, M, N, K, s);
   }
   return PRISM_EUNSUPPORTED;
 }
@@ -674,7 +629,7 @@ static int launch_head(int kind, const QkvEpilogue &e, const OT *A, const OT *W,
     case kHead256: return launch_cfg<OT, 256, 256, 2, 2, kEpiQkv, 2>(A, W, e.QK, M, N, K, s, e);
     case kHead128: return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 2>(A, W, e.QK, M, N, K, s, e);
     case kHead128Deep: return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 3>(A, W, e.QK, M, N, K, s, e);
-    default: return launch_cfg<OT, 64, 128, 2, 1, kEpiQkv, 3>(A, W, e.QK, M, N, K, s, e);
+    default: return launch_cfg<OT, 64, 128, 4, 1, kEpiQkv, 3>(A, W, e.QK, M, N, K, s, e);
   }
 }
 

@@ -31,6 +31,8 @@ free of branches.  The stage offsets are immediates, so the loop is unrolled ove
 
 The W fragment is the first MFMA operand, so accumulator tiles come out transposed (a lane owns one row of A).
 """
+import math
+
 # ---- register plan (all clobbered) ----
 AA, AA2, AB, AB2 = [116, 117], [118, 119], [120, 121], [122, 123]   # LDS address of the lane's first fragment row, per step: A stages
                                                                     # 0 and 1, A stage 2, B columns 0-63, B columns 64-127 of the wave
@@ -49,9 +51,7 @@ def v4(r):
 
 
 def acc(i, j):
-    """16 x 16 tile (i, j) of the wave: the 32 x 32 block (i / 2, j / 2) is operand acc[i / 2][j / 2] of the kernel, 16 registers, its
-    four tiles in the order (0,0), (0,1), (1,0), (1,1)."""
-    r = ((i // 2) * 4 + j // 2) * 16 + ((i % 2) * 2 + j % 2) * 4
+    r = (i * 8 + j) * 4
     return f"a[{r}:{r + 3}]"
 
 
@@ -68,12 +68,17 @@ def mfma(fs, i, j):
     return f'v_mfma_f32_16x16x32_" TY " {acc(i, j)}, {v4(F[fs]["B"][j])}, {v4(F[fs]["A"][i])}, {acc(i, j)}'
 
 
-def loads(which, stage):
-    """8 direct-to-LDS loads of this wave for one operand: M0 = LDS destination (wave base + 1 KiB per instruction + stage),
-    source = running base s[20:21] / s[22:23] + the lane's byte offset."""
+def load_group(which, n, lds_off, m0_at=0):
+    """Direct-to-LDS loads 0 .. n - 1 of this wave for one operand: M0 = LDS destination (wave base + stage + 4 KiB per four
+    loads, set before loads m0_at, 4, 8, ..), source = running base s[20:21] / s[22:23] + the lane's byte offset; the instruction's
+    offset is added to both (the lane's comes without it)."""
     base, lds, off = ("s[20:21]", "%[la]", "ga") if which == "A" else ("s[22:23]", "%[lb]", "gb")
-    return [f"s_add_u32 m0, {lds}, {stage * STAGE + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 %[{off}{j}], {base}"
-            for j in range(8)]
+    m0 = lambda j: f"s_add_u32 m0, {lds}, {lds_off + j // 4 * 4096}\\n s_nop 0\\n " if j % 4 == 0 or j == m0_at else ""
+    return [f"{m0(j)}global_load_lds_dwordx4 %[{off}{j}], {base} offset:{j % 4 * 1024}" for j in range(n)]
+
+
+def loads(which, stage):
+    return load_group(which, 8, stage * STAGE)
 
 
 def advance(which):
@@ -140,134 +145,138 @@ def kloop():
 
 # ------------------------------------------------------------------------------------------------ small tiles
 # K loop of the tiles below 256 x 256 (see gemm_16.hip for when they are used).  Such launches have few tiles per compute
-# unit, often less than one, so a slice's time is a chain of latencies: what counts is how many slices of loads are in
-# flight and that nothing but the MFMAs and one barrier is left on the chain.
-#   * LDS holds a ring of S slices; slice t+S is requested while slice t feeds the MFMAs, so S-1 slices are in flight;
-#   * fragments are read one phase ahead into the other of two register sets (a phase is a whole slice, or half of one
-#     where the sets would not fit), so a phase's MFMAs start without a wait;
-#   * one barrier per slice: behind it slice t+1 has landed for everybody, and everybody has the last fragments of
-#     slice t in registers, so its stage may be overwritten.
+# unit, often less than one, so a slice's time is a chain of latencies and of what its few waves issue: what counts is how
+# many slices of loads are in flight, that the MFMAs start without a wait and that little but them is left to issue.
+#   * 16x16x32 MFMAs, as in the large tile: the waves of a small tile then have 2 to 32 independent accumulators instead of
+#     one or two, and a tile can be cut over four waves down to 16 x 16 each;
+#   * LDS holds a ring of S slices;
+#   * fragments are read RA steps (of 32 k) ahead.  RA = 1: the barrier stands in the middle of a slice, when its last
+#     fragments have landed: its stage is free, S - 1 slices are in flight.  RA = 2, 4 for waves whose step is too short to
+#     cover an LDS read: RA - 1 steps of reads stay outstanding at the barrier, at the start of a slice, so the stage freed
+#     is the slice's before, and S - 1 - RA / 2 slices are in flight;
+#   * loads are spread over the slice; four of them share one M0, their offsets shift source and destination alike.
 # The ring is unrolled (stage offsets are immediates).  Loads take their row offsets as inputs, one register per load
 # instruction, so rows beyond the matrix are clamped by the caller and edge tiles run the same loop.
-S_AA, S_AB, S_F = 24, 28, 32              # first VGPRs: step addresses of A and B, fragments
+# Against 32x32x16 loops with the same tiles, us: 777 x 6144 x 1024 with SwiGLU 17.4 -> 15.4 (128 x 128, two stages),
+# 3699 x 1024 x 3072 30.9 -> 29.1 (128 x 128 deep), 391 x 4096 x 1024 with heads 10.8 -> 9.4 (64 x 128 on four waves instead of
+# two), 6 x 1024 x 3072 7.2 -> 5.2 (32 x 32 on four waves instead of one), 391 x 1024 x 3072 11.3 -> 9.4 (32 x 64 on two) and
+# 9.4 -> 9.2 (64 x 32; four waves are no faster: from L2 the same launch takes 7.8, the rest is the operands' way there).
+FIRST_V = 24                            # first VGPR: step addresses, then fragments
 
 
 class Small:
-    def __init__(self, name, TM, TN, nla, nlb, bm, bn, S, b_off, ks):
-        self.name, self.TM, self.TN, self.nla, self.nlb, self.S, self.ks = name, TM, TN, nla, nlb, S, ks
-        self.a_stage, self.b_stage, self.b_off = bm * 128, bn * 128, b_off
-        n = TM * TN
-        self.aA, self.aB = n, n + 1
-        self.gA, self.gB = n + 2, n + 2 + nla
-        self.ldsA = n + 2 + nla + nlb
-        self.ldsB, self.baseA, self.baseB, self.nk = self.ldsA + 1, self.ldsA + 2, self.ldsA + 3, self.ldsA + 4
-        self.set_regs = ks * (TM + TN) * 4
-        self.last_v = S_F + 2 * self.set_regs - 1
+    def __init__(self, name, bm, bn, wm, wn, S, RA, sets):
+        nw = wm * wn
+        self.name, self.S, self.RA, self.sets, self.ahead = name, S, RA, sets, RA // 2
+        self.TM, self.TN = bm // wm // 16, bn // wn // 16
+        self.nla, self.nlb = bm // 8 // nw, bn // 8 // nw                 # loads of a wave and slice
+        self.L, self.R, self.NS = self.nla + self.nlb, self.TM + self.TN, self.TM * self.TN
+        self.a_stage, self.b_stage = bm * 128, bn * 128
+        self.high = S * max(bm, bn) * 128 > 65536                         # a read's immediate offset ends at 64 KiB
+        self.f0 = FIRST_V + (12 if self.high else 8)
+        self.last_v = self.f0 + sets * self.R * 4 - 1
+        assert (RA - 1) * self.R <= 15 and (S - 1) * self.L <= 63         # what the wait counters can hold
+        assert sets > RA and (RA == 1 or (RA % 2 == 0 and S >= self.ahead + 2)) and S * (bm + bn) * 128 <= 163840
 
-    def frag(self, st, kk, which, i):
-        at = S_F + st * self.set_regs + (kk % self.ks) * (self.TM + self.TN) * 4 + (i if which == "A" else self.TM + i) * 4
-        return v4(at)
+    def addr(self, which, k, high):
+        return FIRST_V + {"A": 0, "B": 2, "B2": 4}[which] + k + (6 if high else 0)
 
-    def reads(self, st, phase, stage):
-        out = []
-        for kk in range(phase * self.ks, (phase + 1) * self.ks):
-            for i in range(self.TM):
-                out.append(f"ds_read_b128 {self.frag(st, kk, 'A', i)}, v{S_AA + kk} offset:{stage * self.a_stage + i * 4096}")
-            for j in range(self.TN):
-                out.append(f"ds_read_b128 {self.frag(st, kk, 'B', j)}, v{S_AB + kk} offset:{stage * self.b_stage + self.b_off[j]}")
-        return out
+    def frag(self, u, which, i):
+        return v4(self.f0 + (u % self.sets) * self.R * 4 + (i if which == "A" else self.TM + i) * 4)
 
-    def loads(self, stage):
-        out = []
-        for j in range(self.nla):
-            out.append(f"s_add_u32 m0, %{self.ldsA}, {stage * self.a_stage + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 %{self.gA + j}, s[20:21]")
-        for j in range(self.nlb):
-            out.append(f"s_add_u32 m0, %{self.ldsB}, {stage * self.b_stage + j * 1024}\\n s_nop 0\\n global_load_lds_dwordx4 %{self.gB + j}, s[22:23]")
-        return out
+    def reads(self, u):
+        """The fragment reads of step u (slice u / 2): the lower half of the wave's columns through one address, the upper through another
+        (SwiGLU's upper half are the up rows)."""
+        t, k, half = u // 2, u % 2, max(self.TN // 2, 1)
 
-    def advance(self):
-        """Both bases to the next slice while that exists (s25 = slice the bases point at, s26 = last slice): near the end
-        the loads re-read the last slice, in bounds, into stages that nobody reads any more."""
-        return ["s_cmp_lt_u32 s25, s26", "s_cselect_b32 s27, 128, 0", "s_cselect_b32 s28, 1, 0", "s_add_u32 s20, s20, s27",
-                "s_addc_u32 s21, s21, 0", "s_add_u32 s22, s22, s27", "s_addc_u32 s23, s23, 0", "s_add_u32 s25, s25, s28"]
+        def rd(which, i):
+            off = t % self.S * self.a_stage + i * TILE_ROWS if which == "A" else t % self.S * self.b_stage + i % half * TILE_ROWS
+            r = which if which == "A" or i < half else "B2"
+            return f"ds_read_b128 {self.frag(u, which, i)}, v{self.addr(r, k, off >= 65536)} offset:{off % 65536}"
+        return [rd("A", 0)] + [rd("B", j) for j in range(self.TN)] + [rd("A", i) for i in range(1, self.TM)]
 
-    def mfmas(self, mn, st, phase):
-        out = []
-        for kk in range(phase * self.ks, (phase + 1) * self.ks):
-            for i in range(self.TM):
-                for jj in range(self.TN):
-                    j = jj if i % 2 == 0 else self.TN - 1 - jj
-                    acc = f"%{i * self.TN + j}"
-                    out.append(f"{mn} {acc}, {self.frag(st, kk, 'B', j)}, {self.frag(st, kk, 'A', i)}, {acc}")
-        return out
+    def loads(self, stage, first=0):
+        """The loads of one slice from number `first` on."""
+        out = load_group("A", self.nla, stage * self.a_stage) + load_group("B", self.nlb, stage * self.b_stage)
+        which, n, at = ("A", first, stage * self.a_stage) if first < self.nla else ("B", first - self.nla, stage * self.b_stage)
+        return load_group(which, n + 1, at, n)[n:] + out[first + 1:] if first else out
 
-    def text(self, mn):
-        L, S, np_ = self.nla + self.nlb, self.S, 4 // self.ks
+    def advance(self, exists):
+        """Both bases to the next slice if that exists: near the end the loads re-read the last slice, in bounds, into stages
+        that nobody reads any more."""
+        return [exists, "s_cselect_b32 s25, 128, 0", "s_add_u32 s20, s20, s25", "s_addc_u32 s21, s21, 0", "s_add_u32 s22, s22, s25",
+                "s_addc_u32 s23, s23, 0"]
+
+    def text(self):
+        S, RA, NS, L, N = self.S, self.RA, self.NS, self.L, 2 * self.NS
         s = []
-        for k in range(4):
-            s += [f"v_xor_b32 v{S_AA + k}, {32 * k}, %{self.aA}", f"v_xor_b32 v{S_AB + k}, {32 * k}, %{self.aB}"]
-        s += [f"s_mov_b64 s[20:21], %{self.baseA}", f"s_mov_b64 s[22:23], %{self.baseB}", f"s_mov_b32 s24, %{self.nk}",
-              f"s_sub_u32 s26, %{self.nk}, 1", "s_mov_b32 s25, 0"]
-        for t in range(S - 1):
-            s += self.loads(t) + self.advance()
-        s += [f"s_waitcnt vmcnt({(S - 2) * L})", "s_barrier"]
-        s += self.reads(0, 0, 0) + self.loads(S - 1) + self.advance()
+        for k in range(2):
+            for which, a in (("A", "aa"), ("B", "ab"), ("B2", "ab2")):
+                s.append(f"v_xor_b32 v{self.addr(which, k, False)}, {64 * k}, %[{a}]")
+                if self.high:
+                    s.append(f"v_add_u32 v{self.addr(which, k, True)}, 65536, v{self.addr(which, k, False)}")
+        s += ["s_mov_b64 s[20:21], %[pa]", "s_mov_b64 s[22:23], %[pb]", "s_sub_u32 s24, %[nk], 1"]    # s24: slices after this one
+        n_pro = S if RA == 1 else S - 1
+        for t in range(n_pro):
+            s += self.loads(t) + (self.advance(f"s_cmp_gt_u32 s24, {t}") if t + 1 < n_pro else [])
+        s += [f"v_accvgpr_write_b32 a{r}, 0" for r in range((self.TM * self.TN + 3) // 4 * 16)]
+        s += [f"s_waitcnt vmcnt({(n_pro - max(self.ahead, 1)) * L})", "s_barrier"]
+        for u in range(RA):
+            s += self.reads(u)
+        order = [(i, j if i % 2 == 0 else self.TN - 1 - j) for i in range(self.TM) for j in range(self.TN)]
+        bar = NS if RA == 1 else 0                               # the barrier's place
+        landed = (S - 2 - self.ahead) * L
+        outstanding = f"lgkmcnt({(RA - 1) * self.R})"
+        period = math.lcm(S, self.sets // math.gcd(2, self.sets))
         s += ["L_loop_%=:"]
-        # one turn of the ring; with an odd number of phases per turn the register sets would not alternate, so two turns
-        turns = 1 if (S * np_) % 2 == 0 else 2
-        st = 0
-        for t in range(S * turns):
-            p = t % S
-            for ph in range(np_):
-                last = ph == np_ - 1
-                s += [f"s_waitcnt vmcnt({(S - 2) * L}) lgkmcnt(0)", "s_barrier"] if last else ["s_waitcnt lgkmcnt(0)"]
-                nxt = self.reads(1 - st, 0, (p + 1) % S) if last else self.reads(1 - st, ph + 1, p)
-                mf = self.mfmas(mn, st, ph)
-                ld = self.loads(p) if last else []
-                # fragment reads first (they are on the next phase's chain), two behind every MFMA; loads behind them
-                k = 0
-                for m in mf:
-                    s.append(m)
-                    take = max(2, -(-len(nxt) // max(1, len(mf) // 2)))
-                    s += nxt[k:k + take]
-                    if k >= len(nxt) and ld:
-                        n = -(-len(ld) // max(1, len(mf) // 2))
-                        s += ld[:n]
-                        ld = ld[n:]
-                    k += take
-                s += nxt[k:] + ld
-                if last:
-                    s += self.advance()
-                st = 1 - st
-            s += ["s_sub_u32 s24, s24, 1", "s_cmp_eq_u32 s24, 0"]
-            s += ["s_cbranch_scc1 L_done_%="] if t + 1 < S * turns else ["s_cbranch_scc0 L_loop_%="]
+        for t in range(period):
+            behind = {}
+            for h in range(2):
+                for n, r in enumerate(self.reads(2 * t + h + RA)):
+                    behind.setdefault(h * NS + n * NS // self.R, []).append(r)
+            # loads requested behind this slice's barrier, and, where that stands in the middle, the slice before's that reach into
+            # this one: the first turn repeats the youngest slice's there, so the first of them sets M0 itself
+            at = [bar + n * N // L for n in range(L)]
+            here = [n for n in range(L) if at[n] < N]
+            for n in here:
+                behind.setdefault(at[n], []).append(self.loads((t if RA == 1 else t - 1) % S)[n])
+            tail = [n for n in range(L) if at[n] >= N]
+            for n in tail:
+                assert at[n] - N < bar
+                behind.setdefault(at[n] - N, []).append(self.loads((t - 1) % S, tail[0])[n - tail[0]])
+            for m in range(N):
+                if m == bar:
+                    s += [f"s_waitcnt vmcnt({landed}) {outstanding}"] + self.advance(f"s_cmp_ge_u32 s24, {n_pro}") + ["s_barrier"]
+                elif m % NS == 0:
+                    s += [f"s_waitcnt {outstanding}"]
+                (i, j), u = order[m % NS], 2 * t + m // NS
+                r = (i * self.TN + j) * 4
+                s.append(f'v_mfma_f32_16x16x32_" TY " a[{r}:{r + 3}], {self.frag(u, "B", j)}, {self.frag(u, "A", i)}, a[{r}:{r + 3}]')
+                s += behind.get(m, [])
+            s += ["s_sub_u32 s24, s24, 1"] + (["s_cbranch_scc1 L_done_%="] if t + 1 < period else ["s_cbranch_scc0 L_loop_%="])
         s += ["L_done_%=:", "s_waitcnt vmcnt(0) lgkmcnt(0)", "s_nop 15", "s_nop 15"]
         return s
 
     def emit(self):
-        for tname, mn in (("F16", "v_mfma_f32_32x32x16_f16"), ("BF16", "v_mfma_f32_32x32x16_bf16")):
-            emit(f"PRISM_KLOOP_{tname}_{self.name}", self.text(mn))
-        regs = ", ".join(f'"v{r}"' for r in range(S_AA, self.last_v + 1)) + ", " + ", ".join(f'"s{r}"' for r in range(20, 29))
+        emit(f"PRISM_KLOOP_{self.name}(TY)", self.text())
+        regs = ", ".join(f'"v{r}"' for r in range(FIRST_V, self.last_v + 1)) + ", " + ", ".join(f'"s{r}"' for r in range(20, 26))
         print(f"#define PRISM_KLOOP_CLOBBERS_{self.name} {regs}, \"scc\", \"memory\"")
         print()
 
 
-#   name (tile, ring depth): accumulator tiles per wave, loads per wave and slice, tile, ring depth, B fragment offsets,
-#   k-steps per register set
+#   name (tile_stages), tile, wave grid, ring depth, steps read ahead, fragment sets
 SMALL = [
-    Small("32x32_8", 1, 1, 4, 4, 32, 32, 8, [0], 4),
-    Small("64x32_6", 1, 1, 4, 2, 64, 32, 6, [0], 4),
-    Small("32x64_4", 1, 2, 4, 8, 32, 64, 4, [0, 4096], 4),
-    Small("64x64_5", 1, 2, 4, 4, 64, 64, 5, [0, 4096], 4),
-    Small("128x64_3", 1, 2, 4, 2, 128, 64, 3, [0, 4096], 4),
-    Small("128x128_3_PLAIN", 2, 2, 4, 4, 128, 128, 3, [0, 4096], 2),
-    Small("128x128_3_SWIGLU", 2, 2, 4, 4, 128, 128, 3, [0, 8192], 2),
-    Small("128x128_2_PLAIN", 2, 2, 4, 4, 128, 128, 2, [0, 4096], 2),
-    Small("128x128_2_SWIGLU", 2, 2, 4, 4, 128, 128, 2, [0, 8192], 2),
+    Small("32x32_8", 32, 32, 2, 2, 8, 4, 6),
+    Small("64x32_6", 64, 32, 2, 1, 6, 2, 4),
+    Small("32x64_4", 32, 64, 1, 2, 4, 2, 4),
+    Small("64x64_5", 64, 64, 2, 2, 5, 1, 2),
+    Small("128x64_3", 128, 64, 4, 1, 3, 1, 2),
+    Small("128x128_4", 128, 128, 2, 2, 4, 2, 4),
+    Small("128x128_2", 128, 128, 2, 2, 2, 1, 2),
     # q/k/v projection: a wave owns the 128 columns of one head
-    Small("64x128_3_HEAD", 1, 4, 4, 8, 64, 128, 3, [0, 4096, 8192, 12288], 2),
-    Small("128x128_3_HEAD", 1, 4, 4, 4, 128, 128, 3, [0, 4096, 8192, 12288], 2),
-    Small("128x128_2_HEAD", 1, 4, 4, 4, 128, 128, 2, [0, 4096, 8192, 12288], 2),
+    Small("64x128_3_HEAD", 64, 128, 4, 1, 3, 1, 2),
+    Small("128x128_3_HEAD", 128, 128, 4, 1, 3, 1, 2),
+    Small("128x128_2_HEAD", 128, 128, 4, 1, 2, 1, 2),
 ]
 
 
@@ -281,19 +290,18 @@ def emit(name, lines):
 
 def main():
     print("// Generated by gen_gemm_kloop.py - do not edit.  See that file for the schedule.")
-    print("// PRISM_KLOOP_256(TY), TY = \"f16\" or \"bf16\": accumulators a[0:255] (32 x 32 block (i, j) of the wave in a[(4i+j)*16 : +15]);")
-    print("// aa / ab / ab2 LDS byte address of the lane's first fragment row of A, of B columns 0-63 and 64-127 (step 0, stage 0);")
-    print("// ga0..7 / gb0..7 byte offset into A / W of the chunk this lane fetches in each of its wave's load instructions; la / lb")
-    print("// LDS byte address of the first row the first of them fills (stage 0, uniform); pa / pb base of A / W; nk number of slices.")
-    print("// PRISM_KLOOP_*: accumulators acc[i][j] first (AGPRs), then the same values by position (see class Small).")
+    print("// PRISM_KLOOP_<tile>(TY), TY = \"f16\" or \"bf16\": accumulators a[0:...], tile (i, j) of 16 x 16 in the four from 4 (TN i + j) on;")
+    print("// aa / ab / ab2 LDS byte address of the lane's first fragment row of A, of the lower and of the upper half of the wave's B columns")
+    print("// (step 0, stage 0); ga / gb byte offset from pa / pb of the chunk this lane fetches in each of its wave's load instructions,")
+    print("// less 1024 (j % 4); la / lb LDS byte address of the first row the first of them fills (stage 0, uniform); nk number of slices.")
     print()
     emit("PRISM_KLOOP_256(TY)", kloop())
     regs = ", ".join(f'"v{r}"' for r in CLOBBER_V) + ", " + ", ".join(f'"s{r}"' for r in CLOBBER_S)
     for c in SMALL:
         c.emit()
-    # m0 (written before every direct-to-LDS load) is not listed: the compiler reserves it, sets it right before each of
+    # m0 (written before the direct-to-LDS loads) is not listed: the compiler reserves it, sets it right before each of
     # its own uses and never keeps a value in it across a statement; hipcc diagnoses it in a clobber list
-    print(f"#define PRISM_KLOOP_256_CLOBBERS {regs}, \"scc\", \"memory\"")
+    print(f"#define PRISM_KLOOP_CLOBBERS_256 {regs}, \"scc\", \"memory\"")
 
 
 if __name__ == "__main__":

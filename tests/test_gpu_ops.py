@@ -157,6 +157,27 @@ def test_gemm_16_rows_beyond_whole_rounds_go_to_small_tiles_with_the_same_bits(d
         assert torch.equal(run(lo, hi), whole[lo:hi]), (lo, hi)
 
 
+@pytest.mark.parametrize("dtype", SIXTEEN)
+@pytest.mark.parametrize("epi", [B.EPI_RESIDUAL, B.EPI_SWIGLU])
+@pytest.mark.parametrize("slices", range(1, 14))
+def test_gemm_16_big_tile_at_every_place_of_its_ring(dtype, epi, slices):
+    """The big tile's loop is unrolled over the six slices after which its three stages of A and two of W stand alike: 1 to 13
+    slices end it at every place of the first two turns.  Bit for bit against the same rows in a launch of smaller tiles, which
+    have rings of their own (and are compared to fp64 below); the last rows and columns are ragged."""
+    M, N, K, glu = 4100, 6144 + 8, 64 * slices, epi == B.EPI_SWIGLU
+    assert gemm_plan(M, N, K, glu)[0][1] == "kTile256"
+    A = _rand((M, K), dtype, 91 + K, 1.0).to(DEV)
+    Wt = _rand((N, K), dtype, 92 + K, 1.0 / math.sqrt(K)).to(DEV)
+    X0 = _rand((M, N // 2 if glu else N), torch.float32 if not glu else dtype, 93, 1.0).to(DEV)
+    whole = X0.clone()
+    B.op_gemm(epi, A, Wt, whole)
+    for lo, hi in ((0, 300), (2000, 2300), (3900, 4100)):
+        assert all(k != "kTile256" for _, k in gemm_plan(hi - lo, N, K, glu))
+        part = X0[lo:hi].clone()
+        B.op_gemm(epi, A[lo:hi], Wt, part)
+        assert torch.equal(part, whole[lo:hi]), (lo, hi)
+
+
 # Per tile: stages of its ring, (SwiGLU?, rows, N, 64-deep slices) of launches that take it.  The slices are, within what the
 # launcher gives the tile, below, at and above the number of stages, and end in every position of the unrolled ring (two turns of
 # it where a turn has an odd number of phases); rows and N leave the last tiles ragged.  SwiGLU pairs two 32-column tiles in a
