@@ -36,6 +36,7 @@ namespace prism {
 
 static constexpr int HD = 128;           // head_dim served by this kernel
 static constexpr int BKV = 64;           // keys per staged tile
+static constexpr int VP = 3;             // 32-row blocks of V^T whose fragments are read ahead of the softmax
 #define PRISM_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define PRISM_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
@@ -171,20 +172,31 @@ void attention_16_kernel(const OT *__restrict__ QK, const f16 *__restrict__ Vt, 
     // two variants are separate code so that tiles below the diagonal carry no masking arithmetic at all.
     auto tile_step = [&](auto mask_tag) {
       constexpr bool MASK = decltype(mask_tag)::value;
-      // ---- S^T = K Q^T for the 2 key blocks of the tile
+      // ---- S^T = K Q^T for the 2 key blocks of the tile, one after the other
       f32x16 s[2];
+      vec8 kf[2][HD / 16];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int kk = 0; kk < HD / 16; ++kk) kf[kb][kk] = *reinterpret_cast<const vec8 *>(&lK[(rdK ^ (kk * 16)) + kb * 32 * HD]);
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[kb][e] = 0.f;
+        if (kb == 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int kk = 0; kk < HD / 16; ++kk) {
-          const vec8 kf = *reinterpret_cast<const vec8 *>(&lK[(rdK ^ (kk * 16)) + kb * 32 * HD]);
-          s[kb] = Mfma<OT>::mma(kf, qf[kk], s[kb]);
-        }
+        for (int kk = 0; kk < HD / 16; ++kk) s[kb] = Mfma<OT>::mma(kf[kb][kk], qf[kk], s[kb]);
       }
+      // The V^T fragments of three of the four blocks of d are requested here, into the registers that K's leave: behind the
+      // softmax each of these reads would hold up the matrix pipe (three sequences of 4000-8192 tokens, 32 heads: 1010 -> 982 us,
+      // a hundred of 288-1024: 749 -> 736; two blocks 987, all four spill).
+      f16x8 vf[VP][4];
+#pragma unroll
+      for (int t = 0; t < VP; ++t)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) vf[t][ks] = *reinterpret_cast<const f16x8 *>(&lV[(rdV ^ (ks * 16)) + t * 32 * BKV]);
       // ---- causal mask + online softmax (lane owns query qi; partner lane ^ 32 owns the other keys)
-      float mx = -INFINITY;
+      float mxk[2] = {-INFINITY, -INFINITY};
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -193,8 +205,10 @@ void attention_16_kernel(const OT *__restrict__ QK, const f16 *__restrict__ Vt, 
             const int key = kt * BKV + kb * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
             if (key > qi) s[kb][e] = -INFINITY;
           }
-          mx = fmaxf(mx, s[kb][e]);
+          mxk[kb] = fmaxf(mxk[kb], s[kb][e]);
         }
+      float mx = fmaxf(mxk[0], mxk[1]);
+      __builtin_amdgcn_sched_barrier(0);
       {
         float lo, hi;
         half_wave_pair(mx, lo, hi);
@@ -238,8 +252,8 @@ void attention_16_kernel(const OT *__restrict__ QK, const f16 *__restrict__ Vt, 
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
           // contraction slots 0-3 <- keys ks*16 + (lane/32)*4 .. +4 ; slots 4-7 <- the same + 8: chunk 2 ks + lane/32
-          const f16x8 vf = *reinterpret_cast<const f16x8 *>(&lV[(rdV ^ (ks * 16)) + t * 32 * BKV]);
-          o[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[ks], o[t], 0, 0, 0);
+          const f16x8 v = t < VP ? vf[t < VP ? t : 0][ks] : *reinterpret_cast<const f16x8 *>(&lV[(rdV ^ (ks * 16)) + t * 32 * BKV]);
+          o[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v, pf[ks], o[t], 0, 0, 0);
         }
       }
         };
