@@ -31,43 +31,54 @@ __device__ __forceinline__ double run_cost(const double *P, const double *Q, int
 // prescribed order (n of them, about 4 ns each); the table of the third has n^2 / 2 entries per stage, each with an fp64
 // division when done plainly.  Small pools (up to kOneGroup) run all phases in one workgroup on LDS; larger ones as
 // 2 + (k - 2) launches: phase 1 and 2 side by side on two compute units, the table on all of them, the rest on one.
-// us per call, 3 clusters, one workgroup on global memory before -> now: 12 candidates 12 -> 11, 100: 53 -> 17, 500: 232 -> 36,
-// 4096: 4895 -> 181; 8 clusters on 4096: 18700 -> 330.  (128 candidates, 8 clusters: 41 as one workgroup, 45 at 129.)
+// us of kernels per call, 3 clusters, sums over floats as they were sorted -> over doubles laid out for them: 12 candidates
+// 7.8 -> 7.6, 100: 15.6 -> 14.7, 500: 36 -> 33, 1000: 53 -> 47, 4096: 183 -> 142 (one workgroup on global memory took 53 for 100,
+// 232 for 500, 4895 for 4096).  The border between the two forms: 128 candidates, 8 clusters took 41 as one workgroup, 129 took 45
+// (launches included, before the sums were changed).
 
-// f(i, x[i]) for i = 0 .. n - 1, in order, by one thread; x in LDS, 16-byte aligned.  Sixteen values are read ahead, so that
-// the chain of additions in f is all there is to wait for.
+// f(i, x[i]) for i = 0 .. n - 1, in order, by one thread; x in LDS, 16-byte aligned, and already what is summed: one wavefront issues
+// its fp64 instructions one after another, so a conversion or a product beside each addition lengthens the chain (the last
+// launch on 4096 candidates: 34 us with a conversion from float in it, 23 without).  Sixteen values are read ahead, so that the chain of additions in f is
+// all there is to wait for.
 template <typename F>
-__device__ __forceinline__ void in_order(const float *x, int n, F f) {
-  const f32x4 *q = reinterpret_cast<const f32x4 *>(x);
+__device__ __forceinline__ void in_order(const double *x, int n, F f) {
+  typedef __attribute__((ext_vector_type(2))) double f64x2;
+  const f64x2 *q = reinterpret_cast<const f64x2 *>(x);
   int i = 0;
   if (n >= 16) {
-    f32x4 cur[4];
+    f64x2 cur[8];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) cur[j] = q[j];
+    for (int j = 0; j < 8; ++j) cur[j] = q[j];
     for (; i + 16 <= n; i += 16) {
-      f32x4 next[4];
-      const int at = i + 32 <= n ? i / 4 + 4 : 0;
+      f64x2 next[8];
+      const int at = i + 32 <= n ? i / 2 + 8 : 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) next[j] = q[at + j];
+      for (int j = 0; j < 8; ++j) next[j] = q[at + j];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) f(i + j, cur[j / 4][j % 4]);
+      for (int j = 0; j < 16; ++j) f(i + j, cur[j / 2][j % 2]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) cur[j] = next[j];
+      for (int j = 0; j < 8; ++j) cur[j] = next[j];
     }
   }
   for (; i < n; ++i) f(i, x[i]);
 }
 
-// ---- phase 1: mean and population std, sequential in index order; the gate.  One thread; sc is in LDS.
-__device__ void stats_phase(const float *sc, int n, int K_rem, float tau, double *stats) {
+// ---- phase 1: mean and population std, sequential in index order; the gate.  In two halves, each a chain of one thread, with the
+// squared deviations between them by the whole workgroup (deviate).  x is in LDS.
+__device__ __forceinline__ double mean_phase(const double *x, int n) {
   double tot = 0.0;
-  in_order(sc, n, [&](int, float x) { tot = tot + (double)x; });
-  const double mean = n > 0 ? tot / (double)n : 0.0;
+  in_order(x, n, [&](int, double v) { tot = tot + v; });
+  return n > 0 ? tot / (double)n : 0.0;
+}
+__device__ __forceinline__ void deviate(double *x, int n, double mean) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const double d = x[i] - mean;
+    x[i] = d * d;
+  }
+}
+__device__ __forceinline__ void stats_phase(const double *sq, int n, int K_rem, float tau, double mean, double *stats) {
   double acc = 0.0;
-  in_order(sc, n, [&](int, float x) {
-    const double d = (double)x - mean;
-    acc = acc + d * d;
-  });
+  in_order(sq, n, [&](int, double v) { acc = acc + v; });
   const double sd = n > 0 ? sqrt(acc / (double)n) : 0.0;
   const int gate = (n > K_rem) && (sd > (double)tau * fabs(mean));   // CV > tau, division-free
   stats[0] = mean;
@@ -76,28 +87,33 @@ __device__ void stats_phase(const float *sc, int n, int K_rem, float tau, double
   stats[3] = 0.0;
 }
 
-// ---- phase 2, from the scores in rank order (sorted, in LDS): sequential prefix sums of x and x^2 (a thread each, in different
-// wavefronts), number of clusters, first row of costs E[1][i] = cost(i, n).  The whole workgroup.
-__device__ void prefix_phase(const float *sorted, int n, int k_req, int *sh_distinct, const RouteWs &ws) {
+// ---- phase 2, from the scores in rank order (sorted, in LDS): sequential prefix sums P, Q of x and x^2 (a thread each, in different
+// wavefronts; in LDS, so that a sum costs its thread no store to memory), number of clusters, first row of costs
+// E[1][i] = cost(i, n).  The whole workgroup.
+__device__ void prefix_phase(const float *sorted, int n, int k_req, int *sh_distinct, double *x, double *xx, double *P, double *Q,
+                             const RouteWs &ws) {
   const int tid = threadIdx.x, nt = blockDim.x;
   if (tid == 0) *sh_distinct = 0;
   __syncthreads();
   int local = 0;
   for (int r = tid; r < n; r += nt) {
-    ws.ranked[r] = (double)sorted[r];
+    const double v = (double)sorted[r];
+    ws.ranked[r] = x[r] = v;
+    xx[r] = v * v;
     local += r == 0 || sorted[r - 1] != sorted[r];
   }
   if (local) atomicAdd(sh_distinct, local);
+  __syncthreads();
   double run = 0.0;
   if (tid == 0) {
-    ws.P[0] = 0.0;
-    in_order(sorted, n, [&](int i, float x) { ws.P[i + 1] = run = run + (double)x; });
+    P[0] = 0.0;
+    in_order(x, n, [&](int i, double v) { P[i + 1] = run = run + v; });
   } else if (tid == 64) {
-    ws.Q[0] = 0.0;
-    in_order(sorted, n, [&](int i, float x) { ws.Q[i + 1] = run = run + (double)x * (double)x; });
+    Q[0] = 0.0;
+    in_order(xx, n, [&](int i, double v) { Q[i + 1] = run = run + v; });
   }
   __syncthreads();
-  for (int i = tid; i < n; i += nt) ws.E0[i] = run_cost(ws.P, ws.Q, i, n);
+  for (int i = tid; i < n; i += nt) ws.E0[i] = run_cost(P, Q, i, n);
   if (tid == 0) ws.arg[0] = k_req < *sh_distinct ? k_req : *sh_distinct;       // row 0 of the split table is not used otherwise
   __syncthreads();
 }
@@ -126,8 +142,12 @@ __device__ void sort_phase(float *sc, int n, unsigned long long *key, const Rout
         const unsigned long long x = key[i], y = key[j];
         if ((x > y) == ((i & size) == 0)) { key[i] = y; key[j] = x; }
       }
-      __syncthreads();
+      // pairs up to 64 apart: a wavefront's 64 pairs are the same 128 keys in every such step, and LDS serves it in order
+      const int next = d > 1 ? d / 2 : size;
+      if (d > 64 || next > 64) __syncthreads();
+      else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
+  __syncthreads();
   float mine[PRISM_MAX_CANDS / 1024];
 #pragma unroll
   for (int j = 0; j < PRISM_MAX_CANDS / 1024; ++j) {
@@ -196,7 +216,7 @@ struct RouteShared {
   int idx[16], splits[PRISM_MAX_CLUSTERS + 1], b;
   double means[PRISM_MAX_CLUSTERS];
 };
-__device__ void fate_phase(int k, int n, int K_rem, int8_t *fate, double *stats, const RouteWs &ws, RouteShared &sh) {
+__device__ void fate_phase(int k, int n, int K_rem, int8_t *fate, double *stats, const double *ranked, const RouteWs &ws, RouteShared &sh) {
   const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
   const double *Eprev = k % 2 == 0 ? ws.E0 : ws.E1;
   double best = INFINITY;
@@ -232,10 +252,12 @@ __device__ void fate_phase(int k, int n, int K_rem, int8_t *fate, double *stats,
   __syncthreads();
   if (lane == 0)
   for (int cl = wave; cl < k; cl += nt >> 6) {               // a cluster per wavefront
+    const int from = sh.splits[cl], to = sh.splits[cl + 1];
     double tot = 0.0;
-#pragma unroll 8
-    for (int r = sh.splits[cl]; r < sh.splits[cl + 1]; ++r) tot = tot + ws.ranked[r];
-    sh.means[cl] = tot / (double)(sh.splits[cl + 1] - sh.splits[cl]);
+    int r = from;
+    for (; r < to && r % 2 != 0; ++r) tot = tot + ranked[r];
+    in_order(ranked + r, to - r, [&](int, double v) { tot = tot + v; });
+    sh.means[cl] = tot / (double)(to - from);
   }
   __syncthreads();
   const double mb = sh.means[sh.b];
@@ -253,7 +275,7 @@ static constexpr int kOneGroup = 128;
 __global__ __launch_bounds__(512) void route_small_kernel(const float *__restrict__ scores, int n, int K_rem, int k_req, float tau,
                                                           int8_t *__restrict__ fate, double *__restrict__ stats) {
   __shared__ __align__(16) float sc[kOneGroup], sorted[kOneGroup];
-  __shared__ double arr[5][kOneGroup + 1];
+  __shared__ __align__(16) double arr[5][kOneGroup + 2], x[kOneGroup], xx[kOneGroup];
   __shared__ int32_t order[kOneGroup], arg[(PRISM_MAX_CLUSTERS + 1) * (kOneGroup + 1)];
   __shared__ double st[4];
   __shared__ int distinct;
@@ -262,6 +284,7 @@ __global__ __launch_bounds__(512) void route_small_kernel(const float *__restric
   const int tid = threadIdx.x;
   if (tid < n) {
     sc[tid] = scores[tid];
+    x[tid] = (double)scores[tid];
     fate[tid] = PRISM_FATE_DEFERRED;
   }
   __syncthreads();
@@ -280,11 +303,15 @@ __global__ __launch_bounds__(512) void route_small_kernel(const float *__restric
       sorted[r] = si;
     }
   }
-  if (tid == 511) stats_phase(sc, n, K_rem, tau, st);
+  if (tid == 511) st[0] = mean_phase(x, n);
+  __syncthreads();
+  deviate(x, n, st[0]);
+  __syncthreads();
+  if (tid == 511) stats_phase(x, n, K_rem, tau, st[0], st);
   __syncthreads();
   if (tid < 4) stats[tid] = st[tid];
   if (st[2] == 0.0) return;
-  prefix_phase(sorted, n, k_req, &distinct, ws);
+  prefix_phase(sorted, n, k_req, &distinct, x, xx, ws.P, ws.Q, ws);
   const int k = arg[0];
   if (k <= 1) return;
   for (int m = 2; m < k; ++m) {
@@ -310,26 +337,34 @@ __global__ __launch_bounds__(512) void route_small_kernel(const float *__restric
     }
     __syncthreads();
   }
-  fate_phase(k, n, K_rem, fate, stats, ws, sh);
+  fate_phase(k, n, K_rem, fate, stats, ws.ranked, ws, sh);
 }
 
 // n > kOneGroup.  Block 0: phase 1 and the default fates; block 1: phase 2 (wasted when the gate turns out closed).
 __global__ __launch_bounds__(1024) void route_prepare_kernel(const float *__restrict__ scores, int n, int K_rem, int k_req, float tau,
                                                              int8_t *__restrict__ fate, double *__restrict__ stats, RouteWs ws) {
+  // (xx is the sort's key array first)
   __shared__ __align__(16) float sc[PRISM_MAX_CANDS];
-  __shared__ unsigned long long key[PRISM_MAX_CANDS];
+  __shared__ __align__(16) double x[PRISM_MAX_CANDS], xx[PRISM_MAX_CANDS], P[PRISM_MAX_CANDS + 1], Q[PRISM_MAX_CANDS + 1];
   __shared__ int distinct;
+  __shared__ double mean;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     sc[i] = scores[i];
+    x[i] = (double)scores[i];
     if (blockIdx.x == 0) fate[i] = PRISM_FATE_DEFERRED;
   }
   __syncthreads();
   if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) stats_phase(sc, n, K_rem, tau, stats);
+    if (threadIdx.x == 0) mean = mean_phase(x, n);
+    __syncthreads();
+    deviate(x, n, mean);
+    __syncthreads();
+    if (threadIdx.x == 0) stats_phase(x, n, K_rem, tau, mean, stats);
     return;
   }
-  sort_phase(sc, n, key, ws);
-  prefix_phase(sc, n, k_req, &distinct, ws);
+  sort_phase(sc, n, reinterpret_cast<unsigned long long *>(xx), ws);
+  prefix_phase(sc, n, k_req, &distinct, x, xx, P, Q, ws);
+  for (int i = threadIdx.x; i <= n; i += blockDim.x) { ws.P[i] = P[i]; ws.Q[i] = Q[i]; }
 }
 
 __global__ __launch_bounds__(256) void route_table_kernel(int m, int n, const double *__restrict__ stats, RouteWs ws) {
@@ -339,8 +374,10 @@ __global__ __launch_bounds__(256) void route_table_kernel(int m, int n, const do
 
 __global__ __launch_bounds__(1024) void route_fate_kernel(int n, int K_rem, int8_t *__restrict__ fate, double *__restrict__ stats, RouteWs ws) {
   __shared__ RouteShared sh;
+  __shared__ __align__(16) double ranked[PRISM_MAX_CANDS];
   if (stats[2] == 0.0 || ws.arg[0] <= 1) return;
-  fate_phase(ws.arg[0], n, K_rem, fate, stats, ws, sh);
+  for (int r = threadIdx.x; r < n; r += blockDim.x) ranked[r] = ws.ranked[r];
+  fate_phase(ws.arg[0], n, K_rem, fate, stats, ranked, ws, sh);
 }
 
 static RouteWs carve(void *workspace, int n, int k) {
