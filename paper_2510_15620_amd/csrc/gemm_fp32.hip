@@ -9,7 +9,8 @@
 // consecutive k of its row as one 16-byte operand chunk and feeds them to four instructions, so instruction s of a
 // 16-deep block sums k = s, 4 + s, 8 + s, 12 + s of it; the order is the same for every tile size.
 // Layer of the tiny configuration (hidden 256, ffn 688): q/k/v, down and gate/up projections on 354 rows 44, 132 and 52 us
-// on the vector pipes -> 5, 9 and 10 us; on 12859 rows 100, 183 and 195 -> 43, 63 and 104 (78-87 TFLOP/s).
+// on the vector pipes -> 5, 9 and 10 us; on 12859 rows 100, 183 and 195 -> 44, 58 and 107 (77-84 TFLOP/s).
+// What is left there: without loads 95 % of the time, without LDS stores or reads 85 % each, with MFMAs alone 74 %.
 #include "common.h"
 
 namespace prism {
@@ -117,19 +118,45 @@ __global__ __launch_bounds__(256) void gemm_fp32_kernel(const float *__restrict_
     }
 }
 
+template <int BM, int BN, int BK, int WM, int WN, int EPI, bool VEC>
+static void launch_tile(const float *A, const float *W, float *out, int M, int N, int K, hipStream_t s) {
+  const int F = EPI == PRISM_EPI_SWIGLU ? N / 2 : N, cols = EPI == PRISM_EPI_SWIGLU ? BN / 2 : BN;
+  gemm_fp32_kernel<BM, BN, BK, WM, WN, EPI, VEC><<<dim3(cdiv(F, cols), cdiv(M, BM)), 256, 0, s>>>(A, W, out, M, N, K);
+}
+
+// The tile with the least modelled time: rounds of one tile per compute unit x round (us at K = 256; a tile's start and end are
+// put at 32 of K) + call (us), from 32 to 128 rows and columns.  A large tile reads less LDS per product, a small one leaves less
+// of the last round idle; 64 rows x 32 columns over four waves of 16 rows was the best small one of the shapes tried.  SwiGLU's
+// smallest tile has 64 columns (its waves pair gate and up tiles) and is taken where it fills no second round: 8 rows 5.9 us, 6.2
+// with 64 x 32.  Constants: fit to 26 launches (700-40000 rows of the tiny configuration's four projections, 777 and 3000 of 1024
+// hidden), of whose best tile the rule misses 0.6 % on average, against 6.5 % for the border of 512 tiles between 32 x 32 and
+// 64 x 64 that stood here.  us before -> now: gate/up 1500 rows 20.1 -> 16.7, 6000 58 -> 51, 12859 113 -> 107, 40000 305 -> 283;
+// down 12859 64 -> 58; q/k/v 40000 134 -> 122.
+struct TileTime { int bm, bn; double round, call; };
+static constexpr TileTime kFp32Tiles[] = {{32, 32, 1.80, 1.3}, {64, 32, 3.03, 2.9}, {64, 64, 5.34, 4.0}, {128, 64, 10.4, 3.6}, {128, 128, 19.6, 7.3}};
+static constexpr TileTime kFp32SmallGlu = {32, 64, 3.20, 2.7};
+
+static int fp32_tile(int epilogue, int M, int N, int K) {
+  int best = 0;
+  double least = 0;
+  for (int i = 0; i < 5; ++i) {
+    const TileTime &t = i == 0 && epilogue == PRISM_EPI_SWIGLU ? kFp32SmallGlu : kFp32Tiles[i];
+    const int64_t tiles = (int64_t)cdiv(M, t.bm) * cdiv(N, t.bn);
+    const double time = (double)((tiles + 255) / 256) * t.round * (K + 32) / 288 + t.call;
+    if (i == 0 || time < least) { best = i; least = time; }
+  }
+  return best;
+}
+
 template <int EPI, bool VEC>
 static void launch_tiles(const float *A, const float *W, float *out, int M, int N, int K, hipStream_t s) {
-  const int F = EPI == PRISM_EPI_SWIGLU ? N / 2 : N, half = EPI == PRISM_EPI_SWIGLU ? 2 : 1;
-  // Fewer than two 64 x 64 tiles per compute unit: 32 x 32 tiles (32 x 64 for SwiGLU, whose waves pair gate and up tiles)
-  // with twice the slice depth keep more units busy and halve the number of slices in the chain.
-  if ((int64_t)cdiv(M, 64) * cdiv(F, 64 / half) < 512) {
-    if constexpr (EPI == PRISM_EPI_SWIGLU)
-      gemm_fp32_kernel<32, 64, 64, 2, 2, EPI, VEC><<<dim3(cdiv(F, 32), cdiv(M, 32)), 256, 0, s>>>(A, W, out, M, N, K);
-    else
-      gemm_fp32_kernel<32, 32, 64, 2, 2, EPI, VEC><<<dim3(cdiv(F, 32), cdiv(M, 32)), 256, 0, s>>>(A, W, out, M, N, K);
-    return;
+  switch (fp32_tile(EPI, M, N, K)) {
+    case 0: launch_tile<32, EPI == PRISM_EPI_SWIGLU ? 64 : 32, 64, 2, 2, EPI, VEC>(A, W, out, M, N, K, s); break;
+    case 1: launch_tile<64, 32, 32, 4, 1, EPI, VEC>(A, W, out, M, N, K, s); break;
+    case 2: launch_tile<64, 64, 32, 2, 2, EPI, VEC>(A, W, out, M, N, K, s); break;
+    case 3: launch_tile<128, 64, 16, 2, 2, EPI, VEC>(A, W, out, M, N, K, s); break;
+    default: launch_tile<128, 128, 16, 2, 2, EPI, VEC>(A, W, out, M, N, K, s);
   }
-  gemm_fp32_kernel<64, 64, 32, 2, 2, EPI, VEC><<<dim3(cdiv(F, 64 / half), cdiv(M, 64)), 256, 0, s>>>(A, W, out, M, N, K);
 }
 
 int launch_gemm_fp32(int epilogue, const float *A, const float *W, void *out, int M, int N, int K, hipStream_t s) {

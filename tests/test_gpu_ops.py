@@ -267,6 +267,24 @@ def test_gemm_fp32_tiles(epi, N, K):
         assert torch.equal(run(rows), whole[:rows]), rows
 
 
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
+@pytest.mark.parametrize("M,N,K", [(3001, 1378, 130), (6001, 1378, 128), (4201, 1378, 100), (20001, 1378, 130), (20001, 1378, 132)])
+def test_gemm_fp32_larger_tiles(epi, M, N, K):
+    """64 x 32, 64 x 64, 128 x 64 and 128 x 128 tiles (taken by the number of rounds each needs), with ragged rows, columns and K.
+    Every tile sums in the same order, so rows at the start, the middle and the end equal, bit for bit, the same rows in calls of at
+    most 200, which take the smallest tiles and are compared to fp64 above."""
+    g = torch.Generator().manual_seed(M + N + K)
+    A, Wt = torch.randn(M, K, generator=g).to(DEV), (torch.randn(N, K, generator=g) / math.sqrt(K)).to(DEV)
+    X0 = torch.randn(M, N // 2 if epi == B.EPI_SWIGLU else N, generator=g).to(DEV)
+    whole = X0.clone()
+    B.op_gemm(epi, A, Wt, whole)
+    for lo in (0, 1984, M // 64 * 64 - 128, M - 33):
+        for rows in (32, 200):
+            part = X0[lo:lo + rows].clone()
+            B.op_gemm(epi, A[lo:lo + rows], Wt, part)
+            assert torch.equal(part, whole[lo:lo + rows]), (lo, rows)
+
+
 @pytest.mark.parametrize("epi,N", [(B.EPI_STORE, 8), (B.EPI_RESIDUAL, 8), (B.EPI_SWIGLU, 4)])
 def test_gemm_fp32_row_panels(epi, N):
     """More rows than one grid covers (65535 blocks of 32): the launcher cuts the call into panels of 2 097 120 rows.  Bound as
