@@ -124,17 +124,18 @@ static void launch_tile(const float *A, const float *W, float *out, int M, int N
   gemm_fp32_kernel<BM, BN, BK, WM, WN, EPI, VEC><<<dim3(cdiv(F, cols), cdiv(M, BM)), 256, 0, s>>>(A, W, out, M, N, K);
 }
 
-// The tile with the least modelled time: rounds of one tile per compute unit x round (us at K = 256; a tile's start and end are
-// put at 32 of K) + call (us), from 32 to 128 rows and columns.  A large tile reads less LDS per product, a small one leaves less
-// of the last round idle; 64 rows x 32 columns over four waves of 16 rows was the best small one of the shapes tried.  SwiGLU's
-// smallest tile has 64 columns (its waves pair gate and up tiles) and is taken where it fills no second round: 8 rows 5.9 us, 6.2
-// with 64 x 32.  Constants: fit to 26 launches (700-40000 rows of the tiny configuration's four projections, 777 and 3000 of 1024
-// hidden), of whose best tile the rule misses 0.6 % on average, against 6.5 % for the border of 512 tiles between 32 x 32 and
-// 64 x 64 that stood here.  us before -> now: gate/up 1500 rows 20.1 -> 16.7, 6000 58 -> 51, 12859 113 -> 107, 40000 305 -> 283;
-// down 12859 64 -> 58; q/k/v 40000 134 -> 122.
-struct TileTime { int bm, bn; double round, call; };
-static constexpr TileTime kFp32Tiles[] = {{32, 32, 1.80, 1.3}, {64, 32, 3.03, 2.9}, {64, 64, 5.34, 4.0}, {128, 64, 10.4, 3.6}, {128, 128, 19.6, 7.3}};
-static constexpr TileTime kFp32SmallGlu = {32, 64, 3.20, 2.7};
+// The tile with the least modelled time: K / 256 x (rounds of one tile per compute unit x round + fill) + call, us; tiles from 32
+// to 128 rows and columns.  A large tile reads less LDS per product, a small one leaves less of the last round idle and waits less
+// for its slices where a unit holds one or two; 64 rows x 32 columns over four waves of 16 rows was the best small one of the shapes
+// tried.  SwiGLU's smallest tile has 64 columns (its waves pair gate and up tiles).  Constants: fit to 68 launches (60-20000 rows of
+// the tiny configuration's four projections, 60-4000 of others), of whose best tile the rule misses 0.2 % on average, against 2.1 %
+// for the border of 512 tiles between 32 x 32 and 64 x 64 that stood here; no launch up to K = 1024 is more than 1 % slower than by
+// that border.  us, by the border -> now: gate/up 1500 rows 19.4 -> 17.8, 12859 103 -> 96.5, 20000 156 -> 148; down 6000 30.4 -> 28.3,
+// 8000 38.6 -> 33.1.
+struct TileTime { int bm, bn; double round, fill, call; };
+static constexpr TileTime kFp32Tiles[] = {{32, 32, 1.66, 0.75, 2.22}, {64, 32, 3.01, 1.45, 2.07}, {64, 64, 5.25, 0.03, 4.32},
+                                          {128, 64, 9.44, 1.04, 4.87}, {128, 128, 18.43, 1.63, 5.15}};
+static constexpr TileTime kFp32SmallGlu = {32, 64, 3.10, 0.40, 3.00};
 
 static int fp32_tile(int epilogue, int M, int N, int K) {
   int best = 0;
@@ -142,7 +143,7 @@ static int fp32_tile(int epilogue, int M, int N, int K) {
   for (int i = 0; i < 5; ++i) {
     const TileTime &t = i == 0 && epilogue == PRISM_EPI_SWIGLU ? kFp32SmallGlu : kFp32Tiles[i];
     const int64_t tiles = (int64_t)cdiv(M, t.bm) * cdiv(N, t.bn);
-    const double time = (double)((tiles + 255) / 256) * t.round * (K + 32) / 288 + t.call;
+    const double time = ((double)((tiles + 255) / 256) * t.round + t.fill) * K / 256 + t.call;
     if (i == 0 || time < least) { best = i; least = time; }
   }
   return best;

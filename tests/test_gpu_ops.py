@@ -272,7 +272,7 @@ def test_gemm_fp32_tiles(epi, N, K):
 def test_gemm_fp32_larger_tiles(epi, M, N, K):
     """64 x 32, 64 x 64, 128 x 64 and 128 x 128 tiles (taken by the number of rounds each needs), with ragged rows, columns and K.
     Every tile sums in the same order, so rows at the start, the middle and the end equal, bit for bit, the same rows in calls of at
-    most 200, which take the smallest tiles and are compared to fp64 above."""
+    most 200, which take the smaller tiles and are compared to fp64 above."""
     g = torch.Generator().manual_seed(M + N + K)
     A, Wt = torch.randn(M, K, generator=g).to(DEV), (torch.randn(N, K, generator=g) / math.sqrt(K)).to(DEV)
     X0 = torch.randn(M, N // 2 if epi == B.EPI_SWIGLU else N, generator=g).to(DEV)
