@@ -9,7 +9,7 @@
 // consecutive k of its row as one 16-byte operand chunk and feeds them to four instructions, so instruction s of a
 // 16-deep block sums k = s, 4 + s, 8 + s, 12 + s of it; the order is the same for every tile size.
 // Layer of the tiny configuration (hidden 256, ffn 688): q/k/v, down and gate/up projections on 354 rows 44, 132 and 52 us
-// on the vector pipes -> 5, 9 and 10 us; on 12859 rows 100, 183 and 195 -> 44, 58 and 107 (77-84 TFLOP/s).
+// on the vector pipes -> 5, 9 and 10 us; on 12859 rows 100, 183 and 195 -> 44, 58-64 and 97-107 (71-94 TFLOP/s; boxes differ).
 // What is left there: without loads 95 % of the time, without LDS stores or reads 85 % each, with MFMAs alone 74 %.
 #include "common.h"
 
