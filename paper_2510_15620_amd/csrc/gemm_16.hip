@@ -38,9 +38,10 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 #define PRISM_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define PRISM_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
-// silu(g) * u in fp32, rounded to 16 bits by its callers.  The reciprocal instruction (1 ulp) instead of the ten instructions of a
-// correctly rounded division, which were half of the SwiGLU epilogue: 13.8 -> 9.2 thousand cycles of a 256 x 256 tile.
-__device__ __forceinline__ float silu_mul(float g, float u) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u; }
+// silu(g) * u in fp32, rounded to 16 bits by its callers.  The division is correctly rounded: a product with the reciprocal
+// instruction would take half of this epilogue's arithmetic away (13.8 -> 9.2 thousand cycles of a 256 x 256 tile), but is off by
+// an ulp more and returns 0 where 1 + e^-g exceeds 2^126, values that bf16 still holds.
+__device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
 
 // LDS bytes of a tile's operand stages
 template <int BM, int BN, int S> constexpr int stage_bytes() { return ((BM == 256 ? 3 : S) * BM + S * BN) * BK * 2; }

@@ -113,6 +113,25 @@ def _gemm_16_case(dtype, epi, M, N, K):
 
 
 @pytest.mark.parametrize("dtype", SIXTEEN)
+def test_gemm_16_swiglu_over_the_range_of_the_gate(dtype):
+    """Gates with the factor 1 + e^-g from 1 to just below the largest fp32 number, on whole and cut column tiles.  The result
+    is one 16-bit rounding of gate / (1 + e^-gate) * up with an fp32 exponential, whose argument's rounding is worth up to
+    |gate| 2^-24 of it, some 2^-17 at the largest; below the smallest normal number of the type, half a unit there."""
+    gates = torch.tensor([-88.5, -88.25, -88.0, -87.5, -87.0, -80.0, -16.5, -3.25, -0.5, 0.0, 0.5, 3.25, 16.5, 90.0], dtype=dtype)
+    K, F, ups = 64, 40, torch.tensor([1.0, -3.0, 0.25, 512.0], dtype=dtype)
+    A, Wt = torch.zeros(len(gates), K, dtype=dtype), torch.zeros(2 * F, K, dtype=dtype)
+    A[:, 0], A[:, 1] = gates, 1.0
+    Wt[:F, 0] = 1.0
+    Wt[F:, 1] = ups.repeat(F // len(ups))
+    out = torch.full((len(gates), F), 7.0, dtype=dtype, device=DEV)
+    B.op_gemm(B.EPI_SWIGLU, A.to(DEV), Wt.to(DEV), out)
+    g, u = _f64(gates)[:, None], _f64(Wt[F:, 1])[None]
+    ref = g / (1.0 + np.exp(-g)) * u
+    tiny = torch.finfo(dtype).tiny
+    np.testing.assert_array_less(np.abs(_f64(out) - ref), (EPS16[dtype] + 2.0 ** -16) * np.maximum(np.abs(ref), tiny) + 1e-45)
+
+
+@pytest.mark.parametrize("dtype", SIXTEEN)
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 @pytest.mark.parametrize("K", [64, 128, 192, 320, 448])
 def test_gemm_16_big_tile_with_few_and_odd_slice_counts(dtype, epi, K):
