@@ -142,10 +142,16 @@ __device__ void sort_phase(float *sc, int n, unsigned long long *key, const Rout
         const unsigned long long x = key[i], y = key[j];
         if ((x > y) == ((i & size) == 0)) { key[i] = y; key[j] = x; }
       }
-      // pairs up to 64 apart: a wavefront's 64 pairs are the same 128 keys in every such step, and LDS serves it in order
+      // pairs up to 64 apart: a wavefront's 64 pairs are the same 128 keys in every such step, and LDS serves it in order.  The
+      // barrier of the wavefront (no instruction) is what makes its lanes meet behind the exchange, which each enters or not; the
+      // fences order its memory accesses only.
       const int next = d > 1 ? d / 2 : size;
       if (d > 64 || next > 64) __syncthreads();
-      else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
     }
   __syncthreads();
   float mine[PRISM_MAX_CANDS / 1024];
