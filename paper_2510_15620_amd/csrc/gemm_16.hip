@@ -451,9 +451,9 @@ __global__ __launch_bounds__(WM *WN * 64, (stage_bytes<BM, BN, S>() > 81920 ? 1 
   else if constexpr (kHeads && BM == 64) PRISM_RUN(64x128_3_HEAD, PRISM_ACC2);
   else if constexpr (kHeads && S == 3) PRISM_RUN(128x128_3_HEAD, PRISM_ACC4);
   else if constexpr (kHeads) PRISM_RUN(128x128_2_HEAD, PRISM_ACC4);
-  else if constexpr (BM == 32 && BN == 32) PRISM_RUN(32x32_8, PRISM_ACC1);
-  else if constexpr (BM == 64 && BN == 32) PRISM_RUN(64x32_6, PRISM_ACC1);
-  else if constexpr (BM == 32 && BN == 64) PRISM_RUN(32x64_4, PRISM_ACC1);
+  else if constexpr (BM == 32 && BN == 32) PRISM_RUN(32x32_9, PRISM_ACC1);
+  else if constexpr (BM == 64 && BN == 32) PRISM_RUN(64x32_7, PRISM_ACC1);
+  else if constexpr (BM == 32 && BN == 64) PRISM_RUN(32x64_4, PRISM_ACC2);
   else if constexpr (BM == 64 && BN == 64) PRISM_RUN(64x64_5, PRISM_ACC1);
   else if constexpr (BM == 128 && BN == 64) PRISM_RUN(128x64_3, PRISM_ACC2);
   else if constexpr (S == 4) PRISM_RUN(128x128_4, PRISM_ACC4);
@@ -508,7 +508,7 @@ struct TileCost {
 enum { kTile256, kTile128, kTile128Deep, kTile128x64, kTile64, kTile32x64, kTile64x32, kTile32, kTileKinds };
 static constexpr TileCost kTileCost[kTileKinds] = {
     {256, 256, 1, 1.45f, 1.45f, 9.2f}, {128, 128, 2, 0.72f, 0.50f, 4.5f}, {128, 128, 1, 0.52f, 0.52f, 3.4f}, {128, 64, 2, 0.34f, 0.36f, 2.3f},
-    {64, 64, 2, 0.204f, 0.204f, 2.1f}, {32, 64, 3, 0.176f, 0.149f, 2.4f}, {64, 32, 2, 0.128f, 0.128f, 2.3f}, {32, 32, 2, 0.106f, 0.083f, 2.6f}};
+    {64, 64, 2, 0.204f, 0.204f, 2.1f}, {32, 64, 3, 0.176f, 0.149f, 2.4f}, {64, 32, 1, 0.128f, 0.128f, 2.3f}, {32, 32, 2, 0.106f, 0.083f, 2.6f}};
 // The fused q/k/v projection: tiles whose waves own whole heads (34 launches of 1 to 12000 rows: within 11-19 %, the picked
 // size on average within 1 % of the best, at worst 12 %).  Its epilogue is longer: two dependent loads (position, rotation)
 // and the per-head arithmetic.  391 x 4096 x 1024: 11 us, where the projection to fp32 and its two finishing kernels took 48;
@@ -559,12 +559,12 @@ static int launch_kind(int kind, const OT *A, const OT *W, void *out, int M, int
     case kTile128Deep: return launch_cfg<OT, 128, 128, 2, 2, EPI, 4>(A, W, out, M, N, K, s);
     case kTile128x64: return launch_cfg<OT, 128, 64, 4, 1, EPI, 3>(A, W, out, M, N, K, s);
     case kTile64: return launch_cfg<OT, 64, 64, 2, 2, EPI, 5>(A, W, out, M, N, K, s);
-    case kTile32x64: return launch_cfg<OT, 32, 64, 1, 2, EPI, 4>(A, W, out, M, N, K, s);
+    case kTile32x64: return launch_cfg<OT, 32, 64, 1, 1, EPI, 4>(A, W, out, M, N, K, s);
     default: break;
   }
   if constexpr (EPI != PRISM_EPI_SWIGLU) {
-    if (kind == kTile64x32) return launch_cfg<OT, 64, 32, 2, 1, EPI, 6>(A, W, out, M, N, K, s);
-    return launch_cfg<OT, 32, 32, 2, 2, EPI, 8>(A, W, out, M, N, K, s);
+    if (kind == kTile64x32) return launch_cfg<OT, 64, 32, 2, 1, EPI, 7>(A, W, out, M, N, K, s);
+    return launch_cfg<OT, 32, 32, 2, 2, EPI, 9>(A, W, out, M, N, K, s);
   }
   return PRISM_EUNSUPPORTED;
 }

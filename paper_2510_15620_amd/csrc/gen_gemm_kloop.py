@@ -154,13 +154,19 @@ def kloop():
 #     fragments have landed: its stage is free, S - 1 slices are in flight.  RA = 2, 4 for waves whose step is too short to
 #     cover an LDS read: RA - 1 steps of reads stay outstanding at the barrier, at the start of a slice, so the stage freed
 #     is the slice's before, and S - 1 - RA / 2 slices are in flight;
+#   * a launch of a few rows streams its weights from memory, and the slices in flight are what it has to cover that latency
+#     with: 7 of 32 x 32, 5 of 64 x 32, 3 of 32 x 64.  Fragments four steps ahead in a ring of 8, or two steps ahead in rings of 6 and 4,
+#     left 5, 4 and 2 and were level or faster only on operands that stay in the caches.  us, weights from memory, those rings -> these:
+#     1 x 4096 x 12288 29.7 -> 24.1, 33 x 2560 x 9728 22.3 -> 18.5, 6 x 1024 x 3072 8.6 -> 7.4 (32 x 32); 100 x 4096 x 12288 38.0 ->
+#     37.0, 391 x 1024 x 3072 10.5 -> 9.8 (64 x 32); with SwiGLU 1 x 6144 x 1024 8.0 -> 7.2, 1 x 24576 x 4096 40.9 -> 39.1 (32 x 64; two waves
+#     with the same ring: 6.7 and 38.8, but 32 x 19456 x 2560 28.2 instead of 27.4, two tiles on a few units being what it waits for);
 #   * loads are spread over the slice; four of them share one M0, their offsets shift source and destination alike.
 # The ring is unrolled (stage offsets are immediates).  Loads take their row offsets as inputs, one register per load
 # instruction, so rows beyond the matrix are clamped by the caller and edge tiles run the same loop.
-# Against 32x32x16 loops with the same tiles, us: 777 x 6144 x 1024 with SwiGLU 17.4 -> 15.4 (128 x 128, two stages),
-# 3699 x 1024 x 3072 30.9 -> 29.1 (128 x 128 deep), 391 x 4096 x 1024 with heads 10.8 -> 9.4 (64 x 128 on four waves instead of
-# two), 6 x 1024 x 3072 7.2 -> 5.2 (32 x 32 on four waves instead of one), 391 x 1024 x 3072 11.3 -> 9.4 (32 x 64 on two) and
-# 9.4 -> 9.2 (64 x 32; four waves are no faster: from L2 the same launch takes 7.8, the rest is the operands' way there).
+# Against 32x32x16 loops with the same tiles, us, operands that stay in the caches: 777 x 6144 x 1024 with SwiGLU 17.4 -> 15.4
+# (128 x 128, two stages), 3699 x 1024 x 3072 30.9 -> 29.1 (128 x 128 deep), 391 x 4096 x 1024 with heads 10.8 -> 9.4 (64 x 128 on four
+# waves instead of two), 6 x 1024 x 3072 7.2 -> 5.3 (32 x 32 on four waves instead of one), 391 x 1024 x 3072 8.9 -> 8.7 (64 x 32;
+# four waves are no faster); weights from memory: the last two 7.7 -> 7.4 and 9.9 -> 9.8.
 FIRST_V = 24                            # first VGPR: step addresses, then fragments
 
 
@@ -266,9 +272,9 @@ class Small:
 
 #   name (tile_stages), tile, wave grid, ring depth, steps read ahead, fragment sets
 SMALL = [
-    Small("32x32_8", 32, 32, 2, 2, 8, 4, 6),
-    Small("64x32_6", 64, 32, 2, 1, 6, 2, 4),
-    Small("32x64_4", 32, 64, 1, 2, 4, 2, 4),
+    Small("32x32_9", 32, 32, 2, 2, 9, 2, 4),
+    Small("64x32_7", 64, 32, 2, 1, 7, 2, 4),
+    Small("32x64_4", 32, 64, 1, 1, 4, 1, 2),
     Small("64x64_5", 64, 64, 2, 2, 5, 1, 2),
     Small("128x64_3", 128, 64, 4, 1, 3, 1, 2),
     Small("128x128_4", 128, 128, 2, 2, 4, 2, 4),

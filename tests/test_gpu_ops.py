@@ -136,8 +136,8 @@ def test_gemm_16_swiglu_over_the_range_of_the_gate(dtype):
 @pytest.mark.parametrize("K", [64, 128, 192, 320, 448])
 def test_gemm_16_big_tile_with_few_and_odd_slice_counts(dtype, epi, K):
     """4100 x 6144 outputs are 17 x 24 tiles of 256 x 256 (SwiGLU: 17 x 24 of 256 x 128), enough for the launcher to pick
-    the big tile, whose K loop is scheduled by hand two 64-deep slices per iteration: 1, 2, 3, 5 and 7 slices exercise
-    its prologue-only, single-iteration and mid-iteration exits."""
+    the big tile, whose K loop is unrolled over six 64-deep slices: 1, 2, 3, 5 and 7 slices exercise exits inside the first
+    turn and in the second."""
     assert gemm_plan(4100, 6144, K, epi == B.EPI_SWIGLU)[0][1] == "kTile256"
     _gemm_16_case(dtype, epi, 4100, 6144, K)
 
@@ -197,19 +197,19 @@ def test_gemm_16_big_tile_at_every_place_of_its_ring(dtype, epi, slices):
         assert torch.equal(part, whole[lo:hi]), (lo, hi)
 
 
-# Per tile: stages of its ring, (SwiGLU?, rows, N, 64-deep slices) of launches that take it.  The slices are, within what the
-# launcher gives the tile, below, at and above the number of stages, and end in every position of the unrolled ring (two turns of
-# it where a turn has an odd number of phases); rows and N leave the last tiles ragged.  SwiGLU pairs two 32-column tiles in a
-# wave, so the 32-wide tiles have none.
+# Per tile: its loop, (SwiGLU?, rows, N, 64-deep slices) of launches that take it.  The slices end a launch, within what the
+# launcher gives the tile, at every place of the unrolled ring in its first and second turn (test_tile_plan.py checks that against
+# the loops' generator; the big tile has a test of its own above); rows and N leave the last tiles ragged.  SwiGLU pairs two
+# 32-column tiles in a wave, so the 32-wide tiles have none.
 TILE_LAUNCHES = {
-    "kTile256": (2, [(g, 2001, 6152, k) for g in (False, True) for k in (1, 2, 3)]),
-    "kTile128": (2, [(g, 4101, 1000, k) for g in (False, True) for k in (1, 2, 3, 4, 5)]),
-    "kTile128Deep": (3, [(g, 9001, 200, k) for g in (False, True) for k in (6, 7, 8, 9, 10, 11)]),
-    "kTile128x64": (3, [(False, 9001, 200, k) for k in (1, 2, 3, 4, 5)] + [(False, 2601, 392, k) for k in (6, 7)] + [(True, 9001, 200, k) for k in (1, 2, 3, 4)] + [(True, 9001, 72, k) for k in (5, 6)]),
-    "kTile64": (5, [(False, 65, 4104, k) for k in range(3, 11)] + [(False, 1, 40, 1), (False, 33, 40, 2)] + [(True, 33, 40, k) for k in range(1, 10)]),
-    "kTile32x64": (4, [(False, 129, 6152, k) for k in (3, 4, 5, 6, 7, 8)] + [(True, 33, 40, k) for k in (11, 12, 13, 14)]),
-    "kTile64x32": (6, [(False, 33, 72, k) for k in range(3, 13)]),
-    "kTile32": (8, [(False, 33, 72, k) for k in range(16, 25)] + [(False, 1, 1000, 16), (False, 65, 1000, 48)]),
+    "kTile256": ("256", [(g, 2001, 6152, k) for g in (False, True) for k in (1, 2, 3)]),
+    "kTile128": ("128x128_2", [(g, 4101, 1000, k) for g in (False, True) for k in (1, 2, 3, 4, 5)]),
+    "kTile128Deep": ("128x128_4", [(g, 9001, 200, k) for g in (False, True) for k in (6, 7, 8, 9, 10, 11)]),
+    "kTile128x64": ("128x64_3", [(False, 9001, 200, k) for k in (1, 2, 3, 4, 5)] + [(False, 2601, 392, k) for k in (6, 7)] + [(True, 9001, 200, k) for k in (1, 2, 3, 4)] + [(True, 9001, 72, k) for k in (5, 6)]),
+    "kTile64": ("64x64_5", [(False, 65, 4104, k) for k in range(3, 11)] + [(False, 1, 40, 1), (False, 33, 40, 2)] + [(True, 33, 40, k) for k in range(1, 11)]),
+    "kTile32x64": ("32x64_4", [(False, 129, 6152, k) for k in (3, 4, 5, 6, 7, 8)] + [(True, 33, 40, k) for k in (11, 12, 13, 14)]),
+    "kTile64x32": ("64x32_7", [(False, 33, 72, k) for k in range(3, 13)] + [(False, 33, 4104, k) for k in range(13, 29)]),
+    "kTile32": ("32x32_9", [(False, 33, 72, k) for k in range(16, 37)] + [(False, 1, 1000, 16), (False, 65, 1000, 48)]),
 }
 
 
@@ -739,6 +739,8 @@ def _layer_by_entry_points(m, lw, X, cu, dtype):
 @pytest.mark.parametrize("nq,nkv,H,lens,kind", [
     (2, 1, 256, [40, 18], "kHead64"), (16, 8, 256, [33, 1, 200], "kHead64"), (1, 1, 64, [70, 5], "kHead64"),
     (32, 8, 192, [300, 70, 1], "kHead128Deep"), (3, 3, 128, [1200, 1, 781], "kHead128Deep"),
+    (2, 1, 320, [40, 18], "kHead64"), (2, 1, 384, [40, 18], "kHead64"),              # every place of the rings' second turn
+    (32, 8, 256, [300, 70, 1], "kHead128Deep"), (32, 8, 320, [300, 70, 1], "kHead128Deep"), (32, 8, 384, [300, 70, 1], "kHead128Deep"),
     (32, 8, 256, [700, 63], "kHead128"), (1, 1, 320, [4000, 4001, 3900, 5], "kHead128"),
     (8, 8, 1024, [1500, 1, 1024, 64, 1490], "kHead256")])
 def test_projection_of_a_whole_call_has_the_bits_of_its_entry_points(dtype, nq, nkv, H, lens, kind):

@@ -2,7 +2,9 @@
 code: the cost tables and plan_tiles are cut out of the source, compiled for the host and asked about the same launches.  The GPU
 tests assert through the model which tile a shape takes, so a retuned table cannot empty them unnoticed."""
 import ctypes
+import importlib.util
 import itertools
+import os
 import subprocess
 
 import pytest
@@ -61,3 +63,33 @@ def test_head_plan_is_the_launchers(launcher):
         seen |= {k for _, k in got} | ({"split"} if len(got) == 2 else set())
     assert len(seen) == 5
     assert all(k != "kHead256" for M in ROWS for _, k in H.head_plan(M, 3, 3, 1024))        # an odd number of heads
+
+
+@pytest.fixture(scope="module")
+def loops():
+    spec = importlib.util.spec_from_file_location("gen_gemm_kloop", os.path.join(os.path.dirname(H.GEMM_SOURCE), "gen_gemm_kloop.py"))
+    gen = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(gen)
+    return {c.name: c for c in gen.SMALL}
+
+
+def test_launches_of_the_bit_test_end_at_every_place_of_each_ring(loops):
+    from tests.test_gpu_ops import TILE_LAUNCHES
+    for kind, (loop, launches) in TILE_LAUNCHES.items():
+        for glu in {l[0] for l in launches}:
+            slices = [k for g, _, _, k in launches if g == glu]
+            assert all(H.gemm_plan(M, N, 64 * k, glu) == [(M, kind)] for g, M, N, k in launches if g == glu), kind
+            if loop in loops:                                # the big tile's loop is none of the small ones
+                c = loops[loop]
+                period = sum("v_mfma" in line for line in c.text()) // (2 * c.NS)       # slices of a turn; 2 NS products in each
+                assert {(k - 1) % period for k in slices if k > period} == set(range(period)), (kind, glu)
+
+
+def test_tiles_for_few_rows_keep_their_slices_in_flight(loops):
+    """A launch of a few rows streams its weights from memory; the slices requested ahead are what it covers that latency with."""
+    for name, in_flight in (("32x32_9", 7), ("64x32_7", 5), ("32x64_4", 3), ("64x64_5", 4)):
+        c = loops[name]
+        body = c.text()[c.text().index("L_loop_%=:"):]
+        wait = next(line for line in body if "vmcnt(" in line)
+        left = int(wait.split("vmcnt(")[1].split(")")[0])    # of the loads requested before a barrier, those it does not wait for
+        assert left // c.L + 1 == in_flight, name            # and the slice requested behind it
