@@ -127,15 +127,16 @@ static void launch_tile(const float *A, const float *W, float *out, int M, int N
 // The tile with the least modelled time: K / 256 x (rounds of one tile per compute unit x round + fill) + call, us; tiles from 32
 // to 128 rows and columns.  A large tile reads less LDS per product, a small one leaves less of the last round idle and waits less
 // for its slices where a unit holds one or two; 64 rows x 32 columns over four waves of 16 rows was the best small one of the shapes
-// tried.  SwiGLU's smallest tile has 64 columns (its waves pair gate and up tiles).  Constants: fit to 68 launches (60-20000 rows of
-// the tiny configuration's four projections, 60-4000 of others), of whose best tile the rule misses 0.2 % on average, against 2.1 %
-// for the border of 512 tiles between 32 x 32 and 64 x 64 that stood here; no launch up to K = 1024 is more than 1 % slower than by
-// that border.  us, by the border -> now: gate/up 1500 rows 19.4 -> 17.8, 12859 103 -> 96.5, 20000 156 -> 148; down 6000 30.4 -> 28.3,
-// 8000 38.6 -> 33.1.
+// tried.  SwiGLU's smallest tile has 64 columns (its waves pair gate and up tiles).  Constants: fit to 404 launches (17 to 20000 rows;
+// the fp32 configurations' projections, and 256 to 4096 columns at K up to 4096).  Against the best tile of each the rule loses 0.2 % on
+// average and 6 % at worst; against 32 x 32 below 512 tiles of 64 x 64 and those from there on, which stood here once, it gains 2 % on average
+// and loses 2 % at worst.  us, that border -> now: gate/up 12859 rows 94 -> 89, 20000 140 -> 135, 1500 18.7 -> 16.7; down 6000 30.5 -> 27.8,
+// 8000 38.3 -> 33.2; 16000 x 1536 x 1536 690 -> 639.  A fit to K up to 1024 only, without the first round's extra time, put 354 x 2048 x 2048 and
+// 150 x 4096 x 4096 on 64 x 64 tiles: 51 and 101 us instead of 40 and 76.
 struct TileTime { int bm, bn; double round, fill, call; };
-static constexpr TileTime kFp32Tiles[] = {{32, 32, 1.66, 0.75, 2.22}, {64, 32, 3.01, 1.45, 2.07}, {64, 64, 5.25, 0.03, 4.32},
-                                          {128, 64, 9.44, 1.04, 4.87}, {128, 128, 18.43, 1.63, 5.15}};
-static constexpr TileTime kFp32SmallGlu = {32, 64, 3.10, 0.40, 3.00};
+static constexpr TileTime kFp32Tiles[] = {{32, 32, 1.39, 0.58, 2.73}, {64, 32, 2.57, 1.09, 2.57}, {64, 64, 4.78, 1.38, 2.76},
+                                          {128, 64, 8.96, 1.98, 3.56}, {128, 128, 17.80, 1.91, 4.79}};
+static constexpr TileTime kFp32SmallGlu = {32, 64, 2.69, 0.64, 2.65};
 
 static int fp32_tile(int epilogue, int M, int N, int K) {
   int best = 0;

@@ -90,6 +90,23 @@ def head_plan(M, nq, nkv, K):
     return plan if heads % 2 == 0 or all(k != "kHead256" for _, k in plan) else [(M, "kHead128")]
 
 
+FP32_SOURCE = os.path.join(os.path.dirname(GEMM_SOURCE), "gemm_fp32.hip")
+
+
+def fp32_tile(M, N, K, glu=False):
+    """(rows, columns) of the tile that an fp32 prism_op_gemm takes, from the launcher's own table."""
+    src = open(FP32_SOURCE).read()
+    table = [tuple(float(v) for v in r.split(",")) for r in re.findall(r"\{([^{}]*)\}", re.search(r"kFp32Tiles\[\] = \{(.*?)\};", src, re.S).group(1))]
+    small_glu = tuple(float(v) for v in re.search(r"kFp32SmallGlu = \{([^}]*)\}", src).group(1).split(","))
+
+    def time(t):
+        bm, bn, per_round, fill, call = t
+        tiles = -(-M // int(bm)) * -(-N // int(bn))
+        return ((tiles + 255) // 256 * per_round + fill) * K / 256 + call
+    best = min(([small_glu] if glu else table[:1]) + table[1:], key=time)
+    return int(best[0]), int(best[1])
+
+
 # --------------------------------------------------------------------------- full-size goldens and the margin rule
 
 GOLDEN_DIR = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden")

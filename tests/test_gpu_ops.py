@@ -9,7 +9,7 @@ import torch
 from oracle import prism_oracle as O
 from paper_2510_15620_amd import binding as B
 from paper_2510_15620_amd import workloads as W
-from tests.helpers import gemm_plan, head_plan, oracle_model, oracle_weights
+from tests.helpers import fp32_tile, gemm_plan, head_plan, oracle_model, oracle_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -258,7 +258,7 @@ def test_gemm_16_every_tile_size_gives_a_row_the_same_bits(dtype, epi, kind):
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 @pytest.mark.parametrize("N,K", [(200, 64), (200, 68), (202, 688), (198, 67), (1376, 256), (2, 1)])
 def test_gemm_fp32_tiles(epi, N, K):
-    """fp32 on the matrix instruction: two tile sizes (chosen by the number of tiles), rows of 16-byte aligned and other
+    """fp32 on the matrix instruction: the two smallest tiles (SwiGLU: 32 x 64 and 64 x 32), rows of 16-byte aligned and other
     lengths, slices cut off by K, columns cut off by N.  Against fp64: |error| of a K-term fp32 sum of products is at most
     K 2^-24 sum |a w| (SwiGLU: of each factor, plus the exponential's and two products' roundings); and rows do not
     depend on how many are computed with them."""
@@ -287,14 +287,17 @@ def test_gemm_fp32_tiles(epi, N, K):
 
 
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
-@pytest.mark.parametrize("M,N,K", [(3001, 1378, 130), (6001, 1378, 128), (4201, 1378, 100), (20001, 1378, 130), (20001, 1378, 132)])
-def test_gemm_fp32_larger_tiles(epi, M, N, K):
-    """64 x 32, 64 x 64, 128 x 64 and 128 x 128 tiles (taken by the number of rounds each needs), with ragged rows, columns and K.
-    Every tile sums in the same order, so rows at the start, the middle and the end equal, bit for bit, the same rows in calls of at
-    most 200, which take the smaller tiles and are compared to fp64 above."""
+@pytest.mark.parametrize("M,N,K,tile", [(3001, 1378, 130, (64, 32)), (6001, 1378, 128, (64, 32)), (4201, 1378, 100, (64, 64)), (20001, 1378, 130, (128, 64)),
+                                        (20001, 1378, 132, (128, 64)), (20001, 2018, 260, (128, 128)), (20001, 2018, 270, (128, 128))])
+def test_gemm_fp32_larger_tiles(epi, M, N, K, tile):
+    """The larger tiles (taken by the number of rounds each needs), with ragged rows, columns and K, rows of 16-byte aligned and other
+    lengths.  Every tile sums in the same order, so rows at the start, the middle and the end equal, bit for bit, the same rows in
+    calls of at most 200, which take smaller tiles, those of 32 the smallest, and are compared to fp64 above."""
+    glu = epi == B.EPI_SWIGLU
+    assert fp32_tile(M, N, K, glu) == tile and fp32_tile(32, N, K, glu) == ((32, 64) if glu else (32, 32))
     g = torch.Generator().manual_seed(M + N + K)
     A, Wt = torch.randn(M, K, generator=g).to(DEV), (torch.randn(N, K, generator=g) / math.sqrt(K)).to(DEV)
-    X0 = torch.randn(M, N // 2 if epi == B.EPI_SWIGLU else N, generator=g).to(DEV)
+    X0 = torch.randn(M, N // 2 if glu else N, generator=g).to(DEV)
     whole = X0.clone()
     B.op_gemm(epi, A, Wt, whole)
     for lo in (0, 1984, M // 64 * 64 - 128, M - 33):
