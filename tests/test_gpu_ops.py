@@ -473,14 +473,12 @@ def test_qkv_project_fused(dtype, qk_norm, nq, H, lens, kinds):
     np.testing.assert_allclose(vt[:, :, vt_col], ref_v, rtol=EPS16[dtype] * 1.01, atol=atol)
     pad = np.setdiff1d(np.arange(ncol), vt_col)
     assert (vt[:, :, pad] == 0).all()
-    # the unfused device path: same arithmetic except the order of the sum of squares
+    # the unfused device path: one order of every sum, so the same bits
     QKV = torch.zeros(T, (nq + 2 * nkv) * hd, dtype=torch.float32, device=DEV)
     B.op_gemm(B.EPI_STORE_F32, Xn.to(DEV), Wt.to(DEV), QKV)
     QK2, Vt2 = torch.zeros_like(QK), torch.zeros_like(Vt)
     B.op_qkv_finish(B._dt(QK), QKV, dpos, 1024, gq.to(DEV), gk.to(DEV), nq, nkv, hd, 1e-6, 1e6, qk_norm, QK2, Vt2, dcol, ncol)
-    assert torch.equal(Vt, Vt2)
-    assert (QK != QK2).float().mean().item() < 1e-3
-    np.testing.assert_allclose(_f64(QK), _f64(QK2), rtol=2 * EPS16[dtype] * 1.01, atol=atol)   # neighbouring 16-bit values at most
+    assert torch.equal(Vt, Vt2) and torch.equal(QK, QK2)
 
 
 def test_qkv_project_rejects_small_problems():
