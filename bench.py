@@ -253,7 +253,7 @@ def main():
     dom_n = sum(r.kind_launches[DOM] for r in dom_reps)
     achieved = dom_fl / dom_ms / 1e9
     op_t = "float" if m.dtype == "fp32" else args.operand
-    traffic, traffic_source = stored_traffic(w.name, f"gemm_16_kernel<{op_t},256,256,2,2,2>")
+    traffic, traffic_source = stored_traffic(w.name, f"gemm_16_kernel<{op_t},256,256,2,2,2,2>")
     roofline = {"bound": "mfma", "kernel": f"gemm_16_kernel<{op_t},256,256,2,2,SWIGLU>", "achieved": round(achieved, 1),
                 "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                 "traffic": traffic, "traffic_source": traffic_source,

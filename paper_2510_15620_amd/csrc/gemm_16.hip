@@ -39,7 +39,8 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 #define PRISM_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
 // silu(g) * u in fp32, rounded to 16 bits by its callers.  The division is correctly rounded: a product with the reciprocal
-// instruction would take half of this epilogue's arithmetic away (13.8 -> 9.2 thousand cycles of a 256 x 256 tile), but is off by
+// instruction takes half of this epilogue's arithmetic away (13.8 -> 9.2 thousand cycles of a 256 x 256 tile) and no time where the
+// chip is full and at its power limit (24576 x 24576 x 4096: 3350 us, with the division 3337), but is off by
 // an ulp more and returns 0 where 1 + e^-g exceeds 2^126, values that bf16 still holds.
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
 
@@ -494,11 +495,13 @@ static int launch_cfg(const OT *A, const OT *W, void *out, int M, int N, int K, 
 // Rows are independent, columns are independent, and every tile size gives an element the same bits (one accumulator, K in
 // order), so the choice is made on time alone.  A launch deals its tiles over 256 compute units; n = tiles per unit, rounded
 // up.  A tile's time is its K slices plus a fixed part (dispatch, first slice, epilogue), and a slice's time depends on how
-// many tiles share the unit: alone it is a chain of latencies, together the matrix pipes and LDS.  The constants describe
-// every tile size on 171 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues) within 12-18 % (root mean
-// square); the size picked by them is on average within 1 % of the best one measured, at worst 9 %.  Examples, in us, 128 x 128
-// compiler-scheduled loop before -> now: 100 x 4096 x 12288 167 -> 36 (64 x 32), 391 x 1024 x 3072 44 -> 10 (64 x 32),
-// 777 x 6144 x 1024 with SwiGLU 23 -> 17 (128 x 128), 3699 x 1024 x 3072 49 -> 30 (128 x 128, three stages).
+// many tiles share the unit: alone it is a chain of latencies, together the matrix pipes and LDS.  The constants were fit to loops
+// on 32x32x16 MFMAs with operands that stay in the caches (256 x 256: to those of today); with weights from memory and the loops of
+// today they are off by 11-23 % (root mean square) per tile, 256 x 256 by 30 % where the chip is not full, but what counts is the pick: on
+// 265 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues) it is on average 0.5 % above the best tile, at worst 15 %
+// (391 x 2560 x 9728 stored: 59 us on 128 x 64, 51 on 64 x 64).  Examples, us with weights from memory, 32x32x16 loops -> now: 100 x 4096 x 12288
+// 38.8 -> 38.7 (64 x 32), 391 x 1024 x 3072 10.2 -> 10.0 (64 x 32), 33 x 2560 x 9728 19.3 -> 18.5 (32 x 32), 777 x 6144 x 1024 with SwiGLU
+// 19.7 -> 19.1 (128 x 128), 3699 x 1024 x 3072 34.0 -> 33.4 (128 x 128, four stages).
 // (256 x 256: on chips of different speed a slice takes 1.34-1.7 us, the fixed part 11 us with SwiGLU and 17 with a residual or a
 // head; 1024 x 24576 x 4096 with SwiGLU 233 us on 128 x 128 tiles, 203 on these; 1536 x 6144 x 4096 with heads 103 and 90.)
 struct TileCost {
@@ -509,10 +512,10 @@ enum { kTile256, kTile128, kTile128Deep, kTile128x64, kTile64, kTile32x64, kTile
 static constexpr TileCost kTileCost[kTileKinds] = {
     {256, 256, 1, 1.45f, 1.45f, 9.2f}, {128, 128, 2, 0.72f, 0.50f, 4.5f}, {128, 128, 1, 0.52f, 0.52f, 3.4f}, {128, 64, 2, 0.34f, 0.36f, 2.3f},
     {64, 64, 2, 0.204f, 0.204f, 2.1f}, {32, 64, 3, 0.176f, 0.149f, 2.4f}, {64, 32, 1, 0.128f, 0.128f, 2.3f}, {32, 32, 2, 0.106f, 0.083f, 2.6f}};
-// The fused q/k/v projection: tiles whose waves own whole heads (34 launches of 1 to 12000 rows: within 11-19 %, the picked
-// size on average within 1 % of the best, at worst 12 %).  Its epilogue is longer: two dependent loads (position, rotation)
+// The fused q/k/v projection: tiles whose waves own whole heads (the same: off by 9-18 %, 256 x 256 by 25 %; the pick is the best tile of
+// all 34 launches of 1 to 12000 rows).  Its epilogue is longer: two dependent loads (position, rotation)
 // and the per-head arithmetic.  391 x 4096 x 1024: 11 us, where the projection to fp32 and its two finishing kernels took 48;
-// 777 x 6144 x 4096: 56.
+// 777 x 6144 x 4096: 62.
 enum { kHead256, kHead128, kHead128Deep, kHead64, kHeadKinds };
 static constexpr TileCost kHeadCost[kHeadKinds] = {
     {256, 256, 1, 1.40f, 1.40f, 17.f}, {128, 128, 2, 0.70f, 0.55f, 5.5f}, {128, 128, 1, 0.52f, 0.52f, 5.0f}, {64, 128, 2, 0.29f, 0.37f, 5.0f}};
