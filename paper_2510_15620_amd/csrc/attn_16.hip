@@ -52,10 +52,10 @@ __device__ __forceinline__ void half_wave_pair(float x, float &lo, float &hi) {
   hi = __uint_as_float(r[1]);
 }
 
-template <typename OT, int G, int NW>
+template <typename OT, int G, int NW, typename Items>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attention_16_kernel(const OT *__restrict__ QK, const f16 *__restrict__ Vt, int64_t vt_stride,
-                         const AttnTile *__restrict__ tiles, int nq, int nkv, OT *__restrict__ out) {
+                         const Items items, int nq, int nkv, OT *__restrict__ out) {
   typedef typename Mfma<OT>::vec8 vec8;
   typedef typename Mfma<OT>::vec4 vec4;
   constexpr int QB = NW / G;             // 32-query blocks per item
@@ -69,7 +69,7 @@ void attention_16_kernel(const OT *__restrict__ QK, const f16 *__restrict__ Vt, 
   // consecutive workgroup ids go to consecutive XCDs: with the KV head in the low digits of the id, all query blocks
   // of one (sequence, KV head) run on one XCD when nkv is a multiple of 8, one after the other, so its L2 holds their K/V
   const int kvh = blockIdx.x % nkv;
-  const AttnTile it = tiles[blockIdx.x / nkv];
+  const AttnTile it = items(blockIdx.x / nkv);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int hq = kvh * G + wave % G, qb = wave / G;
   const int row_elems = (nq + nkv) * HD;
@@ -302,27 +302,28 @@ int attention_16_block_queries(int nq, int nkv) {
   return 32 * (waves_per_group(g) / g);
 }
 
-template <typename OT, int G, int NW>
-static hipError_t launch_one(int n_groups, const OT *QK, const f16 *Vt, int64_t vt_stride, const AttnTile *tiles, int nq, int nkv,
+template <typename OT, int G, int NW, typename Items>
+static hipError_t launch_one(int n_groups, const OT *QK, const f16 *Vt, int64_t vt_stride, const Items &items, int nq, int nkv,
                              OT *out, hipStream_t s) {
-  attention_16_kernel<OT, G, NW><<<n_groups, NW * 64, 0, s>>>(QK, Vt, vt_stride, tiles, nq, nkv, out);
+  attention_16_kernel<OT, G, NW, Items><<<n_groups, NW * 64, 0, s>>>(QK, Vt, vt_stride, items, nq, nkv, out);
   return hipGetLastError();
 }
 
-template <typename OT>
-static hipError_t launch_typed(int n_groups, int g, const OT *QK, const f16 *Vt, int64_t vt_stride, const AttnTile *tiles, int nq,
+template <typename OT, typename Items>
+static hipError_t launch_typed(int n_groups, int g, const OT *QK, const f16 *Vt, int64_t vt_stride, const Items &items, int nq,
                                int nkv, OT *out, hipStream_t s) {
   switch (g) {
-    case 1: return launch_one<OT, 1, 4>(n_groups, QK, Vt, vt_stride, tiles, nq, nkv, out, s);
-    case 2: return launch_one<OT, 2, 4>(n_groups, QK, Vt, vt_stride, tiles, nq, nkv, out, s);
-    case 4: return launch_one<OT, 4, 4>(n_groups, QK, Vt, vt_stride, tiles, nq, nkv, out, s);
-    default: return launch_one<OT, 8, 8>(n_groups, QK, Vt, vt_stride, tiles, nq, nkv, out, s);
+    case 1: return launch_one<OT, 1, 4>(n_groups, QK, Vt, vt_stride, items, nq, nkv, out, s);
+    case 2: return launch_one<OT, 2, 4>(n_groups, QK, Vt, vt_stride, items, nq, nkv, out, s);
+    case 4: return launch_one<OT, 4, 4>(n_groups, QK, Vt, vt_stride, items, nq, nkv, out, s);
+    default: return launch_one<OT, 8, 8>(n_groups, QK, Vt, vt_stride, items, nq, nkv, out, s);
   }
 }
 
-int launch_attention_16(int dtype, const void *QK, const void *Vt, int64_t vt_stride, const AttnTile *tiles, int n_tiles,
-                        int T, int nq, int nkv, int hd, void *out, hipStream_t s) {
-  PRISM_REQUIRE(QK && Vt && tiles && out && n_tiles >= 0 && T >= 0 && is16(dtype), PRISM_EINVAL, "attention: bad arguments");
+template <typename Items>
+static int launch_items(int dtype, const void *QK, const void *Vt, int64_t vt_stride, const Items &items, int n_tiles, int nq, int nkv, int hd,
+                        void *out, hipStream_t s) {
+  PRISM_REQUIRE(QK && Vt && out && n_tiles >= 0 && is16(dtype), PRISM_EINVAL, "attention: bad arguments");
   PRISM_REQUIRE(attention_16_supported(nq, nkv, hd), PRISM_EUNSUPPORTED,
                 "attention: 16-bit modes need head_dim 128 and 1, 2, 4 or 8 query heads per KV head (got hd %d, %d/%d)", hd, nq, nkv);
   PRISM_REQUIRE(vt_stride % 8 == 0, PRISM_EINVAL, "attention: V^T row stride must be a multiple of 8");
@@ -333,10 +334,22 @@ int launch_attention_16(int dtype, const void *QK, const void *Vt, int64_t vt_st
   if (n_tiles == 0) return PRISM_OK;
   const int n_groups = n_tiles * nkv;
   if (dtype == PRISM_DTYPE_BF16)
-    PRISM_HIP(launch_typed<bf16>(n_groups, nq / nkv, (const bf16 *)QK, (const f16 *)Vt, vt_stride, tiles, nq, nkv, (bf16 *)out, s));
+    PRISM_HIP(launch_typed<bf16>(n_groups, nq / nkv, (const bf16 *)QK, (const f16 *)Vt, vt_stride, items, nq, nkv, (bf16 *)out, s));
   else
-    PRISM_HIP(launch_typed<f16>(n_groups, nq / nkv, (const f16 *)QK, (const f16 *)Vt, vt_stride, tiles, nq, nkv, (f16 *)out, s));
+    PRISM_HIP(launch_typed<f16>(n_groups, nq / nkv, (const f16 *)QK, (const f16 *)Vt, vt_stride, items, nq, nkv, (f16 *)out, s));
   return PRISM_OK;
+}
+
+int launch_attention_16(int dtype, const void *QK, const void *Vt, int64_t vt_stride, const AttnTile *tiles, int n_tiles,
+                        int T, int nq, int nkv, int hd, void *out, hipStream_t s) {
+  PRISM_REQUIRE(tiles && T >= 0, PRISM_EINVAL, "attention: bad arguments");
+  return launch_items(dtype, QK, Vt, vt_stride, AttnList{tiles}, n_tiles, nq, nkv, hd, out, s);
+}
+
+int launch_attention_16_seqs(int dtype, const void *QK, const void *Vt, int64_t vt_stride, const AttnSeqs &seqs, int nq, int nkv, int hd,
+                             void *out, hipStream_t s) {
+  PRISM_REQUIRE(seqs.n > 0 && seqs.n <= kAttnSeqs && seqs.bq == attention_16_block_queries(nq, nkv), PRISM_EINVAL, "attention: bad sequences");
+  return launch_items(dtype, QK, Vt, vt_stride, seqs, seqs.end[seqs.n - 1], nq, nkv, hd, out, s);
 }
 
 }  // namespace prism

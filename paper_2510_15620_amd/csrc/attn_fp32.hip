@@ -19,11 +19,11 @@
 
 namespace prism {
 
-template <int NB>
-__global__ __launch_bounds__(256) void attention_fp32_kernel(const float *__restrict__ QKV, const AttnTile *__restrict__ tiles,
+template <int NB, typename Items>
+__global__ __launch_bounds__(256) void attention_fp32_kernel(const float *__restrict__ QKV, const Items items,
                                                              int nq, int nkv, float *__restrict__ out) {
   constexpr int HD = 16 * NB;
-  const AttnTile it = tiles[blockIdx.x / nq];
+  const AttnTile it = items(blockIdx.x / nq);
   const int h = blockIdx.x % nq, kvh = h / (nq / nkv);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
   const int L = it.seq_len, q0 = it.q0 + wave * 16;
@@ -193,21 +193,31 @@ __global__ __launch_bounds__(128) void attention_fp32_any_kernel(const float *__
 
 bool attention_fp32_tiled(int hd) { return hd == 32 || hd == 64 || hd == 128; }
 
+template <typename Items>
+static int launch_items(const float *QKV, const Items &items, int n_tiles, int nq, int nkv, int hd, float *out, hipStream_t s) {
+  if (n_tiles == 0) return PRISM_OK;
+  PRISM_REQUIRE((int64_t)n_tiles * nq < (int64_t)1 << 31, PRISM_EINVAL, "attention: too many work items (%d x %d)", n_tiles, nq);
+  const int grid = n_tiles * nq;
+  if (hd == 32) attention_fp32_kernel<2><<<grid, 256, 0, s>>>(QKV, items, nq, nkv, out);
+  else if (hd == 64) attention_fp32_kernel<4><<<grid, 256, 0, s>>>(QKV, items, nq, nkv, out);
+  else attention_fp32_kernel<8><<<grid, 256, 0, s>>>(QKV, items, nq, nkv, out);
+  PRISM_HIP(hipGetLastError());
+  return PRISM_OK;
+}
+
+int launch_attention_fp32_seqs(const float *QKV, const AttnSeqs &seqs, int nq, int nkv, int hd, float *out, hipStream_t s) {
+  PRISM_REQUIRE(QKV && out && nq > 0 && nkv > 0 && nq % nkv == 0 && attention_fp32_tiled(hd) && ((uintptr_t)QKV | (uintptr_t)out) % 16 == 0 &&
+                seqs.n > 0 && seqs.n <= kAttnSeqs && seqs.bq == kAttn32BQ, PRISM_EINVAL, "attention fp32: bad arguments");
+  return launch_items(QKV, seqs, seqs.end[seqs.n - 1], nq, nkv, hd, out, s);
+}
+
 int launch_attention_fp32(const float *QKV, const int32_t *pos, const AttnTile *tiles, int n_tiles, int T, int nq, int nkv, int hd, float *out,
                           hipStream_t s) {
   PRISM_REQUIRE(QKV && out && T >= 0 && nq > 0 && nkv > 0 && nq % nkv == 0 && hd > 0, PRISM_EINVAL,
                 "attention fp32: bad arguments");
   if (T == 0) return PRISM_OK;
-  if (tiles && attention_fp32_tiled(hd) && ((uintptr_t)QKV | (uintptr_t)out) % 16 == 0) {
-    if (n_tiles == 0) return PRISM_OK;
-    PRISM_REQUIRE((int64_t)n_tiles * nq < (int64_t)1 << 31, PRISM_EINVAL, "attention: too many work items (%d x %d)", n_tiles, nq);
-    const int grid = n_tiles * nq;
-    if (hd == 32) attention_fp32_kernel<2><<<grid, 256, 0, s>>>(QKV, tiles, nq, nkv, out);
-    else if (hd == 64) attention_fp32_kernel<4><<<grid, 256, 0, s>>>(QKV, tiles, nq, nkv, out);
-    else attention_fp32_kernel<8><<<grid, 256, 0, s>>>(QKV, tiles, nq, nkv, out);
-    PRISM_HIP(hipGetLastError());
-    return PRISM_OK;
-  }
+  if (tiles && attention_fp32_tiled(hd) && ((uintptr_t)QKV | (uintptr_t)out) % 16 == 0)
+    return launch_items(QKV, AttnList{tiles}, n_tiles, nq, nkv, hd, out, s);
   PRISM_REQUIRE(pos, PRISM_EINVAL, "attention fp32: bad arguments");
   const size_t lds = (size_t)(PRISM_MAX_SEQ + hd) * sizeof(float);
   PRISM_REQUIRE(lds <= 64 * 1024, PRISM_EUNSUPPORTED, "attention fp32: head_dim %d too large", hd);

@@ -132,13 +132,16 @@ int launch_convert_bf16(const void *src, int64_t n, int dtype, void *dst, hipStr
 // cos/sin table for RoPE: tab[pos * (hd/2) + i] = (cos, sin)(pos * base^(-2i/hd)), evaluated in fp64; transposed:
 // tab[i * n_pos + pos]
 int launch_rope_table(float2 *tab, int n_pos, int head_dim, float rope_base, hipStream_t s, bool transposed = false);
-// q/k per-head RMSNorm + RoPE from the fp32 projection, in place (fp32 mode)
+// q/k per-head RMSNorm + RoPE from the fp32 projection, in place (fp32 mode).  Without a table (rope_tab null; head sizes that
+// qk_finish_fp32_tiled names) the kernel evaluates the rotations itself, the same values
+bool qk_finish_fp32_tiled(int hd);
 int launch_qk_finish_fp32(float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv, int hd,
-                          float eps, int qk_norm, const float2 *rope_tab, hipStream_t s);
+                          float eps, int qk_norm, const float2 *rope_tab, float rope_base, hipStream_t s);
 // 16-bit modes: q, k -> QK [T, (nq+nkv)*hd] in the operand type; v -> Vt [nkv][hd][vt_stride], IEEE half (in bf16-operand
-// mode: bf16-rounded values)
+// mode: bf16-rounded values).  Where qkv_finish_16_direct holds the kernel evaluates the rotations itself; elsewhere it needs the table
+bool qkv_finish_16_direct(const void *QKV, const void *q_gain, const void *k_gain, int hd, int qk_norm, const void *QK);
 int launch_qkv_finish_16(int dtype, const float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv,
-                         int hd, float eps, int qk_norm, const float2 *rope_tab, void *QK, void *Vt, const int32_t *vt_col,
+                         int hd, float eps, int qk_norm, const float2 *rope_tab, float rope_base, void *QK, void *Vt, const int32_t *vt_col,
                          int64_t vt_stride, hipStream_t s);
 // Copies the last, incomplete group of 16 V^T columns of a chunk's shared query (positions [ql & ~15, ql), at columns
 // vt_column_of_key(position) of the chunk, whose query sequence starts at column 0) into the column range of each of n_seq
@@ -156,8 +159,36 @@ int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, co
 // out_base: the tile's output for position p goes to row out_base + p (normally row_base; it differs when the layout the
 // q/k rows were projected in is not the one the layer continues in).
 struct AttnTile { int32_t row_base, seq_len, q0, vt_col0, pre_len, pre_row0, out_base, reserved; };
+// Where a workgroup finds its work item: in a list in device memory (prism_select uploads one with each pool's metadata), or in
+// the launch's arguments, as the sequences themselves (a call of its own: no list to allocate, copy and wait for).  Item i of
+// the second kind is found by counting the sequences that end at or before it, 64 at a time, in one load latency; items are
+// in the list's order (sequence by sequence, last block of queries first).  256 sequences are 3 KiB of the 4 KiB that a launch's
+// arguments may take; longer calls go by a list.  8 sequences of 32-64 tokens, fp32 layer through the separate entry points, this
+// and the finishing kernel without a table: 133 -> 91 us; 7 sequences of 56-301 in bf16 92 -> 87.
+struct AttnList {
+  const AttnTile *tiles;
+  __device__ __forceinline__ AttnTile operator()(int i) const { return tiles[i]; }
+};
+static const int kAttnSeqs = 256;
+struct AttnSeqs {
+  int32_t n, bq;                                // sequences, queries of an item
+  int32_t end[kAttnSeqs];                       // items of sequences 0 .. s
+  int32_t cu[kAttnSeqs + 1], vt_col0[kAttnSeqs];
+  __device__ __forceinline__ AttnTile operator()(int i) const {
+    int s = 0;
+    for (int b = 0; b < n; b += 64) {
+      const int j = b + (int)(threadIdx.x & 63);
+      s += __popcll(__builtin_amdgcn_ballot_w64(j < n && end[j < n ? j : 0] <= i));
+    }
+    s = __builtin_amdgcn_readfirstlane(s);
+    const int row = cu[s];
+    return {row, cu[s + 1] - row, (end[s] - 1 - i) * bq, vt_col0[s], 0, 0, row, 0};
+  }
+};
 int launch_attention_16(int dtype, const void *QK, const void *Vt, int64_t vt_stride, const AttnTile *tiles, int n_tiles,
                         int T, int nq, int nkv, int hd, void *out, hipStream_t s);
+int launch_attention_16_seqs(int dtype, const void *QK, const void *Vt, int64_t vt_stride, const AttnSeqs &seqs, int nq, int nkv, int hd,
+                             void *out, hipStream_t s);
 bool attention_16_supported(int nq, int nkv, int hd);
 // fp32 attention.  tiles: work items of kAttn32BQ queries (row_base, seq_len, q0 and out_base are read), for the head sizes
 // that attention_fp32_tiled names; other head sizes go by pos[t], the position of token t in its sequence.
@@ -165,6 +196,7 @@ static const int kAttn32BQ = 64;
 bool attention_fp32_tiled(int hd);
 int launch_attention_fp32(const float *QKV, const int32_t *pos, const AttnTile *tiles, int n_tiles, int T, int nq, int nkv, int hd, float *out,
                           hipStream_t s);
+int launch_attention_fp32_seqs(const float *QKV, const AttnSeqs &seqs, int nq, int nkv, int hd, float *out, hipStream_t s);
 int attention_16_block_queries(int nq, int nkv);   // queries per AttnTile for this head grouping
 // Column of key p of a sequence in the V^T buffer, relative to the sequence's first column: within every group of 16
 // the keys are stored in the order 0-3, 8-11, 4-7, 12-15 (the order in which the matrix cores' accumulator layout hands

@@ -124,13 +124,17 @@ int launch_rmsnorm(const float *X, const void *gain, int T, int hidden, float ep
 // ------------------------------------------------------------------------------------------------
 // RoPE table, evaluated in fp64 and rounded once: (cos, sin)(pos * base^(-2 i / hd)) at tab[pos * half + i], or, transposed,
 // at tab[i * n_pos + pos] (the layout the fused q/k/v epilogue reads: consecutive tokens of a sequence are then neighbours).
+__device__ __forceinline__ float2 rotation(int pos, int i, int half, double log2_base) {
+  const double theta = exp2(-(double)i / (double)half * log2_base);
+  const double a = (double)pos * theta;
+  return make_float2((float)cos(a), (float)sin(a));
+}
+
 __global__ void rope_table_kernel(float2 *tab, int n_pos, int half, double log2_base, int transposed) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n_pos * half) return;
   const int pos = transposed ? idx % n_pos : idx / half, i = transposed ? idx / n_pos : idx % half;
-  const double theta = exp2(-(double)i / (double)half * log2_base);
-  const double a = (double)pos * theta;
-  tab[idx] = make_float2((float)cos(a), (float)sin(a));
+  tab[idx] = rotation(pos, i, half, log2_base);
 }
 
 int launch_rope_table(float2 *tab, int n_pos, int head_dim, float rope_base, hipStream_t s, bool transposed) {
@@ -222,80 +226,92 @@ __global__ __launch_bounds__(256) void qk_finish_kernel(float *__restrict__ QKV,
 }
 
 // The same and the V part in one launch, for the 16-bit modes at head_dim 128.  Launch- and latency-bound at the sizes it is
-// for (the fused projection serves large ones).  Blocks of 16 tokens x one group of 4 heads (y): q and k heads take 16 lanes
-// each, a lane holding 4 + 4 values of the two rotation halves as 16-byte loads of all its tokens issued together; V heads
-// (last y) go through LDS, 64 tokens at a time, and leave as 64 consecutive tokens of one d per wave instruction.
-// 0.6B shape, 1154 tokens: 37 us as two kernels that waited for each value in turn.
+// for (the fused projection serves large ones).  V first: a workgroup takes 64 tokens of one head through LDS, and they leave
+// as 64 consecutive tokens of one d per wave instruction.  Then q and k: a workgroup takes all heads of 4 tokens, 16 lanes each,
+// a lane holding 4 + 4 values of the two rotation halves; a lane's token stays the same over its heads.  So the tokens' 4 x 64
+// rotations are one fp64 evaluation per thread, while the first values are on their way, and no table has to be allocated,
+// filled and waited for: 1154 tokens of 16 + 8 heads 3.0 (table) + 9.9 us in two launches -> 9.8 in one.
 template <typename T>
 __global__ __launch_bounds__(256) void qkv_finish_16_kernel(const float *__restrict__ QKV, const int32_t *__restrict__ pos,
                                                             const T *__restrict__ q_gain, const T *__restrict__ k_gain, int n_tok,
-                                                            int nq, int nkv, float eps, int qk_norm,
-                                                            const float2 *__restrict__ rope_tab, T *__restrict__ out,
+                                                            int nq, int nkv, float eps, int qk_norm, double log2_base, T *__restrict__ out,
                                                             f16 *__restrict__ Vt, const int32_t *__restrict__ vt_col, int64_t vt_stride) {
-  constexpr int HD = 128, kTok = 16;
+  constexpr int HD = 128, kTok = 4, kHeads = 6;              // tokens of a workgroup, heads whose values a lane requests together
   typedef typename Mfma<T>::vec4 vec4;
-  __shared__ f16 tile[kTok * 4][HD + 2];
-  const int heads = nq + nkv, row = (nq + 2 * nkv) * HD, groups = (heads + 3) / 4;
+  const int heads = nq + nkv, row = (nq + 2 * nkv) * HD;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if ((int)blockIdx.y < groups) {
-    const int h = blockIdx.y * 4 + (lane >> 4), i = (lane & 15) * 4;            // head, first of the lane's 4 rotation pairs
-    if (h >= heads) return;
-    const T *g = h < nq ? q_gain : k_gain;
-    vec4 ga, gb;
+  const int v_groups = (n_tok + 63) / 64 * nkv;
+  if ((int)blockIdx.x >= v_groups) {
+    __shared__ __align__(16) float2 rot[kTok][HD / 2];
+    const int t0 = ((int)blockIdx.x - v_groups) * kTok;
+    const int i = (lane & 15) * 4, tk = lane >> 4;           // first of the lane's 4 rotation pairs, its token
+    const int t = t0 + tk < n_tok ? t0 + tk : n_tok - 1;
+    const int rt = t0 + wave < n_tok ? t0 + wave : n_tok - 1;
+    const int rpos = pos[rt];
+    vec4 gq[2], gk[2];
     if (qk_norm) {
-      ga = *reinterpret_cast<const vec4 *>(g + i);
-      gb = *reinterpret_cast<const vec4 *>(g + i + 64);
+      gq[0] = *reinterpret_cast<const vec4 *>(q_gain + i);
+      gq[1] = *reinterpret_cast<const vec4 *>(q_gain + i + 64);
+      gk[0] = *reinterpret_cast<const vec4 *>(k_gain + i);
+      gk[1] = *reinterpret_cast<const vec4 *>(k_gain + i + 64);
     }
-    constexpr int N = kTok / 4;                                                // tokens per wave
-    const int t0 = blockIdx.x * kTok + wave * N;
-    f32x4 a[N], b[N], c0[N], c1[N];
+    const float *x = QKV + (int64_t)t * row + i;
+    T *o = out + (int64_t)t * heads * HD + i;
+    f32x4 a[kHeads], b[kHeads];
+    auto fetch = [&](int h0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-      const int t = t0 + k < n_tok ? t0 + k : n_tok - 1;
-      const float *x = QKV + (int64_t)t * row + h * HD + i;
-      a[k] = *reinterpret_cast<const f32x4 *>(x);
-      b[k] = *reinterpret_cast<const f32x4 *>(x + 64);
-      const f32x4 *cs = reinterpret_cast<const f32x4 *>(rope_tab + (int64_t)pos[t] * 64 + i);
-      c0[k] = cs[0];
-      c1[k] = cs[1];
-    }
+      for (int k = 0; k < kHeads; ++k) {
+        const int h = h0 + 4 * k < heads ? h0 + 4 * k : heads - 1;
+        a[k] = *reinterpret_cast<const f32x4 *>(x + h * HD);
+        b[k] = *reinterpret_cast<const f32x4 *>(x + h * HD + 64);
+      }
+    };
+    fetch(wave);
+    rot[wave][lane] = rotation(rpos, lane, HD / 2, log2_base);
+    __syncthreads();
+    float2 cs[4];
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-      float r = 1.f;
-      if (qk_norm) {
-        // pairs (d, d + 64), then halving over the bits of d, 32 first: the order of wave_sum with a pair per lane
-        float p[4];
+    for (int q = 0; q < 4; ++q) cs[q] = rot[tk][i + q];
+    for (int h0 = wave; h0 < heads; h0 += 4 * kHeads) {
+      if (h0 != wave) fetch(h0);
+#pragma unroll
+      for (int k = 0; k < kHeads; ++k) {
+        const int h = h0 + 4 * k;
+        if (h >= heads) break;                               // the same for the whole wave
+        float r = 1.f;
+        if (qk_norm) {
+          // pairs (d, d + 64), then halving over the bits of d, 32 first: the order of wave_sum with a pair per lane
+          float p[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            p[q] = __builtin_fmaf(a[k][q], a[k][q], b[k][q] * b[k][q]);
+#pragma unroll
+            for (int m = 8; m > 0; m >>= 1) p[q] += __shfl_xor(p[q], m, 64);
+          }
+          const float ss = (p[0] + p[2]) + (p[1] + p[3]);
+          r = 1.0f / sqrtf(ss / (float)HD + eps);
+        }
+        vec4 lo, hi;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          p[q] = __builtin_fmaf(a[k][q], a[k][q], b[k][q] * b[k][q]);
-#pragma unroll
-          for (int o = 8; o > 0; o >>= 1) p[q] += __shfl_xor(p[q], o, 64);
+          float u = a[k][q], v = b[k][q];
+          if (qk_norm) {
+            u = u * r * to_f32(h < nq ? gq[0][q] : gk[0][q]);
+            v = v * r * to_f32(h < nq ? gq[1][q] : gk[1][q]);
+          }
+          lo[q] = from_f32<T>(__builtin_fmaf(u, cs[q].x, -(v * cs[q].y)));
+          hi[q] = from_f32<T>(__builtin_fmaf(v, cs[q].x, u * cs[q].y));
         }
-        const float ss = (p[0] + p[2]) + (p[1] + p[3]);
-        r = 1.0f / sqrtf(ss / (float)HD + eps);
-      }
-      if (t0 + k >= n_tok) continue;
-      vec4 lo, hi;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float u = a[k][q], v = b[k][q];
-        if (qk_norm) {
-          u = u * r * to_f32(ga[q]);
-          v = v * r * to_f32(gb[q]);
+        if (t0 + tk < n_tok) {
+          *reinterpret_cast<vec4 *>(o + h * HD) = lo;
+          *reinterpret_cast<vec4 *>(o + h * HD + 64) = hi;
         }
-        const float c = q < 2 ? c0[k][2 * q] : c1[k][2 * q - 4], s = q < 2 ? c0[k][2 * q + 1] : c1[k][2 * q - 3];
-        lo[q] = from_f32<T>(__builtin_fmaf(u, c, -(v * s)));
-        hi[q] = from_f32<T>(__builtin_fmaf(v, c, u * s));
       }
-      T *o = out + ((int64_t)(t0 + k) * heads + h) * HD + i;
-      *reinterpret_cast<vec4 *>(o) = lo;
-      *reinterpret_cast<vec4 *>(o + 64) = hi;
     }
     return;
   }
-  // V: blocks of 64 tokens of one head
-  if (blockIdx.x % 4 != 0) return;
-  const int h = blockIdx.y - groups, t0 = blockIdx.x * kTok;
+  __shared__ f16 tile[64][HD + 2];
+  const int h = blockIdx.x % nkv, t0 = blockIdx.x / nkv * 64;
   const float *src = QKV + (int64_t)(heads + h) * HD;
   f32x4 v[8];
 #pragma unroll
@@ -317,63 +333,66 @@ __global__ __launch_bounds__(256) void qkv_finish_16_kernel(const float *__restr
 }
 
 // The same in place for the fp32 mode where a head's pairs fit a power of two of lanes (head sizes 32, 64 and 128): P lanes per
-// (token, head), so that no lane idles, and U of them per lane with their loads issued together: four where that still gives
-// every compute unit two workgroups, one below (354 tokens: 3.6 us, with four 5.0).
-// 12859 tokens, 6 heads of 64: 26 -> 12 us.  The sum of squares keeps wave_sum's order (lanes beyond P added zeros).
+// token, so that no lane idles, each with the same pair of up to U heads, their loads issued together; one rotation serves all
+// of them, from the table or, where there is none (a call of its own), evaluated while the loads are on their way.  One wave per
+// workgroup: a few hundred tokens then reach most compute units.  The sum of squares keeps wave_sum's order (lanes beyond P
+// added zeros).  6 heads of 64, a call of its own: 12859 tokens 4.8 (table) + 11.2 us -> 12.0, 354 tokens 2.6 + 2.8 us and the gap
+// between them -> 5.1.
 template <int P, int U>
-__global__ __launch_bounds__(256) void qk_finish_fp32_kernel(float *__restrict__ QKV, const int32_t *__restrict__ pos,
-                                                             const float *__restrict__ q_gain, const float *__restrict__ k_gain, int64_t items,
-                                                             int nq, int nkv, float eps, int qk_norm, const float2 *__restrict__ rope_tab) {
-  constexpr int HD = 2 * P, G = 256 / P;                     // G items side by side in a workgroup, U rounds
-  const int heads = nq + nkv, i = threadIdx.x % P;
-  const int64_t first = (int64_t)blockIdx.x * (G * U) + threadIdx.x / P;
-  float a[U], b[U];
-  float2 cs[U];
-  float *x[U];
-  int h[U];
+__global__ __launch_bounds__(64) void qk_finish_fp32_kernel(float *__restrict__ QKV, const int32_t *__restrict__ pos,
+                                                            const float *__restrict__ q_gain, const float *__restrict__ k_gain, int n_tok,
+                                                            int nq, int nkv, float eps, int qk_norm, const float2 *__restrict__ rope_tab,
+                                                            double log2_base) {
+  constexpr int HD = 2 * P, G = 64 / P;                      // tokens of a workgroup
+  const int heads = nq + nkv, i = threadIdx.x % P, h0 = blockIdx.y * U;
+  const int tw = blockIdx.x * G + threadIdx.x / P, t = tw < n_tok ? tw : n_tok - 1;
+  float *x = QKV + (int64_t)t * (nq + 2 * nkv) * HD + i;
+  const int p = pos[t];
+  float a[U], b[U], gq[2], gk[2];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int64_t item = first + u * G < items ? first + u * G : items - 1;
-    const int t = (int)(item / heads);
-    h[u] = (int)(item - (int64_t)t * heads);
-    x[u] = QKV + (int64_t)t * (nq + 2 * nkv) * HD + h[u] * HD + i;
-    a[u] = x[u][0];
-    b[u] = x[u][P];
-    cs[u] = rope_tab[(int64_t)pos[t] * P + i];
+    const int h = h0 + u < heads ? h0 + u : heads - 1;
+    a[u] = x[h * HD];
+    b[u] = x[h * HD + P];
   }
+  if (qk_norm) {
+    gq[0] = q_gain[i];
+    gq[1] = q_gain[i + P];
+    gk[0] = k_gain[i];
+    gk[1] = k_gain[i + P];
+  }
+  const float2 cs = rope_tab ? rope_tab[(int64_t)p * P + i] : rotation(p, i, P, log2_base);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
+    const int h = h0 + u;
+    if (h >= heads) break;                                   // the same for the whole wave
     if (qk_norm) {
       float ss = __builtin_fmaf(a[u], a[u], b[u] * b[u]);
 #pragma unroll
       for (int o = P / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
       const float r = 1.0f / sqrtf(ss / (float)HD + eps);
-      const float *g = h[u] < nq ? q_gain : k_gain;
-      a[u] = a[u] * r * g[i];
-      b[u] = b[u] * r * g[i + P];
+      a[u] = a[u] * r * (h < nq ? gq[0] : gk[0]);
+      b[u] = b[u] * r * (h < nq ? gq[1] : gk[1]);
     }
-    if (first + u * G >= items) return;
-    x[u][0] = __builtin_fmaf(a[u], cs[u].x, -(b[u] * cs[u].y));
-    x[u][P] = __builtin_fmaf(b[u], cs[u].x, a[u] * cs[u].y);
+    if (tw < n_tok) {
+      x[h * HD] = __builtin_fmaf(a[u], cs.x, -(b[u] * cs.y));
+      x[h * HD + P] = __builtin_fmaf(b[u], cs.x, a[u] * cs.y);
+    }
   }
 }
 
+bool qk_finish_fp32_tiled(int hd) { return hd == 32 || hd == 64 || hd == 128; }
+
 int launch_qk_finish_fp32(float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv, int hd,
-                          float eps, int qk_norm, const float2 *rope_tab, hipStream_t s) {
-  PRISM_REQUIRE(QKV && pos && rope_tab && T >= 0 && nq > 0 && nkv > 0 && hd > 0 && hd % 2 == 0, PRISM_EINVAL,
-                "qk_finish: bad arguments");
+                          float eps, int qk_norm, const float2 *rope_tab, float rope_base, hipStream_t s) {
+  PRISM_REQUIRE(QKV && pos && (rope_tab || (qk_finish_fp32_tiled(hd) && rope_base > 0)) && T >= 0 && nq > 0 && nkv > 0 && hd > 0 && hd % 2 == 0,
+                PRISM_EINVAL, "qk_finish: bad arguments");
   PRISM_REQUIRE(!qk_norm || (q_gain && k_gain), PRISM_EINVAL, "qk_finish: gains missing");
   if (T == 0) return PRISM_OK;
-  const int64_t items = (int64_t)T * (nq + nkv);
   auto run = [&](auto p) {
-    constexpr int P = decltype(p)::value;
-    auto go = [&](auto u) {
-      constexpr int U = decltype(u)::value;
-      qk_finish_fp32_kernel<P, U><<<cdiv(items, 256 / P * U), 256, 0, s>>>(QKV, pos, (const float *)q_gain, (const float *)k_gain, items, nq, nkv, eps,
-                                                                          qk_norm, rope_tab);
-    };
-    if (cdiv(items, 256 / P * 4) >= 512) go(std::integral_constant<int, 4>{});
-    else go(std::integral_constant<int, 1>{});
+    constexpr int P = decltype(p)::value, U = 6;
+    qk_finish_fp32_kernel<P, U><<<dim3(cdiv(T, 64 / P), cdiv(nq + nkv, U)), 64, 0, s>>>(QKV, pos, (const float *)q_gain, (const float *)k_gain, T, nq,
+                                                                                     nkv, eps, qk_norm, rope_tab, log2((double)rope_base));
   };
   if (hd == 32) run(std::integral_constant<int, 16>{});
   else if (hd == 64) run(std::integral_constant<int, 32>{});
@@ -408,20 +427,25 @@ __global__ __launch_bounds__(256) void v_finish_kernel(const float *__restrict__
   }
 }
 
+bool qkv_finish_16_direct(const void *QKV, const void *q_gain, const void *k_gain, int hd, int qk_norm, const void *QK) {
+  return hd == 128 && (uintptr_t)QKV % 16 == 0 && ((uintptr_t)QK | (qk_norm ? (uintptr_t)q_gain | (uintptr_t)k_gain : 0)) % 8 == 0;
+}
+
 int launch_qkv_finish_16(int dtype, const float *QKV, const int32_t *pos, const void *q_gain, const void *k_gain, int T, int nq, int nkv,
-                         int hd, float eps, int qk_norm, const float2 *rope_tab, void *QK, void *Vt, const int32_t *vt_col,
+                         int hd, float eps, int qk_norm, const float2 *rope_tab, float rope_base, void *QK, void *Vt, const int32_t *vt_col,
                          int64_t vt_stride, hipStream_t s) {
-  PRISM_REQUIRE(QKV && pos && rope_tab && QK && Vt && vt_col && T >= 0 && nq > 0 && nkv > 0 && is16(dtype) && hd > 0 && hd <= 128, PRISM_EINVAL,
+  const bool direct = qkv_finish_16_direct(QKV, q_gain, k_gain, hd, qk_norm, QK);
+  PRISM_REQUIRE(QKV && pos && (direct ? rope_base > 0 : rope_tab != nullptr) && QK && Vt && vt_col && T >= 0 && nq > 0 && nkv > 0 && is16(dtype) && hd > 0 && hd <= 128, PRISM_EINVAL,
                 "qkv_finish: bad arguments");
   PRISM_REQUIRE(!qk_norm || (q_gain && k_gain), PRISM_EINVAL, "qk_finish: gains missing");
   if (T == 0) return PRISM_OK;
   auto run = [&](auto tag) {
     typedef decltype(tag) OT;
     const OT *gq = (const OT *)q_gain, *gk = (const OT *)k_gain;
-    // one launch where every access of four values is aligned; otherwise value by value
-    if (hd == 128 && ((uintptr_t)QKV | (uintptr_t)rope_tab) % 16 == 0 && ((uintptr_t)QK | (qk_norm ? (uintptr_t)gq | (uintptr_t)gk : 0)) % 8 == 0) {
-      qkv_finish_16_kernel<OT><<<dim3(cdiv(T, 16), (nq + nkv + 3) / 4 + nkv), 256, 0, s>>>(QKV, pos, gq, gk, T, nq, nkv, eps, qk_norm, rope_tab,
-                                                                                        (OT *)QK, (f16 *)Vt, vt_col, vt_stride);
+    // one launch where every access of four values is aligned; otherwise value by value, by the table
+    if (direct) {
+      qkv_finish_16_kernel<OT><<<cdiv(T, 64) * nkv + cdiv(T, 4), 256, 0, s>>>(QKV, pos, gq, gk, T, nq, nkv, eps, qk_norm, log2((double)rope_base),
+                                                                             (OT *)QK, (f16 *)Vt, vt_col, vt_stride);
       return;
     }
     qk_finish_kernel<OT><<<cdiv((int64_t)T * (nq + nkv), 4), 256, 0, s>>>(const_cast<float *>(QKV), pos, gq, gk, T, nq, nkv, hd, eps, qk_norm, rope_tab,

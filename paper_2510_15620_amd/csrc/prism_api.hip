@@ -864,7 +864,7 @@ static int run_layer(prism_ctx *c, const Plan &p, const MetaOff &mo, float *X, c
     }, Tc));
     if (!bf) PRISM_TRY(timed_span(c, 5, 0.0, [&] {
       return launch_qk_finish_fp32((float *)c->QKV, pos, wbuf + L.q_norm, wbuf + L.k_norm, Tc, m.n_q_heads, m.n_kv_heads, m.head_dim,
-                                   m.rms_eps, m.qk_norm, c->rope_tab, s);
+                                   m.rms_eps, m.qk_norm, c->rope_tab, m.rope_base, s);
     }));
     if (p.ql % 16 != 0)   // the query's last, incomplete group of V^T columns goes into every sequence's columns
       PRISM_TRY(timed_span(c, 5, 0.0, [&] {
@@ -1364,14 +1364,18 @@ extern "C" int prism_op_qkv_finish(int32_t dtype, void *QKV, const int32_t *pos,
   PRISM_REQUIRE(max_pos > 0 && max_pos <= PRISM_MAX_SEQ && head_dim > 0 && head_dim % 2 == 0, PRISM_EINVAL, "qkv_finish: max_pos / head_dim");
   PRISM_REQUIRE(dtype == PRISM_DTYPE_FP32 || (is16(dtype) && QK && Vt && vt_col && vt_stride > 0), PRISM_EINVAL, "qkv_finish: 16-bit modes need QK, Vt, vt_col");
   hipStream_t s = (hipStream_t)stream;
-  TmpDev tab;
-  PRISM_TRY(tab.alloc((size_t)max_pos * (head_dim / 2) * sizeof(float2)));
-  PRISM_TRY(launch_rope_table((float2 *)tab.p, max_pos, head_dim, rope_base, s));
+  PRISM_REQUIRE(rope_base > 0, PRISM_EINVAL, "rope table: bad arguments");
+  TmpDev tab;                                // stays empty where the finishing kernel evaluates the rotations itself
+  if (is16(dtype) ? !qkv_finish_16_direct(QKV, q_gain, k_gain, head_dim, qk_norm, QK) : !qk_finish_fp32_tiled(head_dim)) {
+    PRISM_TRY(tab.alloc((size_t)max_pos * (head_dim / 2) * sizeof(float2)));
+    PRISM_TRY(launch_rope_table((float2 *)tab.p, max_pos, head_dim, rope_base, s));
+  }
   if (is16(dtype))
     PRISM_TRY(launch_qkv_finish_16(dtype, (const float *)QKV, pos, q_gain, k_gain, T, n_q_heads, n_kv_heads, head_dim, eps, qk_norm,
-                                   (const float2 *)tab.p, QK, Vt, vt_col, vt_stride, s));
+                                   (const float2 *)tab.p, rope_base, QK, Vt, vt_col, vt_stride, s));
   else
-    PRISM_TRY(launch_qk_finish_fp32((float *)QKV, pos, q_gain, k_gain, T, n_q_heads, n_kv_heads, head_dim, eps, qk_norm, (const float2 *)tab.p, s));
+    PRISM_TRY(launch_qk_finish_fp32((float *)QKV, pos, q_gain, k_gain, T, n_q_heads, n_kv_heads, head_dim, eps, qk_norm, (const float2 *)tab.p,
+                                    rope_base, s));
   PRISM_HIP(hipStreamSynchronize(s));   // the table is freed on return
   return PRISM_OK;
 }
@@ -1418,12 +1422,31 @@ extern "C" int prism_op_attention(int32_t dtype, const void *QK, const void *Vt,
     PRISM_REQUIRE(cu[i + 1] > cu[i] && cu[i + 1] - cu[i] <= PRISM_MAX_SEQ, PRISM_EINVAL, "attention: sequence %d has bad length", i);
   const bool bf = is16(dtype);
   PRISM_REQUIRE(bf || dtype == PRISM_DTYPE_FP32, PRISM_EINVAL, "attention: unknown dtype %d", dtype);
+  // the sequences as launch arguments (see AttnSeqs); false where they don't fit
+  auto as_arguments = [&](AttnSeqs &a, int bq, const int32_t *col0) {
+    if (n_seqs > kAttnSeqs) return false;
+    a.n = n_seqs;
+    a.bq = bq;
+    for (int i = 0; i < n_seqs; ++i) {
+      a.end[i] = (i ? a.end[i - 1] : 0) + cdiv(cu[i + 1] - cu[i], bq);
+      a.cu[i] = cu[i];
+      a.vt_col0[i] = col0 ? col0[i] : 0;
+    }
+    a.cu[n_seqs] = T;
+    return true;
+  };
+  AttnSeqs args;
   if (!bf) {
     // what goes to the device: work items, or every token's position for the head sizes served without them.  The kernels
     // run over [0, T): tokens in front of the first sequence belong to none and attend to themselves only
     std::vector<AttnTile> tiles;
     std::vector<int32_t> pos;
     const bool tiled = attention_fp32_tiled(hd) && ((uintptr_t)QK | (uintptr_t)out) % 16 == 0;
+    if (tiled && cu[0] == 0 && as_arguments(args, kAttn32BQ, nullptr)) {
+      PRISM_TRY(launch_attention_fp32_seqs((const float *)QK, args, nq, nkv, hd, (float *)out, s));
+      PRISM_HIP(hipStreamSynchronize(s));
+      return PRISM_OK;
+    }
     for (int t = 0; t < cu[0]; ++t) {
       if (tiled) tiles.push_back({t, 1, 0, 0, 0, 0, t, 0});
       else pos.push_back(0);
@@ -1444,12 +1467,18 @@ extern "C" int prism_op_attention(int32_t dtype, const void *QK, const void *Vt,
   }
   PRISM_REQUIRE(attention_16_supported(nq, nkv, hd), PRISM_EUNSUPPORTED, "attention bf16: unsupported head shape");
   PRISM_REQUIRE(Vt && vt_col0 && vt_stride > 0, PRISM_EINVAL, "attention bf16: Vt / vt_col0 missing");
-  std::vector<AttnTile> tiles;
   const int bq = attention_16_block_queries(nq, nkv);
+  for (int i = 0; i < n_seqs; ++i)
+    PRISM_REQUIRE(vt_col0[i] >= 0 && vt_col0[i] % 64 == 0 && vt_col0[i] + round_up(cu[i + 1] - cu[i], 64) <= vt_stride, PRISM_EINVAL,
+                  "attention bf16: sequence %d: V^T columns must start at a multiple of 64 and fit the row stride", i);
+  if (as_arguments(args, bq, vt_col0)) {
+    PRISM_TRY(launch_attention_16_seqs(dtype, QK, Vt, vt_stride, args, nq, nkv, hd, out, s));
+    PRISM_HIP(hipStreamSynchronize(s));
+    return PRISM_OK;
+  }
+  std::vector<AttnTile> tiles;
   for (int i = 0; i < n_seqs; ++i) {
     const int L = cu[i + 1] - cu[i];
-    PRISM_REQUIRE(vt_col0[i] >= 0 && vt_col0[i] % 64 == 0 && vt_col0[i] + round_up(L, 64) <= vt_stride, PRISM_EINVAL,
-                  "attention bf16: sequence %d: V^T columns must start at a multiple of 64 and fit the row stride", i);
     for (int q0 = L > 0 ? (L - 1) / bq * bq : -1; q0 >= 0; q0 -= bq) tiles.push_back({cu[i], L, q0, vt_col0[i], 0, 0, cu[i], 0});
   }
   TmpDev d_tiles;

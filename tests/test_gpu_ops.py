@@ -609,6 +609,47 @@ def test_attention_fp32_sequences_that_start_behind_token_zero(hd):
     assert torch.equal(behind[:skip].cpu(), v.reshape(skip, -1))
 
 
+@pytest.mark.parametrize("dtype,nq,nkv,hd", [(torch.float32, 2, 1, 64), (torch.float16, 4, 2, 128), (torch.bfloat16, 8, 1, 128)])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 256])
+def test_attention_by_sequences_and_by_list(dtype, nq, nkv, hd, n):
+    """Up to 256 sequences travel in the launch's arguments, searched 64 at a time; 257 and more go by a list of work items.
+    The n sequences have the same bits alone and at the front of a longer call, of one block of queries and of several."""
+    lens = np.array([1 + (i * 37) % 150 for i in range(257)])
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col0, vt_col, ncol = _vt_layout(lens)
+    QKV = _rand((int(cu[-1]), (nq + 2 * nkv) * hd), dtype, 91, 1.0).to(DEV)
+    QK, Vt = QKV, None
+    if dtype != torch.float32:
+        QK = QKV[:, :(nq + nkv) * hd].contiguous()
+        Vt = torch.zeros(nkv, hd, ncol, dtype=torch.float16, device=DEV)
+        Vt[:, :, torch.from_numpy(vt_col.astype(np.int64)).to(DEV)] = QKV.view(len(QKV), -1, hd)[:, nq + nkv:].permute(1, 2, 0).to(torch.float16)
+    code = B.DTYPE_FP32 if Vt is None else B._dt(QK)
+    few, many = (torch.zeros(len(QKV), nq * hd, dtype=dtype, device=DEV) for _ in range(2))
+    B.op_attention(code, QK, Vt, ncol, cu[:n + 1], col0[:n], nq, nkv, hd, few)
+    B.op_attention(code, QK, Vt, ncol, cu, col0, nq, nkv, hd, many)
+    T = int(cu[n])
+    assert torch.equal(few[:T], many[:T]) and not few[T:].any()
+    assert many.float().abs().sum(1).min() > 0
+
+
+@pytest.mark.parametrize("nq,nkv", [(1, 1), (16, 8), (32, 8)])
+@pytest.mark.parametrize("T", [1, 3, 65])
+def test_qkv_finish_16_evaluates_the_tables_rotations(nq, nkv, T):
+    """The one-launch kernel (a part of a round of heads, one, more than one; tokens that fill no workgroup) against the kernels
+    that read the table, to the bit."""
+    hd, dtype = 128, torch.float16
+    pos = torch.arange(4096 - T, 4096, dtype=torch.int32, device=DEV)
+    col = torch.from_numpy(B.vt_column_of_key(np.arange(T, dtype=np.int32))).to(DEV)
+    QKV = _rand((T, (nq + 2 * nkv) * hd), torch.float32, 44, 1.5).to(DEV)
+    g = (1 + _rand((hd,), torch.float32, 41, 0.1)).to(dtype).to(DEV)
+    got = []
+    for x in (QKV, _off_by_one(QKV)):
+        QK, Vt = torch.zeros(T, (nq + nkv) * hd, dtype=dtype, device=DEV), torch.zeros(nkv, hd, 128, dtype=torch.float16, device=DEV)
+        B.op_qkv_finish(B._dt(QK), x, pos, 4096, g, g, nq, nkv, hd, 1e-6, 1e6, True, QK, Vt, col, 128)
+        got.append((QK, Vt))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 def test_attention_refuses_a_transposed_v_stride_beyond_its_32_bit_offsets():
     """The 16-bit kernel addresses the 128 rows of a KV head's V^T with 32-bit byte offsets: a row stride of 2^24 columns
     (128 rows x 2 bytes = 4 GiB) is refused before anything is launched (the buffers here are tiny and never touched)."""
