@@ -449,14 +449,18 @@ __global__ __launch_bounds__(WM *WN * 64, (stage_bytes<BM, BN, S>() > 81920 ? 1 
     else PRISM_RUN_TY(PRISM_KLOOP_##NAME("bf16"), PRISM_KLOOP_CLOBBERS_##NAME, __VA_ARGS__);                                    \
   } while (0)
   if constexpr (BM == 256) PRISM_RUN(256, PRISM_ACC16);
+  else if constexpr (kHeads && BM == 64 && S == 6) PRISM_RUN(64x128_6_HEAD, PRISM_ACC2);
   else if constexpr (kHeads && BM == 64) PRISM_RUN(64x128_3_HEAD, PRISM_ACC2);
+  else if constexpr (kHeads && S == 5) PRISM_RUN(128x128_5_HEAD, PRISM_ACC4);
   else if constexpr (kHeads && S == 3) PRISM_RUN(128x128_3_HEAD, PRISM_ACC4);
   else if constexpr (kHeads) PRISM_RUN(128x128_2_HEAD, PRISM_ACC4);
   else if constexpr (BM == 32 && BN == 32) PRISM_RUN(32x32_9, PRISM_ACC1);
   else if constexpr (BM == 64 && BN == 32) PRISM_RUN(64x32_7, PRISM_ACC1);
   else if constexpr (BM == 32 && BN == 64) PRISM_RUN(32x64_4, PRISM_ACC2);
   else if constexpr (BM == 64 && BN == 64) PRISM_RUN(64x64_5, PRISM_ACC1);
+  else if constexpr (BM == 128 && BN == 64 && S == 6) PRISM_RUN(128x64_6, PRISM_ACC2);
   else if constexpr (BM == 128 && BN == 64) PRISM_RUN(128x64_3, PRISM_ACC2);
+  else if constexpr (S == 5) PRISM_RUN(128x128_5, PRISM_ACC4);
   else if constexpr (S == 4) PRISM_RUN(128x128_4, PRISM_ACC4);
   else PRISM_RUN(128x128_2, PRISM_ACC4);
 #undef PRISM_RUN
@@ -554,8 +558,24 @@ static TilePlan plan_tiles(const TileCost *costs, int kinds, int M, int ncols, i
   return p;
 }
 
+// Tiles of 128 rows, and of the heads' 64 x 128, have a second ring of slices that takes a whole compute unit's LDS: two more
+// slices in flight (128 x 64 and 64 x 128: 6 stages for 3, 128 x 128: 5 for 4 or 3).  It pays where no unit has a second tile to
+// run beside the first (over 256 tiles of 128 x 64: up to 25 % slower) and the loop is long enough for its longer start.  us, weights from
+// memory, 128 x 64: 391 x 4096 x 12288 78.7 -> 63.6, 391 x 2560 x 9728 59.5 -> 46.6, 1154 x 1024 x 3072 21.0 -> 17.6, with SwiGLU 200 x
+// 6144 x 1024 9.7 -> 9.1; of the 59 launches that the rule takes 4-26 % faster or level, where a residual add of K = 1024, which it leaves out, lost up to
+// 14 % (2000 x 1024 x 1024 9.1 -> 10.4).  128 x 128: 1154 x 2560 x 9728 76.1 -> 69.0, 900 x 4096 x 12288 103 -> 93, level (under
+// 1 %) where all rows of the tiles are inside the matrix; K = 1024 lost 2-27 % (777 x 4096 x 1024 11.8 -> 14.7).
+static bool deep_ring(int bm, int bn, bool long_only, int64_t M, int64_t ncols, int K) {
+  const int64_t tiles = (M + bm - 1) / bm * ((ncols + bn - 1) / bn);
+  return tiles <= 256 && K / BK >= (long_only ? 32 : 16);
+}
+
 template <typename OT, int EPI>
 static int launch_kind(int kind, const OT *A, const OT *W, void *out, int M, int N, int K, hipStream_t s) {
+  constexpr bool kGlu = EPI == PRISM_EPI_SWIGLU, kRes = EPI == PRISM_EPI_RESIDUAL;
+  const int ncols = kGlu ? N / 2 : N;
+  if (kind == kTile128Deep && deep_ring(128, kGlu ? 64 : 128, true, M, ncols, K)) return launch_cfg<OT, 128, 128, 2, 2, EPI, 5>(A, W, out, M, N, K, s);
+  if (kind == kTile128x64 && deep_ring(128, kGlu ? 32 : 64, kRes, M, ncols, K)) return launch_cfg<OT, 128, 64, 4, 1, EPI, 6>(A, W, out, M, N, K, s);
   switch (kind) {
     case kTile256: return launch_cfg<OT, 256, 256, 2, 2, EPI, 2>(A, W, out, M, N, K, s);
     case kTile128: return launch_cfg<OT, 128, 128, 2, 2, EPI, 2>(A, W, out, M, N, K, s);
@@ -629,6 +649,8 @@ bool gemm_16_qkv_supported(int nq, int nkv, int hd, int K) {
 
 template <typename OT>
 static int launch_head(int kind, const QkvEpilogue &e, const OT *A, const OT *W, int M, int N, int K, hipStream_t s) {
+  if (kind == kHead128Deep && deep_ring(128, 128, true, M, N, K)) return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 5>(A, W, e.QK, M, N, K, s, e);
+  if (kind == kHead64 && deep_ring(64, 128, false, M, N, K)) return launch_cfg<OT, 64, 128, 4, 1, kEpiQkv, 6>(A, W, e.QK, M, N, K, s, e);
   switch (kind) {
     case kHead256: return launch_cfg<OT, 256, 256, 2, 2, kEpiQkv, 2>(A, W, e.QK, M, N, K, s, e);
     case kHead128: return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 2>(A, W, e.QK, M, N, K, s, e);

@@ -160,6 +160,9 @@ def kloop():
 #     1 x 4096 x 12288 29.7 -> 24.1, 33 x 2560 x 9728 22.3 -> 18.5, 6 x 1024 x 3072 8.6 -> 7.4 (32 x 32); 100 x 4096 x 12288 38.0 ->
 #     37.0, 391 x 1024 x 3072 10.5 -> 9.8 (64 x 32); with SwiGLU 1 x 6144 x 1024 8.0 -> 7.2, 1 x 24576 x 4096 40.9 -> 39.1 (32 x 64; two waves
 #     with the same ring: 6.7 and 38.8, but 32 x 19456 x 2560 28.2 instead of 27.4, two tiles on a few units being what it waits for);
+#   * the tiles of 128 rows have a second, deeper ring for launches that give a compute unit one tile at most, where the LDS that
+#     a second workgroup would use is free (gemm_16.hip: deep_ring).  Not the smaller tiles: rings of 8 to 18 slices, fragments 4 to 8 steps
+#     ahead or not, change their times by under 3 % (they stand at some 25 bytes per cycle and unit, whatever is in flight);
 #   * loads are spread over the slice; four of them share one M0, their offsets shift source and destination alike.
 # The ring is unrolled (stage offsets are immediates).  Loads take their row offsets as inputs, one register per load
 # instruction, so rows beyond the matrix are clamped by the caller and edge tiles run the same loop.
@@ -279,7 +282,12 @@ SMALL = [
     Small("128x64_3", 128, 64, 4, 1, 3, 1, 2),
     Small("128x128_4", 128, 128, 2, 2, 4, 2, 4),
     Small("128x128_2", 128, 128, 2, 2, 2, 1, 2),
+    # the ring over nearly a whole compute unit's LDS, for launches of at most one tile per unit
+    Small("128x64_6", 128, 64, 4, 1, 6, 1, 2),
+    Small("128x128_5", 128, 128, 2, 2, 5, 1, 2),
     # q/k/v projection: a wave owns the 128 columns of one head
+    Small("64x128_6_HEAD", 64, 128, 4, 1, 6, 1, 2),
+    Small("128x128_5_HEAD", 128, 128, 4, 1, 5, 1, 2),
     Small("64x128_3_HEAD", 64, 128, 4, 1, 3, 1, 2),
     Small("128x128_3_HEAD", 128, 128, 4, 1, 3, 1, 2),
     Small("128x128_2_HEAD", 128, 128, 4, 1, 2, 1, 2),
