@@ -214,6 +214,20 @@ int launch_topk(const float *scores, int n, int K, int32_t *out_pos, float *out_
 // same, restricted to the entries whose tag equals `want` (tag may be null: all entries)
 int launch_topk_masked(const float *scores, const int8_t *tag, int want, int n, int K, int32_t *out_pos,
                        float *out_scores, hipStream_t s);
+// ranges [first, first + n) of a buffer, in 8-byte words, copied from pinned host memory (its device-visible address)
+static const int kCopyParts = 8;
+struct CopyParts {
+  int count = 0;
+  uint32_t first[kCopyParts], n[kCopyParts];
+  void add(int64_t byte0, int64_t bytes) {           // byte0 a multiple of 8; the end is rounded up to one
+    if (bytes <= 0) return;
+    first[count] = (uint32_t)(byte0 / 8);
+    n[count++] = (uint32_t)((bytes + 7) / 8);
+  }
+};
+int launch_fetch_host(const void *src, void *dst, const CopyParts &parts, hipStream_t s);
+// bytes (a multiple of 8) to pinned host memory, then `done` to *flag there, behind all of them
+int launch_post_host(const void *src, void *dst, size_t bytes, uint64_t *flag, uint64_t done, hipStream_t s);
 int launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 // in place: n bf16 values -> the same values in IEEE half (exact for every bf16 value of normal half range)
 int launch_bf16_to_f16(void *p, size_t n, hipStream_t s);

@@ -609,6 +609,46 @@ __global__ void fill_zero_kernel(uint4 *p, size_t n16) {
   for (; i < n16; i += stride) p[i] = make_uint4(0, 0, 0, 0);
 }
 
+// Copies between pinned host memory and the device as kernels on the compute stream.  A check's results and the metadata rebuilt
+// from them are a few KiB to some 100 KiB on the call's critical path; as copies of the runtime they cross to a DMA engine and
+// back, and a host that slept until the stream drained wakes late.  From a decision to the next kernel, traced: 37 us -> 14-22
+// without a compaction, 67 + 10 -> 59 + 12 with one; with the layers' shared moments six short candidates on the 0.6B shape 2280 -> 2205 us,
+// forty of 128-480 tokens 7000 -> 6940.  Accesses on the host's side have system scope, past every cache, since the host rewrites
+// the buffers between calls; 8 bytes per lane, the largest such.
+//
+// host -> device: up to kCopyParts ranges of one pair of buffers (blockIdx.y).
+__global__ __launch_bounds__(256) void fetch_host_kernel(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst, const CopyParts parts) {
+  const uint32_t first = parts.first[blockIdx.y], n = parts.n[blockIdx.y];
+  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256)
+    dst[first + i] = __hip_atomic_load(src + first + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// device -> host, then `done` to *flag: one workgroup, so that its barrier orders the flag behind every word.
+__global__ __launch_bounds__(1024) void post_host_kernel(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst, int n, uint64_t *flag, uint64_t done) {
+  for (int i = threadIdx.x; i < n; i += 1024) __hip_atomic_store(dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flag, done, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+int launch_fetch_host(const void *src, void *dst, const CopyParts &parts, hipStream_t s) {
+  PRISM_REQUIRE(src && dst && parts.count >= 0 && parts.count <= kCopyParts && ((uintptr_t)src | (uintptr_t)dst) % 8 == 0, PRISM_EINVAL, "host copy: bad arguments");
+  uint32_t most = 0;
+  for (int i = 0; i < parts.count; ++i) most = parts.n[i] > most ? parts.n[i] : most;
+  if (most == 0) return PRISM_OK;
+  fetch_host_kernel<<<dim3(cdiv(most, 256) < 64 ? cdiv(most, 256) : 64, parts.count), 256, 0, s>>>((const uint64_t *)src, (uint64_t *)dst, parts);
+  PRISM_HIP(hipGetLastError());
+  return PRISM_OK;
+}
+
+int launch_post_host(const void *src, void *dst, size_t bytes, uint64_t *flag, uint64_t done, hipStream_t s) {
+  PRISM_REQUIRE(src && dst && flag && bytes % 8 == 0 && bytes < (size_t)1 << 31 && ((uintptr_t)src | (uintptr_t)dst | (uintptr_t)flag) % 8 == 0, PRISM_EINVAL,
+                "host copy: bad arguments");
+  post_host_kernel<<<1, 1024, 0, s>>>((const uint64_t *)src, (uint64_t *)dst, (int)(bytes / 8), flag, done);
+  PRISM_HIP(hipGetLastError());
+  return PRISM_OK;
+}
+
 // In place, 8 elements (16 bytes) per lane and step over the first n8 * 8 elements, one element per lane over the rest.
 __global__ __launch_bounds__(256) void bf16_to_f16_kernel(unsigned short *p, size_t n, size_t n8) {
   const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;

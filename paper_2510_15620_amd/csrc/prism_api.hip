@@ -3,6 +3,7 @@
 // overlapped layer streaming from pinned host memory on a side stream (Sec. 4.2).
 #include <algorithm>
 #include <array>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -125,6 +126,9 @@ struct prism_ctx {
   int64_t chunk_cap = 0, vt_cap = 0;              // tokens / V^T columns
   int32_t *d_meta = nullptr; int64_t meta_cap = 0;   // int32 words
   int32_t *h_meta = nullptr; int64_t h_meta_cap = 0; // pinned staging
+  int32_t *h_meta_dev = nullptr;                     // its device-visible address, and that of h_res
+  char *h_res_dev = nullptr;
+  uint64_t n_posted = 0;                             // results posted to h_res so far; the last one's number stands behind them
   // what a check or the final ranking hands to the host, in one block so that one copy brings it over; a call of n candidates
   // lays it out by n: [stats][scores n][fate n][top positions n][top scores n], h_res (pinned) alike
   char *d_res = nullptr, *h_res = nullptr;
@@ -373,7 +377,9 @@ extern "C" int prism_create(const prism_model *model, const prism_weights *weigh
   CREATE_TRY(launch_rope_table(c->rope_tab, PRISM_MAX_SEQ, model->head_dim, model->rope_base, c->stream, is16(c->op)));
   CREATE_TRY(dev_alloc(c, (void **)&c->d_res, kResultBytes));
   CREATE_TRY(dev_alloc(c, &c->route_ws, route_workspace_bytes(PRISM_MAX_CANDS, PRISM_MAX_CLUSTERS)));
-  CREATE_HIP(hipHostMalloc((void **)&c->h_res, kResultBytes, hipHostMallocDefault));
+  CREATE_HIP(hipHostMalloc((void **)&c->h_res, kResultBytes + 64, hipHostMallocCoherent));
+  CREATE_HIP(hipHostGetDevicePointer((void **)&c->h_res_dev, c->h_res, 0));
+  memset(c->h_res + kResultBytes, 0, 64);
   if (c->offload) {
     CREATE_HIP(hipStreamCreateWithFlags(&c->xin_stream, hipStreamNonBlocking));
     CREATE_HIP(hipStreamCreateWithFlags(&c->xout_stream, hipStreamNonBlocking));
@@ -620,8 +626,9 @@ static int ensure_scratch(prism_ctx *c, const Plan &p, bool need_second_x, int n
   const MetaOff mo = meta_offsets(p.T, n_cands, max_tiles);
   PRISM_TRY(grow(c, &c->d_meta, &c->meta_cap, mo.words, 4));
   if (mo.words > c->h_meta_cap) {
-    if (c->h_meta) { PRISM_HIP(hipStreamSynchronize(c->stream)); (void)hipHostFree(c->h_meta); c->h_meta = nullptr; }
-    PRISM_HIP(hipHostMalloc((void **)&c->h_meta, (size_t)mo.words * 4, hipHostMallocDefault));
+    if (c->h_meta) { PRISM_HIP(hipStreamSynchronize(c->stream)); (void)hipHostFree(c->h_meta); c->h_meta = nullptr; c->h_meta_cap = 0; }
+    PRISM_HIP(hipHostMalloc((void **)&c->h_meta, (size_t)mo.words * 4, hipHostMallocCoherent));
+    PRISM_HIP(hipHostGetDevicePointer((void **)&c->h_meta_dev, c->h_meta, 0));
     c->h_meta_cap = mo.words;
   }
   return PRISM_OK;
@@ -651,11 +658,16 @@ static int upload_meta(prism_ctx *c, const Plan &p, const MetaOff &mo, bool with
   if (!p.tiles.empty()) memcpy(h + mo.tiles, p.tiles.data(), p.tiles.size() * sizeof(AttnTile));
   if (!p.last_tiles.empty()) memcpy(h + mo.ltiles, p.last_tiles.data(), p.last_tiles.size() * sizeof(AttnTile));
   if (!p.xtiles.empty()) memcpy(h + mo.xtiles, p.xtiles.data(), p.xtiles.size() * sizeof(AttnTile));
-  // one copy for [pos .. tiles], a second for the tokens (first upload only)
-  PRISM_HIP(hipMemcpyAsync(c->d_meta, h, (size_t)mo.tokens * 4, hipMemcpyHostToDevice, c->stream));
-  if (with_tokens)
-    PRISM_HIP(hipMemcpyAsync(c->d_meta + mo.tokens, h + mo.tokens, (size_t)p.T * 4, hipMemcpyHostToDevice, c->stream));
-  return PRISM_OK;
+  // what this pool has of each list; the lists start where the call's first pool put them
+  CopyParts parts;
+  parts.add(mo.pos * 4, p.T * 4);
+  parts.add(mo.vtcol * 4, p.T * 4);
+  parts.add(mo.lastrow * 4, (mo.tiles - mo.lastrow) * 4);
+  parts.add(mo.tiles * 4, (int64_t)(p.tiles.size() * sizeof(AttnTile)));
+  parts.add(mo.ltiles * 4, (int64_t)(p.last_tiles.size() * sizeof(AttnTile)));
+  parts.add(mo.xtiles * 4, (int64_t)(p.xtiles.size() * sizeof(AttnTile)));
+  if (with_tokens) parts.add(mo.tokens * 4, p.T * 4);        // first upload only
+  return launch_fetch_host(c->h_meta_dev, c->d_meta, parts, c->stream);
 }
 
 // The moment on the compute stream behind everything queued so far, as an event of the pool.  What such a record costs is idle
@@ -1035,6 +1047,7 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   typedef std::array<hipEvent_t, 2> Interval;
   Interval t_call{};
   std::vector<Interval> t_check, t_layer;
+  bool layer_open = false;             // resident layers that follow one another share one interval: nothing is queued between them
   queued(c);
   if (timed) PRISM_TRY(mark(c, &t_call[0]));
   queued(c);
@@ -1095,12 +1108,22 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   const float *h_scores = (const float *)(c->h_res + res_scores), *h_top_scores = (const float *)(c->h_res + res_top + 4 * n_res);
   const int8_t *h_fate = (const int8_t *)(c->h_res + res_fate);
   const int32_t *h_top_pos = (const int32_t *)(c->h_res + res_top);
-  // bytes [from, to) of the result block, on the host when this returns; `copied` becomes the moment behind the copy
-  auto fetch = [&](size_t from, size_t to, hipEvent_t *copied = nullptr) -> int {
+  // bytes [from, to) of the result block, on the host when this returns; `copied` becomes the moment behind the copy.  The host
+  // watches the posted number for as long as a late wake-up would show in a call's time (a sleeping thread took 20-50 us to
+  // come back: 1 % of what it waited for and less beyond kWatch), then sleeps until the stream has drained.
+  auto fetch = [&](size_t from, size_t to, bool last = false, hipEvent_t *copied = nullptr) -> int {
     queued(c);
-    PRISM_HIP(hipMemcpyAsync(c->h_res + from, c->d_res + from, to - from, hipMemcpyDeviceToHost, s));
+    const uint64_t number = ++c->n_posted;
+    PRISM_TRY(launch_post_host(c->d_res + from, c->h_res_dev + from, to - from, (uint64_t *)(c->h_res_dev + kResultBytes), number, s));
     if (copied) PRISM_TRY(mark(c, copied));
-    PRISM_HIP(hipStreamSynchronize(s));
+    constexpr auto kWatch = std::chrono::milliseconds(4);
+    const auto start = std::chrono::steady_clock::now();
+    const uint64_t *flag = (const uint64_t *)(c->h_res + kResultBytes);
+    while (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != number) {
+      __builtin_ia32_pause();
+      if (std::chrono::steady_clock::now() - start > kWatch) { PRISM_HIP(hipStreamSynchronize(s)); break; }
+    }
+    if (last) PRISM_HIP(hipStreamSynchronize(s));            // the call leaves a drained stream, and reads its events
     return PRISM_OK;
   };
 
@@ -1125,7 +1148,7 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   for (int l = 0; l < m.n_layers && !terminated; ++l) {
     const int slot = c->two_slot ? l % c->ring : l;
     if (c->two_slot) { PRISM_HIP(hipStreamWaitEvent(s, c->ev_ready[slot], 0)); queued(c); }
-    if (timed) { t_layer.emplace_back(); PRISM_TRY(mark(c, &t_layer.back()[0])); }
+    if (timed && !layer_open) { t_layer.emplace_back(); PRISM_TRY(mark(c, &t_layer.back()[0])); }
     // known before the layer runs: will its output be scored for pruning, and is it the last one
     while (next_ckpt < c->checkpoints.size() && c->checkpoints[next_ckpt] < l + 1) ++next_ckpt;
     const bool check_after = next_ckpt < c->checkpoints.size() && c->checkpoints[next_ckpt] == l + 1 && l + 1 < m.n_layers &&
@@ -1139,7 +1162,8 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     const bool peek = check_after && !c->offload && !c->opt.single_pass_checks;
     PRISM_TRY(run_layer(c, p, mo, c->X[cur], c->layer_buf[slot], check_after || last_layer, !last_layer,
                         !last_layer && !check_after, last_layer || peek));
-    if (timed) PRISM_TRY(mark(c, &t_layer.back()[1]));
+    layer_open = timed && !c->two_slot && !check_after && !last_layer;
+    if (timed && !layer_open) PRISM_TRY(mark(c, &t_layer.back()[1]));
     token_layers += p.seq_tokens;
     layers_run = l + 1;
     // this layer's kernels are queued: the layer that arrived last (the one the ring's newest slot holds) can be finished
@@ -1265,7 +1289,7 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
     const int k_out = std::min(K_rem, n_live);
     // (the last layer has scored every candidate from its gathered last-token state)
     PRISM_TRY(launch_topk(c->d_scores, n_live, k_out, c->d_top_pos, c->d_top_scores, s));
-    PRISM_TRY(fetch(res_scores, res_end, timed ? &t_call[1] : nullptr));     // the call's time includes its results' copy
+    PRISM_TRY(fetch(res_scores, res_end, true, timed ? &t_call[1] : nullptr));     // the call's time includes its results' copy
     for (int i = 0; i < k_out; ++i) { final_idx.push_back(p.live[h_top_pos[i]]); final_scores.push_back(h_top_scores[i]); }
     record_event(m.n_layers, n_live, p.live, false, 0, 0.0, 0.0, nullptr, nullptr);
   } else {

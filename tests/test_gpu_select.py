@@ -352,3 +352,34 @@ def test_a_call_whose_scores_are_all_nan_returns_k_candidates(mode):
         assert idx.tolist() == list(range(K)) and np.isnan(scores).all()
         assert not rep.gate.any() and (rep.n_after == len(pool)).all()
     p.destroy()
+
+
+@pytest.mark.parametrize("n", [1, 9, 600, 2500])
+def test_results_and_metadata_of_any_pool_size_reach_their_side(n):
+    """A check's results are posted to the host by one workgroup, 1024 words at a time, and the survivors' metadata fetched by a
+    kernel: pools whose parts end inside a round, fill one and take several.  Every candidate's score at the check equals the
+    score of a call that asks for all of them at the end of the same number of layers."""
+    m = W.ModelShape(2, 128, 2, 1, 128, 128, 64, "bf16")
+    d = torch.Generator().manual_seed(11)
+    draw = lambda *s, std=0.05: (torch.randn(*s, generator=d) * std).to(torch.bfloat16)
+    layers = [{k: ((1 + draw(s[0])).to(torch.bfloat16) if len(s) == 1 else draw(*s)).cuda() for k, s in W.layer_tensor_shapes(m).items()} for _ in range(2)]
+    embed, norm = draw(64, 128, std=1.0).cuda(), (1 + draw(128)).to(torch.bfloat16).cuda()
+    r = np.random.RandomState(5)
+    q, cands = r.randint(0, 64, 5).astype(np.int32), [r.randint(0, 64, 1 + i % 7).astype(np.int32) for i in range(n)]
+    one = B.Prism(dataclasses.replace(m, n_layers=1), W.Weights(embed, layers[:1], norm))
+    _, _, want = one.select(q, cands, n)
+    one.destroy()
+    p = B.Prism(m, W.Weights(embed, layers, norm), checkpoints=[1])
+    if n > 1:
+        p.set_forced_keep(np.ones((1, n), np.int8) - (np.arange(n) % 2 == 1).astype(np.int8))
+    K = max(1, n // 4)
+    idx, scores, rep = p.select(q, cands, K)
+    again = p.select(q, cands, K)
+    p.destroy()
+    assert np.array_equal(idx, again[0]) and np.array_equal(scores, again[1]) and np.array_equal(rep.scores, again[2].scores, equal_nan=True)
+    if n > 1:
+        assert np.array_equal(rep.scores[0], want.scores[-1])
+        assert rep.n_after[0] == (n + 1) // 2 and (idx % 2 == 0).all()
+        assert np.array_equal(np.isnan(rep.scores[-1]), np.arange(n) % 2 == 1)
+        best = O.rank_order(rep.scores[-1][::2].astype(np.float64))[:K] * 2
+        assert np.array_equal(idx, best)
