@@ -12,7 +12,9 @@
 // zero times a non-finite value of a token in the future would otherwise reach the sum.  Until a query has met a finite score
 // its running maximum is -inf and its weights are taken relative to 0, so leading keys that score -inf weigh nothing.  Partial
 // sums of values have weights of up to 1 per key, so values need to stay below the largest fp32 number over the sequence length.
-// 4 heads of 64, 12859 tokens of 160-512-token sequences: 771 us as one workgroup per (token, head) -> 85 us.
+// 4 heads of 64, 12859 tokens of 160-512-token sequences: 771 us as one workgroup per (token, head) -> 86 us; -> 79 with the next
+// tile's loads held in front of a tile's work, the accumulators in vector registers and the diagonal's values handed over in LDS;
+// -> 55 with the items longest first (AttnLevels).  8 sequences of 32-64 tokens 11.2 -> 8.5.
 //
 // attention_fp32_any_kernel: any other head size: the definition, one workgroup per (token, query head), score row in LDS.
 #include "common.h"
@@ -20,9 +22,10 @@
 namespace prism {
 
 template <int NB, typename Items>
-__global__ __launch_bounds__(256) void attention_fp32_kernel(const float *__restrict__ QKV, const Items items,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB <= 4 ? 3 : 2))) void attention_fp32_kernel(const float *__restrict__ QKV, const Items items,
                                                              int nq, int nkv, float *__restrict__ out) {
   constexpr int HD = 16 * NB;
+  __shared__ __align__(16) float diag[4 * 16 * HD];          // per wave: the values of its diagonal tile
   const AttnTile it = items(blockIdx.x / nq);
   const int h = blockIdx.x % nq, kvh = h / (nq / nkv);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
@@ -98,29 +101,51 @@ __global__ __launch_bounds__(256) void attention_fp32_kernel(const float *__rest
     for (int b = 0; b < NB; ++b) o[b] *= alpha;
   };
 
-  Tile cur;
-  fetch(0, cur);
   float p[4];
-  for (int k0 = 0; k0 < q0; k0 += 16) {                      // every key of these tiles is in every query's past
-    Tile next;
-    fetch(k0 + 16, next);
-    weigh(k0, cur, false, p);
+  auto past = [&](int k0, const Tile &t) __attribute__((always_inline)) {      // a tile whose keys are all in every query's past
+    weigh(k0, t, false, p);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int b = 0; b < NB; ++b) o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.v[s][b], p[s], o[b], 0, 0, 0);
+      for (int b = 0; b < NB; ++b) o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.v[s][b], p[s], o[b], 0, 0, 0);
+  };
+  // Two tiles' registers in turn.  The scheduling barriers keep a tile's loads in front of the work on the tile before: without
+  // them the compiler moves them behind it to save registers, and every tile waits for memory.
+  Tile cur, next;
+  fetch(0, cur);
+  int k0 = 0;
+  for (; k0 + 32 <= q0; k0 += 32) {
+    fetch(k0 + 16, next);
+    __builtin_amdgcn_sched_barrier(0);
+    past(k0, cur);
+    fetch(k0 + 32, cur);
+    __builtin_amdgcn_sched_barrier(0);
+    past(k0 + 16, next);
+  }
+  if (k0 < q0) {
+    fetch(k0 + 16, next);
+    __builtin_amdgcn_sched_barrier(0);
+    past(k0, cur);
     cur = next;
   }
   weigh(q0, cur, true, p);
-  // the diagonal tile: o[b][e] is dimension NB (4 g + e) + b of query lane % 16; four keys' values are requested together
+  // the diagonal tile: o[b][e] is dimension NB (4 g + e) + b of query lane % 16.  A lane needs 4 NB dimensions of every key here; the
+  // wave has the tile's values, other dimensions of four keys in a lane, and hands them over through LDS of its own
+  float *vd = diag + (threadIdx.x >> 6) * (16 * HD);
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) vd[(4 * g + s) * HD + NB * c + j] = cur.v[s][j];
+  // (LDS serves a wave in order; the fences keep the compiler to it, the barrier, no instruction, makes the lanes meet)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   for (int k0 = 0; k0 < 16 && q0 + k0 < L; k0 += 4) {
     f32x4 v[4][NB];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float *vp = vcol + (int64_t)(q0 + k0 + u < L ? q0 + k0 + u : L - 1) * row + NB * 4 * g;
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) v[u][j] = *reinterpret_cast<const f32x4 *>(vp + 4 * j);
-    }
+      for (int j = 0; j < NB; ++j) v[u][j] = *reinterpret_cast<const f32x4 *>(vd + (k0 + u) * HD + NB * 4 * g + 4 * j);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const float w = __shfl(p[u], k0 * 4 + c);              // key k0 + u: register u of group k0 / 4
@@ -205,10 +230,10 @@ static int launch_items(const float *QKV, const Items &items, int n_tiles, int n
   return PRISM_OK;
 }
 
-int launch_attention_fp32_seqs(const float *QKV, const AttnSeqs &seqs, int nq, int nkv, int hd, float *out, hipStream_t s) {
+int launch_attention_fp32_levels(const float *QKV, const AttnLevels &levels, int nq, int nkv, int hd, float *out, hipStream_t s) {
   PRISM_REQUIRE(QKV && out && nq > 0 && nkv > 0 && nq % nkv == 0 && attention_fp32_tiled(hd) && ((uintptr_t)QKV | (uintptr_t)out) % 16 == 0 &&
-                seqs.n > 0 && seqs.n <= kAttnSeqs && seqs.bq == kAttn32BQ, PRISM_EINVAL, "attention fp32: bad arguments");
-  return launch_items(QKV, seqs, seqs.end[seqs.n - 1], nq, nkv, hd, out, s);
+                levels.n_levels > 0 && levels.n_levels <= PRISM_MAX_SEQ / kAttn32BQ, PRISM_EINVAL, "attention fp32: bad arguments");
+  return launch_items(QKV, levels, levels.end[levels.n_levels - 1], nq, nkv, hd, out, s);
 }
 
 int launch_attention_fp32(const float *QKV, const int32_t *pos, const AttnTile *tiles, int n_tiles, int T, int nq, int nkv, int hd, float *out,

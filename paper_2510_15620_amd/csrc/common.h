@@ -192,11 +192,32 @@ int launch_attention_16_seqs(int dtype, const void *QK, const void *Vt, int64_t 
 bool attention_16_supported(int nq, int nkv, int hd);
 // fp32 attention.  tiles: work items of kAttn32BQ queries (row_base, seq_len, q0 and out_base are read), for the head sizes
 // that attention_fp32_tiled names; other head sizes go by pos[t], the position of token t in its sequence.
-static const int kAttn32BQ = 64;
 bool attention_fp32_tiled(int hd);
 int launch_attention_fp32(const float *QKV, const int32_t *pos, const AttnTile *tiles, int n_tiles, int T, int nq, int nkv, int hd, float *out,
                           hipStream_t s);
-int launch_attention_fp32_seqs(const float *QKV, const AttnSeqs &seqs, int nq, int nkv, int hd, float *out, hipStream_t s);
+// fp32 items in launch arguments: longest first, over all sequences.  The fp32 kernel's workgroups are all resident at once in
+// pools of up to some 15 000 tokens, so nothing evens out what a compute unit was dealt at the start: item by item of one
+// sequence after the other, the fullest unit has twice the average (a block's work grows with its place in the sequence).  Dealt by
+// falling size, a unit gets one of each.  Level l holds block n_levels - 1 - l of the sequences that have it, which lead the
+// sequences when those are sorted by their blocks.  40 sequences of 160-512 tokens, 4 heads of
+// 64: 79 -> 55 us.
+static const int kAttn32BQ = 64;
+struct AttnLevels {
+  int32_t n_levels;
+  int32_t end[PRISM_MAX_SEQ / kAttn32BQ];       // items of levels 0 .. l
+  int32_t row[kAttnSeqs], len[kAttnSeqs];
+  __device__ __forceinline__ AttnTile operator()(int i) const {
+    int l = 0;
+    for (int b = 0; b < n_levels; b += 64) {
+      const int j = b + (int)(threadIdx.x & 63);
+      l += __popcll(__builtin_amdgcn_ballot_w64(j < n_levels && end[j < n_levels ? j : 0] <= i));
+    }
+    l = __builtin_amdgcn_readfirstlane(l);
+    const int s = i - (l ? end[l - 1] : 0), r = row[s];
+    return {r, len[s], (n_levels - 1 - l) * kAttn32BQ, 0, 0, 0, r, 0};
+  }
+};
+int launch_attention_fp32_levels(const float *QKV, const AttnLevels &levels, int nq, int nkv, int hd, float *out, hipStream_t s);
 int attention_16_block_queries(int nq, int nkv);   // queries per AttnTile for this head grouping
 // Column of key p of a sequence in the V^T buffer, relative to the sequence's first column: within every group of 16
 // the keys are stored in the order 0-3, 8-11, 4-7, 12-15 (the order in which the matrix cores' accumulator layout hands

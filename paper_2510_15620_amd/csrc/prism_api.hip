@@ -533,6 +533,9 @@ static void build_plan(const prism_ctx *c, Plan &p) {
     }
     ch.r1 = r;
     ch.n_tiles = (int)p.tiles.size() - ch.tile0;
+    // fp32: longest items first (see AttnLevels)
+    if (!is16(c->op))
+      std::stable_sort(p.tiles.begin() + ch.tile0, p.tiles.end(), [](const AttnTile &x, const AttnTile &y) { return x.q0 > y.q0; });
     ch.vt_cols = col;
     p.chunks.push_back(ch);
     p.max_chunk_tokens = std::max(p.max_chunk_tokens, ch.r1 - ch.r0);
@@ -1446,28 +1449,25 @@ extern "C" int prism_op_attention(int32_t dtype, const void *QK, const void *Vt,
     PRISM_REQUIRE(cu[i + 1] > cu[i] && cu[i + 1] - cu[i] <= PRISM_MAX_SEQ, PRISM_EINVAL, "attention: sequence %d has bad length", i);
   const bool bf = is16(dtype);
   PRISM_REQUIRE(bf || dtype == PRISM_DTYPE_FP32, PRISM_EINVAL, "attention: unknown dtype %d", dtype);
-  // the sequences as launch arguments (see AttnSeqs); false where they don't fit
-  auto as_arguments = [&](AttnSeqs &a, int bq, const int32_t *col0) {
-    if (n_seqs > kAttnSeqs) return false;
-    a.n = n_seqs;
-    a.bq = bq;
-    for (int i = 0; i < n_seqs; ++i) {
-      a.end[i] = (i ? a.end[i - 1] : 0) + cdiv(cu[i + 1] - cu[i], bq);
-      a.cu[i] = cu[i];
-      a.vt_col0[i] = col0 ? col0[i] : 0;
-    }
-    a.cu[n_seqs] = T;
-    return true;
-  };
-  AttnSeqs args;
   if (!bf) {
     // what goes to the device: work items, or every token's position for the head sizes served without them.  The kernels
     // run over [0, T): tokens in front of the first sequence belong to none and attend to themselves only
     std::vector<AttnTile> tiles;
     std::vector<int32_t> pos;
     const bool tiled = attention_fp32_tiled(hd) && ((uintptr_t)QK | (uintptr_t)out) % 16 == 0;
-    if (tiled && cu[0] == 0 && as_arguments(args, kAttn32BQ, nullptr)) {
-      PRISM_TRY(launch_attention_fp32_seqs((const float *)QK, args, nq, nkv, hd, (float *)out, s));
+    if (tiled && cu[0] == 0 && n_seqs <= kAttnSeqs) {          // they fit a launch's arguments (see AttnLevels)
+      AttnLevels a;
+      std::vector<int> order(n_seqs);
+      for (int i = 0; i < n_seqs; ++i) order[i] = i;
+      auto blocks = [&](int i) { return cdiv(cu[i + 1] - cu[i], kAttn32BQ); };
+      std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return blocks(x) > blocks(y); });
+      a.n_levels = blocks(order[0]);
+      for (int l = 0, n = 0, items = 0; l < a.n_levels; ++l) {
+        while (n < n_seqs && blocks(order[n]) >= a.n_levels - l) ++n;
+        a.end[l] = items += n;
+      }
+      for (int i = 0; i < n_seqs; ++i) { a.row[i] = cu[order[i]]; a.len[i] = cu[order[i] + 1] - cu[order[i]]; }
+      PRISM_TRY(launch_attention_fp32_levels((const float *)QK, a, nq, nkv, hd, (float *)out, s));
       PRISM_HIP(hipStreamSynchronize(s));
       return PRISM_OK;
     }
@@ -1495,8 +1495,17 @@ extern "C" int prism_op_attention(int32_t dtype, const void *QK, const void *Vt,
   for (int i = 0; i < n_seqs; ++i)
     PRISM_REQUIRE(vt_col0[i] >= 0 && vt_col0[i] % 64 == 0 && vt_col0[i] + round_up(cu[i + 1] - cu[i], 64) <= vt_stride, PRISM_EINVAL,
                   "attention bf16: sequence %d: V^T columns must start at a multiple of 64 and fit the row stride", i);
-  if (as_arguments(args, bq, vt_col0)) {
-    PRISM_TRY(launch_attention_16_seqs(dtype, QK, Vt, vt_stride, args, nq, nkv, hd, out, s));
+  if (n_seqs <= kAttnSeqs) {                                   // they fit a launch's arguments (see AttnSeqs)
+    AttnSeqs a;
+    a.n = n_seqs;
+    a.bq = bq;
+    for (int i = 0; i < n_seqs; ++i) {
+      a.end[i] = (i ? a.end[i - 1] : 0) + cdiv(cu[i + 1] - cu[i], bq);
+      a.cu[i] = cu[i];
+      a.vt_col0[i] = vt_col0[i];
+    }
+    a.cu[n_seqs] = T;
+    PRISM_TRY(launch_attention_16_seqs(dtype, QK, Vt, vt_stride, a, nq, nkv, hd, out, s));
     PRISM_HIP(hipStreamSynchronize(s));
     return PRISM_OK;
   }

@@ -632,6 +632,20 @@ def test_attention_by_sequences_and_by_list(dtype, nq, nkv, hd, n):
     assert many.float().abs().sum(1).min() > 0
 
 
+@pytest.mark.parametrize("hd", [32, 64, 128])
+@pytest.mark.parametrize("lens", [[8192, 1, 64, 65, 4097, 130], [16, 17, 32, 33, 48, 49], [200] * 5 + [64] * 3 + [129]])
+def test_attention_fp32_longest_first_and_by_list(hd, lens):
+    """Work items dealt longest first (up to 128 blocks of a sequence, searched 64 at a time; tiles in turn in two sets of registers,
+    odd and even numbers of them) against the list, which a call takes whose first sequence starts behind token 0, to the bit."""
+    nq, nkv = 2, 1
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    QKV = _rand((1 + sum(lens), (nq + 2 * nkv) * hd), torch.float32, 810 + hd, 1.0).to(DEV)
+    levels, by_list = torch.zeros(sum(lens), nq * hd, device=DEV), torch.zeros(1 + sum(lens), nq * hd, device=DEV)
+    B.op_attention(B.DTYPE_FP32, QKV[1:].contiguous(), None, 0, cu, None, nq, nkv, hd, levels)
+    B.op_attention(B.DTYPE_FP32, QKV, None, 0, cu + 1, None, nq, nkv, hd, by_list)
+    assert torch.equal(levels, by_list[1:]) and levels.abs().sum(1).min() > 0
+
+
 @pytest.mark.parametrize("nq,nkv", [(1, 1), (16, 8), (32, 8)])
 @pytest.mark.parametrize("T", [1, 3, 65])
 def test_qkv_finish_16_evaluates_the_tables_rotations(nq, nkv, T):
@@ -891,6 +905,18 @@ def test_topk_ranks_nan_behind_every_number(n, K):
     order = np.array(sorted(range(n), key=lambda i: (np.isnan(s[i]), -s[i] if not np.isnan(s[i]) else 0.0, i)))[:K]
     assert np.array_equal(pos.cpu().numpy(), order)
     assert np.array_equal(sc.cpu().numpy().view(np.int32), s[order].view(np.int32))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("T,hidden", [(1, 4), (5, 252), (4095, 256), (4097, 256), (4098, 64), (7, 260)])
+def test_rmsnorm_of_short_rows(T, hidden, dtype):
+    """A wave per row up to 256 values, one or four rows to a workgroup; 260 values take a workgroup."""
+    X, g = _rand((T, hidden), torch.float32, 7, 3.0), (1 + _rand((hidden,), torch.float32, 8, 0.1)).to(dtype)
+    out = torch.zeros(T, hidden, dtype=dtype, device=DEV)
+    B.op_rmsnorm(X.to(DEV), g.to(DEV), 1e-6, out)
+    ref = O.rmsnorm(_f64(X), _f64(g), 1e-6)
+    # fp32: sum of 256 squares, reciprocal root, two products; a 16-bit result is rounded once more
+    np.testing.assert_allclose(_f64(out), ref, rtol=2e-6 if dtype == torch.float32 else EPS16[dtype] * 1.01, atol=1e-7)
 
 
 @pytest.mark.parametrize("hd,nq,nkv,T", [(32, 3, 1, 5), (64, 4, 2, 354), (64, 4, 2, 12859), (128, 1, 1, 9001), (48, 2, 1, 77)])
