@@ -227,8 +227,22 @@ __host__ __device__ inline int vt_column_of_key(int p) { return (p & ~12) | ((p 
 int launch_score(const float *X, const int32_t *last_row, int n, int hidden, const void *final_norm,
                  const void *w_yes, const void *w_no, int dtype, float eps, float *scores, hipStream_t s);
 size_t route_workspace_bytes(int n, int k);
+// What a kernel of one workgroup leaves in pinned host memory: words 8-byte words, then `done` in *flag, behind all of them.
+struct HostPost {
+  uint64_t *dst = nullptr, *flag = nullptr;      // device-visible addresses; no flag: nothing is posted
+  uint64_t done = 0;
+  int words = 0;
+};
+__device__ __forceinline__ void post_host(const uint64_t *src, const HostPost &post) {
+  for (int i = threadIdx.x; i < post.words; i += blockDim.x) __hip_atomic_store(post.dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(post.flag, post.done, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+int launch_post_host(const void *src, const HostPost &post, hipStream_t s);
+// with a post, of the words from stats on: scores and fate have to stand behind stats in one block
 int launch_route(const float *scores, int n, int K_rem, int n_clusters, float tau, int8_t *fate, double *stats,
-                 void *workspace, hipStream_t s);
+                 void *workspace, hipStream_t s, const HostPost &post = HostPost{});
 int launch_compact(const float *Xs, float *Xd, const int32_t *src_start, const int32_t *dst_start,
                    const int32_t *len, int n_keep, int hidden, hipStream_t s);
 int launch_topk(const float *scores, int n, int K, int32_t *out_pos, float *out_scores, hipStream_t s);
@@ -247,8 +261,6 @@ struct CopyParts {
   }
 };
 int launch_fetch_host(const void *src, void *dst, const CopyParts &parts, hipStream_t s);
-// bytes (a multiple of 8) to pinned host memory, then `done` to *flag there, behind all of them
-int launch_post_host(const void *src, void *dst, size_t bytes, uint64_t *flag, uint64_t done, hipStream_t s);
 int launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 // in place: n bf16 values -> the same values in IEEE half (exact for every bf16 value of normal half range)
 int launch_bf16_to_f16(void *p, size_t n, hipStream_t s);

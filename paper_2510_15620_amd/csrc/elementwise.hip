@@ -649,13 +649,8 @@ __global__ __launch_bounds__(256) void fetch_host_kernel(const uint64_t *__restr
     dst[first + i] = __hip_atomic_load(src + first + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// device -> host, then `done` to *flag: one workgroup, so that its barrier orders the flag behind every word.
-__global__ __launch_bounds__(1024) void post_host_kernel(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst, int n, uint64_t *flag, uint64_t done) {
-  for (int i = threadIdx.x; i < n; i += 1024) __hip_atomic_store(dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(flag, done, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
+// device -> host, in one workgroup, so that its barrier orders the flag behind every word.
+__global__ __launch_bounds__(1024) void post_host_kernel(const uint64_t *__restrict__ src, const HostPost post) { post_host(src, post); }
 
 int launch_fetch_host(const void *src, void *dst, const CopyParts &parts, hipStream_t s) {
   PRISM_REQUIRE(src && dst && parts.count >= 0 && parts.count <= kCopyParts && ((uintptr_t)src | (uintptr_t)dst) % 8 == 0, PRISM_EINVAL, "host copy: bad arguments");
@@ -667,10 +662,10 @@ int launch_fetch_host(const void *src, void *dst, const CopyParts &parts, hipStr
   return PRISM_OK;
 }
 
-int launch_post_host(const void *src, void *dst, size_t bytes, uint64_t *flag, uint64_t done, hipStream_t s) {
-  PRISM_REQUIRE(src && dst && flag && bytes % 8 == 0 && bytes < (size_t)1 << 31 && ((uintptr_t)src | (uintptr_t)dst | (uintptr_t)flag) % 8 == 0, PRISM_EINVAL,
+int launch_post_host(const void *src, const HostPost &post, hipStream_t s) {
+  PRISM_REQUIRE(src && post.dst && post.flag && post.words >= 0 && ((uintptr_t)src | (uintptr_t)post.dst | (uintptr_t)post.flag) % 8 == 0, PRISM_EINVAL,
                 "host copy: bad arguments");
-  post_host_kernel<<<1, 1024, 0, s>>>((const uint64_t *)src, (uint64_t *)dst, (int)(bytes / 8), flag, done);
+  post_host_kernel<<<1, 1024, 0, s>>>((const uint64_t *)src, post);
   PRISM_HIP(hipGetLastError());
   return PRISM_OK;
 }

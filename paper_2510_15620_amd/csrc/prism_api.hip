@@ -1111,14 +1111,14 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
   const float *h_scores = (const float *)(c->h_res + res_scores), *h_top_scores = (const float *)(c->h_res + res_top + 4 * n_res);
   const int8_t *h_fate = (const int8_t *)(c->h_res + res_fate);
   const int32_t *h_top_pos = (const int32_t *)(c->h_res + res_top);
-  // bytes [from, to) of the result block, on the host when this returns; `copied` becomes the moment behind the copy.  The host
-  // watches the posted number for as long as a late wake-up would show in a call's time (a sleeping thread took 20-50 us to
-  // come back: 1 % of what it waited for and less beyond kWatch), then sleeps until the stream has drained.
-  auto fetch = [&](size_t from, size_t to, bool last = false, hipEvent_t *copied = nullptr) -> int {
-    queued(c);
-    const uint64_t number = ++c->n_posted;
-    PRISM_TRY(launch_post_host(c->d_res + from, c->h_res_dev + from, to - from, (uint64_t *)(c->h_res_dev + kResultBytes), number, s));
-    if (copied) PRISM_TRY(mark(c, copied));
+  // The result block, or its bytes [from, to), reaches the host as a post with a number of its own behind it.  The host watches
+  // that number for as long as a late wake-up would show in a call's time (a sleeping thread took 20-50 us to come back: 1 % of
+  // what it waited for and less beyond kWatch), then sleeps until the stream has drained.
+  auto next_post = [&](size_t from, size_t to) {
+    return HostPost{(uint64_t *)(c->h_res_dev + from), (uint64_t *)(c->h_res_dev + kResultBytes), ++c->n_posted, (int)((to - from) / 8)};
+  };
+  auto posted = [&]() -> int {                               // the last of them is on the host when this returns
+    const uint64_t number = c->n_posted;
     constexpr auto kWatch = std::chrono::milliseconds(4);
     const auto start = std::chrono::steady_clock::now();
     const uint64_t *flag = (const uint64_t *)(c->h_res + kResultBytes);
@@ -1126,6 +1126,14 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
       __builtin_ia32_pause();
       if (std::chrono::steady_clock::now() - start > kWatch) { PRISM_HIP(hipStreamSynchronize(s)); break; }
     }
+    return PRISM_OK;
+  };
+  // (copied: becomes the moment behind the post)
+  auto fetch = [&](size_t from, size_t to, bool last = false, hipEvent_t *copied = nullptr) -> int {
+    queued(c);
+    PRISM_TRY(launch_post_host(c->d_res + from, next_post(from, to), s));
+    if (copied) PRISM_TRY(mark(c, copied));
+    PRISM_TRY(posted());
     if (last) PRISM_HIP(hipStreamSynchronize(s));            // the call leaves a drained stream, and reads its events
     return PRISM_OK;
   };
@@ -1191,8 +1199,9 @@ static int select_impl(prism_ctx *c, const int32_t *query_tokens, int32_t query_
       PRISM_TRY(launch_score(c->X[cur], c->d_meta + mo.lastrow, n_live, m.hidden, c->final_norm, c->w_yes, c->w_no, m.dtype,
                              m.rms_eps, c->d_scores, s));
     PRISM_TRY(launch_route(c->d_scores, n_live, K_rem, c->opt.n_clusters, c->opt.cv_threshold, c->d_fate, c->d_stats,
-                           c->route_ws, s));
-    PRISM_TRY(fetch(0, res_top));
+                           c->route_ws, s, next_post(0, res_top)));
+    queued(c);
+    PRISM_TRY(posted());
     const bool gate = h_stats[2] != 0.0;
     const int n_clu = (int)h_stats[3];
     std::vector<char> keep(n_live, 1);
