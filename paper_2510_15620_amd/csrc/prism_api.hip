@@ -1412,7 +1412,7 @@ extern "C" int prism_op_qkv_finish(int32_t dtype, void *QKV, const int32_t *pos,
   else
     PRISM_TRY(launch_qk_finish_fp32((float *)QKV, pos, q_gain, k_gain, T, n_q_heads, n_kv_heads, head_dim, eps, qk_norm, (const float2 *)tab.p,
                                     rope_base, s));
-  PRISM_HIP(hipStreamSynchronize(s));   // the table is freed on return
+  PRISM_HIP(hipStreamSynchronize(s));   // as promised; the table, if there is one, is freed on return
   return PRISM_OK;
 }
 
