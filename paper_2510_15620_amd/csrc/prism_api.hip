@@ -638,7 +638,8 @@ static int ensure_scratch(prism_ctx *c, const Plan &p, bool need_second_x, int n
 }
 
 // Writes pos / vtcol / lastrow / tiles for the current live set into the pinned staging buffer and
-// uploads them.  The staging buffer is only rewritten after a stream synchronisation.
+// uploads them.  The staging buffer is only rewritten behind a later result of the same stream (a post that has arrived, or a
+// synchronisation), so the kernel that reads it has ended.
 static int upload_meta(prism_ctx *c, const Plan &p, const MetaOff &mo, bool with_tokens) {
   int32_t *h = c->h_meta;
   const int n = (int)p.live.size();

@@ -922,7 +922,7 @@ def test_rmsnorm_of_short_rows(T, hidden, dtype):
 @pytest.mark.parametrize("hd,nq,nkv,T", [(32, 3, 1, 5), (64, 4, 2, 354), (64, 4, 2, 12859), (128, 1, 1, 9001), (48, 2, 1, 77)])
 @pytest.mark.parametrize("qk_norm", [True, False])
 def test_qk_finish_fp32_head_sizes(hd, nq, nkv, T, qk_norm):
-    """fp32 finishing, one or four (token, head) items per lane group by the number of items, other head sizes one at a time:
+    """fp32 finishing, up to six heads of a token per lane with rotations evaluated in the kernel, other head sizes one at a time by the table:
     against fp64 at the bound of the single-kernel test; v is left as it was."""
     pos = (np.arange(T) % 517).astype(np.int32)
     QKV = _rand((T, (nq + 2 * nkv) * hd), torch.float32, T + hd, 1.5)
