@@ -218,6 +218,18 @@ __global__ __launch_bounds__(128) void attention_fp32_any_kernel(const float *__
 
 bool attention_fp32_tiled(int hd) { return hd == 32 || hd == 64 || hd == 128; }
 
+// The order of a launch's items.  Longest first evens out the compute units' shares, worth up to 40 % while a unit gets few items, but
+// keeps every sequence's K/V in use from the first item to the last.  Sequence by sequence only a few are: that wins, by up to 30 %, once
+// the pool's K/V are more than the caches hold, the earlier the more heads read them on different XCDs.  Over 267 pools (14 000 to 360 000
+// tokens of sequences of 60 to 8192, 2 to 32 query heads of 32 to 128) the rule's order is on average 0.4 % behind the faster one (always
+// longest first 1.4 %, never 7.4 %) and at worst 7 %, but for one pool of equal lengths (100 of 512, 16 / 16 heads of 32: a unit is dealt the
+// same block of every sequence; ms by sequence 0.447, longest first 0.394).  ms likewise, 16 / 8 heads of 64: 14 065 tokens 0.179,
+// 0.158; 45 907 of 512-1024 0.93, 0.99; 327 680 of 8192 57.1, 74.8; 8 / 8 heads of 64: 64 624 of 288-1024 0.64, 0.59; 362 962 of 200-512 2.22, 2.36.
+bool attention_fp32_longest_first(int64_t tokens, int nq, int nkv, int hd) {
+  const int64_t kv_bytes = tokens * nkv * hd * 8;
+  return kv_bytes <= (nq <= 12 ? 512000000 : 128000000);
+}
+
 template <typename Items>
 static int launch_items(const float *QKV, const Items &items, int n_tiles, int nq, int nkv, int hd, float *out, hipStream_t s) {
   if (n_tiles == 0) return PRISM_OK;

@@ -195,10 +195,11 @@ bool attention_16_supported(int nq, int nkv, int hd);
 bool attention_fp32_tiled(int hd);
 int launch_attention_fp32(const float *QKV, const int32_t *pos, const AttnTile *tiles, int n_tiles, int T, int nq, int nkv, int hd, float *out,
                           hipStream_t s);
-// fp32 items in launch arguments: longest first, over all sequences.  The fp32 kernel's workgroups are all resident at once in
-// pools of up to some 15 000 tokens, so nothing evens out what a compute unit was dealt at the start: item by item of one
-// sequence after the other, the fullest unit has twice the average (a block's work grows with its place in the sequence).  Dealt by
-// falling size, a unit gets one of each.  Level l holds block n_levels - 1 - l of the sequences that have it, which lead the
+// Whether fp32 items go longest first, over all sequences, or sequence by sequence (attn_fp32.hip has the measurements)
+bool attention_fp32_longest_first(int64_t tokens, int nq, int nkv, int hd);
+// fp32 items in launch arguments: longest first.  A small pool's workgroups are all resident at once, so nothing evens out what a
+// compute unit was dealt at the start: item by item of one sequence after the other, the fullest unit has twice the average (a
+// block's work grows with its place in the sequence).  Dealt by falling size, a unit gets one of each.  Level l holds block n_levels - 1 - l of the sequences that have it, which lead the
 // sequences when those are sorted by their blocks.  40 sequences of 160-512 tokens, 4 heads of
 // 64: 79 -> 55 us.
 static const int kAttn32BQ = 64;

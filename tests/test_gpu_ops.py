@@ -646,6 +646,46 @@ def test_attention_fp32_longest_first_and_by_list(hd, lens):
     assert torch.equal(levels, by_list[1:]) and levels.abs().sum(1).min() > 0
 
 
+@pytest.mark.parametrize("nq,nkv,hd,n,longest_first", [(16, 8, 32, 136, True), (16, 8, 32, 137, False), (16, 8, 64, 68, True), (16, 8, 64, 69, False),
+                                                       (16, 8, 128, 34, True), (16, 8, 128, 35, False), (12, 6, 128, 180, True), (12, 6, 128, 183, False),
+                                                       (2, 1, 64, 300, True), (16, 16, 64, 300, False)])
+def test_attention_fp32_on_both_sides_of_its_order_rule(nq, nkv, hd, n, longest_first):
+    """Pools whose K/V lie just below and above the limits between longest first and sequence by sequence, in launch arguments and by list: every
+    sequence has the bits that it has in a call of its own."""
+    lens = np.array([300 + (i * 37) % 320 for i in range(n)])
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    kv, limit = int(cu[-1]) * nkv * hd * 8, 512e6 if nq <= 12 else 128e6
+    assert (kv <= limit) == longest_first and (n == 300 or abs(kv / limit - 1) < 0.05)
+    QKV = torch.randn(int(cu[-1]), (nq + 2 * nkv) * hd, generator=torch.Generator(DEV).manual_seed(n), device=DEV)
+    out = torch.zeros(int(cu[-1]), nq * hd, device=DEV)
+    B.op_attention(B.DTYPE_FP32, QKV, None, 0, cu, None, nq, nkv, hd, out)
+    for i in range(n):
+        a, b = int(cu[i]), int(cu[i + 1])
+        alone = torch.zeros(b - a, nq * hd, device=DEV)
+        B.op_attention(B.DTYPE_FP32, QKV[a:b].clone(), None, 0, np.array([0, b - a], np.int32), None, nq, nkv, hd, alone)
+        assert torch.equal(out[a:b], alone), i
+
+
+def test_fp32_call_on_both_sides_of_the_attention_order_rule():
+    """A whole fp32 call whose K/V exceed the limit for longest first, against the same call in chunks that do not."""
+    m = W.ModelShape(2, 128, 16, 8, 64, 192, 64, "fp32")
+    d = torch.Generator().manual_seed(5)
+    draw = lambda *s: torch.randn(*s, generator=d) * 0.05
+    layers = [{n: (1 + draw(*s) if len(s) == 1 else draw(*s)).to(DEV) for n, s in W.layer_tensor_shapes(m).items()} for _ in range(2)]
+    wt = W.Weights(draw(64, 128).to(DEV), layers, (1 + draw(128)).to(DEV))
+    r = np.random.RandomState(4)
+    q, cands = r.randint(0, 64, 9).astype(np.int32), [r.randint(0, 64, 200 + (i * 53) % 480).astype(np.int32) for i in range(80)]
+    T = sum(len(c) + len(q) for c in cands)
+    assert T * 8 * 64 * 8 > 128e6
+    scores = []
+    for chunk in (0, 16):
+        p = B.Prism(m, wt, chunk_cands=chunk)
+        _, _, rep = p.select(q, cands, len(cands))
+        p.destroy()
+        scores.append(rep.scores[-1])
+    assert np.array_equal(scores[0], scores[1]) and len(set(scores[0])) == len(cands)
+
+
 @pytest.mark.parametrize("nq,nkv", [(1, 1), (16, 8), (32, 8)])
 @pytest.mark.parametrize("T", [1, 3, 65])
 def test_qkv_finish_16_evaluates_the_tables_rotations(nq, nkv, T):
