@@ -563,19 +563,38 @@ static TilePlan plan_tiles(const TileCost *costs, int kinds, int M, int ncols, i
 // run beside the first (over 256 tiles of 128 x 64: up to 25 % slower) and the loop is long enough for its longer start.  us, weights from
 // memory, 128 x 64: 391 x 4096 x 12288 78.7 -> 63.6, 391 x 2560 x 9728 59.5 -> 46.6, 1154 x 1024 x 3072 21.0 -> 17.6, with SwiGLU 200 x
 // 6144 x 1024 9.7 -> 9.1; of the 59 launches that the rule takes 4-26 % faster or level, where a residual add of K = 1024, which it leaves out, lost up to
-// 14 % (2000 x 1024 x 1024 9.1 -> 10.4).  128 x 128: 1154 x 2560 x 9728 76.1 -> 69.0, 900 x 4096 x 12288 103 -> 93, level (under
-// 1 %) where all rows of the tiles are inside the matrix; K = 1024 lost 2-27 % (777 x 4096 x 1024 11.8 -> 14.7).
-static bool deep_ring(int bm, int bn, bool long_only, int64_t M, int64_t ncols, int K) {
-  const int64_t tiles = (M + bm - 1) / bm * ((ncols + bn - 1) / bn);
-  return tiles <= 256 && K / BK >= (long_only ? 32 : 16);
+// 14 % (2000 x 1024 x 1024 9.1 -> 10.4).  128 x 128: 1154 x 2560 x 9728 76.1 -> 69.0, 900 x 4096 x 12288 103 -> 93; K = 1024 lost 2-27 %
+// (777 x 4096 x 1024 11.8 -> 14.7).  64 x 128 of the heads: 391 x 4096 x 1024 11.4 -> 10.8, 200 x 6144 x 4096 31.1 -> 27.1, 64 x 6144 x 2560 26.6 -> 26.9 (the
+// worst).  The gain is that of a last row tile with few rows inside the matrix, whose unit loads less: stores and residual adds are level
+// (within 0.5 %) where it is full, but SwiGLU lost 1-4 % there unless the loop is longer still, the 128 x 128 tile of the heads 0-2 %.  SwiGLU of
+// 128 x 128: 391 x 8192 x 2048 21.9 -> 21.0, but 256 x 16384 x 2048 25.2 -> 26.3, 100 x 19456 x 2560 32.3 -> 32.9 (level from K = 4096: 100 x 24576 x
+// 4096 49.3 -> 49.4); of 128 x 64: 200 x 8192 x 1024 10.0 -> 9.6, 256 x 8192 x 1024 10.5 -> 10.7, 256 x 5504 x 2048 17.0 -> 16.6; heads: 777 x 4096 x
+// 2048 21.1 -> 20.1, 896 x 4096 x 2048 23.3 -> 23.5, 1024 x 4096 x 4096 41.1 -> 41.3 to 42.0.
+static constexpr int kNever = 1 << 30;
+struct DeepRing { int slices, full_slices, last_rows; };       // K from `slices` on if the last row tile has up to last_rows rows, else from full_slices on
+static bool deep_ring(const TileCost &t, bool glu, const DeepRing &r, int64_t M, int64_t ncols, int K) {
+  const int bn = glu ? t.bn / 2 : t.bn;
+  const int64_t tiles = (M + t.bm - 1) / t.bm * ((ncols + bn - 1) / bn), last = (M - 1) % t.bm + 1;
+  return tiles <= 256 && K / BK >= (last <= r.last_rows ? r.slices : r.full_slices);
+}
+static bool deep_tile(int kind, int epi, int M, int ncols, int K) {
+  const bool glu = epi == PRISM_EPI_SWIGLU;
+  if (kind == kTile128Deep) return deep_ring(kTileCost[kind], glu, glu ? DeepRing{32, 64, 64} : DeepRing{32, 32, 128}, M, ncols, K);
+  if (kind == kTile128x64)
+    return deep_ring(kTileCost[kind], glu, glu ? DeepRing{16, 32, 96} : epi == PRISM_EPI_RESIDUAL ? DeepRing{32, 32, 128} : DeepRing{16, 16, 128}, M, ncols, K);
+  return false;
+}
+static bool deep_head(int kind, int M, int ncols, int K) {
+  if (kind == kHead128Deep) return deep_ring(kHeadCost[kind], false, DeepRing{32, kNever, 96}, M, ncols, K);
+  return kind == kHead64 && deep_ring(kHeadCost[kind], false, DeepRing{16, 16, 64}, M, ncols, K);
 }
 
 template <typename OT, int EPI>
 static int launch_kind(int kind, const OT *A, const OT *W, void *out, int M, int N, int K, hipStream_t s) {
-  constexpr bool kGlu = EPI == PRISM_EPI_SWIGLU, kRes = EPI == PRISM_EPI_RESIDUAL;
-  const int ncols = kGlu ? N / 2 : N;
-  if (kind == kTile128Deep && deep_ring(128, kGlu ? 64 : 128, true, M, ncols, K)) return launch_cfg<OT, 128, 128, 2, 2, EPI, 5>(A, W, out, M, N, K, s);
-  if (kind == kTile128x64 && deep_ring(128, kGlu ? 32 : 64, kRes, M, ncols, K)) return launch_cfg<OT, 128, 64, 4, 1, EPI, 6>(A, W, out, M, N, K, s);
+  if (deep_tile(kind, EPI, M, EPI == PRISM_EPI_SWIGLU ? N / 2 : N, K)) {
+    if (kind == kTile128Deep) return launch_cfg<OT, 128, 128, 2, 2, EPI, 5>(A, W, out, M, N, K, s);
+    return launch_cfg<OT, 128, 64, 4, 1, EPI, 6>(A, W, out, M, N, K, s);
+  }
   switch (kind) {
     case kTile256: return launch_cfg<OT, 256, 256, 2, 2, EPI, 2>(A, W, out, M, N, K, s);
     case kTile128: return launch_cfg<OT, 128, 128, 2, 2, EPI, 2>(A, W, out, M, N, K, s);
@@ -649,8 +668,10 @@ bool gemm_16_qkv_supported(int nq, int nkv, int hd, int K) {
 
 template <typename OT>
 static int launch_head(int kind, const QkvEpilogue &e, const OT *A, const OT *W, int M, int N, int K, hipStream_t s) {
-  if (kind == kHead128Deep && deep_ring(128, 128, true, M, N, K)) return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 5>(A, W, e.QK, M, N, K, s, e);
-  if (kind == kHead64 && deep_ring(64, 128, false, M, N, K)) return launch_cfg<OT, 64, 128, 4, 1, kEpiQkv, 6>(A, W, e.QK, M, N, K, s, e);
+  if (deep_head(kind, M, N, K)) {
+    if (kind == kHead128Deep) return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 5>(A, W, e.QK, M, N, K, s, e);
+    return launch_cfg<OT, 64, 128, 4, 1, kEpiQkv, 6>(A, W, e.QK, M, N, K, s, e);
+  }
   switch (kind) {
     case kHead256: return launch_cfg<OT, 256, 256, 2, 2, kEpiQkv, 2>(A, W, e.QK, M, N, K, s, e);
     case kHead128: return launch_cfg<OT, 128, 128, 4, 1, kEpiQkv, 2>(A, W, e.QK, M, N, K, s, e);

@@ -876,26 +876,32 @@ def test_projection_of_a_whole_call_has_the_bits_of_its_entry_points(dtype, nq, 
         assert err < WHOLE_CALL_ERROR[dtype]
 
 
-@pytest.mark.parametrize("nq,nkv,H,lens,kind", [(16, 8, 1024 + 64 * k, [300, 1, 60], "kHead64") for k in range(6)] +
-                         [(32, 8, 2048 + 64 * k, [300, 70, 1], "kHead128Deep") for k in range(5)])
+HEAD_RING_LAUNCHES = [(16, 8, 1024 + 64 * k, [300, 1, 60], "kHead64") for k in range(6)] + [(32, 8, 2048 + 64 * k, [300, 70, 1], "kHead128Deep") for k in range(5)]
+
+
+@pytest.mark.parametrize("nq,nkv,H,lens,kind", HEAD_RING_LAUNCHES)
 def test_projection_on_the_deep_rings(nq, nkv, H, lens, kind):
-    """At most 256 tiles and a long K: rings of 6 and 5 slices, ended at every place."""
+    """At most 256 tiles and a long K: rings of 6 and 5 slices, ended at every place (that these launches take them: test_tile_plan.py)."""
     test_projection_of_a_whole_call_has_the_bits_of_its_entry_points(torch.float16, nq, nkv, H, lens, kind)
 
 
+# (epilogue, tile, rows, N, K slices, rows of the taller launch that it is compared with)
+RING_LAUNCHES = [(e, *c) for e in (B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_STORE_F32) for c in (
+    ("kTile128x64", 391, 2552, range(32, 38), 2000), ("kTile128Deep", 777, 2552, range(32, 37), 4100))] + [
+    (e, "kTile128x64", 391, 4088, range(16, 22), 1500) for e in (B.EPI_STORE, B.EPI_STORE_F32)] + [
+    (B.EPI_SWIGLU, "kTile128x64", 200, 6152, range(16, 22), 1500), (B.EPI_SWIGLU, "kTile128Deep", 391, 6152, range(32, 37), 1500)]
+
+
 @pytest.mark.parametrize("dtype", SIXTEEN)
-@pytest.mark.parametrize("epi,kind,M,N,slices,tall", [(e, *c) for e in (B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_STORE_F32) for c in (
-    ("kTile128x64", 391, 2552, range(32, 38), 2000), ("kTile128Deep", 777, 2552, range(32, 37), 4100))] +
-    [(B.EPI_SWIGLU, "kTile128x64", 200, 6152, range(16, 22), 1500), (B.EPI_SWIGLU, "kTile128Deep", 391, 6152, range(32, 37), 1500)])
+@pytest.mark.parametrize("epi,kind,M,N,slices,tall", RING_LAUNCHES)
 def test_gemm_16_deep_rings_give_a_row_the_same_bits(dtype, epi, kind, M, N, slices, tall):
     """Tiles of 128 rows on their ring for one tile per compute unit, a loop's end at every place of it, ragged last tiles: bit for
-    bit the same rows inside a taller launch, which takes more than 256 tiles or others (each of those is compared with fp64 above)."""
+    bit the same rows inside a taller launch, which takes the other ring or other tiles (test_tile_plan.py asks the launcher; each of
+    those is compared with fp64 above)."""
     glu = epi == B.EPI_SWIGLU
-    bm, bn = (128, 64) if kind == "kTile128x64" else (128, 128)
-    assert -(-M // bm) * -(-N // bn) <= 256
     for k in slices:
         K = 64 * k
-        assert gemm_plan(M, N, K, glu) == [(M, kind)] and (kind not in [t for _, t in gemm_plan(tall, N, K, glu)] or -(-tall // bm) * -(-N // bn) > 256)
+        assert gemm_plan(M, N, K, glu) == [(M, kind)]
         A, Wt = _rand((tall, K), dtype, 75, 1.0).to(DEV), _rand((N, K), dtype, 76, 1.0 / math.sqrt(K)).to(DEV)
         X0 = _rand((tall, N), torch.float32, 77, 1.0).to(DEV)
 

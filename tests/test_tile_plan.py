@@ -9,11 +9,13 @@ import subprocess
 
 import pytest
 
+from paper_2510_15620_amd import binding as B
 from tests import helpers as H
 
 GLUE = """
 #include <algorithm>
 #include <cstdint>
+enum { PRISM_EPI_STORE, PRISM_EPI_RESIDUAL, PRISM_EPI_SWIGLU, PRISM_EPI_STORE_F32 };
 static constexpr int BK = 64;
 static int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 %s
@@ -22,6 +24,7 @@ extern "C" void plan(int heads, int M, int ncols, int K, int glu, int *out) {
   out[0] = p.rows_big;
   out[1] = p.kind;
 }
+extern "C" int deep(int heads, int kind, int epi, int M, int ncols, int K) { return heads ? deep_head(kind, M, ncols, K) : deep_tile(kind, epi, M, ncols, K); }
 """
 
 
@@ -40,6 +43,12 @@ def launcher(tmp_path_factory):
         lib.plan(int(heads), M, ncols, K, int(glu), out)
         big, kind = out[0], kinds[out[1]]
         return [(big, kinds[0]), (M - big, kind)] if big else [(M, kind)]
+
+    def deep(heads, kind, epi, M, ncols, K):
+        """Does a launch of tile `kind` run on its deeper ring."""
+        kinds = [t[0] for t in (H._tile_table(src, "kHead256", "kHeadCost") if heads else H._tile_table(src, "kTile256", "kTileCost"))]
+        return bool(lib.deep(int(heads), kinds.index(kind), epi, M, ncols, K))
+    ask.deep = deep
     return ask
 
 
@@ -83,6 +92,44 @@ def test_launches_of_the_bit_test_end_at_every_place_of_each_ring(loops):
                 c = loops[loop]
                 period = sum("v_mfma" in line for line in c.text()) // (2 * c.NS)       # slices of a turn; 2 NS products in each
                 assert {(k - 1) % period for k in slices if k > period} == set(range(period)), (kind, glu)
+
+
+def test_launches_of_the_ring_tests_run_on_the_deep_rings(launcher, loops):
+    """The GPU tests compare bits, which every ring gives alike: that the launch under test takes the deeper ring, and the one that it is
+    compared with does not, is the launcher's own word."""
+    from tests.test_gpu_ops import HEAD_RING_LAUNCHES, RING_LAUNCHES
+    for epi, kind, M, N, slices, tall in RING_LAUNCHES:
+        glu, ncols = epi == B.EPI_SWIGLU, N // 2 if epi == B.EPI_SWIGLU else N
+        for k in slices:
+            assert H.gemm_plan(M, N, 64 * k, glu) == [(M, kind)] and launcher.deep(False, kind, epi, M, ncols, 64 * k), (epi, kind, k)
+            assert not any(t == kind and launcher.deep(False, t, epi, rows, ncols, 64 * k) for rows, t in H.gemm_plan(tall, N, 64 * k, glu)), (epi, kind, k)
+        stages = loops[{"kTile128x64": "128x64_6", "kTile128Deep": "128x128_5"}[kind]].S
+        assert {k % stages for k in slices} == set(range(stages))                  # the loop ends at every place of the ring
+    assert {(e, t) for e, t, *_ in RING_LAUNCHES} == set(itertools.product(range(4), ("kTile128x64", "kTile128Deep")))
+    for nq, nkv, hidden, lens, kind in HEAD_RING_LAUNCHES:
+        T, N = sum(lens) + 7 * len(lens), (nq + 2 * nkv) * 128
+        assert H.head_plan(T, nq, nkv, hidden) == [(T, kind)] and launcher.deep(True, kind, 0, T, N, hidden)
+
+
+STORE, RESIDUAL, SWIGLU, STORE_F32 = range(4)
+
+
+@pytest.mark.parametrize("heads,kind,epi,taken,left", [
+    # (rows, columns out, slices) on the two sides of each limit: tiles, slices, rows of the last row tile
+    *[(False, "kTile128x64", e, (128, 256 * 64, 16), (128, 257 * 64, 16)) for e in (STORE, STORE_F32)],
+    *[(False, "kTile128x64", e, (512, 1024, 16), (512, 1024, 15)) for e in (STORE, STORE_F32)],
+    (False, "kTile128x64", RESIDUAL, (512, 1024, 32), (512, 1024, 31)),
+    (False, "kTile128x64", SWIGLU, (128, 256 * 32, 32), (128, 257 * 32, 32)), (False, "kTile128x64", SWIGLU, (224, 1024, 16), (225, 1024, 16)),
+    (False, "kTile128x64", SWIGLU, (224, 1024, 16), (224, 1024, 15)), (False, "kTile128x64", SWIGLU, (225, 1024, 32), (225, 1024, 31)),
+    *[(False, "kTile128Deep", e, (128, 256 * 128, 32), (128, 257 * 128, 32)) for e in (STORE, RESIDUAL, STORE_F32)],
+    *[(False, "kTile128Deep", e, (512, 1024, 32), (512, 1024, 31)) for e in (STORE, RESIDUAL, STORE_F32)],
+    (False, "kTile128Deep", SWIGLU, (64, 256 * 64, 32), (64, 257 * 64, 32)), (False, "kTile128Deep", SWIGLU, (192, 1024, 32), (193, 1024, 32)),
+    (False, "kTile128Deep", SWIGLU, (192, 1024, 32), (192, 1024, 31)), (False, "kTile128Deep", SWIGLU, (193, 1024, 64), (193, 1024, 63)),
+    (True, "kHead64", 0, (64, 256 * 128, 16), (64, 257 * 128, 16)), (True, "kHead64", 0, (64, 1024, 16), (64, 1024, 15)),
+    (True, "kHead128Deep", 0, (96, 256 * 128, 32), (96, 257 * 128, 32)), (True, "kHead128Deep", 0, (224, 1024, 32), (225, 1024, 32)),
+    (True, "kHead128Deep", 0, (224, 1024, 32), (224, 1024, 31)), (True, "kHead128Deep", 0, (224, 1024, 1024), (225, 1024, 1024))])
+def test_limits_of_the_deep_rings(launcher, heads, kind, epi, taken, left):
+    assert launcher.deep(heads, kind, epi, taken[0], taken[1], 64 * taken[2]) and not launcher.deep(heads, kind, epi, left[0], left[1], 64 * left[2])
 
 
 def test_tiles_for_few_rows_keep_their_slices_in_flight(loops):
