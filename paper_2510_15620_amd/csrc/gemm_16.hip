@@ -570,23 +570,28 @@ static TilePlan plan_tiles(const TileCost *costs, int kinds, int M, int ncols, i
 // 128 x 128: 391 x 8192 x 2048 21.9 -> 21.0, but 256 x 16384 x 2048 25.2 -> 26.3, 100 x 19456 x 2560 32.3 -> 32.9 (level from K = 4096: 100 x 24576 x
 // 4096 49.3 -> 49.4); of 128 x 64: 200 x 8192 x 1024 10.0 -> 9.6, 256 x 8192 x 1024 10.5 -> 10.7, 256 x 5504 x 2048 17.0 -> 16.6; heads: 777 x 4096 x
 // 2048 21.1 -> 20.1, 896 x 4096 x 2048 23.3 -> 23.5, 1024 x 4096 x 4096 41.1 -> 41.3 to 42.0.
+// 128 x 128 on all units: from K = 3072 on (916 x 4096 x 3072 of heads 30.8 -> 30.7, x 4096 38.5 -> 36.3, but x 2048 22.7 -> 25.5, residual 956 x 4096 x 2048 23.9
+// -> 24.5, SwiGLU 148 x 16384 x 2048 22.5 -> 23.9; 224 tiles, 788 x 4096 x 2048 of heads 22.1 -> 21.6, residual 21.9 -> 21.4).
 static constexpr int kNever = 1 << 30;
-struct DeepRing { int slices, full_slices, last_rows; };       // K from `slices` on if the last row tile has up to last_rows rows, else from full_slices on
+struct DeepRing {
+  int slices, last_rows, full_slices;      // K from `slices` on where the last row tile has up to last_rows rows, else from full_slices on
+  int chip_slices;                         // more than 224 tiles: from here on
+};
 static bool deep_ring(const TileCost &t, bool glu, const DeepRing &r, int64_t M, int64_t ncols, int K) {
   const int bn = glu ? t.bn / 2 : t.bn;
   const int64_t tiles = (M + t.bm - 1) / t.bm * ((ncols + bn - 1) / bn), last = (M - 1) % t.bm + 1;
-  return tiles <= 256 && K / BK >= (last <= r.last_rows ? r.slices : r.full_slices);
+  return tiles <= 256 && K / BK >= (last <= r.last_rows ? r.slices : r.full_slices) && (tiles <= 224 || K / BK >= r.chip_slices);
 }
 static bool deep_tile(int kind, int epi, int M, int ncols, int K) {
   const bool glu = epi == PRISM_EPI_SWIGLU;
-  if (kind == kTile128Deep) return deep_ring(kTileCost[kind], glu, glu ? DeepRing{32, 64, 64} : DeepRing{32, 32, 128}, M, ncols, K);
+  if (kind == kTile128Deep) return deep_ring(kTileCost[kind], glu, glu ? DeepRing{32, 64, 64, 48} : DeepRing{32, 128, 32, 48}, M, ncols, K);
   if (kind == kTile128x64)
-    return deep_ring(kTileCost[kind], glu, glu ? DeepRing{16, 32, 96} : epi == PRISM_EPI_RESIDUAL ? DeepRing{32, 32, 128} : DeepRing{16, 16, 128}, M, ncols, K);
+    return deep_ring(kTileCost[kind], glu, glu ? DeepRing{16, 96, 32, 0} : epi == PRISM_EPI_RESIDUAL ? DeepRing{32, 128, 32, 0} : DeepRing{16, 128, 16, 0}, M, ncols, K);
   return false;
 }
 static bool deep_head(int kind, int M, int ncols, int K) {
-  if (kind == kHead128Deep) return deep_ring(kHeadCost[kind], false, DeepRing{32, kNever, 96}, M, ncols, K);
-  return kind == kHead64 && deep_ring(kHeadCost[kind], false, DeepRing{16, 16, 64}, M, ncols, K);
+  if (kind == kHead128Deep) return deep_ring(kHeadCost[kind], false, DeepRing{32, 96, kNever, 48}, M, ncols, K);
+  return kind == kHead64 && deep_ring(kHeadCost[kind], false, DeepRing{16, 64, 16, 0}, M, ncols, K);
 }
 
 template <typename OT, int EPI>
