@@ -161,27 +161,35 @@ int launch_vt_prefix_broadcast(void *Vt, int64_t vt_stride, int rows, int ql, co
 struct AttnTile { int32_t row_base, seq_len, q0, vt_col0, pre_len, pre_row0, out_base, reserved; };
 // Where a workgroup finds its work item: in a list in device memory (prism_select uploads one with each pool's metadata), or in
 // the launch's arguments, as the sequences themselves (a call of its own: no list to allocate, copy and wait for).  Item i of
-// the second kind is found by counting the sequences that end at or before it, 64 at a time, in one load latency; items are
+// the second kind is found by counting the sequences that end at or before it, in one load latency; items are
 // in the list's order (sequence by sequence, last block of queries first).  256 sequences are 3 KiB of the 4 KiB that a launch's
-// arguments may take; longer calls go by a list.  8 sequences of 32-64 tokens, fp32 layer through the separate entry points, this
-// and the finishing kernel without a table: 133 -> 91 us; 7 sequences of 56-301 in bf16 92 -> 87.
+// arguments may take; longer calls go by a list.  A call of prism_op_attention with 16 / 8 heads, us by a list and this way: 7 sequences of
+// 56-301 tokens 29.2, 25.4; 256 of 20-60 53.4, 49.3; 256 of 300-512, 32 / 8 heads 820, 817.
 struct AttnList {
   const AttnTile *tiles;
   __device__ __forceinline__ AttnTile operator()(int i) const { return tiles[i]; }
 };
 static const int kAttnSeqs = 256;
+// How many of the first n of N running sums are at most i, by a whole wave; all loads are requested together (64 sums and their
+// count after the other, the last call above took 2 % longer than by the list).
+template <int N>
+__device__ __forceinline__ int count_ended(const int32_t (&end)[N], int n, int i) {
+  static_assert(N % 64 == 0, "a load per lane and 64 sums");
+  const int lane = threadIdx.x & 63;
+  int32_t e[N / 64];
+#pragma unroll
+  for (int b = 0; b < N / 64; ++b) e[b] = end[b * 64 + lane];
+  int c = 0;
+#pragma unroll
+  for (int b = 0; b < N / 64; ++b) c += __popcll(__builtin_amdgcn_ballot_w64(b * 64 + lane < n && e[b] <= i));
+  return __builtin_amdgcn_readfirstlane(c);
+}
 struct AttnSeqs {
   int32_t n, bq;                                // sequences, queries of an item
   int32_t end[kAttnSeqs];                       // items of sequences 0 .. s
   int32_t cu[kAttnSeqs + 1], vt_col0[kAttnSeqs];
   __device__ __forceinline__ AttnTile operator()(int i) const {
-    int s = 0;
-    for (int b = 0; b < n; b += 64) {
-      const int j = b + (int)(threadIdx.x & 63);
-      s += __popcll(__builtin_amdgcn_ballot_w64(j < n && end[j < n ? j : 0] <= i));
-    }
-    s = __builtin_amdgcn_readfirstlane(s);
-    const int row = cu[s];
+    const int s = count_ended<kAttnSeqs>(end, n, i), row = cu[s];
     return {row, cu[s + 1] - row, (end[s] - 1 - i) * bq, vt_col0[s], 0, 0, row, 0};
   }
 };
@@ -199,21 +207,17 @@ int launch_attention_fp32(const float *QKV, const int32_t *pos, const AttnTile *
 bool attention_fp32_longest_first(int64_t tokens, int nq, int nkv, int hd);
 // fp32 items in launch arguments: longest first.  A small pool's workgroups are all resident at once, so nothing evens out what a
 // compute unit was dealt at the start: item by item of one sequence after the other, the fullest unit has twice the average (a
-// block's work grows with its place in the sequence).  Dealt by falling size, a unit gets one of each.  Level l holds block n_levels - 1 - l of the sequences that have it, which lead the
-// sequences when those are sorted by their blocks.  40 sequences of 160-512 tokens, 4 heads of
-// 64: 79 -> 55 us.
+// block's work grows with its place in the sequence).  Dealt by falling size, a unit gets one of each.  Level l holds block
+// n_levels - 1 - l of the sequences that have it, which lead the sequences when those are sorted by their blocks.  40 sequences of
+// 160-512 tokens, 4 heads of 64: 79 -> 55 us.  8 sequences of 32-64 tokens, fp32 layer through the separate entry points, without a
+// list here and without a table in the finishing kernel: 133 -> 91.
 static const int kAttn32BQ = 64;
 struct AttnLevels {
   int32_t n_levels;
   int32_t end[PRISM_MAX_SEQ / kAttn32BQ];       // items of levels 0 .. l
   int32_t row[kAttnSeqs], len[kAttnSeqs];
   __device__ __forceinline__ AttnTile operator()(int i) const {
-    int l = 0;
-    for (int b = 0; b < n_levels; b += 64) {
-      const int j = b + (int)(threadIdx.x & 63);
-      l += __popcll(__builtin_amdgcn_ballot_w64(j < n_levels && end[j < n_levels ? j : 0] <= i));
-    }
-    l = __builtin_amdgcn_readfirstlane(l);
+    const int l = count_ended<PRISM_MAX_SEQ / kAttn32BQ>(end, n_levels, i);
     const int s = i - (l ? end[l - 1] : 0), r = row[s];
     return {r, len[s], (n_levels - 1 - l) * kAttn32BQ, 0, 0, 0, r, 0};
   }

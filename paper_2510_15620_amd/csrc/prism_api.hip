@@ -1473,7 +1473,7 @@ extern "C" int prism_op_attention(int32_t dtype, const void *QK, const void *Vt,
     std::vector<int32_t> pos;
     const bool tiled = attention_fp32_tiled(hd) && ((uintptr_t)QK | (uintptr_t)out) % 16 == 0;
     if (tiled && cu[0] == 0 && n_seqs <= kAttnSeqs && attention_fp32_longest_first(T, nq, nkv, hd)) {   // by launch arguments (see AttnLevels)
-      AttnLevels a;
+      AttnLevels a{};
       std::vector<int> order(n_seqs);
       for (int i = 0; i < n_seqs; ++i) order[i] = i;
       auto blocks = [&](int i) { return cdiv(cu[i + 1] - cu[i], kAttn32BQ); };
@@ -1515,7 +1515,7 @@ extern "C" int prism_op_attention(int32_t dtype, const void *QK, const void *Vt,
     PRISM_REQUIRE(vt_col0[i] >= 0 && vt_col0[i] % 64 == 0 && vt_col0[i] + round_up(cu[i + 1] - cu[i], 64) <= vt_stride, PRISM_EINVAL,
                   "attention bf16: sequence %d: V^T columns must start at a multiple of 64 and fit the row stride", i);
   if (n_seqs <= kAttnSeqs) {                                   // they fit a launch's arguments (see AttnSeqs)
-    AttnSeqs a;
+    AttnSeqs a{};
     a.n = n_seqs;
     a.bq = bq;
     for (int i = 0; i < n_seqs; ++i) {
