@@ -256,24 +256,33 @@ __global__ __launch_bounds__(256) void qk_finish_kernel(float *__restrict__ QKV,
 // as 64 consecutive tokens of one d per wave instruction.  Then q and k: a workgroup takes all heads of 4 tokens, 16 lanes each,
 // a lane holding 4 + 4 values of the two rotation halves; a lane's token stays the same over its heads.  So the tokens' 4 x 64
 // rotations are one fp64 evaluation per thread, while the first values are on their way, and no table has to be allocated,
-// filled and waited for: 1154 tokens of 16 + 8 heads 3.0 (table) + 9.9 us in two launches -> 9.8 in one.
-template <typename T>
+// filled and waited for: 1154 tokens of 16 + 8 heads 3.0 (table) + 9.9 us in two launches -> 9.8 in one.  kFew, for up to 6 heads of
+// many tokens: a wave takes all heads of 4 tokens of its own, 16 to a workgroup.  With 4 to a workgroup most waves have a head or
+// none, and starting workgroups is what the launch takes its time for: us of the call, by the two launches, 4 tokens and 16: 1 + 1 heads 96 064
+// tokens 72, 83, 60, 20 000 33.5, 31.8, 28.3; 2 + 1 of 200 000 154, 209, 139; 4 + 2 of 50 000 89, 86, 71.  Up to some 8000 tokens the
+// evaluations of four rotations in a row are the longer way (400 tokens 18.3, 16 to a workgroup 19.7), and from 8 + 2 heads on it is level or worse.
+template <typename T, bool kFew>
 __global__ __launch_bounds__(256) void qkv_finish_16_kernel(const float *__restrict__ QKV, const int32_t *__restrict__ pos,
                                                             const T *__restrict__ q_gain, const T *__restrict__ k_gain, int n_tok,
                                                             int nq, int nkv, float eps, int qk_norm, double log2_base, T *__restrict__ out,
                                                             f16 *__restrict__ Vt, const int32_t *__restrict__ vt_col, int64_t vt_stride) {
-  constexpr int HD = 128, kTok = 4, kHeads = 6;              // tokens of a workgroup, heads whose values a lane requests together
+  constexpr int HD = 128, kTok = kFew ? 16 : 4, kHeads = 6;  // tokens of a workgroup, heads whose values a lane requests together
+  constexpr int kStep = kFew ? 1 : 4;                        // from one head of a wave to its next
   typedef typename Mfma<T>::vec4 vec4;
   const int heads = nq + nkv, row = (nq + 2 * nkv) * HD;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int v_groups = (n_tok + 63) / 64 * nkv;
   if ((int)blockIdx.x >= v_groups) {
     __shared__ __align__(16) float2 rot[kTok][HD / 2];
-    const int t0 = ((int)blockIdx.x - v_groups) * kTok;
-    const int i = (lane & 15) * 4, tk = lane >> 4;           // first of the lane's 4 rotation pairs, its token
+    const int t0 = ((int)blockIdx.x - v_groups) * kTok, h_first = kFew ? 0 : wave;
+    const int i = (lane & 15) * 4, tk = (kFew ? wave * 4 : 0) + (lane >> 4);   // first of the lane's 4 rotation pairs, its token
     const int t = t0 + tk < n_tok ? t0 + tk : n_tok - 1;
-    const int rt = t0 + wave < n_tok ? t0 + wave : n_tok - 1;
-    const int rpos = pos[rt];
+    int rpos[kTok / 4];                                      // positions of the tokens whose rotations this wave evaluates
+#pragma unroll
+    for (int r = 0; r < kTok / 4; ++r) {
+      const int rt = t0 + wave * (kTok / 4) + r;
+      rpos[r] = pos[rt < n_tok ? rt : n_tok - 1];
+    }
     vec4 gq[2], gk[2];
     if (qk_norm) {
       gq[0] = *reinterpret_cast<const vec4 *>(q_gain + i);
@@ -287,22 +296,23 @@ __global__ __launch_bounds__(256) void qkv_finish_16_kernel(const float *__restr
     auto fetch = [&](int h0) __attribute__((always_inline)) {
 #pragma unroll
       for (int k = 0; k < kHeads; ++k) {
-        const int h = h0 + 4 * k < heads ? h0 + 4 * k : heads - 1;
+        const int h = h0 + kStep * k < heads ? h0 + kStep * k : heads - 1;
         a[k] = *reinterpret_cast<const f32x4 *>(x + h * HD);
         b[k] = *reinterpret_cast<const f32x4 *>(x + h * HD + 64);
       }
     };
-    fetch(wave);
-    rot[wave][lane] = rotation(rpos, lane, HD / 2, log2_base);
+    fetch(h_first);
+#pragma unroll
+    for (int r = 0; r < kTok / 4; ++r) rot[wave * (kTok / 4) + r][lane] = rotation(rpos[r], lane, HD / 2, log2_base);
     __syncthreads();
     float2 cs[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) cs[q] = rot[tk][i + q];
-    for (int h0 = wave; h0 < heads; h0 += 4 * kHeads) {
-      if (h0 != wave) fetch(h0);
+    for (int h0 = h_first; h0 < heads; h0 += kStep * kHeads) {
+      if (h0 != h_first) fetch(h0);
 #pragma unroll
       for (int k = 0; k < kHeads; ++k) {
-        const int h = h0 + 4 * k;
+        const int h = h0 + kStep * k;
         if (h >= heads) break;                               // the same for the whole wave
         float r = 1.f;
         if (qk_norm) {
@@ -470,8 +480,13 @@ int launch_qkv_finish_16(int dtype, const float *QKV, const int32_t *pos, const 
     const OT *gq = (const OT *)q_gain, *gk = (const OT *)k_gain;
     // one launch where every access of four values is aligned; otherwise value by value, by the table
     if (direct) {
-      qkv_finish_16_kernel<OT><<<cdiv(T, 64) * nkv + cdiv(T, 4), 256, 0, s>>>(QKV, pos, gq, gk, T, nq, nkv, eps, qk_norm, log2((double)rope_base),
-                                                                             (OT *)QK, (f16 *)Vt, vt_col, vt_stride);
+      auto go = [&](auto few) {
+        constexpr bool kFew = decltype(few)::value;
+        qkv_finish_16_kernel<OT, kFew><<<cdiv(T, 64) * nkv + cdiv(T, kFew ? 16 : 4), 256, 0, s>>>(QKV, pos, gq, gk, T, nq, nkv, eps, qk_norm,
+                                                                                                log2((double)rope_base), (OT *)QK, (f16 *)Vt, vt_col, vt_stride);
+      };
+      if (nq + nkv <= 6 && T >= 8192) go(std::true_type{});
+      else go(std::false_type{});
       return;
     }
     qk_finish_kernel<OT><<<cdiv((int64_t)T * (nq + nkv), 4), 256, 0, s>>>(const_cast<float *>(QKV), pos, gq, gk, T, nq, nkv, hd, eps, qk_norm, rope_tab,
