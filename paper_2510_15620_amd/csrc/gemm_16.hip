@@ -502,10 +502,12 @@ static int launch_cfg(const OT *A, const OT *W, void *out, int M, int N, int K, 
 // many tiles share the unit: alone it is a chain of latencies, together the matrix pipes and LDS.  The constants were fit to loops
 // on 32x32x16 MFMAs with operands that stay in the caches (256 x 256: to those of today); with weights from memory and the loops of
 // today they are off by 11-23 % (root mean square) per tile, 256 x 256 by 30 % where the chip is not full, but what counts is the pick: on
-// 265 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues) it is on average 0.5 % above the best tile, at worst 15 %
-// (391 x 2560 x 9728 stored: 59 us on 128 x 64, 51 on 64 x 64).  Examples, us with weights from memory, 32x32x16 loops -> now: 100 x 4096 x 12288
+// 265 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues) it is on average 0.5 % above the best tile and ring.  The
+// costs are of the shallow rings (deep_ring, below, only says which ring the picked tile runs on), so the worst picks stand beside a 128 x 64
+// tile on its deeper one: 150 x 6144 x 2560 stored 21.6 us on 32 x 64, 16.8 there, 150 x 6144 x 4096 28.5 and 23.2; next 64 x 19456 x 2560 with
+// SwiGLU, 35.2 on 64 x 64 and 30.5 on 128 x 128.  Examples, us with weights from memory, 32x32x16 loops -> now: 100 x 4096 x 12288
 // 38.8 -> 38.7 (64 x 32), 391 x 1024 x 3072 10.2 -> 10.0 (64 x 32), 33 x 2560 x 9728 19.3 -> 18.5 (32 x 32), 777 x 6144 x 1024 with SwiGLU
-// 19.7 -> 19.1 (128 x 128), 3699 x 1024 x 3072 34.0 -> 33.4 (128 x 128, four stages).
+// 19.7 -> 19.1 (128 x 128), 3699 x 1024 x 3072 34.0 -> 32.8 (128 x 128, four stages).
 // (256 x 256: on chips of different speed a slice takes 1.34-1.7 us, the fixed part 11 us with SwiGLU and 17 with a residual or a
 // head; 1024 x 24576 x 4096 with SwiGLU 233 us on 128 x 128 tiles, 203 on these; 1536 x 6144 x 4096 with heads 103 and 90.)
 struct TileCost {
@@ -565,11 +567,11 @@ static TilePlan plan_tiles(const TileCost *costs, int kinds, int M, int ncols, i
 // 6144 x 1024 9.7 -> 9.1; of the 59 launches that the rule takes 4-26 % faster or level, where a residual add of K = 1024, which it leaves out, lost up to
 // 14 % (2000 x 1024 x 1024 9.1 -> 10.4).  128 x 128: 1154 x 2560 x 9728 76.1 -> 69.0, 900 x 4096 x 12288 103 -> 93; K = 1024 lost 2-27 %
 // (777 x 4096 x 1024 11.8 -> 14.7).  64 x 128 of the heads: 391 x 4096 x 1024 11.4 -> 10.8, 200 x 6144 x 4096 31.1 -> 27.1, 64 x 6144 x 2560 26.6 -> 26.9 (the
-// worst).  The gain is that of a last row tile with few rows inside the matrix, whose unit loads less: stores and residual adds are level
-// (within 0.5 %) where it is full, but SwiGLU lost 1-4 % there unless the loop is longer still, the 128 x 128 tile of the heads 0-2 %.  SwiGLU of
-// 128 x 128: 391 x 8192 x 2048 21.9 -> 21.0, but 256 x 16384 x 2048 25.2 -> 26.3, 100 x 19456 x 2560 32.3 -> 32.9 (level from K = 4096: 100 x 24576 x
-// 4096 49.3 -> 49.4); of 128 x 64: 200 x 8192 x 1024 10.0 -> 9.6, 256 x 8192 x 1024 10.5 -> 10.7, 256 x 5504 x 2048 17.0 -> 16.6; heads: 777 x 4096 x
-// 2048 21.1 -> 20.1, 896 x 4096 x 2048 23.3 -> 23.5, 1024 x 4096 x 4096 41.1 -> 41.3 to 42.0.
+// worst).  The gain is that of a last row tile with few rows inside the matrix, whose unit loads less.  Where it is fuller, 128 x 128 and SwiGLU
+// are level or gain a little on a long K and lose up to 6 % on a shorter one: 128 x 128, residual 3699 x 1024 x 3072 32.8 -> 34.1, 2000 x 1024 x 3072 27.5 -> 29.1,
+// SwiGLU 256 x 16384 x 2048 25.2 -> 26.3, 100 x 19456 x 2560 32.3 -> 32.9, heads 896 x 4096 x 2048 23.3 -> 23.5, 1024 x 4096 x 4096 41.1 -> 41.3 to 42.0, but 391 x 8192 x
+// 2048 with SwiGLU 21.9 -> 21.0, 777 x 4096 x 2048 of heads 21.1 -> 20.1, and from K = 4096 on 1500 x 2560 x 4096 39.7 -> 39.4, 100 x 24576 x 4096 with SwiGLU 49.3 -> 49.4;
+// 128 x 64 with SwiGLU, 200 x 8192 x 1024 10.0 -> 9.6, 256 x 8192 x 1024 10.5 -> 10.7, 256 x 5504 x 2048 17.0 -> 16.6.
 // 128 x 128 on all units: from K = 3072 on (916 x 4096 x 3072 of heads 30.8 -> 30.7, x 4096 38.5 -> 36.3, but x 2048 22.7 -> 25.5, residual 956 x 4096 x 2048 23.9
 // -> 24.5, SwiGLU 148 x 16384 x 2048 22.5 -> 23.9; 224 tiles, 788 x 4096 x 2048 of heads 22.1 -> 21.6, residual 21.9 -> 21.4).
 static constexpr int kNever = 1 << 30;
@@ -584,7 +586,7 @@ static bool deep_ring(const TileCost &t, bool glu, const DeepRing &r, int64_t M,
 }
 static bool deep_tile(int kind, int epi, int M, int ncols, int K) {
   const bool glu = epi == PRISM_EPI_SWIGLU;
-  if (kind == kTile128Deep) return deep_ring(kTileCost[kind], glu, glu ? DeepRing{32, 64, 64, 48} : DeepRing{32, 128, 32, 48}, M, ncols, K);
+  if (kind == kTile128Deep) return deep_ring(kTileCost[kind], glu, DeepRing{32, 64, 64, 48}, M, ncols, K);
   if (kind == kTile128x64)
     return deep_ring(kTileCost[kind], glu, glu ? DeepRing{16, 96, 32, 0} : epi == PRISM_EPI_RESIDUAL ? DeepRing{32, 128, 32, 0} : DeepRing{16, 128, 16, 0}, M, ncols, K);
   return false;
