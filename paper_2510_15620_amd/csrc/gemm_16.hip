@@ -567,13 +567,14 @@ static TilePlan plan_tiles(const TileCost *costs, int kinds, int M, int ncols, i
 // 6144 x 1024 9.7 -> 9.1; of the 59 launches that the rule takes 4-26 % faster or level, where a residual add of K = 1024, which it leaves out, lost up to
 // 14 % (2000 x 1024 x 1024 9.1 -> 10.4).  128 x 128: 1154 x 2560 x 9728 76.1 -> 69.0, 900 x 4096 x 12288 103 -> 93; K = 1024 lost 2-27 %
 // (777 x 4096 x 1024 11.8 -> 14.7).  64 x 128 of the heads: 391 x 4096 x 1024 11.4 -> 10.8, 200 x 6144 x 4096 31.1 -> 27.1, 64 x 6144 x 2560 26.6 -> 26.9 (the
-// worst).  The gain is that of a last row tile with few rows inside the matrix, whose unit loads less.  Where it is fuller, 128 x 128 and SwiGLU
-// are level or gain a little on a long K and lose up to 6 % on a shorter one: 128 x 128, residual 3699 x 1024 x 3072 32.8 -> 34.1, 2000 x 1024 x 3072 27.5 -> 29.1,
-// SwiGLU 256 x 16384 x 2048 25.2 -> 26.3, 100 x 19456 x 2560 32.3 -> 32.9, heads 896 x 4096 x 2048 23.3 -> 23.5, 1024 x 4096 x 4096 41.1 -> 41.3 to 42.0, but 391 x 8192 x
-// 2048 with SwiGLU 21.9 -> 21.0, 777 x 4096 x 2048 of heads 21.1 -> 20.1, and from K = 4096 on 1500 x 2560 x 4096 39.7 -> 39.4, 100 x 24576 x 4096 with SwiGLU 49.3 -> 49.4;
-// 128 x 64 with SwiGLU, 200 x 8192 x 1024 10.0 -> 9.6, 256 x 8192 x 1024 10.5 -> 10.7, 256 x 5504 x 2048 17.0 -> 16.6.
+// worst).  The gain is that of a last row tile with few rows inside the matrix, whose unit loads less.  Where it is more than half full, 128 x 128
+// is level on a long K (SwiGLU 100 x 24576 x 4096 48.1 -> 48.2, 128 x 24576 x 4096 50.3 -> 50.8, residual 1500 x 2560 x 4096 39.7 -> 39.4) and loses up to 6 % on a
+// shorter one: residual 3699 x 1024 x 3072 32.8 -> 34.1, 2000 x 1024 x 3072 27.5 -> 29.1, SwiGLU 256 x 16384 x 2048 25.2 -> 26.3, 100 x 19456 x 2560 32.3 -> 32.9, heads
+// 896 x 4096 x 2048 23.3 -> 23.5, where SwiGLU of 391 x 8192 x 2048 takes 21.9 -> 21.0 and heads of 777 x 4096 x 2048 21.1 -> 20.1.  128 x 64 with SwiGLU,
+// 200 x 8192 x 1024 10.0 -> 9.6, 256 x 8192 x 1024 10.5 -> 10.7, 256 x 5504 x 2048 17.0 -> 16.6.
 // 128 x 128 on all units: from K = 3072 on (916 x 4096 x 3072 of heads 30.8 -> 30.7, x 4096 38.5 -> 36.3, but x 2048 22.7 -> 25.5, residual 956 x 4096 x 2048 23.9
-// -> 24.5, SwiGLU 148 x 16384 x 2048 22.5 -> 23.9; 224 tiles, 788 x 4096 x 2048 of heads 22.1 -> 21.6, residual 21.9 -> 21.4).
+// -> 24.5, SwiGLU 148 x 16384 x 2048 22.5 -> 23.9; 224 tiles, 788 x 4096 x 2048 of heads 22.1 -> 21.6, residual 21.9 -> 21.4).  Four contexts that call at once share units no worse: six short
+// candidates, eight layers of the 0.6B shape 205 us a call with these rings, 206 without.
 static constexpr int kNever = 1 << 30;
 struct DeepRing {
   int slices, last_rows, full_slices;      // K from `slices` on where the last row tile has up to last_rows rows, else from full_slices on
@@ -586,7 +587,7 @@ static bool deep_ring(const TileCost &t, bool glu, const DeepRing &r, int64_t M,
 }
 static bool deep_tile(int kind, int epi, int M, int ncols, int K) {
   const bool glu = epi == PRISM_EPI_SWIGLU;
-  if (kind == kTile128Deep) return deep_ring(kTileCost[kind], glu, DeepRing{32, 64, 64, 48}, M, ncols, K);
+  if (kind == kTile128Deep) return deep_ring(kTileCost[kind], glu, DeepRing{32, 64, kNever, 48}, M, ncols, K);
   if (kind == kTile128x64)
     return deep_ring(kTileCost[kind], glu, glu ? DeepRing{16, 96, 32, 0} : epi == PRISM_EPI_RESIDUAL ? DeepRing{32, 128, 32, 0} : DeepRing{16, 128, 16, 0}, M, ncols, K);
   return false;

@@ -124,7 +124,7 @@ STORE, RESIDUAL, SWIGLU, STORE_F32 = range(4)
     *[(False, "kTile128Deep", e, *c) for e in range(4) for c in (
         ((64, 256 * 64, 48), (64, 257 * (64 if e == SWIGLU else 128), 48)), ((64, 224 * 64, 32), (64, 225 * (64 if e == SWIGLU else 128), 32)),
         ((64, 256 * (64 if e == SWIGLU else 128), 48), (64, 256 * (64 if e == SWIGLU else 128), 47)),
-        ((192, 1024, 32), (193, 1024, 32)), ((192, 1024, 32), (192, 1024, 31)), ((193, 1024, 64), (193, 1024, 63)))],
+        ((192, 1024, 32), (193, 1024, 32)), ((192, 1024, 32), (192, 1024, 31)), ((192, 1024, 1024), (193, 1024, 1024)))],
     (True, "kHead64", 0, (64, 256 * 128, 16), (64, 257 * 128, 16)), (True, "kHead64", 0, (64, 1024, 16), (64, 1024, 15)),
     (True, "kHead128Deep", 0, (96, 256 * 128, 48), (96, 257 * 128, 48)), (True, "kHead128Deep", 0, (96, 256 * 128, 48), (96, 256 * 128, 47)),
     (True, "kHead128Deep", 0, (96, 224 * 128, 32), (96, 225 * 128, 32)), (True, "kHead128Deep", 0, (224, 1024, 32), (225, 1024, 32)),
