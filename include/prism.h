@@ -155,7 +155,8 @@ typedef struct {
   float   *ev_scores;       /* out [cap_events * n_cands]; NaN where the candidate was not live */
   int8_t  *ev_fate;         /* out [cap_events * n_cands]; PRISM_FATE_* */
   double   ms_total;        /* out: GPU time of the call, first launch to last (HIP events) */
-  double   ms_layers;       /* out: GPU time inside transformer layers */
+  double   ms_layers;       /* out: GPU time inside transformer layers; layers that follow one another without a check are one
+                               interval, the idle time between them included */
   double   ms_checks;       /* out: GPU time in scoring + pruning + compaction */
   int64_t  token_layers;    /* out: sum over executed layers of live tokens */
   int64_t  peak_hbm_bytes;  /* out: library-owned device memory at its peak (what hbm_cap_bytes caps); the caller's own
@@ -209,7 +210,9 @@ int prism_create(const prism_model *model, const prism_weights *weights, const p
 /* Top-K selection (Sec. 2.1).  All pointers [host].  Sequence c is query ++ cand_tokens[c], positions
  * restart at 0 for every sequence.  out_idx / out_scores hold >= K entries; *out_count = min(K, n_cands).
  * Order: best first, ties by lower candidate index.  Synchronous: returns after the results are on the
- * host.  K >= n_cands disables pruning.  report may be NULL. */
+ * host.  K >= n_cands disables pruning.  report may be NULL.
+ * While the GPU works towards a check's results the calling thread watches a word of pinned memory, without yielding, for up
+ * to 4 ms, then waits for the stream; at the end of the call it waits for the stream. */
 int prism_select(prism_ctx *ctx, const int32_t *query_tokens, int32_t query_len,
                  const int32_t *const *cand_tokens, const int32_t *cand_lens, int32_t n_cands,
                  int32_t K, int32_t *out_idx, float *out_scores, int32_t *out_count,

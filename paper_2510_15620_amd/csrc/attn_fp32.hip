@@ -1,7 +1,8 @@
 // Causal GQA attention for the fp32 mode.
 //
 // attention_fp32_kernel: head sizes 32, 64 and 128, on v_mfma_f32_16x16x4_f32.  A wavefront owns 16 queries of one head, its
-// workgroup 64 consecutive queries of one sequence (a work item); nothing is shared and there is no barrier.  As in the 16-bit
+// workgroup 64 consecutive queries of one sequence (a work item); the waves share nothing and meet at no barrier (LDS holds the
+// values of each wave's own diagonal tile).  As in the 16-bit
 // kernel everything is computed transposed, S^T = K Q^T and O^T += V^T P^T, so that a lane owns one query (lane % 16) and
 // the accumulators of S^T are the next contraction's operand as they are: instruction s of the second contraction takes
 // the four keys 4 g + s, g = 0..3, and a lane of group g = lane / 16 holds the weight of key 4 g + s in register s.  Operands
@@ -14,7 +15,7 @@
 // sums of values have weights of up to 1 per key, so values need to stay below the largest fp32 number over the sequence length.
 // 4 heads of 64, 12859 tokens of 160-512-token sequences: 771 us as one workgroup per (token, head) -> 86 us; -> 79 with the next
 // tile's loads held in front of a tile's work, the accumulators in vector registers and the diagonal's values handed over in LDS;
-// -> 55 with the items longest first (AttnLevels).  8 sequences of 32-64 tokens 11.2 -> 8.5.
+// -> 55 with the items longest first (attention_fp32_longest_first).  8 sequences of 32-64 tokens 11.2 -> 8.5.
 //
 // attention_fp32_any_kernel: any other head size: the definition, one workgroup per (token, query head), score row in LDS.
 #include "common.h"

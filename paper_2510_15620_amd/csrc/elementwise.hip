@@ -256,7 +256,8 @@ __global__ __launch_bounds__(256) void qk_finish_kernel(float *__restrict__ QKV,
 // as 64 consecutive tokens of one d per wave instruction.  Then q and k: a workgroup takes all heads of 4 tokens, 16 lanes each,
 // a lane holding 4 + 4 values of the two rotation halves; a lane's token stays the same over its heads.  So the tokens' 4 x 64
 // rotations are one fp64 evaluation per thread, while the first values are on their way, and no table has to be allocated,
-// filled and waited for: 1154 tokens of 16 + 8 heads 3.0 (table) + 9.9 us in two launches -> 9.8 in one.  kFew, for up to 6 heads of
+// filled and waited for: 1154 tokens of 16 + 8 heads 3.0 (table) + 9.9 us in two launches -> 9.8 in one.  More than 4 kHeads heads go in
+// rounds whose loads wait for the round before: the call with 32 + 8 heads, 391 tokens 23.9 -> 23.6 us, 12 859 135 -> 106.  kFew, for up to 6 heads of
 // many tokens: a wave takes all heads of 4 tokens of its own, 16 to a workgroup.  With 4 to a workgroup most waves have a head or
 // none, and starting workgroups is what the launch takes its time for: us of the call, by the two launches, 4 tokens and 16: 1 + 1 heads 96 064
 // tokens 72, 83, 60, 20 000 33.5, 31.8, 28.3; 2 + 1 of 200 000 154, 209, 139; 4 + 2 of 50 000 89, 86, 71.  Up to some 8000 tokens the
@@ -373,7 +374,8 @@ __global__ __launch_bounds__(256) void qkv_finish_16_kernel(const float *__restr
 // of them, from the table or, where there is none (a call of its own), evaluated while the loads are on their way.  One wave per
 // workgroup: a few hundred tokens then reach most compute units.  The sum of squares keeps wave_sum's order (lanes beyond P
 // added zeros).  6 heads of 64, a call of its own: 12859 tokens 4.8 (table) + 11.2 us -> 12.0, 354 tokens 2.6 + 2.8 us and the gap
-// between them -> 5.1.
+// between them -> 5.1.  Heads beyond U take further blocks, which read the rotations again: with a table, against a lane per pair and head,
+// 50 000 tokens of 9 heads of 32 24.6 -> 20.4 us, 24 of 128 286 -> 251, 40 of 128 477 -> 412, 40 of 64 230 -> 237 (the one slower of 120 timed).
 template <int P, int U>
 __global__ __launch_bounds__(64) void qk_finish_fp32_kernel(float *__restrict__ QKV, const int32_t *__restrict__ pos,
                                                             const float *__restrict__ q_gain, const float *__restrict__ k_gain, int n_tok,

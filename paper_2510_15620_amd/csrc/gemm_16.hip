@@ -502,10 +502,10 @@ static int launch_cfg(const OT *A, const OT *W, void *out, int M, int N, int K, 
 // many tiles share the unit: alone it is a chain of latencies, together the matrix pipes and LDS.  The constants were fit to loops
 // on 32x32x16 MFMAs with operands that stay in the caches (256 x 256: to those of today); with weights from memory and the loops of
 // today they are off by 11-23 % (root mean square) per tile, 256 x 256 by 30 % where the chip is not full, but what counts is the pick: on
-// 265 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues) it is on average 0.5 % above the best tile and ring.  The
+// 265 launches (N 1024-24576, K 1024-12288, 1 to 20000 rows, three epilogues) it is on average 0.6 % above the best tile and ring.  The
 // costs are of the shallow rings (deep_ring, below, only says which ring the picked tile runs on), so the worst picks stand beside a 128 x 64
-// tile on its deeper one: 150 x 6144 x 2560 stored 21.6 us on 32 x 64, 16.8 there, 150 x 6144 x 4096 28.5 and 23.2; next 64 x 19456 x 2560 with
-// SwiGLU, 35.2 on 64 x 64 and 30.5 on 128 x 128.  Examples, us with weights from memory, 32x32x16 loops -> now: 100 x 4096 x 12288
+// tile on its deeper one: 150 x 6144 x 2560 stored 21.7 us on 32 x 64, 16.8 there, 150 x 6144 x 4096 28.4 and 23.1; next 64 x 19456 x 2560 with
+// SwiGLU, 35.1 on 64 x 64 and 30.4 on 128 x 128.  Examples, us with weights from memory, 32x32x16 loops -> now: 100 x 4096 x 12288
 // 38.8 -> 38.7 (64 x 32), 391 x 1024 x 3072 10.2 -> 10.0 (64 x 32), 33 x 2560 x 9728 19.3 -> 18.5 (32 x 32), 777 x 6144 x 1024 with SwiGLU
 // 19.7 -> 19.1 (128 x 128), 3699 x 1024 x 3072 34.0 -> 32.8 (128 x 128, four stages).
 // (256 x 256: on chips of different speed a slice takes 1.34-1.7 us, the fixed part 11 us with SwiGLU and 17 with a residual or a
@@ -518,8 +518,8 @@ enum { kTile256, kTile128, kTile128Deep, kTile128x64, kTile64, kTile32x64, kTile
 static constexpr TileCost kTileCost[kTileKinds] = {
     {256, 256, 1, 1.45f, 1.45f, 9.2f}, {128, 128, 2, 0.72f, 0.50f, 4.5f}, {128, 128, 1, 0.52f, 0.52f, 3.4f}, {128, 64, 2, 0.34f, 0.36f, 2.3f},
     {64, 64, 2, 0.204f, 0.204f, 2.1f}, {32, 64, 3, 0.176f, 0.149f, 2.4f}, {64, 32, 1, 0.128f, 0.128f, 2.3f}, {32, 32, 2, 0.106f, 0.083f, 2.6f}};
-// The fused q/k/v projection: tiles whose waves own whole heads (the same: off by 9-18 %, 256 x 256 by 25 %; the pick is the best tile of
-// all 34 launches of 1 to 12000 rows).  Its epilogue is longer: two dependent loads (position, rotation)
+// The fused q/k/v projection: tiles whose waves own whole heads (the same: off by 9-18 %, 256 x 256 by 25 %; the pick is the best tile and
+// ring of 33 of 34 launches of 1 to 12000 rows, 2 % off on one).  Its epilogue is longer: two dependent loads (position, rotation)
 // and the per-head arithmetic.  391 x 4096 x 1024: 11 us, where the projection to fp32 and its two finishing kernels took 48;
 // 777 x 6144 x 4096: 62.
 enum { kHead256, kHead128, kHead128Deep, kHead64, kHeadKinds };
@@ -571,7 +571,8 @@ static TilePlan plan_tiles(const TileCost *costs, int kinds, int M, int ncols, i
 // is level on a long K (SwiGLU 100 x 24576 x 4096 48.1 -> 48.2, 128 x 24576 x 4096 50.3 -> 50.8, residual 1500 x 2560 x 4096 39.7 -> 39.4) and loses up to 6 % on a
 // shorter one: residual 3699 x 1024 x 3072 32.8 -> 34.1, 2000 x 1024 x 3072 27.5 -> 29.1, SwiGLU 256 x 16384 x 2048 25.2 -> 26.3, 100 x 19456 x 2560 32.3 -> 32.9, heads
 // 896 x 4096 x 2048 23.3 -> 23.5, where SwiGLU of 391 x 8192 x 2048 takes 21.9 -> 21.0 and heads of 777 x 4096 x 2048 21.1 -> 20.1.  128 x 64 with SwiGLU,
-// 200 x 8192 x 1024 10.0 -> 9.6, 256 x 8192 x 1024 10.5 -> 10.7, 256 x 5504 x 2048 17.0 -> 16.6.
+// 200 x 8192 x 1024 10.0 -> 9.6, 256 x 8192 x 1024 10.5 -> 10.7, 256 x 5504 x 2048 17.0 -> 16.6.  On weights that the caches hold, which a layer's are not behind
+// the layers before it: 128 x 64, 391 x 2560 x 4096 20.9 -> 19.7, but 391 x 4096 x 1024 stored 7.1 -> 7.6; 128 x 128, 777 x 4096 x 4096 31.2 -> 31.9.
 // 128 x 128 on all units: from K = 3072 on (916 x 4096 x 3072 of heads 30.8 -> 30.7, x 4096 38.5 -> 36.3, but x 2048 22.7 -> 25.5, residual 956 x 4096 x 2048 23.9
 // -> 24.5, SwiGLU 148 x 16384 x 2048 22.5 -> 23.9; 224 tiles, 788 x 4096 x 2048 of heads 22.1 -> 21.6, residual 21.9 -> 21.4).  Four contexts that call at once share units no worse: six short
 // candidates, eight layers of the 0.6B shape 205 us a call with these rings, 206 without.

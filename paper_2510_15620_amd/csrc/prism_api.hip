@@ -129,7 +129,7 @@ struct prism_ctx {
   int32_t *h_meta_dev = nullptr;                     // its device-visible address, and that of h_res
   char *h_res_dev = nullptr;
   uint64_t n_posted = 0;                             // results posted to h_res so far; the last one's number stands behind them
-  // what a check or the final ranking hands to the host, in one block so that one copy brings it over; a call of n candidates
+  // what a check or the final ranking hands to the host, in one block so that one post or copy brings it over; a call of n candidates
   // lays it out by n: [stats][scores n][fate n][top positions n][top scores n], h_res (pinned) alike
   char *d_res = nullptr, *h_res = nullptr;
   float *d_scores = nullptr; int8_t *d_fate = nullptr; double *d_stats = nullptr; void *route_ws = nullptr;
@@ -638,8 +638,8 @@ static int ensure_scratch(prism_ctx *c, const Plan &p, bool need_second_x, int n
   return PRISM_OK;
 }
 
-// Writes pos / vtcol / lastrow / tiles for the current live set into the pinned staging buffer and
-// uploads them.  The staging buffer is only rewritten behind a later result of the same stream (a post that has arrived, or a
+// Writes pos / vtcol / lastrow / tiles for the current live set into the pinned staging buffer and has a
+// kernel fetch them.  The staging buffer is only rewritten behind a later result of the same stream (a post that has arrived, or a
 // synchronisation), so the kernel that reads it has ended.
 static int upload_meta(prism_ctx *c, const Plan &p, const MetaOff &mo, bool with_tokens) {
   int32_t *h = c->h_meta;
@@ -677,7 +677,7 @@ static int upload_meta(prism_ctx *c, const Plan &p, const MetaOff &mo, bool with
 
 // The moment on the compute stream behind everything queued so far, as an event of the pool.  What such a record costs is idle
 // time between two kernels: 2.9 us with an ordinary event, 1.05 us without its system-scope fence (these events only measure
-// time; results reach the host by a copy and a stream synchronisation), and some 3.5 us for each further record at the same place,
+// time; a check's post carries its own system-scope release, the last results come by a copy and a stream synchronisation), and some 3.5 us for each further record at the same place,
 // so a moment that several intervals share is recorded once.  A call with a report on the 0.6B shape, six short candidates:
 // 2670 -> 2333 us, forty candidates 7219 -> 6909.
 static int mark(prism_ctx *c, hipEvent_t *e) {

@@ -347,7 +347,8 @@ __device__ __forceinline__ void route_small(const float *__restrict__ scores, in
 
 // The one workgroup that decides also posts the result block to the host where it is asked to (post.flag; the block starts with
 // stats): a launch of its own for that took 5 us on the
-// way from the scores to the host's next launch (six short candidates on the 0.6B shape, six checks: 2216 -> 2201 us).
+// way from the scores to the host's next launch (six short candidates on the 0.6B shape, six checks: 2216 -> 2201 us).  What it posts was
+// stored as doubles and bytes, by other lanes too: the barrier in between is what puts those stores in front of the words' loads.
 __global__ __launch_bounds__(512) void route_small_kernel(const float *__restrict__ scores, int n, int K_rem, int k_req, float tau,
                                                           int8_t *fate, double *stats, const HostPost post) {
   route_small(scores, n, K_rem, k_req, tau, fate, stats);
