@@ -686,21 +686,37 @@ def test_fp32_call_on_both_sides_of_the_attention_order_rule():
     assert np.array_equal(scores[0], scores[1]) and len(set(scores[0])) == len(cands)
 
 
-@pytest.mark.parametrize("nq,nkv,T", [(nq, nkv, T) for nq, nkv in ((1, 1), (16, 8), (32, 8)) for T in (1, 3, 65)] +
-                         [(1, 1, 8191), (1, 1, 8192), (2, 1, 8193), (4, 2, 8207), (5, 1, 8208), (4, 3, 8200)])
+@pytest.mark.parametrize("nq,nkv", [(1, 1), (16, 8), (32, 8)])
+@pytest.mark.parametrize("T", [1, 3, 65])
 def test_qkv_finish_16_evaluates_the_tables_rotations(nq, nkv, T):
-    """The one-launch kernel (a part of a round of heads, one, more than one; tokens that fill no workgroup; from 8192 tokens on up to six
-    heads a wave) against the kernels that read the table, to the bit."""
+    """The one-launch kernel (a part of a round of heads, one, more than one; tokens that fill no workgroup) against the kernels
+    that read the table, to the bit."""
     hd, dtype = 128, torch.float16
-    pos = 4095 - torch.arange(T, dtype=torch.int32, device=DEV) % 4096
+    pos = torch.arange(4096 - T, 4096, dtype=torch.int32, device=DEV)
     col = torch.from_numpy(B.vt_column_of_key(np.arange(T, dtype=np.int32))).to(DEV)
-    stride = -(-T // 64) * 64 + 64
     QKV = _rand((T, (nq + 2 * nkv) * hd), torch.float32, 44, 1.5).to(DEV)
     g = (1 + _rand((hd,), torch.float32, 41, 0.1)).to(dtype).to(DEV)
     got = []
     for x in (QKV, _off_by_one(QKV)):
+        QK, Vt = torch.zeros(T, (nq + nkv) * hd, dtype=dtype, device=DEV), torch.zeros(nkv, hd, 128, dtype=torch.float16, device=DEV)
+        B.op_qkv_finish(B._dt(QK), x, pos, 4096, g, g, nq, nkv, hd, 1e-6, 1e6, True, QK, Vt, col, 128)
+        got.append((QK, Vt))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("nq,nkv,T", [(1, 1, 8191), (1, 1, 8192), (2, 1, 8193), (4, 2, 8207), (5, 1, 8208), (4, 3, 8200)])
+def test_qkv_finish_16_of_few_heads_and_many_tokens(nq, nkv, T):
+    """From 8192 tokens on a wave takes up to six heads of four tokens: both sides of each limit and workgroups that tokens do not fill,
+    against the kernels that read the table, to the bit."""
+    hd, dtype, stride = 128, torch.float16, -(-T // 64) * 64
+    pos = 4095 - torch.arange(T, dtype=torch.int32, device=DEV) % 4096
+    col = torch.from_numpy(B.vt_column_of_key(np.arange(T, dtype=np.int32))).to(DEV)
+    QKV = _rand((T, (nq + 2 * nkv) * hd), torch.float32, 45, 1.5).to(DEV)
+    gq, gk = ((1 + _rand((hd,), torch.float32, seed, 0.1)).to(dtype).to(DEV) for seed in (41, 42))
+    got = []
+    for x in (QKV, _off_by_one(QKV)):
         QK, Vt = torch.zeros(T, (nq + nkv) * hd, dtype=dtype, device=DEV), torch.zeros(nkv, hd, stride, dtype=torch.float16, device=DEV)
-        B.op_qkv_finish(B._dt(QK), x, pos, 4096, g, g, nq, nkv, hd, 1e-6, 1e6, True, QK, Vt, col, stride)
+        B.op_qkv_finish(B._dt(QK), x, pos, 4096, gq, gk, nq, nkv, hd, 1e-6, 1e6, True, QK, Vt, col, stride)
         got.append((QK, Vt))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]) and got[0][0].float().abs().sum(1).min() > 0
 
